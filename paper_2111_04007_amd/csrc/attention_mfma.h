@@ -623,7 +623,6 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-inline bool attn_mfma_supported(int s, int d) { return (d == 64 || d == 96 || d == 128) && s >= 128 && s % 128 == 0; }
 
 template <int D, bool DROP>
 inline hipError_t attn_fwd_mfma_d(const bf16* qkv, bf16* ctx, float* lse, int b, int s, int heads, int causal,
@@ -635,7 +634,7 @@ inline hipError_t attn_fwd_mfma_d(const bf16* qkv, bf16* ctx, float* lse, int b,
   return hipGetLastError();
 }
 
-inline hipError_t launch_attention_fwd_mfma(const bf16* qkv, bf16* ctx, float* lse, int b, int s, int heads, int d,
+hipError_t launch_attention_fwd_mfma(const bf16* qkv, bf16* ctx, float* lse, int b, int s, int heads, int d,
                                             int causal, const DropArgs& drop, hipStream_t st) {
   const bool dr = drop.thr != 0;
   if (d == 64) return dr ? attn_fwd_mfma_d<64, true>(qkv, ctx, lse, b, s, heads, causal, drop, st) : attn_fwd_mfma_d<64, false>(qkv, ctx, lse, b, s, heads, causal, drop, st);
@@ -659,7 +658,7 @@ inline hipError_t attn_bwd_mfma_d(const bf16* qkv, const bf16* ctx, const float*
   return hipGetLastError();
 }
 
-inline hipError_t launch_attention_bwd_mfma(const bf16* qkv, const bf16* ctx, const float* lse, const bf16* dctx,
+hipError_t launch_attention_bwd_mfma(const bf16* qkv, const bf16* ctx, const float* lse, const bf16* dctx,
                                             bf16* dqkv, float* delta, int b, int s, int heads, int d, int causal,
                                             const DropArgs& drop, hipStream_t st) {
   const bool dr = drop.thr != 0;

@@ -5,12 +5,10 @@
 //
 // qkv is [b*s, 3h]: Q at column j*d, K at h + j*d, V at 2h + j*d for head j.
 #pragma once
+#include "attention.h"
 #include "common.h"
 
 namespace varuna {
-
-constexpr int ATS_MAX_S = 4096;
-constexpr int ATS_MAX_D = 256;
 
 // ctx_i = sum_k P_ik V_k with P = softmax over k of scale * q_i.k_k (k <= i if causal).
 // lse[b, j, i] = max + log(sum) (natural log), written when lse != null.
@@ -188,7 +186,7 @@ inline int ats_waves(size_t bytes_per_wave) {
 }
 
 template <typename T>
-inline hipError_t launch_attention_fwd_simple(const T* qkv, T* ctx, float* lse, int b, int s,
+hipError_t launch_attention_fwd_simple(const T* qkv, T* ctx, float* lse, int b, int s,
                                               int heads, int d, int causal, const DropArgs& drop, hipStream_t st) {
   const int nw = ats_waves((size_t)(d + s) * sizeof(float));
   if (nw == 0) return hipErrorInvalidValue;
@@ -200,7 +198,7 @@ inline hipError_t launch_attention_fwd_simple(const T* qkv, T* ctx, float* lse, 
 }
 
 template <typename T>
-inline hipError_t launch_attention_bwd_simple(const T* qkv, const T* ctx, const float* lse,
+hipError_t launch_attention_bwd_simple(const T* qkv, const T* ctx, const float* lse,
                                               const T* dctx, T* dqkv, float* delta, int b, int s,
                                               int heads, int d, int causal, const DropArgs& drop, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)d);
@@ -222,5 +220,14 @@ inline hipError_t launch_attention_bwd_simple(const T* qkv, const T* ctx, const 
   }
   return hipGetLastError();
 }
+
+#define VARUNA_ATS(T)                                                                                                  \
+  template hipError_t launch_attention_fwd_simple<T>(const T*, T*, float*, int, int, int, int, int, const DropArgs&,    \
+                                                     hipStream_t);                                                     \
+  template hipError_t launch_attention_bwd_simple<T>(const T*, const T*, const float*, const T*, T*, float*, int, int,  \
+                                                     int, int, int, const DropArgs&, hipStream_t);
+VARUNA_ATS(float)
+VARUNA_ATS(bf16)
+#undef VARUNA_ATS
 
 }  // namespace varuna

@@ -742,49 +742,6 @@ inline int dg_pick(int op, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t
   return dg_flavour(tile, op);
 }
 
-template <int BM, int BN, int WGM, int WGN, bool AK, bool BK_, int MODE, int LS = 0>
-inline hipError_t dg_launch_one(const bf16* a, int64_t lda, const bf16* b, int64_t ldb, int64_t M, int64_t N,
-                                int64_t K, const EpiArgs<bf16>& epi, int splits, hipStream_t st) {
-  auto kern = gemm_dma_kernel<BM, BN, WGM, WGN, AK, BK_, MODE, LS>;
-  constexpr size_t smem = dg_smem_bytes<BM, BN, WGM, WGN, MODE, LS>();
-  static_assert(smem <= 160 * 1024, "one workgroup's LDS");
-  // the first call raises the kernel's dynamic LDS limit (thread-safe: initialisation of a local static)
-  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-  if (attr_err != hipSuccess) return attr_err;
-  const int tm = (int)(M / BM), tn = (int)(N / BN);
-  constexpr int xcd_remap = 1, group = 8;   // tile order: contiguous range per XCD, walked in groups of 8 tile rows
-  if (splits < 1 || (MODE != EPI_STORE_F32 && splits != 1) || (K / DG_BK) % splits != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn), (unsigned)splits), dim3(WGM * WGN * kWave), smem, st, a, lda, b, ldb,
-                     (int)K, tm, tn, epi, xcd_remap, group);
-  return hipGetLastError();
-}
-
-template <bool AK, bool BK_, int MODE>
-inline hipError_t dg_launch_variant(int variant, const bf16* a, int64_t lda, const bf16* b, int64_t ldb,
-                                    int64_t M, int64_t N, int64_t K, const EpiArgs<bf16>& epi, int splits, hipStream_t st) {
-  switch (variant) {
-    case 5: return dg_launch_one<256, 256, 2, 4, AK, BK_, MODE>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 6: return dg_launch_one<256, 256, 2, 2, AK, BK_, MODE>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 7: return dg_launch_one<128, 128, 2, 2, AK, BK_, MODE>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 8: return dg_launch_one<256, 128, 2, 2, AK, BK_, MODE>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 9: return dg_launch_one<256, 256, 2, 4, AK, BK_, MODE, 1>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 10: return dg_launch_one<128, 128, 2, 2, AK, BK_, MODE, 1>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 11: return dg_launch_one<256, 256, 2, 2, AK, BK_, MODE, 1>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 12: return dg_launch_one<256, 256, 2, 4, AK, BK_, MODE, 2>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 13: return dg_launch_one<256, 256, 2, 2, AK, BK_, MODE, 2>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 14: return dg_launch_one<128, 128, 2, 2, AK, BK_, MODE, 2>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 15: return dg_launch_one<128, 256, 2, 4, AK, BK_, MODE, 2>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 16: return dg_launch_one<256, 128, 4, 2, AK, BK_, MODE, 2>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 17: return dg_launch_one<256, 256, 2, 2, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 18: return dg_launch_one<256, 256, 2, 4, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 19: return dg_launch_one<128, 128, 2, 2, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 20: return dg_launch_one<128, 256, 2, 4, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 21: return dg_launch_one<256, 128, 4, 2, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    default: return hipErrorInvalidValue;
-  }
-}
-
 // Split-K for weight-gradient GEMMs whose output has too few tiles to fill the chip: the
 // reduction is cut into `splits` equal parts, each workgroup row of the grid writes its
 // partial tile (EPI_STORE_F32) and splitk_reduce adds the partials to the accumulator in a
@@ -800,43 +757,22 @@ inline int dg_wgrad_splits(int64_t M, int64_t N, int64_t K) {
   return (int)(s < 1 ? 1 : s);
 }
 
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, int splits, int64_t n,
-                                                            float* __restrict__ out) {
-  const int64_t n4 = n / 4;  // n is a multiple of 4 (tile sizes)
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (int64_t)gridDim.x * blockDim.x) {
-    floatx4 acc = reinterpret_cast<floatx4*>(out)[i];
-    for (int s = 0; s < splits; ++s) {
-      const floatx4 p = reinterpret_cast<const floatx4*>(partial + (int64_t)s * n)[i];
-      acc[0] += p[0]; acc[1] += p[1]; acc[2] += p[2]; acc[3] += p[3];
-    }
-    reinterpret_cast<floatx4*>(out)[i] = acc;
-  }
-}
+// The launches, one translation unit per product; variant as above.
+hipError_t launch_gemm_dma_fwd(int mode, int variant, const bf16* a, int64_t lda, const bf16* b, int64_t ldb, int64_t M, int64_t N,
+                                 int64_t K, const EpiArgs<bf16>& epi, hipStream_t st);
+hipError_t launch_gemm_dma_dgrad(int mode, int variant, const bf16* a, int64_t lda, const bf16* b, int64_t ldb, int64_t M, int64_t N,
+                                 int64_t K, const EpiArgs<bf16>& epi, hipStream_t st);
+hipError_t launch_gemm_dma_wgrad(int mode, int variant, const bf16* a, int64_t lda, const bf16* b, int64_t ldb, int64_t M, int64_t N,
+                                 int64_t K, const EpiArgs<bf16>& epi, hipStream_t st, int splits);
+// out[n] += the partial results of `splits` splits, in a fixed order (gemm_wgrad.hip)
+hipError_t launch_splitk_reduce(const float* partial, int splits, int64_t n, float* out, hipStream_t st);
 
-inline hipError_t launch_splitk_reduce(const float* partial, int splits, int64_t n, float* out, hipStream_t st) {
-  int64_t nblk = (n / 4 + 255) / 256;
-  if (nblk > 8192) nblk = 8192;
-  if (nblk < 1) nblk = 1;
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)nblk), dim3(256), 0, st, partial, splits, n, out);
-  return hipGetLastError();
-}
-
-inline hipError_t launch_gemm_dma(int op, int mode, int variant, const bf16* a, int64_t lda, const bf16* b,
-                                  int64_t ldb, int64_t M, int64_t N, int64_t K, const EpiArgs<bf16>& epi,
-                                  hipStream_t st, int splits = 1) {
-  if (op == GEMM_FWD) {
-    if (mode == EPI_BIAS) return dg_launch_variant<true, true, EPI_BIAS>(variant, a, lda, b, ldb, M, N, K, epi, splits, st);
-    if (mode == EPI_BIAS_GELU) return dg_launch_variant<true, true, EPI_BIAS_GELU>(variant, a, lda, b, ldb, M, N, K, epi, splits, st);
-    if (mode == EPI_BIAS_RES) return dg_launch_variant<true, true, EPI_BIAS_RES>(variant, a, lda, b, ldb, M, N, K, epi, splits, st);
-  } else if (op == GEMM_DGRAD) {
-    if (mode == EPI_PLAIN) return dg_launch_variant<true, false, EPI_PLAIN>(variant, a, lda, b, ldb, M, N, K, epi, splits, st);
-    if (mode == EPI_DGELU) return dg_launch_variant<true, false, EPI_DGELU>(variant, a, lda, b, ldb, M, N, K, epi, splits, st);
-  } else if (op == GEMM_WGRAD) {
-    if (mode == EPI_ACCUM_F32) return dg_launch_variant<false, false, EPI_ACCUM_F32>(variant, a, lda, b, ldb, M, N, K, epi, splits, st);
-    if (mode == EPI_STORE_F32) return dg_launch_variant<false, false, EPI_STORE_F32>(variant, a, lda, b, ldb, M, N, K, epi, splits, st);
-    if (mode == EPI_PLAIN) return dg_launch_variant<false, false, EPI_PLAIN>(variant, a, lda, b, ldb, M, N, K, epi, splits, st);
-  }
-  return hipErrorInvalidValue;
+inline hipError_t launch_gemm_dma(int op, int mode, int variant, const bf16* a, int64_t lda, const bf16* b, int64_t ldb, int64_t M,
+                                  int64_t N, int64_t K, const EpiArgs<bf16>& epi, hipStream_t st, int splits = 1) {
+  if (op != GEMM_WGRAD && splits != 1) return hipErrorInvalidValue;
+  if (op == GEMM_FWD) return launch_gemm_dma_fwd(mode, variant, a, lda, b, ldb, M, N, K, epi, st);
+  if (op == GEMM_DGRAD) return launch_gemm_dma_dgrad(mode, variant, a, lda, b, ldb, M, N, K, epi, st);
+  return launch_gemm_dma_wgrad(mode, variant, a, lda, b, ldb, M, N, K, epi, st, splits);
 }
 
 }  // namespace varuna

@@ -25,8 +25,7 @@
 #include <vector>
 
 #include "../../include/varuna_stage.h"
-#include "attention_mfma.h"
-#include "attention_simple.h"
+#include "attention.h"
 #include "common.h"
 #include "gemm_dma.h"
 #include "gemm_simple.h"
