@@ -1,0 +1,210 @@
+// GEMM with fp32 products and fp32 accumulation on the matrix cores (v_mfma_f32_32x32x2_f32):
+//   acc[m,n] = sum_k A(m,k) * B(n,k)
+//   AK: A(m,k) = a[m*lda + k]   else A(m,k) = a[k*lda + m];   BK likewise for B(n,k) = b[n*ldb + k] / b[k*ldb + n]
+// It serves the fp32 path (the 1e-5 tolerance rules out reduced-precision products) and the bf16 shapes the
+// bf16 MFMA kernels cannot address (rows that are not whole 16-byte pieces); bf16 operands are widened on the
+// way into LDS, so their products are exact.  Any M, N, K; every global access is bounds-checked.
+//
+// What bounds it: the fp32 matrix rate, 256 FLOP per clock and CU (157 TFLOP/s nominal, the rate a large library
+// product reaches here); a product of a 32x32 block takes 64 clocks for two LDS words per lane, so neither LDS
+// nor issue is close.  At the sizes of the fp32 path (a few hundred to a thousand tokens) what counts instead is
+// filling 1024 SIMDs: KS waves of a workgroup share an output tile and take every stage's k-range in KS parts,
+// summed through LDS in a fixed order at the end, so a 32x32 tile still occupies all four SIMDs of its CU, and
+// stages are long (64 or 128 k), which leaves a load's latency the products of the resident workgroups.  Measured
+// against the vector-ALU kernel before it (us): [1000,768] over 3072 377 -> 62 (75 TFLOP/s), [128,128] over 512
+// 60 -> 5, and 2048^3 at 111 TFLOP/s.
+#pragma once
+#include "common.h"
+#include "gemm_epilogue.h"
+
+namespace varuna {
+
+// LDS tile of ROWS x BKT floats.  KMAJOR: [row][BKT + 4] (an odd number of 16-byte pieces per row: 16-byte reads of
+// consecutive rows fall into different banks); else [k][ROWS + 8] (k-rows four apart, the distance between the two
+// half waves of a read, are half of the banks apart).
+template <int ROWS, int BKT, bool KMAJOR>
+struct GfTile {
+  static constexpr int PITCH = KMAJOR ? BKT + 4 : ROWS + 8;
+  static constexpr int ELEMS = KMAJOR ? ROWS * PITCH : BKT * PITCH;
+};
+
+// Staging of one operand tile: global -> registers -> LDS, four consecutive elements of the contiguous direction
+// at a time.  VEC: one 16-byte (bf16: 8-byte) load per piece, which needs an aligned base, a leading dimension and a
+// contiguous extent that are multiples of 4; otherwise element by element.  Outside the matrix: zeros.
+template <typename T, int ROWS, int BKT, bool KMAJOR, bool VEC, int NT>
+struct GfLoader {
+  static constexpr int PIECES = ROWS * BKT / 4, PPT = PIECES / NT;
+  static_assert(PIECES % NT == 0, "tile / threads mismatch");
+  typedef T Tx4 __attribute__((ext_vector_type(4)));
+  floatx4 v[PPT];
+  __device__ __forceinline__ void load(const T* __restrict__ g, int64_t ld, int64_t row0, int64_t rows, int64_t k0, int64_t K, int tid) {
+#pragma unroll
+    for (int i = 0; i < PPT; ++i) {
+      const int id = tid + i * NT;
+      constexpr int PPL = (KMAJOR ? BKT : ROWS) / 4;   // pieces per line of the contiguous direction
+      const int line = id / PPL, c = (id % PPL) * 4;
+      const int64_t row = row0 + (KMAJOR ? line : c), k = k0 + (KMAJOR ? c : line);
+      const bool line_ok = KMAJOR ? row < rows : k < K;
+      const int64_t left = KMAJOR ? K - k : rows - row;   // elements of the contiguous direction from here on
+      const T* p = g + (KMAJOR ? row * ld + k : k * ld + row);
+      floatx4 x = {0.f, 0.f, 0.f, 0.f};
+      if constexpr (VEC) {
+        if (line_ok && left > 0) {
+          const Tx4 t = *reinterpret_cast<const Tx4*>(p);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[e] = to_f32((T)t[e]);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (line_ok && left > e) x[e] = to_f32(p[e]);
+      }
+      v[i] = x;
+    }
+  }
+  __device__ __forceinline__ void store(float* __restrict__ lds, int tid) const {
+#pragma unroll
+    for (int i = 0; i < PPT; ++i) {
+      const int id = tid + i * NT;
+      constexpr int PPL = (KMAJOR ? BKT : ROWS) / 4;
+      *reinterpret_cast<floatx4*>(lds + (id / PPL) * GfTile<ROWS, BKT, KMAJOR>::PITCH + (id % PPL) * 4) = v[i];
+    }
+  }
+};
+
+// Four products' worth of one operand: element i of the result belongs to product i, whose two k-values are
+// kg + i (lower half wave) and kg + 4 + i (upper half wave).
+template <int ROWS, int BKT, bool KMAJOR>
+__device__ __forceinline__ floatx4 gf_frag(const float* lds, int row, int kg, int half) {
+  constexpr int P = GfTile<ROWS, BKT, KMAJOR>::PITCH;
+  if constexpr (KMAJOR) return *reinterpret_cast<const floatx4*>(lds + row * P + kg + 4 * half);
+  const float* p = lds + (kg + 4 * half) * P + row;
+  return floatx4{p[0], p[P], p[2 * P], p[3 * P]};
+}
+
+// One workgroup: a BM x BN tile on (BM / WM) * (BN / WN) * KS waves, one stage of BKT k in LDS, the next in registers.
+template <typename T, int MODE, bool AK, bool BK, int BM, int BN, int WM, int WN, int KS, int BKT, bool VEC>
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * KS * kWave) void gemm_f32_kernel(
+    const T* __restrict__ a, int64_t lda, const T* __restrict__ b, int64_t ldb, int64_t M, int64_t N, int64_t K,
+    int tiles_m, int tiles_n, EpiArgs<T> epi) {
+  constexpr int NW = (BM / WM) * (BN / WN) * KS, NT = NW * kWave;
+  constexpr int TM = WM / 32, TN = WN / 32;
+  constexpr int AE = GfTile<BM, BKT, AK>::ELEMS, BE = GfTile<BN, BKT, BK>::ELEMS;
+  constexpr int STAGE = AE + BE;
+  constexpr int RED = KS > 1 ? NW * TM * TN * 1024 : 0;   // floats of the partial sums
+  __shared__ __attribute__((aligned(16))) float smem[STAGE > RED ? STAGE : RED];
+  const int tid = threadIdx.x, lane = tid % kWave, half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int ks = wave % KS, wt = wave / KS, wm = wt / (BN / WN), wn = wt % (BN / WN);
+
+  // Workgroup -> tile: consecutive workgroups go round the 8 XCDs; every XCD gets a contiguous range of tiles,
+  // walked in groups of 8 tile rows (the panels it touches stay in its L2).
+  int logical = blockIdx.x;
+  const int nblk = gridDim.x;
+  if ((nblk & 7) == 0) logical = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+  const int width = 8 * tiles_n, grp = logical / width, first_m = grp * 8;
+  const int gsize = tiles_m - first_m < 8 ? tiles_m - first_m : 8;
+  const int64_t m0 = (int64_t)(first_m + (logical % width) % gsize) * BM, n0 = (int64_t)((logical % width) / gsize) * BN;
+
+  floatx16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  GfLoader<T, BM, BKT, AK, VEC, NT> la;
+  GfLoader<T, BN, BKT, BK, VEC, NT> lb;
+  const int64_t nst = (K + BKT - 1) / BKT;
+  la.load(a, lda, m0, M, 0, K, tid);
+  lb.load(b, ldb, n0, N, 0, K, tid);
+  la.store(smem, tid);
+  lb.store(smem + AE, tid);
+  __syncthreads();
+  const float* sa = smem;
+  const float* sb = smem + AE;
+  for (int64_t st = 0; st < nst; ++st) {
+    if (st + 1 < nst) {   // in flight during this stage's products
+      la.load(a, lda, m0, M, (st + 1) * BKT, K, tid);
+      lb.load(b, ldb, n0, N, (st + 1) * BKT, K, tid);
+    }
+    constexpr int GROUPS = BKT / (8 * KS);
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) {
+      const int kg = (ks * GROUPS + g) * 8;
+      floatx4 fa[TM], fb[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[i] = gf_frag<BM, BKT, AK>(sa, wm * WM + i * 32 + l32, kg, half);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[j] = gf_frag<BN, BKT, BK>(sb, wn * WN + j * 32 + l32, kg, half);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][e], fb[j][e], acc[i][j], 0, 0, 0);
+    }
+    if (st + 1 < nst) {
+      __syncthreads();
+      la.store(smem, tid);
+      lb.store(smem + AE, tid);
+      __syncthreads();
+    }
+  }
+
+  // acc[i][j][r] is row 8*(r/4) + 4*half + r%4, column l32 of its 32x32 block.
+  const int64_t mb = m0 + wm * WM, nb = n0 + wn * WN;
+  auto put = [&](int i, int j, int r, float v) {
+    const int64_t m = mb + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3), n = nb + j * 32 + l32;
+    if (m < M && n < N) epilogue_store<T, MODE>(epi, m, n, v);
+  };
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) put(i, j, r, acc[i][j][r]);
+  } else {
+    __syncthreads();   // the stages are read no more
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) smem[((wave * TM * TN + i * TN + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+    __syncthreads();
+    constexpr int RPW = 16 / KS;   // every wave finishes its share of the rows
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int q = 0; q < RPW; ++q) {
+          const int r = ks * RPW + q;
+          float v = 0.f;
+#pragma unroll
+          for (int p = 0; p < KS; ++p) v += smem[(((wt * KS + p) * TM * TN + i * TN + j) * 16 + r) * 64 + lane];
+          put(i, j, r, v);
+        }
+  }
+}
+
+// Output tile of a product: 64x64 (4 waves of 32x32) or 32x32 (8 waves, each an eighth of every stage's k-range).
+// Either occupies the four SIMDs of a CU, so a product takes about ceil(tiles / 256) times the tile's area, and the
+// small tile loses 1.2x to its larger traffic per product.  Measured (us, 64x64 / 32x32): 1000x768x3072 75 / 62,
+// 768x768x1000 27 / 22, 1000x3072x768 53 / 64, 2048x2048x2048 155 / 188; 128x128x512 15.6 / 9.4 with the launch.
+// (128x128 tiles: 152 at 2048^3, 220 and more at the others.)
+inline bool gf_small_tile(int64_t M, int64_t N) {
+  auto area = [&](int64_t size) { return (double)((((M + size - 1) / size) * ((N + size - 1) / size) + 255) / 256) * (double)(size * size); };
+  return 1.2 * area(32) < area(64);
+}
+
+// One product on contiguous operands (forward: a [M,K], b [N,K]; dgrad: [M,K], [K,N]; wgrad: [K,M], [K,N]), in
+// gemm_f32.hip (T = float) and gemm_f32_bf16.hip.
+template <typename T>
+hipError_t launch_gemm_f32(int op, int mode, const T* a, const T* b, int64_t M, int64_t N, int64_t K, const EpiArgs<T>& epi,
+                           hipStream_t st);
+
+}  // namespace varuna

@@ -1,0 +1,46 @@
+// Launches of the fp32-product GEMM kernels; included by one translation unit per operand type.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "gemm_f32.h"
+
+namespace varuna {
+
+template <typename T, int MODE, bool AK, bool BK, int BM, int BN, int WM, int WN, int KS, int BKT>
+inline hipError_t gf_launch_tile(bool vec, const T* a, int64_t lda, const T* b, int64_t ldb, int64_t M, int64_t N, int64_t K,
+                                 const EpiArgs<T>& epi, hipStream_t st) {
+  const int64_t tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
+  if (tm > (1 << 27) || tn > (1 << 27) || tm * tn >= (1ll << 31)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(tm * tn)), block((BM / WM) * (BN / WN) * KS * kWave);
+  if (vec) hipLaunchKernelGGL((gemm_f32_kernel<T, MODE, AK, BK, BM, BN, WM, WN, KS, BKT, true>), grid, block, 0, st, a, lda, b, ldb, M, N, K, (int)tm, (int)tn, epi);
+  else hipLaunchKernelGGL((gemm_f32_kernel<T, MODE, AK, BK, BM, BN, WM, WN, KS, BKT, false>), grid, block, 0, st, a, lda, b, ldb, M, N, K, (int)tm, (int)tn, epi);
+  return hipGetLastError();
+}
+
+template <typename T, int MODE, bool AK, bool BK>
+inline hipError_t gf_launch(const T* a, int64_t lda, const T* b, int64_t ldb, int64_t M, int64_t N, int64_t K,
+                            const EpiArgs<T>& epi, hipStream_t st) {
+  // whole pieces of four along the contiguous direction of both operands, from an aligned base
+  const uintptr_t align = 4 * sizeof(T) - 1;
+  const bool vec = ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & align) == 0 && lda % 4 == 0 && ldb % 4 == 0;
+  if (gf_small_tile(M, N)) return gf_launch_tile<T, MODE, AK, BK, 32, 32, 32, 32, 8, 128>(vec, a, lda, b, ldb, M, N, K, epi, st);
+  return gf_launch_tile<T, MODE, AK, BK, 64, 64, 32, 32, 1, 64>(vec, a, lda, b, ldb, M, N, K, epi, st);
+}
+
+template <typename T>
+hipError_t launch_gemm_f32(int op, int mode, const T* a, const T* b, int64_t M, int64_t N, int64_t K,
+                                  const EpiArgs<T>& epi, hipStream_t st) {
+  if (op == GEMM_FWD) {
+    if (mode == EPI_BIAS) return gf_launch<T, EPI_BIAS, true, true>(a, K, b, K, M, N, K, epi, st);
+    if (mode == EPI_BIAS_GELU) return gf_launch<T, EPI_BIAS_GELU, true, true>(a, K, b, K, M, N, K, epi, st);
+    if (mode == EPI_BIAS_RES) return gf_launch<T, EPI_BIAS_RES, true, true>(a, K, b, K, M, N, K, epi, st);
+  } else if (op == GEMM_DGRAD) {
+    if (mode == EPI_PLAIN) return gf_launch<T, EPI_PLAIN, true, false>(a, K, b, N, M, N, K, epi, st);
+    if (mode == EPI_DGELU) return gf_launch<T, EPI_DGELU, true, false>(a, K, b, N, M, N, K, epi, st);
+  } else if (op == GEMM_WGRAD) {
+    if (mode == EPI_ACCUM_F32) return gf_launch<T, EPI_ACCUM_F32, false, false>(a, M, b, N, M, N, K, epi, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace varuna

@@ -28,7 +28,7 @@
 #include "attention.h"
 #include "common.h"
 #include "gemm_dma.h"
-#include "gemm_simple.h"
+#include "gemm_f32.h"
 #include "mfma_probe.h"
 #include "norm_reduce.h"
 #include "optimizer.h"
@@ -247,16 +247,14 @@ template <> struct GemmDispatch<float> {
                         const float* b, const EpiArgs<float>& e, hipStream_t s, int splits = 1) {
     (void)variant;
     if (splits != 1) return hipErrorInvalidConfiguration;
-    if (op == GEMM_FWD) return launch_gemm_simple<float>(mode, a, K, 1, b, K, 1, M, N, K, e, s);
-    if (op == GEMM_DGRAD) return launch_gemm_simple<float>(mode, a, K, 1, b, 1, N, M, N, K, e, s);
-    return launch_gemm_simple<float>(mode, a, 1, M, b, 1, N, M, N, K, e, s);
+    return launch_gemm_f32<float>(op, mode, a, b, M, N, K, e, s);
   }
 };
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 template <> struct GemmDispatch<bf16> {
-  // variant 0: library's choice; -1: force the simple kernel; >0: that MFMA configuration
+  // variant 0: library's choice; -1: force the fp32-product kernel; >0: that MFMA configuration
   static hipError_t run(int op, int mode, int variant, int64_t M, int64_t N, int64_t K, const bf16* a,
                         const bf16* b, const EpiArgs<bf16>& e, hipStream_t s, int splits = 1) {
     const int64_t lda = (op == GEMM_WGRAD) ? M : K;
@@ -273,9 +271,7 @@ template <> struct GemmDispatch<bf16> {
       return launch_gemm_dma(op, mode, v, a, lda, b, ldb, M, N, K, e, s, splits);
     }
     if (splits != 1 || v != -1) return hipErrorInvalidConfiguration;
-    if (op == GEMM_FWD) return launch_gemm_simple<bf16>(mode, a, K, 1, b, K, 1, M, N, K, e, s);
-    if (op == GEMM_DGRAD) return launch_gemm_simple<bf16>(mode, a, K, 1, b, 1, N, M, N, K, e, s);
-    return launch_gemm_simple<bf16>(mode, a, 1, M, b, 1, N, M, N, K, e, s);
+    return launch_gemm_f32<bf16>(op, mode, a, b, M, N, K, e, s);
   }
 };
 
