@@ -48,7 +48,14 @@ typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 // of 256 B, which is free of bank conflicts whether the LDS serves 16 or 32 lanes of such a read at once.
 __device__ __forceinline__ constexpr int dg_tr_swizzle(int k) { return ((k & 1) * 6) ^ (((k >> 1) & 1) * 12); }
 
-template <int ROWS, int NW, bool KMAJOR>
+//
+// EDGE: the operand's rows or its reduction may end inside the tile.  Rows past the end repeat the last one (k-major) or
+// read the next k-row (m/n-major); they only reach outputs that are not stored.  k past the end must read as zero in
+// both operands (a foreign value there could be a NaN): it lies past the buffer's extent (m/n-major), and in a k-major
+// operand the last k-tile uses offsets that put every chunk past the end of its row outside the buffer.
+// Only loads of the last k-tile can lie outside as a whole (see the wait before the barrier).
+constexpr uint32_t DG_OUTSIDE = 0x80000000u;   // past the extent of any EDGE operand (below 2 GiB), whatever k-tile is added
+template <int ROWS, int NW, bool KMAJOR, bool EDGE = false>
 struct DgLoader {
   static constexpr int NINS = ROWS * DG_BK * 2 / 1024;  // wave-level 1 KB loads per tile
   static constexpr int LPT = NINS / NW;                  // per wave
@@ -58,17 +65,24 @@ struct DgLoader {
   uint32_t extent;
   uint32_t voff[LPT];           // per-lane byte offset of each of this wave's loads (k-tile 0)
   uint32_t step;                // bytes to advance per k-tile
+  uint32_t vtail[EDGE && KMAJOR ? LPT : 1];   // voff in the last k-tile
+  int last_kt;
 
-  __device__ __forceinline__ void init(const bf16* g, int64_t ld, int64_t row0, int wave, int lane, uint32_t extent_bytes) {
+  // rows: of the whole operand; k_tail: k in the last k-tile (1..64), which has number last_tile
+  __device__ __forceinline__ void init(const bf16* g, int64_t ld, int64_t row0, int wave, int lane, uint32_t extent_bytes,
+                                       int64_t rows, int k_tail, int last_tile) {
     base = g;
     extent = extent_bytes;
+    last_kt = last_tile;
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
       const int q = wave + i * NW;
       if (KMAJOR) {
         const int row = q * 8 + (lane >> 3), p = lane & 7;
         const int c = p ^ ((row ^ (row >> 3)) & 7);
-        voff[i] = (uint32_t)(((row0 + row) * ld + c * 8) * 2);
+        const int64_t grow = EDGE && row0 + row >= rows ? rows - 1 : row0 + row;
+        voff[i] = (uint32_t)((grow * ld + c * 8) * 2);
+        if constexpr (EDGE) vtail[i] = c * 8 < k_tail ? voff[i] : DG_OUTSIDE;
       } else {
         constexpr int CPR = ROWS / 8;  // chunks per k-row
         const int slot = q * 64 + lane, krow = slot / CPR, p = slot % CPR;
@@ -79,6 +93,10 @@ struct DgLoader {
     step = (uint32_t)((KMAJOR ? (int64_t)DG_BK : (int64_t)DG_BK * ld) * 2);
   }
 
+  __device__ __forceinline__ uint32_t offset(int i, int kt) const {
+    if constexpr (EDGE && KMAJOR) return kt == last_kt ? vtail[i] : voff[i];
+    return voff[i];
+  }
   __device__ __forceinline__ void issue(bf16* lds_tile, int kt, int wave) const {
 #if defined(__HIP_DEVICE_COMPILE__)  // the buffer builtins exist in the device pass only
     const uint32_t soff = (uint32_t)kt * step;
@@ -86,7 +104,7 @@ struct DgLoader {
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
       const int q = wave + i * NW;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(lds_tile + q * 512), 16, voff[i], soff, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(lds_tile + q * 512), 16, offset(i, kt), soff, 0, 0);
     }
 #endif
   }
@@ -100,7 +118,7 @@ struct DgLoader {
     const uint32_t soff = (uint32_t)kt * step;
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(base), 0, live ? extent : 0u, 0x00020000);
     const int q = wave + I * NW;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(lds_tile + q * 512), 16, voff[I], live ? soff : 0u, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(lds_tile + q * 512), 16, offset(I, kt), live ? soff : 0u, 0, 0);
 #endif
   }
 };
@@ -236,9 +254,9 @@ struct DgInterleaveMask {
 // bf16 epilogue of one wave's (TM*32) x WN sub-tile whose first output is (row0, col0), through a
 // private LDS buffer of 32 rows x WN floats.  acc[i][j][r] is row m = lane%32 of the 32x32 block,
 // column n = 8*(r/4) + 4*(lane/32) + r%4.
-template <int MODE, int TM, int TN, int WN>
+template <int MODE, int TM, int TN, int WN, bool EDGE>
 __device__ __forceinline__ void dg_epilogue_bf16(floatx16 (&acc)[TM][TN], unsigned char* buf, const EpiArgs<bf16>& epi,
-                                                 int64_t row0, int64_t col0, int lane) {
+                                                 int64_t row0, int64_t col0, int lane, int64_t rows, int64_t cols) {
   constexpr int ROWB = WN * 4;              // bytes per staged fp32 row
   constexpr int LPR = WN / 8;               // lanes per output row (8 columns each)
   constexpr int RPI = 64 / LPR;             // rows per store instruction
@@ -261,7 +279,8 @@ __device__ __forceinline__ void dg_epilogue_bf16(floatx16 (&acc)[TM][TN], unsign
       const floatx4 lo = *reinterpret_cast<const floatx4*>(buf + r * ROWB + (((c0 & ~15) | ((c0 ^ r) & 15)) << 4));
       const floatx4 hi = *reinterpret_cast<const floatx4*>(buf + r * ROWB + ((((c0 + 1) & ~15) | (((c0 + 1) ^ r) & 15)) << 4));
       float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      gemm_epilogue8<MODE>(epi, row0 + i * 32 + r, col0 + rcol, v);
+      if (!EDGE || (row0 + i * 32 + r < rows && col0 + rcol < cols))   // (cols is a multiple of 8)
+        gemm_epilogue8<MODE>(epi, row0 + i * 32 + r, col0 + rcol, v);
     }
     __builtin_amdgcn_s_waitcnt(DG_WAIT_LGKM0);  // reads done before the next pass overwrites
   }
@@ -281,10 +300,13 @@ constexpr size_t dg_smem_bytes() {
 // see below); 1 = every wave sends its share one load at a time between its products, spread
 // over the three k-steps that follow that barrier, so that no wave sits at the texture
 // addresser's full queue while its products wait.
-template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, int MODE, int LS = 0>
+// EDGE: M, N and K need not be multiples of the tile (rows, cols and K are the true extents; rows of both operands are
+// whole 16-byte pieces).
+template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, int MODE, int LS = 0, bool EDGE = false>
 __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
     const bf16* __restrict__ a, int64_t lda, const bf16* __restrict__ b, int64_t ldb, int K,
-    int tiles_m, int tiles_n, EpiArgs<bf16> epi, int xcd_remap, int group) {
+    int tiles_m, int tiles_n, EpiArgs<bf16> epi, int xcd_remap, int group, int64_t rows, int64_t cols) {
+  static_assert(!EDGE || LS == 4, "the other load schedules count loads that may lie outside an EDGE operand");
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -328,11 +350,13 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
   const bool issuer = wave >= NW - NI;
   const int iw = wave - (NW - NI);
   const bool early = !SPLIT || wave < NW / 2;
-  DgLoader<BM, NI, A_KMAJOR> la;
-  DgLoader<BN, NI, B_KMAJOR> lb;
-  la.init(a, lda, m0, issuer ? iw : 0, lane, (uint32_t)((A_KMAJOR ? (int64_t)tiles_m * BM : (int64_t)K) * lda * 2));
-  lb.init(b, ldb, n0, issuer ? iw : 0, lane, (uint32_t)((B_KMAJOR ? (int64_t)tiles_n * BN : (int64_t)K) * ldb * 2));
-  constexpr int LPT = DgLoader<BM, NI, A_KMAJOR>::LPT + DgLoader<BN, NI, B_KMAJOR>::LPT;
+  DgLoader<BM, NI, A_KMAJOR, EDGE> la;
+  DgLoader<BN, NI, B_KMAJOR, EDGE> lb;
+  const int nkt = (K + DG_BK - 1) / DG_BK;   // k-tiles of the whole reduction
+  const int k_tail = K - (nkt - 1) * DG_BK;
+  la.init(a, lda, m0, issuer ? iw : 0, lane, (uint32_t)((A_KMAJOR ? (EDGE ? rows : (int64_t)tiles_m * BM) : (int64_t)K) * lda * 2), rows, k_tail, nkt - 1);
+  lb.init(b, ldb, n0, issuer ? iw : 0, lane, (uint32_t)((B_KMAJOR ? (EDGE ? cols : (int64_t)tiles_n * BN) : (int64_t)K) * ldb * 2), cols, k_tail, nkt - 1);
+  constexpr int LPT = DgLoader<BM, NI, A_KMAJOR, EDGE>::LPT + DgLoader<BN, NI, B_KMAJOR, EDGE>::LPT;
 
   floatx16 acc[TM][TN];
 #pragma unroll
@@ -343,15 +367,23 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   // gridDim.y splits of the reduction (EPI_STORE_F32 only): this workgroup owns k-tiles kt0 .. kt0+nk-1
-  const int nk = K / DG_BK / (int)gridDim.y;
-  const int kt0 = (int)blockIdx.y * nk;
+  int kt0 = 0, nk = nkt;
+  if constexpr (MODE == EPI_STORE_F32) {
+    kt0 = (int)(blockIdx.y * (unsigned)nkt / gridDim.y);
+    nk = (int)((blockIdx.y + 1) * (unsigned)nkt / gridDim.y) - kt0;
+  }
+  // (opaque: bounds rewritten in terms of K cost the unrolled loop its compile-time knowledge of kt + 2 < nk)
+  nk = __builtin_amdgcn_readfirstlane(nk);
+  // Whether the loads of this workgroup's k-tile `kt` retire in order, so that a wait may count them: it exists, and
+  // none of its loads lies outside the operand as a whole (a partly filled k-tile's may).
+  auto counted = [&](int kt) { return kt < nk && (!EDGE || k_tail == DG_BK || kt0 + kt != nkt - 1); };
   // LDS map.  LS 0, 1: two stages of [A tile | B tile].  LS 2: two stages of A, then three of B.
   constexpr int A_STRIDE = (LS >= 2) ? BM * DG_BK : STAGE_ELEMS;
   constexpr int B_STRIDE = (LS >= 2) ? BN * DG_BK : STAGE_ELEMS;
   constexpr int B_BASE = (LS >= 2) ? 2 * BM * DG_BK : BM * DG_BK;
   // LS >= 2: which of a wave's loads (A's LA first, then B's LB) go out in the k-step after the barrier
   // ([0, C3)), and in k-steps 0, 1, 2 of the next tile ([C3, C0), [C0, C1), [C1, LA+LB)).
-  constexpr int LA_ = DgLoader<BM, NI, A_KMAJOR>::LPT, LB_ = DgLoader<BN, NI, B_KMAJOR>::LPT;
+  constexpr int LA_ = DgLoader<BM, NI, A_KMAJOR, EDGE>::LPT, LB_ = DgLoader<BN, NI, B_KMAJOR, EDGE>::LPT;
   // (Halves of A right after the barrier and in k-step 0, halves of B in k-steps 1 and 2; sending all of A
   // right after the barrier, or three quarters of it, measured the same to half a percent.)
   constexpr int C3 = LA_ / 2, C0 = LA_, C1 = LA_ + LB_ / 2;
@@ -360,7 +392,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
   if constexpr (LS == 1) {
     // tile 0 whole; of tile 1 only the loads that in the steady state go out right after a
     // barrier -- the k-loop sends the rest during tile 0's first two k-steps, as for any tile
-    constexpr int LA1 = DgLoader<BM, NI, A_KMAJOR>::LPT, N31 = (LPT + 2) / 3;
+    constexpr int LA1 = DgLoader<BM, NI, A_KMAJOR, EDGE>::LPT, N31 = (LPT + 2) / 3;
     la.issue(smem, kt0, iw);
     lb.issue(smem + BM * DG_BK, kt0, iw);
     dg_static_for<N31>([&](auto j_tag) {
@@ -379,7 +411,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
     lb.issue(b_stage(0), kt0, iw);
     dg_static_for<LB_>([&](auto j_tag) { lb.template issue_one<decltype(j_tag)::value>(b_stage(1), kt0 + 1, iw, nk > 1); });
     dg_static_for<C3>([&](auto j_tag) { la.template issue_one<decltype(j_tag)::value>(a_stage(1), kt0 + 1, iw, nk > 1); });
-    if (nk > 1) __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(LB_ + C3)); else __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(0));
+    if (counted(1)) __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(LB_ + C3)); else __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(0));
   } else if (issuer) {
     la.issue(smem, kt0, iw);
     lb.issue(smem + BM * DG_BK, kt0, iw);
@@ -468,7 +500,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
   //     read: every k-step carries the same number of loads (A's halves in the k-step after the
   //     barrier and the one after it, B's halves in the other two) and the path from L2 into LDS,
   //     which is what bounds a 256x256 tile, never runs dry between barriers.
-  constexpr int LA = DgLoader<BM, NI, A_KMAJOR>::LPT, LB = DgLoader<BN, NI, B_KMAJOR>::LPT, LT = LPT;
+  constexpr int LA = DgLoader<BM, NI, A_KMAJOR, EDGE>::LPT, LB = DgLoader<BN, NI, B_KMAJOR, EDGE>::LPT, LT = LPT;
   constexpr int N3 = (LT + 2) / 3, N0 = (LT - N3 + 1) / 2;
   auto kstep = [&](auto cur_tag, const bf16* ta, const bf16* tb, auto ks_next, auto loads, bf16* lda_stage, int lda_kt,
                    bool lda_live, bf16* ldb_stage, int ldb_kt, bool ldb_live) {
@@ -539,7 +571,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
       kstep(S0{}, ca, cb, KS1{}, DgLoads<C3, C0>{}, na, kt0 + kt + 1, live1, nnb, kt0 + kt + 2, live2);
       kstep(S1{}, ca, cb, KS2{}, DgLoads<C0, C1>{}, na, 0, false, nnb, kt0 + kt + 2, live2);
       kstep(S0{}, ca, cb, KS3{}, DgLoads<C1, LT>{}, na, 0, false, nnb, kt0 + kt + 2, live2);
-      if (live2) __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(LB) & DG_WAIT_LGKM0);   // (see the loop below)
+      if (counted(kt + 2)) __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(LB) & DG_WAIT_LGKM0);   // (see the loop below)
       else __builtin_amdgcn_s_waitcnt(DG_WAIT_VM0_LGKM0);
       __builtin_amdgcn_s_barrier();
       kstep(S1{}, na, nb, KS0{}, DgLoads<0, C3>{}, ca, kt0 + kt + 2, live2, nnb, 0, false);
@@ -608,14 +640,20 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
     unsigned char* mybuf = dg_smem + wave * (2 * PASS_BYTES);
     float* cbase = epi.out_f32 + (MODE == EPI_STORE_F32 ? (int64_t)blockIdx.y * epi.split_stride : 0) +
                    (m0 + wm * WM) * epi.ldc + n0 + wn * WN;
+    // from the sub-tile's first row and column to the end of the matrix; both may be negative when it lies outside
+    const int64_t rows_left = rows - (m0 + wm * WM), cols_left = cols - (n0 + wn * WN);
     auto issue_pass = [&](int pass) {
       unsigned char* buf = mybuf + (pass & 1) * PASS_BYTES;
 #pragma unroll
       for (int q = 0; q < NINS; ++q) {
         const int slot = q * 64 + lane, row = slot / CPR, pc = slot % CPR;
         const int c = pc ^ (row & 15);
-        __builtin_amdgcn_global_load_lds((glb_ptr_t)(cbase + (int64_t)(pass * 32 + row) * epi.ldc + c * 4),
-                                         (lds_ptr_t)(buf + q * 1024), 16, 0, 0);
+        int64_t gr = pass * 32 + row, gc = c * 4;
+        if constexpr (EDGE) {   // outside the matrix: some element inside it (what is loaded there is not stored)
+          gr = gr < rows_left ? gr : rows_left - 1;
+          gc = gc < cols_left ? gc : cols_left - 4;
+        }
+        __builtin_amdgcn_global_load_lds((glb_ptr_t)(cbase + gr * epi.ldc + gc), (lds_ptr_t)(buf + q * 1024), 16, 0, 0);
       }
     };
     if constexpr (MODE == EPI_ACCUM_F32) {
@@ -639,7 +677,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
             v = *reinterpret_cast<const floatx4*>(buf + frow * (WN * 4) + ((c ^ (frow & 15)) << 4));
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] += acc[i][j][g * 4 + e];
-          *reinterpret_cast<floatx4*>(crow + c * 4) = v;
+          if (!EDGE || (i * 32 + frow < rows_left && c * 4 < cols_left)) *reinterpret_cast<floatx4*>(crow + c * 4) = v;
         }
       if (MODE == EPI_ACCUM_F32 && i + 2 < TM) {
         __builtin_amdgcn_s_waitcnt(DG_WAIT_LGKM0);  // this buffer's LDS reads are done before it is refilled
@@ -657,23 +695,24 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
     static_assert(NW * 32 * WN * 4 <= dg_smem_bytes<BM, BN, WGM, WGN, MODE, LS>(), "epilogue staging must fit the workgroup's LDS");
     __builtin_amdgcn_s_waitcnt(DG_WAIT_VM0_LGKM0);
     __builtin_amdgcn_s_barrier();             // every wave is done with the operand stages
-    dg_epilogue_bf16<MODE, TM, TN, WN>(acc, dg_smem + wave * (32 * WN * 4), epi, m0 + wm * WM, n0 + wn * WN, lane);
+    dg_epilogue_bf16<MODE, TM, TN, WN, EDGE>(acc, dg_smem + wave * (32 * WN * 4), epi, m0 + wm * WM, n0 + wn * WN, lane, rows, cols);
   }
 }
 
 // ---------------------------------------------------------------------------
-// host side.  Variant ids (0 is "the library's choice", -1 the plain FMA kernel):
+// host side.  Variant ids (0 is "the library's choice", -1 the fp32-product kernel):
 //   5: 256x256 tile, 8 waves   6: 256x256, 4 waves   7: 128x128, 4 waves   8: 256x128, 4 waves
 //   9: as 5 with the spread load schedule   10: as 7 with the spread load schedule   11: as 6 with it
 //   12: as 5 with three stages of B and loads in every k-step   13: as 6 with that   14: as 7 with that
 //   15: 128x256, 8 waves, that schedule   16: 256x128, 8 waves, that schedule
 //   17: as 13 with the k-tile loop unrolled over the stage period   18: as 12 with that
 //   19, 20, 21: as 14, 15, 16 with that
+//   22, 23: as 19, 18 for sizes that are no multiples of the tile (EDGE)
 // ---------------------------------------------------------------------------
 inline bool dg_variant_tile(int variant, GemmTile* t) {
   switch (variant) {
-    case 5: case 6: case 9: case 11: case 12: case 13: case 17: case 18: *t = {256, 256}; return true;
-    case 7: case 10: case 14: case 19: *t = {128, 128}; return true;
+    case 5: case 6: case 9: case 11: case 12: case 13: case 17: case 18: case 23: *t = {256, 256}; return true;
+    case 7: case 10: case 14: case 19: case 22: *t = {128, 128}; return true;
     case 8: case 16: case 21: *t = {256, 128}; return true;
     case 15: case 20: *t = {128, 256}; return true;
     default: return false;
@@ -685,19 +724,31 @@ inline bool dg_shape_ok(int variant, int64_t M, int64_t N, int64_t K, int64_t ld
   if (!dg_variant_tile(variant, &t)) return false;
   // operands are addressed with 32-bit byte offsets from their base (buffer loads)
   const int64_t a_bytes = (M > K ? M : K) * lda * 2, b_bytes = (N > K ? N : K) * ldb * 2;
+  if (variant >= 22) {   // EDGE: rows of both operands and of the output are whole 16-byte pieces; offsets below DG_OUTSIDE
+    const int64_t pad = 2 * 256 * (lda > ldb ? lda : ldb);
+    return lda % 8 == 0 && ldb % 8 == 0 && N % 8 == 0 && K >= 1 && ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) < (1ll << 31) &&
+           a_bytes + pad < DG_OUTSIDE && b_bytes + pad < DG_OUTSIDE;
+  }
   return M % t.bm == 0 && N % t.bn == 0 && K % DG_BK == 0 && K >= DG_BK && lda % 8 == 0 && ldb % 8 == 0 &&
          (M / t.bm) * (N / t.bn) < (1ll << 31) && a_bytes < (1ll << 32) && b_bytes < (1ll << 32);
 }
 
 // Picks between the 256x256 (one workgroup per CU) and 128x128 (two per CU) tiles by the
-// number of full-chip rounds each needs; 0 if neither fits the shape.
+// number of full-chip rounds each needs; 0 if neither fits the shape.  Sizes that are no multiples of 128 (64 for K)
+// take the EDGE form of the same two tiles, if their rows are whole 16-byte pieces and the product is larger than one
+// tile (of a single one the fp32-product kernel makes 16 small workgroups; both take the launch's time).  Against that
+// kernel (us, forward / dgrad / wgrad): 2000x1600x1600 184 / 161 / 147 -> 18 / 18 / 22 on 128x128 (34 on 256x256),
+// 2000x6400x1600 495 / 481 / 509 -> 42 / 43 / 54 on 256x256 (50 on 128x128).  At sizes both forms take the plain one is
+// 1-5 % faster.
 inline int dg_choose_variant(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
   const bool ok5 = dg_shape_ok(5, M, N, K, lda, ldb), ok7 = dg_shape_ok(7, M, N, K, lda, ldb);
-  if (!ok7) return 0;  // anything divisible by 256 is divisible by 128
-  if (!ok5) return 7;
-  const int64_t t5 = (M / 256) * (N / 256), t7 = (M / 128) * (N / 128);
+  const bool edge = !ok7;   // anything divisible by 256 is divisible by 128
+  if (edge && !(dg_shape_ok(22, M, N, K, lda, ldb) && (M > 128 || N > 128))) return 0;
+  if (ok7 && !ok5) return 7;
+  const int64_t t5 = ((M + 255) / 256) * ((N + 255) / 256), t7 = ((M + 127) / 128) * ((N + 127) / 128);
   const double cost5 = (double)((t5 + 255) / 256) * 4.0 / 1.15;
   const double cost7 = (double)((t7 + 511) / 512) * 2.0;
+  if (edge) return cost5 <= cost7 ? 23 : 22;
   return cost5 <= cost7 ? 5 : 7;
 }
 
@@ -750,10 +801,12 @@ inline int dg_wgrad_splits(int64_t M, int64_t N, int64_t K) {
   const int v = dg_choose_variant(M, N, K, M, N);
   GemmTile t;
   if (v == 0 || !dg_variant_tile(v, &t)) return 1;
-  const int64_t tiles = (M / t.bm) * (N / t.bn), slots = (v == 5) ? 256 : 512, nk = K / DG_BK;
+  const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), slots = t.bm == 256 ? 256 : 512;
+  const int64_t nk = (K + DG_BK - 1) / DG_BK;
   int64_t s = slots / tiles;
   if (s > 8) s = 8;
-  while (s > 1 && (nk % s != 0 || nk / s < 8)) --s;
+  // plain tiles take equal parts only; the EDGE form's may differ by a k-tile
+  while (s > 1 && ((v < 22 && nk % s != 0) || nk / s < 8)) --s;
   return (int)(s < 1 ? 1 : s);
 }
 

@@ -7,21 +7,21 @@
 
 namespace varuna {
 
-template <int BM, int BN, int WGM, int WGN, bool AK, bool BK_, int MODE, int LS = 0>
+template <int BM, int BN, int WGM, int WGN, bool AK, bool BK_, int MODE, int LS = 0, bool EDGE = false>
 inline hipError_t dg_launch_one(const bf16* a, int64_t lda, const bf16* b, int64_t ldb, int64_t M, int64_t N,
                                 int64_t K, const EpiArgs<bf16>& epi, int splits, hipStream_t st) {
-  auto kern = gemm_dma_kernel<BM, BN, WGM, WGN, AK, BK_, MODE, LS>;
+  auto kern = gemm_dma_kernel<BM, BN, WGM, WGN, AK, BK_, MODE, LS, EDGE>;
   constexpr size_t smem = dg_smem_bytes<BM, BN, WGM, WGN, MODE, LS>();
   static_assert(smem <= 160 * 1024, "one workgroup's LDS");
   // the first call raises the kernel's dynamic LDS limit (thread-safe: initialisation of a local static)
   static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (attr_err != hipSuccess) return attr_err;
-  const int tm = (int)(M / BM), tn = (int)(N / BN);
+  const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
   constexpr int xcd_remap = 1, group = 8;   // tile order: contiguous range per XCD, walked in groups of 8 tile rows
-  if (splits < 1 || (MODE != EPI_STORE_F32 && splits != 1) || (K / DG_BK) % splits != 0) return hipErrorInvalidValue;
+  if (splits < 1 || (MODE != EPI_STORE_F32 && splits != 1) || (K + DG_BK - 1) / DG_BK < splits) return hipErrorInvalidValue;
   hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn), (unsigned)splits), dim3(WGM * WGN * kWave), smem, st, a, lda, b, ldb,
-                     (int)K, tm, tn, epi, xcd_remap, group);
+                     (int)K, tm, tn, epi, xcd_remap, group, M, N);
   return hipGetLastError();
 }
 
@@ -46,6 +46,8 @@ inline hipError_t dg_launch_variant(int variant, const bf16* a, int64_t lda, con
     case 19: return dg_launch_one<128, 128, 2, 2, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
     case 20: return dg_launch_one<128, 256, 2, 4, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
     case 21: return dg_launch_one<256, 128, 4, 2, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
+    case 22: return dg_launch_one<128, 128, 2, 2, AK, BK_, MODE, 4, true>(a, lda, b, ldb, M, N, K, epi, splits, st);
+    case 23: return dg_launch_one<256, 256, 2, 4, AK, BK_, MODE, 4, true>(a, lda, b, ldb, M, N, K, epi, splits, st);
     default: return hipErrorInvalidValue;
   }
 }
