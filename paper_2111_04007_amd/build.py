@@ -11,7 +11,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libvaruna_stage.so")
 SOURCES = [  # compiled side by side
     os.path.join(HERE, "csrc", n) for n in ("gemm_fwd.hip", "gemm_dgrad.hip", "gemm_wgrad.hip", "gemm_f32.hip",
-                                            "gemm_f32_bf16.hip", "attention.hip", "stage.hip")
+                                            "gemm_f32_bf16.hip", "attention.hip",
+                                            "attention_edge.hip", "stage.hip")
 ]
 
 HIPCC_FLAGS = [

@@ -1,6 +1,7 @@
 // bf16 MFMA flash-style attention for gfx950: forward, and a two-kernel
 // deterministic backward (no atomics).  Head dim D in {64, 96, 128}, sequence
-// length a multiple of 128.  qkv is [b*s, 3h] (Q | K | V column blocks, head j at
+// length a multiple of 128; with EDGE any sequence length and any head dim d that
+// is a multiple of 8, in the next D of {32, 64, 96, 128}.  qkv is [b*s, 3h] (Q | K | V column blocks, head j at
 // column j*D of each), ctx / dctx are [b*s, h], lse / delta are [b, heads, s] fp32.
 //
 // All three kernels keep two 64-row tiles in LDS (rows of D values, padded pitch)
@@ -30,11 +31,11 @@ typedef short at_shortx4 __attribute__((ext_vector_type(4)));
 
 template <int D>
 struct AttnCfg {
-  static_assert(D == 64 || D == 96 || D == 128, "head dim");
-  // Row pitch in elements: pitch bytes = 13*16 (D=64) or 19*16 (D=96,128).  An odd number
+  static_assert(D == 32 || D == 64 || D == 96 || D == 128, "head dim");
+  // Row pitch in elements: pitch bytes = 7*16 (D=32), 13*16 (D=64) or 19*16 (D=96,128).  An odd number
   // of 16-byte units spreads 16 consecutive rows over all banks for ds_read_b128, and
   // 4 consecutive rows' 32-byte segments do not overlap for the transposing reads.
-  static constexpr int PITCH = (D == 64) ? 104 : 152;
+  static constexpr int PITCH = D == 32 ? 56 : (D == 64 ? 104 : 152);
   static constexpr int CH = D / 8;             // 16-byte chunks per row
   static constexpr int CPT = 64 * CH / 256;    // chunks per thread for a 64-row tile, 256 threads
   static constexpr int TILE = 64 * PITCH;      // elements per LDS tile
@@ -42,25 +43,43 @@ struct AttnCfg {
   static constexpr int DB = D / 32;            // 32-wide blocks of the head dim
 };
 
-// 64 x D tile: global -> registers -> LDS, 256 threads.
-template <int D>
+// 64 x D tile: global -> registers -> LDS, 256 threads.  EDGE: only `rows` rows and `cols` columns exist; the rest of the
+// tile is zero.  What lies outside is loaded from some element inside and replaced on the way into LDS, so that
+// there is no branch around the loads.
+template <int D, bool EDGE>
 struct AttnTileRegs {
   bf16x8 v[AttnCfg<D>::CPT];
-  __device__ __forceinline__ void load(const bf16* __restrict__ base, int64_t row_stride, int tid) {
+  __device__ __forceinline__ void load(const bf16* __restrict__ base, int64_t row_stride, int tid, int rows, int cols) {
 #pragma unroll
     for (int i = 0; i < AttnCfg<D>::CPT; ++i) {
       const int id = tid + i * 256, r = id / AttnCfg<D>::CH, c = id % AttnCfg<D>::CH;
-      v[i] = *reinterpret_cast<const bf16x8*>(base + r * row_stride + c * 8);
+      if constexpr (EDGE) v[i] = *reinterpret_cast<const bf16x8*>(base + (r < rows ? r : 0) * row_stride + (c * 8 < cols ? c * 8 : 0));
+      else v[i] = *reinterpret_cast<const bf16x8*>(base + r * row_stride + c * 8);
     }
   }
-  __device__ __forceinline__ void store(bf16* __restrict__ lds, int tid) const {
+  __device__ __forceinline__ void store(bf16* __restrict__ lds, int tid, int rows, int cols) const {
 #pragma unroll
     for (int i = 0; i < AttnCfg<D>::CPT; ++i) {
       const int id = tid + i * 256, r = id / AttnCfg<D>::CH, c = id % AttnCfg<D>::CH;
-      *reinterpret_cast<bf16x8*>(lds + r * AttnCfg<D>::PITCH + c * 8) = v[i];
+      bf16x8 x = v[i];
+      if constexpr (EDGE) {
+        if (!(r < rows && c * 8 < cols)) x = bf16x8{};
+      }
+      *reinterpret_cast<bf16x8*>(lds + r * AttnCfg<D>::PITCH + c * 8) = x;
     }
   }
 };
+
+// Columns 16t + 8*(lane/32) .. +7 of one row of `cols` columns for every k-step t; zero past the end of the row.
+template <int D, bool EDGE>
+__device__ __forceinline__ void at_load_row(bf16x8 (&f)[AttnCfg<D>::KD], const bf16* __restrict__ row, int hf, int cols) {
+#pragma unroll
+  for (int t = 0; t < AttnCfg<D>::KD; ++t) {
+    const int c = 16 * t + 8 * hf;
+    if (EDGE && c >= cols) f[t] = bf16x8{};
+    else f[t] = *reinterpret_cast<const bf16x8*>(row + c);
+  }
+}
 
 // Row operand from an LDS tile: row (row_base + lane%32), columns col0 + 8*(lane/32) .. +7.
 template <int D>
@@ -122,6 +141,13 @@ __device__ __forceinline__ void at_drop_row_words(const DropArgs& drop, uint32_t
   }
 }
 
+// The same words without the quad exchange, for sequence lengths that are no multiple of 4 (the four lanes of a quad
+// then straddle two rows of patches).
+__device__ __forceinline__ void at_drop_row_words_any(const DropArgs& drop, uint32_t row, uint32_t col_patch0, uint32_t out[4]) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) out[g] = drop_row_word(drop, row, col_patch0 + 2u * (uint32_t)g);
+}
+
 __device__ __forceinline__ bf16x8 at_pack8(const float* p) {
   bf16x8 r;
 #pragma unroll
@@ -129,13 +155,23 @@ __device__ __forceinline__ bf16x8 at_pack8(const float* p) {
   return r;
 }
 
+// What the rounding in at_pack8 left over.  The EDGE kernels multiply probabilities and score gradients in two parts, p =
+// bf16(p) + bf16(p - bf16(p)), which keeps 16 bits of mantissa: the shapes they serve had fp32 factors there (error
+// of a bf16 result against 64 bits unchanged: 2.1e-3 forward, 2.4e-3 backward, both the rounding of the output).
+__device__ __forceinline__ bf16x8 at_pack8_rest(const float* p, const bf16x8& hi) {
+  bf16x8 r;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) r[i] = (bf16)(p[i] - (float)hi[i]);
+  return r;
+}
+
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-template <int D, bool CAUSAL, bool DROP>
+template <int D, bool CAUSAL, bool DROP, bool EDGE>
 __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ ctx,
                                                             float* __restrict__ lse, int s, int heads,
-                                                            float scale_log2e, DropArgs drop) {
+                                                            float scale_log2e, DropArgs drop, int d) {
   using C = AttnCfg<D>;
   __shared__ __attribute__((aligned(16))) bf16 sk[C::TILE];
   __shared__ __attribute__((aligned(16))) bf16 sv[C::TILE];
@@ -146,16 +182,15 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
   // the 8 XCDs, all query blocks of one head (same x mod 8) share one XCD's L2 for K and V.
   const int qb = gridDim.y - 1 - blockIdx.y;
   const int head = blockIdx.x % heads, bi = blockIdx.x / heads;
-  const int h = heads * D;
+  const int cols = EDGE ? d : D, h = heads * cols;
   const int64_t ld = 3 * (int64_t)h;
-  const bf16* base = qkv + (int64_t)bi * s * ld + head * D;
+  const bf16* base = qkv + (int64_t)bi * s * ld + head * cols;
   const int q0 = qb * 128, qw = q0 + wave * 32;  // this wave's first query
   const int query = qw + (lane & 31);
 
+  const int qrow = EDGE && query >= s ? s - 1 : query;   // queries past the end repeat the last one and are not stored
   bf16x8 qf[C::KD];
-#pragma unroll
-  for (int t = 0; t < C::KD; ++t)
-    qf[t] = *reinterpret_cast<const bf16x8*>(base + (int64_t)query * ld + 16 * t + 8 * hf);
+  at_load_row<D, EDGE>(qf, base + (int64_t)qrow * ld, hf, cols);
 
   floatx16 o[C::DB];
 #pragma unroll
@@ -164,18 +199,18 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
     for (int r = 0; r < 16; ++r) o[i][r] = 0.f;
   float m = -INFINITY, l = 0.f;
 
-  const int nkb = CAUSAL ? (q0 + 128) / 64 : s / 64;
-  AttnTileRegs<D> rk, rv;
-  rk.load(base + h, ld, tid);
-  rv.load(base + 2 * h, ld, tid);
+  const int nkt = (s + 63) / 64, nkb = CAUSAL && (!EDGE || (q0 + 128) / 64 < nkt) ? (q0 + 128) / 64 : nkt;
+  AttnTileRegs<D, EDGE> rk, rv;
+  rk.load(base + h, ld, tid, s, cols);
+  rv.load(base + 2 * h, ld, tid, s, cols);
   for (int kb = 0; kb < nkb; ++kb) {
     if (kb) __syncthreads();
-    rk.store(sk, tid);
-    rv.store(sv, tid);
+    rk.store(sk, tid, s - kb * 64, cols);
+    rv.store(sv, tid, s - kb * 64, cols);
     __syncthreads();
     if (kb + 1 < nkb) {
-      rk.load(base + (int64_t)(kb + 1) * 64 * ld + h, ld, tid);
-      rv.load(base + (int64_t)(kb + 1) * 64 * ld + 2 * h, ld, tid);
+      rk.load(base + (int64_t)(kb + 1) * 64 * ld + h, ld, tid, s - (kb + 1) * 64, cols);
+      rv.load(base + (int64_t)(kb + 1) * 64 * ld + 2 * h, ld, tid, s - (kb + 1) * 64, cols);
     }
     const int k0 = kb * 64;
     if (CAUSAL && k0 > qw + 31) continue;  // whole key block is in this wave's future
@@ -206,13 +241,13 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
     // Only key blocks that straddle the diagonal pay for the mask.
     float p[2][16];
     float mx = -INFINITY;
-    if (CAUSAL && k0 + 63 > qw) {
+    if ((CAUSAL && k0 + 63 > qw) || (EDGE && k0 + 64 > s)) {
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int key = k0 + sb * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
-          if (key > query) sc[sb][r] = -INFINITY;
+          if ((CAUSAL && key > query) || (EDGE && key >= s)) sc[sb][r] = -INFINITY;
         }
     }
 #pragma unroll
@@ -253,7 +288,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb) {
         uint32_t w[4];
-        at_drop_row_words(drop, drow >> 2, (uint32_t)(k0 + sb * 32 + 4 * hf) >> 2, lane, w);
+        if (EDGE && (s & 3)) at_drop_row_words_any(drop, drow, (uint32_t)(k0 + sb * 32 + 4 * hf) >> 2, w);
+        else at_drop_row_words(drop, drow >> 2, (uint32_t)(k0 + sb * 32 + 4 * hf) >> 2, lane, w);
 #pragma unroll
         for (int g = 0; g < 4; ++g)
 #pragma unroll
@@ -270,6 +306,12 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
 #pragma unroll
         for (int db = 0; db < C::DB; ++db)
           o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vtr[t][db], pf, o[db], 0, 0, 0);
+        if constexpr (EDGE) {
+          const bf16x8 pl = at_pack8_rest(&p[sb][8 * t], pf);
+#pragma unroll
+          for (int db = 0; db < C::DB; ++db)
+            o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vtr[t][db], pl, o[db], 0, 0, 0);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
       if (sb == 0) {  // the second 32 keys' fragments, into the same registers
@@ -283,12 +325,14 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
   }
   l += __shfl_xor(l, 32, 64);
   const float inv = (DROP ? drop.scale : 1.0f) / l;
+  if (EDGE && query >= s) return;
   if (lse && hf == 0) lse[((int64_t)bi * heads + head) * s + query] = (m + log2f(l)) * 0.6931471805599453f;
-  bf16* crow = ctx + ((int64_t)bi * s + query) * h + head * D;
+  bf16* crow = ctx + ((int64_t)bi * s + query) * h + head * cols;
 #pragma unroll
   for (int db = 0; db < C::DB; ++db)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
+      if (EDGE && db * 32 + 8 * g >= cols) continue;
       bf16x4 v;
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = (bf16)(o[db][4 * g + e] * inv);
@@ -299,38 +343,41 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
 // ---------------------------------------------------------------------------
 // backward, query side: dQ and delta
 // ---------------------------------------------------------------------------
-template <int D, bool CAUSAL, bool DROP>
+template <int D, bool CAUSAL, bool DROP, bool EDGE>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ ctx,
                                                                const float* __restrict__ lse,
                                                                const bf16* __restrict__ dctx, bf16* __restrict__ dqkv,
                                                                float* __restrict__ delta, int s, int heads,
-                                                               float scale, float scale_log2e, DropArgs drop) {
+                                                               float scale, float scale_log2e, DropArgs drop, int d) {
   using C = AttnCfg<D>;
   __shared__ __attribute__((aligned(16))) bf16 sk[C::TILE];
   __shared__ __attribute__((aligned(16))) bf16 sv[C::TILE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hf = lane >> 5;
   const int qb = gridDim.y - 1 - blockIdx.y;   // grid as in the forward kernel: long query blocks of every head first
   const int head = blockIdx.x % heads, bi = blockIdx.x / heads;
-  const int h = heads * D;
+  const int cols = EDGE ? d : D, h = heads * cols;
   const int64_t ld = 3 * (int64_t)h;
-  const bf16* base = qkv + (int64_t)bi * s * ld + head * D;
+  const bf16* base = qkv + (int64_t)bi * s * ld + head * cols;
   const int q0 = qb * 128, qw = q0 + wave * 32;
   const int query = qw + (lane & 31);
-  const int64_t orow = ((int64_t)bi * s + query) * h + head * D;
-  const int64_t sidx = ((int64_t)bi * heads + head) * s + query;
+  const int qrow = EDGE && query >= s ? s - 1 : query;   // queries past the end repeat the last one and store nothing
+  const int64_t orow = ((int64_t)bi * s + qrow) * h + head * cols;
+  const int64_t sidx = ((int64_t)bi * heads + head) * s + qrow;
 
   bf16x8 qf[C::KD], gf[C::KD];
   float dl = 0.f;
+  {
+    bf16x8 of[C::KD];
+    at_load_row<D, EDGE>(qf, base + (int64_t)qrow * ld, hf, cols);
+    at_load_row<D, EDGE>(gf, dctx + orow, hf, cols);
+    at_load_row<D, EDGE>(of, ctx + orow, hf, cols);
 #pragma unroll
-  for (int t = 0; t < C::KD; ++t) {
-    qf[t] = *reinterpret_cast<const bf16x8*>(base + (int64_t)query * ld + 16 * t + 8 * hf);
-    gf[t] = *reinterpret_cast<const bf16x8*>(dctx + orow + 16 * t + 8 * hf);
-    const bf16x8 of = *reinterpret_cast<const bf16x8*>(ctx + orow + 16 * t + 8 * hf);
+    for (int t = 0; t < C::KD; ++t)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) dl += (float)gf[t][e] * (float)of[e];
+      for (int e = 0; e < 8; ++e) dl += (float)gf[t][e] * (float)of[t][e];
   }
   dl += __shfl_xor(dl, 32, 64);
-  if (hf == 0) delta[sidx] = dl;
+  if (hf == 0 && (!EDGE || query < s)) delta[sidx] = dl;
   const float l2 = lse[sidx] * 1.4426950408889634f;  // log-sum-exp in base 2
 
   floatx16 dq[C::DB];
@@ -339,23 +386,23 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
 #pragma unroll
     for (int r = 0; r < 16; ++r) dq[i][r] = 0.f;
 
-  const int nkb = CAUSAL ? (q0 + 128) / 64 : s / 64;
-  AttnTileRegs<D> rk, rv;
-  rk.load(base + h, ld, tid);
-  rv.load(base + 2 * h, ld, tid);
+  const int nkt = (s + 63) / 64, nkb = CAUSAL && (!EDGE || (q0 + 128) / 64 < nkt) ? (q0 + 128) / 64 : nkt;
+  AttnTileRegs<D, EDGE> rk, rv;
+  rk.load(base + h, ld, tid, s, cols);
+  rv.load(base + 2 * h, ld, tid, s, cols);
   for (int kb = 0; kb < nkb; ++kb) {
     if (kb) __syncthreads();
-    rk.store(sk, tid);
-    rv.store(sv, tid);
+    rk.store(sk, tid, s - kb * 64, cols);
+    rv.store(sv, tid, s - kb * 64, cols);
     __syncthreads();
     if (kb + 1 < nkb) {
-      rk.load(base + (int64_t)(kb + 1) * 64 * ld + h, ld, tid);
-      rv.load(base + (int64_t)(kb + 1) * 64 * ld + 2 * h, ld, tid);
+      rk.load(base + (int64_t)(kb + 1) * 64 * ld + h, ld, tid, s - (kb + 1) * 64, cols);
+      rv.load(base + (int64_t)(kb + 1) * 64 * ld + 2 * h, ld, tid, s - (kb + 1) * 64, cols);
     }
     const int k0 = kb * 64;
     // (no per-wave skip of key blocks in this wave's future: the mask zeroes them, and a
     // branch around the products costs registers)
-    const bool need_mask = CAUSAL && (k0 + 63 > qw);
+    const bool need_mask = (CAUSAL && k0 + 63 > qw) || (EDGE && k0 + 64 > s);
 #pragma unroll
     for (int sb = 0; sb < 2; ++sb) {
       floatx16 sc, dp;
@@ -388,7 +435,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
       __builtin_amdgcn_sched_barrier(0);
       if (DROP) {  // dP = dropout'(dO V^T): same mask words as the forward kernel
         uint32_t w[4];
-        at_drop_row_words(drop, (uint32_t)sidx >> 2, (uint32_t)(k0 + sb * 32 + 4 * hf) >> 2, lane, w);
+        // (a query past the end must not take its quad to another row of patches: it stores nothing, so any word serves)
+        const uint32_t drow = (uint32_t)(((int64_t)bi * heads + head) * s + query);
+        if (EDGE && (s & 3)) at_drop_row_words_any(drop, drow, (uint32_t)(k0 + sb * 32 + 4 * hf) >> 2, w);
+        else at_drop_row_words(drop, drow >> 2, (uint32_t)(k0 + sb * 32 + 4 * hf) >> 2, lane, w);
 #pragma unroll
         for (int g = 0; g < 4; ++g)
 #pragma unroll
@@ -402,7 +452,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int key = k0 + sb * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
-          if (key > query) sc[r] = -INFINITY;
+          if ((CAUSAL && key > query) || (EDGE && key >= s)) sc[r] = -INFINITY;
         }
       }
       float ds[16];
@@ -411,7 +461,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
         float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, -l2));
         if (!MASK_BRANCH && need_mask) {
           const int key = k0 + sb * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
-          if (key > query) pr = 0.f;
+          if ((CAUSAL && key > query) || (EDGE && key >= s)) pr = 0.f;
         }
         ds[r] = pr * (dp[r] - dl);
       }
@@ -425,15 +475,23 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
 #pragma unroll
         for (int db = 0; db < C::DB; ++db)
           dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktr[t][db], df, dq[db], 0, 0, 0);
+        if constexpr (EDGE) {
+          const bf16x8 dl8 = at_pack8_rest(&ds[8 * t], df);
+#pragma unroll
+          for (int db = 0; db < C::DB; ++db)
+            dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktr[t][db], dl8, dq[db], 0, 0, 0);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
-  bf16* drow = dqkv + ((int64_t)bi * s + query) * ld + head * D;
+  if (EDGE && query >= s) return;
+  bf16* drow = dqkv + ((int64_t)bi * s + query) * ld + head * cols;
 #pragma unroll
   for (int db = 0; db < C::DB; ++db)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
+      if (EDGE && db * 32 + 8 * g >= cols) continue;
       bf16x4 v;
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = (bf16)(dq[db][4 * g + e] * scale);
@@ -444,12 +502,12 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
 // ---------------------------------------------------------------------------
 // backward, key side: dK and dV
 // ---------------------------------------------------------------------------
-template <int D, bool CAUSAL, bool DROP>
+template <int D, bool CAUSAL, bool DROP, bool EDGE>
 __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __restrict__ qkv, const float* __restrict__ lse,
                                                                 const bf16* __restrict__ dctx,
                                                                 const float* __restrict__ delta, bf16* __restrict__ dqkv,
                                                                 int s, int heads, float scale, float scale_log2e,
-                                                                DropArgs drop) {
+                                                                DropArgs drop, int d) {
   using C = AttnCfg<D>;
   __shared__ __attribute__((aligned(16))) bf16 sq[C::TILE];
   __shared__ __attribute__((aligned(16))) bf16 sg[C::TILE];
@@ -458,20 +516,18 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
   // mask) of every head are dispatched first
   const int kblk = blockIdx.y;
   const int head = blockIdx.x % heads, bi = blockIdx.x / heads;
-  const int h = heads * D;
+  const int cols = EDGE ? d : D, h = heads * cols;
   const int64_t ld = 3 * (int64_t)h;
-  const bf16* base = qkv + (int64_t)bi * s * ld + head * D;
-  const bf16* gbase = dctx + (int64_t)bi * s * h + head * D;
+  const bf16* base = qkv + (int64_t)bi * s * ld + head * cols;
+  const bf16* gbase = dctx + (int64_t)bi * s * h + head * cols;
   const int kb0 = kblk * 128, kw = kb0 + wave * 32;  // this wave's first key
   const int key = kw + (lane & 31);
   const int64_t sbase = ((int64_t)bi * heads + head) * s;
 
+  const int key_row = EDGE && key >= s ? s - 1 : key;   // keys past the end repeat the last one and are not stored
   bf16x8 kf[C::KD], vf[C::KD];
-#pragma unroll
-  for (int t = 0; t < C::KD; ++t) {
-    kf[t] = *reinterpret_cast<const bf16x8*>(base + (int64_t)key * ld + h + 16 * t + 8 * hf);
-    vf[t] = *reinterpret_cast<const bf16x8*>(base + (int64_t)key * ld + 2 * h + 16 * t + 8 * hf);
-  }
+  at_load_row<D, EDGE>(kf, base + (int64_t)key_row * ld + h, hf, cols);
+  at_load_row<D, EDGE>(vf, base + (int64_t)key_row * ld + 2 * h, hf, cols);
   floatx16 dk[C::DB], dv[C::DB];
 #pragma unroll
   for (int i = 0; i < C::DB; ++i)
@@ -482,25 +538,26 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
   // Q / dO tiles: threads 0..63 prefetch lse, 64..127 delta, into registers and then LDS,
   // so the inner loop never waits on a global load.
   __shared__ __attribute__((aligned(16))) float sstat[2][64];
-  const int qs = CAUSAL ? kb0 / 64 : 0, nqb = s / 64;
-  AttnTileRegs<D> rq, rg;
+  const int qs = CAUSAL ? kb0 / 64 : 0, nqb = (s + 63) / 64;
+  AttnTileRegs<D, EDGE> rq, rg;
   float rstat = 0.f;
   auto load_stat = [&](int qb) {
-    if (tid < 64) rstat = lse[sbase + qb * 64 + tid] * 1.4426950408889634f;
-    else if (tid < 128) rstat = delta[sbase + qb * 64 + tid - 64];
+    const bool in = !EDGE || qb * 64 + (tid & 63) < s;   // queries past the end: probability 2^-inf = 0, dO = 0
+    if (tid < 64) rstat = in ? lse[sbase + qb * 64 + tid] * 1.4426950408889634f : INFINITY;
+    else if (tid < 128) rstat = in ? delta[sbase + qb * 64 + tid - 64] : 0.f;
   };
-  rq.load(base + (int64_t)qs * 64 * ld, ld, tid);
-  rg.load(gbase + (int64_t)qs * 64 * h, h, tid);
+  rq.load(base + (int64_t)qs * 64 * ld, ld, tid, s - qs * 64, cols);
+  rg.load(gbase + (int64_t)qs * 64 * h, h, tid, s - qs * 64, cols);
   load_stat(qs);
   for (int qb = qs; qb < nqb; ++qb) {
     if (qb > qs) __syncthreads();
-    rq.store(sq, tid);
-    rg.store(sg, tid);
+    rq.store(sq, tid, s - qb * 64, cols);
+    rg.store(sg, tid, s - qb * 64, cols);
     if (tid < 128) sstat[tid >> 6][tid & 63] = rstat;
     __syncthreads();
     if (qb + 1 < nqb) {
-      rq.load(base + (int64_t)(qb + 1) * 64 * ld, ld, tid);
-      rg.load(gbase + (int64_t)(qb + 1) * 64 * h, h, tid);
+      rq.load(base + (int64_t)(qb + 1) * 64 * ld, ld, tid, s - (qb + 1) * 64, cols);
+      rg.load(gbase + (int64_t)(qb + 1) * 64 * h, h, tid, s - (qb + 1) * 64, cols);
       load_stat(qb + 1);
     }
     const int q0 = qb * 64;
@@ -526,7 +583,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
     };
     // (At d = 64 the kernel fits two waves per SIMD, which overlap by themselves; fetching a
     // half ahead would cost the registers that allow it.)
-    constexpr bool AHEAD = D > 64;
+    // (The EDGE form at d = 128 has no registers left for it either.)
+    constexpr bool AHEAD = D > 64 && !(EDGE && D == 128);
     if (AHEAD) fetch_rows(0);
 #pragma unroll
     for (int sb = 0; sb < 2; ++sb) {
@@ -558,16 +616,20 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
       // key one of its columns; the four lanes of a quad share the patch column, so each
       // generates the patch of group g = lane%4 only and the quad exchanges the words.
       uint32_t own[4];
-      if (DROP) drop_patch(drop, ((uint32_t)(sbase + q0 + sb * 32 + 4 * hf) >> 2) + 2u * (uint32_t)(lane & 3), (uint32_t)key >> 2, own);
+      const bool patches = DROP && !(EDGE && (s & 3));   // groups of 4 queries are rows of patches
+      if (patches) drop_patch(drop, ((uint32_t)(sbase + q0 + sb * 32 + 4 * hf) >> 2) + 2u * (uint32_t)(lane & 3), (uint32_t)key >> 2, own);
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int ql = sb * 32 + 8 * g + 4 * hf;  // 4 consecutive queries of the tile
         const floatx4 l4 = *reinterpret_cast<const floatx4*>(&sstat[0][ql]);
         const floatx4 d4 = *reinterpret_cast<const floatx4*>(&sstat[1][ql]);
         uint32_t mw[4];
-        if (DROP) {
+        if (patches) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) mw[e] = at_quad_bcast(own[e], g);
+        } else if (DROP) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) mw[e] = drop_row_word(drop, (uint32_t)(sbase + q0 + ql + e), (uint32_t)key >> 2);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -594,6 +656,15 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
           at_mfma_acc(dv[db], gtr[t][db], pf);
           at_mfma_acc(dk[db], qtr[t][db], df);
         }
+        if constexpr (EDGE) {
+          const bf16x8 pl = at_pack8_rest(&pr[8 * t], pf);
+          const bf16x8 dl8 = at_pack8_rest(&ds[8 * t], df);
+#pragma unroll
+          for (int db = 0; db < C::DB; ++db) {
+            at_mfma_acc(dv[db], gtr[t][db], pl);
+            at_mfma_acc(dk[db], qtr[t][db], dl8);
+          }
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -606,66 +677,20 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
   }
   at_mfma_settle();
   __builtin_amdgcn_sched_barrier(0);  // the reads of dK/dV below stay below the wait
-  bf16* krow = dqkv + ((int64_t)bi * s + key) * ld + h + head * D;
+  if (EDGE && key >= s) return;
+  bf16* krow = dqkv + ((int64_t)bi * s + key) * ld + h + head * cols;
   bf16* vrow = krow + h;
 #pragma unroll
   for (int db = 0; db < C::DB; ++db)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
+      if (EDGE && db * 32 + 8 * g >= cols) continue;
       bf16x4 a, c;
 #pragma unroll
       for (int e = 0; e < 4; ++e) { a[e] = (bf16)(dk[db][4 * g + e] * scale); c[e] = (bf16)dv[db][4 * g + e]; }
       *reinterpret_cast<bf16x4*>(krow + db * 32 + 8 * g + 4 * hf) = a;
       *reinterpret_cast<bf16x4*>(vrow + db * 32 + 8 * g + 4 * hf) = c;
     }
-}
-
-// ---------------------------------------------------------------------------
-// host side
-// ---------------------------------------------------------------------------
-
-template <int D, bool DROP>
-inline hipError_t attn_fwd_mfma_d(const bf16* qkv, bf16* ctx, float* lse, int b, int s, int heads, int causal,
-                                  const DropArgs& drop, hipStream_t st) {
-  dim3 grid((unsigned)(heads * b), (unsigned)(s / 128));
-  const float sl = 1.4426950408889634f / sqrtf((float)D);
-  if (causal) hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, true, DROP>), grid, dim3(256), 0, st, qkv, ctx, lse, s, heads, sl, drop);
-  else hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, false, DROP>), grid, dim3(256), 0, st, qkv, ctx, lse, s, heads, sl, drop);
-  return hipGetLastError();
-}
-
-hipError_t launch_attention_fwd_mfma(const bf16* qkv, bf16* ctx, float* lse, int b, int s, int heads, int d,
-                                            int causal, const DropArgs& drop, hipStream_t st) {
-  const bool dr = drop.thr != 0;
-  if (d == 64) return dr ? attn_fwd_mfma_d<64, true>(qkv, ctx, lse, b, s, heads, causal, drop, st) : attn_fwd_mfma_d<64, false>(qkv, ctx, lse, b, s, heads, causal, drop, st);
-  if (d == 96) return dr ? attn_fwd_mfma_d<96, true>(qkv, ctx, lse, b, s, heads, causal, drop, st) : attn_fwd_mfma_d<96, false>(qkv, ctx, lse, b, s, heads, causal, drop, st);
-  if (d == 128) return dr ? attn_fwd_mfma_d<128, true>(qkv, ctx, lse, b, s, heads, causal, drop, st) : attn_fwd_mfma_d<128, false>(qkv, ctx, lse, b, s, heads, causal, drop, st);
-  return hipErrorInvalidConfiguration;
-}
-
-template <int D, bool DROP>
-inline hipError_t attn_bwd_mfma_d(const bf16* qkv, const bf16* ctx, const float* lse, const bf16* dctx, bf16* dqkv,
-                                  float* delta, int b, int s, int heads, int causal, const DropArgs& drop, hipStream_t st) {
-  dim3 grid((unsigned)(heads * b), (unsigned)(s / 128));
-  const float sc = 1.0f / sqrtf((float)D), sl = 1.4426950408889634f * sc;
-  if (causal) {
-    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<D, true, DROP>), grid, dim3(256), 0, st, qkv, ctx, lse, dctx, dqkv, delta, s, heads, sc, sl, drop);
-    hipLaunchKernelGGL((attn_bwd_dkv_mfma_kernel<D, true, DROP>), grid, dim3(256), 0, st, qkv, lse, dctx, delta, dqkv, s, heads, sc, sl, drop);
-  } else {
-    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<D, false, DROP>), grid, dim3(256), 0, st, qkv, ctx, lse, dctx, dqkv, delta, s, heads, sc, sl, drop);
-    hipLaunchKernelGGL((attn_bwd_dkv_mfma_kernel<D, false, DROP>), grid, dim3(256), 0, st, qkv, lse, dctx, delta, dqkv, s, heads, sc, sl, drop);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_attention_bwd_mfma(const bf16* qkv, const bf16* ctx, const float* lse, const bf16* dctx,
-                                            bf16* dqkv, float* delta, int b, int s, int heads, int d, int causal,
-                                            const DropArgs& drop, hipStream_t st) {
-  const bool dr = drop.thr != 0;
-  if (d == 64) return dr ? attn_bwd_mfma_d<64, true>(qkv, ctx, lse, dctx, dqkv, delta, b, s, heads, causal, drop, st) : attn_bwd_mfma_d<64, false>(qkv, ctx, lse, dctx, dqkv, delta, b, s, heads, causal, drop, st);
-  if (d == 96) return dr ? attn_bwd_mfma_d<96, true>(qkv, ctx, lse, dctx, dqkv, delta, b, s, heads, causal, drop, st) : attn_bwd_mfma_d<96, false>(qkv, ctx, lse, dctx, dqkv, delta, b, s, heads, causal, drop, st);
-  if (d == 128) return dr ? attn_bwd_mfma_d<128, true>(qkv, ctx, lse, dctx, dqkv, delta, b, s, heads, causal, drop, st) : attn_bwd_mfma_d<128, false>(qkv, ctx, lse, dctx, dqkv, delta, b, s, heads, causal, drop, st);
-  return hipErrorInvalidConfiguration;
 }
 
 }  // namespace varuna

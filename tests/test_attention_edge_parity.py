@@ -1,0 +1,68 @@
+"""The bf16 MFMA attention kernels on sequence lengths and head dims that fit no tile (EDGE form)."""
+import pytest
+import torch
+
+from paper_2111_04007_amd import binding as B, synth
+from tests import parity_util as U
+from tests.test_ops_parity import rnd, run_attention_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("b,s,heads,d,causal", [
+    (1, 1, 1, 8, 1), (2, 33, 3, 24, 0), (1, 64, 2, 32, 1), (2, 63, 1, 40, 1), (1, 65, 2, 64, 0), (1, 127, 1, 72, 1),
+    (1, 129, 2, 96, 1), (2, 191, 1, 104, 0), (1, 200, 1, 128, 1), (1, 257, 2, 120, 0), (3, 130, 2, 64, 1), (1, 256, 1, 48, 0),
+])
+def test_attention_edge(b, s, heads, d, causal):
+    """Same bound as the whole-tile kernels' tests; one to three blocks of queries and keys, every padded head dim."""
+    run_attention_case("bf16", b, s, heads, d, causal, variant=2, seed=50 + d)
+
+
+def test_attention_edge_agrees_with_whole_tiles():
+    """On shapes both forms take they differ by the rounding of the probabilities and score gradients to bf16 (2^-9 each,
+    averaged over a row's keys) and by the rounding of the outputs (2^-9 / sqrt(3) rms): 2^-8 covers both."""
+    for b, s, heads, d, causal in ((1, 256, 2, 64, 1), (2, 128, 1, 96, 0), (1, 256, 1, 128, 1)):
+        h = heads * d
+        qkv, dctx = rnd((b * s, 3 * h), "bf16", 7), rnd((b * s, h), "bf16", 8)
+        got = []
+        for v in (1, 2):
+            ctx, dqkv = torch.empty_like(dctx), torch.empty_like(qkv)
+            lse = torch.empty(b * heads * s, device="cuda")
+            delta = torch.empty_like(lse)
+            B.op_attention_fwd(qkv, ctx, lse, b, s, heads, d, causal, variant=v)
+            B.op_attention_bwd(qkv, ctx, lse, dctx, dqkv, delta, b, s, heads, d, causal, variant=v)
+            got.append((ctx, lse, dqkv))
+        for x, y in zip(*got):
+            assert float((x.double() - y.double()).norm() / x.double().norm()) <= 2.0 ** -8
+
+
+def test_attention_edge_stays_inside_its_tensors():
+    """Tensors end where a guard begins: NaNs behind the inputs must not spread, values behind the outputs must stay."""
+    b, s, heads, d = 2, 77, 3, 40
+    h, T = heads * d, b * s
+
+    def guarded(n, fill, src=None):
+        buf = torch.full((n + 65536,), fill, dtype=torch.bfloat16, device="cuda")
+        if src is not None:
+            buf[:n] = src.reshape(-1)
+        return buf
+
+    qkv, dctx = guarded(T * 3 * h, float("nan"), rnd((T, 3 * h), "bf16", 1)), guarded(T * h, float("nan"), rnd((T, h), "bf16", 2))
+    ctx, dqkv = guarded(T * h, 3.0), guarded(T * 3 * h, 3.0)
+    lse, delta = (torch.full((b * heads * s + 4096,), 5.0, device="cuda") for _ in range(2))
+    for causal in (0, 1):
+        B.op_attention_fwd(qkv, ctx, lse, b, s, heads, d, causal, variant=2)
+        B.op_attention_bwd(qkv, ctx, lse, dctx, dqkv, delta, b, s, heads, d, causal, variant=2)
+        for t, n, fill in ((ctx, T * h, 3.0), (dqkv, T * 3 * h, 3.0), (lse, b * heads * s, 5.0), (delta, b * heads * s, 5.0)):
+            assert bool(torch.isfinite(t[:n]).all()) and bool((t[n:] == fill).all())
+
+
+@pytest.mark.parametrize("s,d,causal", [(132, 40, True), (70, 64, False), (131, 96, True), (45, 128, True)])
+def test_dropout_edge(s, d, causal):
+    """Dropout masks at lengths that are and are not multiples of the 4x4 mask patches, against the oracle's generator."""
+    cfg = synth.StageConfig("edge-dropout", 1, 3 * d, 3, s, 2, 1, 6 * d, causal, "bf16", 0.02, seed=60 + s, dropout_p=0.3)
+    params = synth.make_params(cfg, perturb=0.05)
+    xs, dys = synth.make_activations(cfg, 1)
+    st, ys, dxs = U.gpu_stage_step(cfg, params, xs, dys, seed=9)
+    U.compare_step(cfg, st, ys, dxs, U.oracle_stage_step(cfg, params, xs, dys, seed=9), label=f"s={s} d={d}")
+    st.close()
