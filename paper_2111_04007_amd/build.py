@@ -12,7 +12,7 @@ LIB_PATH = os.path.join(HERE, "libvaruna_stage.so")
 SOURCES = [  # compiled side by side
     os.path.join(HERE, "csrc", n) for n in ("gemm_fwd.hip", "gemm_dgrad.hip", "gemm_wgrad.hip", "gemm_f32.hip",
                                             "gemm_f32_bf16.hip", "attention.hip",
-                                            "attention_edge.hip", "stage.hip")
+                                            "attention_edge.hip", "attention_f32.hip", "attention_f32_bf16.hip", "stage.hip")
 ]
 
 HIPCC_FLAGS = [

@@ -1,0 +1,11 @@
+#include <hip/hip_runtime.h>
+
+#include "attention_f32.h"
+
+namespace varuna {
+
+template hipError_t launch_attention_fwd_f32<bf16>(const bf16*, bf16*, float*, int, int, int, int, int, const DropArgs&, hipStream_t);
+template hipError_t launch_attention_bwd_f32<bf16>(const bf16*, const bf16*, const float*, const bf16*, bf16*, float*, int, int, int, int, int,
+                                                  const DropArgs&, hipStream_t);
+
+}  // namespace varuna

@@ -275,26 +275,33 @@ template <> struct GemmDispatch<bf16> {
   }
 };
 
+// fp32.  variant 0: library's choice; -1: one wave per row (few rows, head dims above 128); 3: fp32 products.
 template <typename T> struct AttnDispatch {
+  static bool per_row(int variant, int b, int s, int a, int d) {
+    return variant == -1 || !attn_f32_supported(d) || (variant == 0 && attn_few_rows(b, s, a));
+  }
   static hipError_t fwd(int variant, const T* qkv, T* ctx, float* lse, int b, int s, int a, int d, int causal,
                         const DropArgs& drop, hipStream_t st) {
-    (void)variant;
-    return launch_attention_fwd_simple<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
+    if (per_row(variant, b, s, a, d)) return launch_attention_fwd_simple<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
+    return launch_attention_fwd_f32<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
   }
   static hipError_t bwd(int variant, const T* qkv, const T* ctx, const float* lse, const T* dctx, T* dqkv,
                         float* delta, int b, int s, int a, int d, int causal, const DropArgs& drop, hipStream_t st) {
-    (void)variant;
-    return launch_attention_bwd_simple<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
+    if (per_row(variant, b, s, a, d)) return launch_attention_bwd_simple<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
+    return launch_attention_bwd_f32<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
   }
 };
 
 template <> struct AttnDispatch<bf16> {
-  // variant 0: library's choice; -1: simple kernels; 1: MFMA kernels on whole tiles; 2: their EDGE form.  The EDGE form takes
+  // variant 0: library's choice; -1: one wave per row; 1: MFMA kernels on whole tiles; 2: their EDGE form; 3: fp32 products
+  // (what the two cannot address, up to head dim 128).  The EDGE form takes
   // what the whole tiles do not (any length, head dims that are multiples of 8 up to 128): against the simple kernels, which
   // read their operands element by element, 594 -> 29 us forward and 2409 -> 98 us backward at 2 x 1000 tokens, 25 heads of 64.
   static int choose(int variant, int s, int d, bool aligned) {
-    if (variant == 0) return attn_mfma_supported(s, d) ? 1 : (attn_edge_supported(d) && aligned ? 2 : -1);
-    if ((variant == 1 && !attn_mfma_supported(s, d)) || (variant == 2 && !(attn_edge_supported(d) && aligned))) return 0;
+    if (variant == 0) return attn_mfma_supported(s, d) ? 1 : (attn_edge_supported(d) && aligned ? 2 : (attn_f32_supported(d) ? 3 : -1));
+    if ((variant == 1 && !attn_mfma_supported(s, d)) || (variant == 2 && !(attn_edge_supported(d) && aligned)) ||
+        (variant == 3 && !attn_f32_supported(d)))
+      return 0;
     return variant;
   }
   static hipError_t fwd(int variant, const bf16* qkv, bf16* ctx, float* lse, int b, int s, int a, int d, int causal,
@@ -303,6 +310,7 @@ template <> struct AttnDispatch<bf16> {
       case 0: return hipErrorInvalidConfiguration;
       case 1: return launch_attention_fwd_mfma(qkv, ctx, lse, b, s, a, d, causal, drop, st);
       case 2: return launch_attention_fwd_mfma_edge(qkv, ctx, lse, b, s, a, d, causal, drop, st);
+      case 3: return launch_attention_fwd_f32<bf16>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
       default: return launch_attention_fwd_simple<bf16>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
     }
   }
@@ -312,6 +320,7 @@ template <> struct AttnDispatch<bf16> {
       case 0: return hipErrorInvalidConfiguration;
       case 1: return launch_attention_bwd_mfma(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
       case 2: return launch_attention_bwd_mfma_edge(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
+      case 3: return launch_attention_bwd_f32<bf16>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
       default: return launch_attention_bwd_simple<bf16>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
     }
   }
