@@ -302,10 +302,10 @@ constexpr size_t dg_smem_bytes() {
 // addresser's full queue while its products wait.
 // EDGE: M, N and K need not be multiples of the tile (rows, cols and K are the true extents; rows of both operands are
 // whole 16-byte pieces).
-template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, int MODE, int LS = 0, bool EDGE = false>
-__global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
+template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, int MODE, int LS, bool EDGE>
+__device__ __forceinline__ void dg_tile(
     const bf16* __restrict__ a, int64_t lda, const bf16* __restrict__ b, int64_t ldb, int K,
-    int tiles_m, int tiles_n, EpiArgs<bf16> epi, int xcd_remap, int group, int64_t rows, int64_t cols) {
+    int tiles_m, int tiles_n, const EpiArgs<bf16>& epi, int group, int64_t rows, int64_t cols, int logical) {
   static_assert(!EDGE || LS == 4, "the other load schedules count loads that may lie outside an EDGE operand");
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
@@ -321,12 +321,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int wm = wave / WGN, wn = wave % WGN;
 
-  // Workgroup -> tile.  Consecutive workgroup ids go round-robin over the 8 XCDs; give
-  // every XCD a contiguous range of logical tiles, walked in groups of `group` tile rows
-  // so the A and B panels an XCD touches stay in its L2.
-  int logical = blockIdx.x;
-  const int nblk = gridDim.x;
-  if (xcd_remap && (nblk & 7) == 0) logical = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+  // Logical tile -> output tile, in groups of `group` tile rows.
   const int width = group * tiles_n;
   const int grp = logical / width;
   const int first_m = grp * group;
@@ -699,6 +694,41 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
   }
 }
 
+// Workgroup -> tile.  Consecutive workgroup ids go round-robin over the 8 XCDs; give every XCD a contiguous range of
+// logical tiles, walked in groups of tile rows so the A and B panels an XCD touches stay in its L2.
+template <int BM, int BN, int WGM, int WGN, bool A_KMAJOR, bool B_KMAJOR, int MODE, int LS = 0, bool EDGE = false>
+__global__ __launch_bounds__(WGM* WGN* kWave) void gemm_dma_kernel(
+    const bf16* __restrict__ a, int64_t lda, const bf16* __restrict__ b, int64_t ldb, int K,
+    int tiles_m, int tiles_n, EpiArgs<bf16> epi, int xcd_remap, int group, int64_t rows, int64_t cols) {
+  int logical = blockIdx.x;
+  const int nblk = gridDim.x;
+  if (xcd_remap && (nblk & 7) == 0) logical = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+  dg_tile<BM, BN, WGM, WGN, A_KMAJOR, B_KMAJOR, MODE, LS, EDGE>(a, lda, b, ldb, K, tiles_m, tiles_n, epi, group, rows, cols, logical);
+}
+
+// Several weight gradients out[M,N] += a[K,M]^T b[K,N] over the same K in one launch.  Alone each of them ends with a
+// partly filled round of workgroups (or leaves slots empty throughout); together only the last one does.
+// Job j owns workgroups first[j] .. first[j+1]-1, a multiple of 8 of them, remapped among themselves as above; those
+// past its last tile end at once.
+typedef WgradJob<bf16> DgJob;
+struct DgGroup {
+  int n, K;
+  int first[kMaxGroupJobs + 1];
+  DgJob job[kMaxGroupJobs];
+};
+template <int BM, int BN, int WGM, int WGN, bool EDGE>
+__global__ __launch_bounds__(WGM* WGN* kWave) void gemm_group_kernel(DgGroup g, int group) {
+  int j = 0;
+  while (j + 1 < g.n && (int)blockIdx.x >= g.first[j + 1]) ++j;
+  const DgJob& w = g.job[j];
+  const int local = (int)blockIdx.x - g.first[j], nblk = g.first[j + 1] - g.first[j];
+  const int logical = (local & 7) * (nblk >> 3) + (local >> 3);
+  const int tiles_m = (w.M + BM - 1) / BM, tiles_n = (w.N + BN - 1) / BN;
+  if (logical >= tiles_m * tiles_n) return;
+  const EpiArgs<bf16> epi{nullptr, nullptr, nullptr, nullptr, w.out, w.N, DropArgs{}, 0};
+  dg_tile<BM, BN, WGM, WGN, false, false, EPI_ACCUM_F32, 4, EDGE>(w.a, w.M, w.b, w.N, g.K, tiles_m, tiles_n, epi, group, w.M, w.N, logical);
+}
+
 // ---------------------------------------------------------------------------
 // host side.  Variant ids (0 is "the library's choice", -1 the fp32-product kernel):
 //   5: 256x256 tile, 8 waves   6: 256x256, 4 waves   7: 128x128, 4 waves   8: 256x128, 4 waves
@@ -809,6 +839,30 @@ inline int dg_wgrad_splits(int64_t M, int64_t N, int64_t K) {
   while (s > 1 && ((v < 22 && nk % s != 0) || nk / s < 8)) --s;
   return (int)(s < 1 ? 1 : s);
 }
+
+// Whether `n` weight gradients over K (all four of a layer, of several layers) run as one launch, and on which kernel
+// configuration (18, 19, 22, 23; 0: one by one).  In units of a full-chip round of 128x128 tiles a group takes its tiles / 512,
+// or the whole rounds of 256x256 tiles its tiles need; one by one every product rounds up by itself.  With fewer tiles than
+// slots cutting the reductions (dg_wgrad_splits) fills the chip better.  Measured (us), one by one with their
+// split sums against one launch, the four matrices of a layer over 4096 tokens: 1920 wide 537 -> 422, 1024 wide 181 -> 125.
+inline int dg_group_choice(const DgJob* jobs, int n, int64_t K) {
+  int64_t t5 = 0, t7 = 0;
+  bool plain5 = true, plain7 = true, edge = true;
+  for (int i = 0; i < n; ++i) {
+    const int64_t M = jobs[i].M, N = jobs[i].N;
+    plain5 = plain5 && dg_shape_ok(5, M, N, K, M, N);
+    plain7 = plain7 && dg_shape_ok(7, M, N, K, M, N);
+    edge = edge && dg_shape_ok(22, M, N, K, M, N);
+    t5 += ((M + 255) / 256) * ((N + 255) / 256);
+    t7 += ((M + 127) / 128) * ((N + 127) / 128);
+  }
+  if (t7 < 512 || !(plain7 || edge)) return 0;
+  const double cost7 = (double)t7 / 512.0 + 0.2;
+  const double cost5 = (double)((t5 + 255) / 256) * 2.0 / 1.15 * (plain5 ? 1.0 : 1.05);
+  if (cost5 <= cost7 && (plain5 || edge)) return plain5 ? 18 : 23;
+  return plain7 ? 19 : 22;
+}
+hipError_t launch_gemm_group(int variant, const DgJob* jobs, int n, int64_t K, hipStream_t st);   // gemm_wgrad.hip
 
 // The launches, one translation unit per product; variant as above.
 hipError_t launch_gemm_dma_fwd(int mode, int variant, const bf16* a, int64_t lda, const bf16* b, int64_t ldb, int64_t M, int64_t N,

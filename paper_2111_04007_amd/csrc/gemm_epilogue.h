@@ -13,6 +13,10 @@ enum GemmOp : int { GEMM_FWD = 0, GEMM_DGRAD = 1, GEMM_WGRAD = 2 };
 
 struct GemmTile { int bm, bn; };
 
+// One weight gradient out[M,N] += a[K,M]^T b[K,N] of several that share a launch.
+template <typename T> struct WgradJob { const T* a; const T* b; float* out; int M, N; };
+constexpr int kMaxGroupJobs = 16;
+
 // Eight consecutive columns of one output row.
 template <int MODE>
 __device__ __forceinline__ void gemm_epilogue8(const EpiArgs<bf16>& e, int64_t m, int64_t n, const float* acc) {

@@ -516,16 +516,39 @@ struct StageOps {
 
   // dW += dY^T X for the four matrices of every layer, over the `cnt` micro-batches whose
   // operands sit in ring slots 0..cnt-1: the slots are stacked along the token dimension,
-  // so each is ONE GEMM with reduction length cnt*T and one fp32 read-modify-write of dW.
+  // so each is ONE product with reduction length cnt*T and one fp32 read-modify-write of dW.
+  // Products of up to four layers share a launch where that pays (dg_group_choice).
   hipError_t flush_wgrads(int cnt) {
     hipError_t e;
     const int64_t K = (int64_t)cnt * D.T;
-    for (int l = D.L - 1; l >= 0; --l) {
-      const LayerArea& A = S->ws.layer[l];
-      if ((e = wgrad(D.h, D.f, K, wsp<T>(A.dyd), wsp<T>(A.g), grad(l, VARUNA_P_W2)))) return e;
-      if ((e = wgrad(D.f, D.h, K, wsp<T>(A.du), wsp<T>(A.xn2), grad(l, VARUNA_P_W1)))) return e;
-      if ((e = wgrad(D.h, D.h, K, wsp<T>(A.dx1d), wsp<T>(A.ctx), grad(l, VARUNA_P_WO)))) return e;
-      if ((e = wgrad(3 * D.h, D.h, K, wsp<T>(A.dqkv), wsp<T>(A.xn1), grad(l, VARUNA_P_WQKV)))) return e;
+    WgradJob<T> jobs[kMaxGroupJobs];
+    for (int top = D.L - 1; top >= 0; top -= kMaxGroupJobs / 4) {
+      int n = 0;
+      for (int l = top; l >= 0 && l > top - kMaxGroupJobs / 4; --l) {
+        const LayerArea& A = S->ws.layer[l];
+        jobs[n++] = {wsp<T>(A.dyd), wsp<T>(A.g), grad(l, VARUNA_P_W2), D.h, D.f};
+        jobs[n++] = {wsp<T>(A.du), wsp<T>(A.xn2), grad(l, VARUNA_P_W1), D.f, D.h};
+        jobs[n++] = {wsp<T>(A.dx1d), wsp<T>(A.ctx), grad(l, VARUNA_P_WO), D.h, D.h};
+        jobs[n++] = {wsp<T>(A.dqkv), wsp<T>(A.xn1), grad(l, VARUNA_P_WQKV), 3 * D.h, D.h};
+      }
+      if constexpr (std::is_same<T, bf16>::value) {
+        bool ok = true;
+        double flops = 0, bytes = 0;
+        for (int i = 0; i < n; ++i) {
+          const double mn = (double)jobs[i].M * jobs[i].N;
+          ok = ok && aligned16(jobs[i].a) && aligned16(jobs[i].b) && aligned16(jobs[i].out);
+          flops += 2.0 * mn * K;
+          bytes += ((double)jobs[i].M + jobs[i].N) * K * sizeof(T) + 8.0 * mn;
+        }
+        const int v = ok ? dg_group_choice(jobs, n, K) : 0;
+        if (v != 0) {
+          Bracket br(S, st, VARUNA_K_GEMM_WGRAD, flops, bytes);
+          if ((e = launch_gemm_group(v, jobs, n, K, st))) return e;
+          continue;
+        }
+      }
+      for (int i = 0; i < n; ++i)
+        if ((e = wgrad(jobs[i].M, jobs[i].N, K, jobs[i].a, jobs[i].b, jobs[i].out))) return e;
     }
     return hipSuccess;
   }
