@@ -4,4 +4,17 @@ namespace varuna {
 
 template hipError_t launch_gemm_f32<float>(int, int, const float*, const float*, int64_t, int64_t, int64_t, const EpiArgs<float>&, hipStream_t);
 
+hipError_t launch_gemm_f32_group(const WgradJob<float>* jobs, int n, int64_t K, hipStream_t st) {
+  int64_t t32 = 0, t64 = 0;
+  bool vec = true;
+  for (int i = 0; i < n; ++i) {
+    t32 += gf_tiles(jobs[i].M, jobs[i].N, 32);
+    t64 += gf_tiles(jobs[i].M, jobs[i].N, 64);
+    vec = vec && ((reinterpret_cast<uintptr_t>(jobs[i].a) | reinterpret_cast<uintptr_t>(jobs[i].b)) & 15) == 0 && jobs[i].M % 4 == 0 && jobs[i].N % 4 == 0;
+  }
+  if (gf_small_tile(t32, t64))
+    return vec ? gf_launch_group<float, 32, 32, 32, 32, 8, 128, true>(jobs, n, K, st) : gf_launch_group<float, 32, 32, 32, 32, 8, 128, false>(jobs, n, K, st);
+  return vec ? gf_launch_group<float, 64, 64, 32, 32, 1, 64, true>(jobs, n, K, st) : gf_launch_group<float, 64, 64, 32, 32, 1, 64, false>(jobs, n, K, st);
+}
+
 }  // namespace varuna

@@ -23,7 +23,7 @@ inline hipError_t gf_launch(const T* a, int64_t lda, const T* b, int64_t ldb, in
   // whole pieces of four along the contiguous direction of both operands, from an aligned base
   const uintptr_t align = 4 * sizeof(T) - 1;
   const bool vec = ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & align) == 0 && lda % 4 == 0 && ldb % 4 == 0;
-  if (gf_small_tile(M, N)) return gf_launch_tile<T, MODE, AK, BK, 32, 32, 32, 32, 8, 128>(vec, a, lda, b, ldb, M, N, K, epi, st);
+  if (gf_small_tile(gf_tiles(M, N, 32), gf_tiles(M, N, 64))) return gf_launch_tile<T, MODE, AK, BK, 32, 32, 32, 32, 8, 128>(vec, a, lda, b, ldb, M, N, K, epi, st);
   return gf_launch_tile<T, MODE, AK, BK, 64, 64, 32, 32, 1, 64>(vec, a, lda, b, ldb, M, N, K, epi, st);
 }
 
@@ -41,6 +41,25 @@ hipError_t launch_gemm_f32(int op, int mode, const T* a, const T* b, int64_t M, 
     if (mode == EPI_ACCUM_F32) return gf_launch<T, EPI_ACCUM_F32, false, false>(a, M, b, N, M, N, K, epi, st);
   }
   return hipErrorInvalidValue;
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int KS, int BKT, bool VEC>
+inline hipError_t gf_launch_group(const WgradJob<T>* jobs, int n, int64_t K, hipStream_t st) {
+  for (int i0 = 0; i0 < n; i0 += kMaxGroupJobs) {
+    GfGroup<T> g{};
+    g.n = n - i0 < kMaxGroupJobs ? n - i0 : kMaxGroupJobs;
+    g.K = K;
+    int64_t blocks = 0;
+    for (int i = 0; i < g.n; ++i) {
+      g.job[i] = jobs[i0 + i];
+      g.first[i] = (int)blocks;
+      blocks += ((int64_t)((g.job[i].M + BM - 1) / BM) * ((g.job[i].N + BN - 1) / BN) + 7) / 8 * 8;
+      if (blocks >= (1ll << 31)) return hipErrorInvalidValue;
+    }
+    g.first[g.n] = (int)blocks;
+    hipLaunchKernelGGL((gemm_f32_group_kernel<T, BM, BN, WM, WN, KS, BKT, VEC>), dim3((unsigned)blocks), dim3((BM / WM) * (BN / WN) * KS * kWave), 0, st, g);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace varuna

@@ -531,21 +531,25 @@ struct StageOps {
         jobs[n++] = {wsp<T>(A.dx1d), wsp<T>(A.ctx), grad(l, VARUNA_P_WO), D.h, D.h};
         jobs[n++] = {wsp<T>(A.dqkv), wsp<T>(A.xn1), grad(l, VARUNA_P_WQKV), 3 * D.h, D.h};
       }
+      bool aligned = true;
+      double flops = 0, bytes = 0;
+      for (int i = 0; i < n; ++i) {
+        const double mn = (double)jobs[i].M * jobs[i].N;
+        aligned = aligned && aligned16(jobs[i].a) && aligned16(jobs[i].b) && aligned16(jobs[i].out);
+        flops += 2.0 * mn * K;
+        bytes += ((double)jobs[i].M + jobs[i].N) * K * sizeof(T) + 8.0 * mn;
+      }
       if constexpr (std::is_same<T, bf16>::value) {
-        bool ok = true;
-        double flops = 0, bytes = 0;
-        for (int i = 0; i < n; ++i) {
-          const double mn = (double)jobs[i].M * jobs[i].N;
-          ok = ok && aligned16(jobs[i].a) && aligned16(jobs[i].b) && aligned16(jobs[i].out);
-          flops += 2.0 * mn * K;
-          bytes += ((double)jobs[i].M + jobs[i].N) * K * sizeof(T) + 8.0 * mn;
-        }
-        const int v = ok ? dg_group_choice(jobs, n, K) : 0;
+        const int v = aligned ? dg_group_choice(jobs, n, K) : 0;
         if (v != 0) {
           Bracket br(S, st, VARUNA_K_GEMM_WGRAD, flops, bytes);
           if ((e = launch_gemm_group(v, jobs, n, K, st))) return e;
           continue;
         }
+      } else {
+        Bracket br(S, st, VARUNA_K_GEMM_WGRAD, flops, bytes);
+        if ((e = launch_gemm_f32_group(jobs, n, K, st))) return e;
+        continue;
       }
       for (int i = 0; i < n; ++i)
         if ((e = wgrad(jobs[i].M, jobs[i].N, K, jobs[i].a, jobs[i].b, jobs[i].out))) return e;
