@@ -262,23 +262,25 @@ __global__ __launch_bounds__(CR_COLS* CR_ROWLANES) void colreduce_partial_kernel
 // outputs per thread lane, the chunks over 8 groups of lanes (summed through LDS in a fixed order): the kernel lasts as
 // long as one thread's serial loads.
 constexpr int CF_COLS = 32, CF_LANES = 8;
-__global__ __launch_bounds__(CF_COLS* CF_LANES) void colreduce_final_kernel(const float* __restrict__ partial,
-                                                              int nchunks, int64_t n,
-                                                              float* __restrict__ out0,
-                                                              float* __restrict__ out1) {
+__device__ __forceinline__ void colreduce_final_block(const float* __restrict__ partial, int64_t pitch, int nchunks, int64_t n,
+                                                      float* __restrict__ out0, float* __restrict__ out1, int64_t blk) {
   __shared__ float sh[CF_LANES][CF_COLS];
   const int c = threadIdx.x % CF_COLS, l = threadIdx.x / CF_COLS;
-  const int64_t width = out1 ? 2 * n : n, col = (int64_t)blockIdx.x * CF_COLS + c;
+  const int64_t width = out1 ? 2 * n : n, col = blk * CF_COLS + c;
   float t = 0.f;
   if (col < width)
 #pragma unroll 4
-    for (int k = l; k < nchunks; k += CF_LANES) t += partial[(int64_t)k * width + col];
+    for (int k = l; k < nchunks; k += CF_LANES) t += partial[(int64_t)k * pitch + col];
   sh[l][c] = t;
   __syncthreads();
   if (l != 0 || col >= width) return;
 #pragma unroll
   for (int i = 1; i < CF_LANES; ++i) t += sh[i][c];
   if (col < n) out0[col] += t; else out1[col - n] += t;
+}
+__global__ __launch_bounds__(CF_COLS* CF_LANES) void colreduce_final_kernel(const float* __restrict__ partial, int nchunks, int64_t n,
+                                                                            float* __restrict__ out0, float* __restrict__ out1) {
+  colreduce_final_block(partial, out1 ? 2 * n : n, nchunks, n, out0, out1, blockIdx.x);
 }
 inline void launch_colreduce_final(const float* partial, int nchunks, int64_t n, float* out0, float* out1, hipStream_t st) {
   const int64_t width = out1 ? 2 * n : n;
@@ -312,15 +314,15 @@ inline hipError_t launch_layernorm_fwd(const T* x, const T* gamma, const T* beta
 // takes 8 column groups of VEC columns (128-byte row segments) x 32 row lanes, which makes four times as many blocks
 // of the same number of partials as 32 groups x 8 row lanes did (480 for 4096 x 1920).  Measured there: gamma / beta
 // sums 16.1 -> 8.7 us (31 MB, mostly from the caches), their second stage 6.7 -> 3.2 us.
+constexpr int CRV_CG = 8, CRV_RL = 32;   // column groups and row lanes of a block
 template <typename T, int LNMODE, int VEC>
-__global__ __launch_bounds__(256) void colreduce_partial_vec_kernel(
-    const T* __restrict__ a, const T* __restrict__ x, const float* __restrict__ stats,
-    float* __restrict__ partial, int64_t rows, int64_t n) {
-  constexpr int CG = 8, RL = 32, COLS = CG * VEC;
-  __shared__ float sh[LNMODE ? 2 : 1][RL][COLS + 4];
+__device__ __forceinline__ void colreduce_partial_block(
+    const T* __restrict__ a, const T* __restrict__ x, const float* __restrict__ stats, int64_t rows, int64_t n, int64_t colblk,
+    int64_t chunk, float (&sh)[2][CRV_RL][CRV_CG * VEC + 4]) {
+  constexpr int CG = CRV_CG, RL = CRV_RL;
   const int cg = threadIdx.x % CG, rl = threadIdx.x / CG;
-  const int64_t col = ((int64_t)blockIdx.x * CG + cg) * VEC;
-  const int64_t r0 = (int64_t)blockIdx.y * CR_CHUNK;
+  const int64_t col = (colblk * CG + cg) * VEC;
+  const int64_t r0 = chunk * CR_CHUNK;
   const int nr = (int)((rows - r0 < CR_CHUNK) ? rows - r0 : CR_CHUNK);
   float s0[VEC], s1[VEC];
 #pragma unroll
@@ -343,19 +345,73 @@ __global__ __launch_bounds__(256) void colreduce_partial_vec_kernel(
     }
   }
 #pragma unroll
-  for (int i = 0; i < VEC; ++i) { sh[0][rl][cg * VEC + i] = s0[i]; if (LNMODE) sh[LNMODE ? 1 : 0][rl][cg * VEC + i] = s1[i]; }
+  for (int i = 0; i < VEC; ++i) { sh[0][rl][cg * VEC + i] = s0[i]; if (LNMODE) sh[1][rl][cg * VEC + i] = s1[i]; }
   __syncthreads();
+}
+// Sum number c of the block (LNMODE: first the columns' dy * xhat, then their dy).
+template <int COLS>
+__device__ __forceinline__ float colreduce_block_sum(const float (&sh)[2][CRV_RL][COLS + 4], int which, int c) {
+  float t = 0.f;
+#pragma unroll
+  for (int i = 0; i < CRV_RL; ++i) t += sh[which][i][c];
+  return t;
+}
+
+template <typename T, int LNMODE, int VEC>
+__global__ __launch_bounds__(256) void colreduce_partial_vec_kernel(
+    const T* __restrict__ a, const T* __restrict__ x, const float* __restrict__ stats,
+    float* __restrict__ partial, int64_t rows, int64_t n) {
+  constexpr int COLS = CRV_CG * VEC;
+  __shared__ float sh[2][CRV_RL][COLS + 4];
+  colreduce_partial_block<T, LNMODE, VEC>(a, x, stats, rows, n, blockIdx.x, blockIdx.y, sh);
   const int64_t width = LNMODE ? 2 * n : n;
   if (threadIdx.x < (LNMODE ? 2 : 1) * COLS) {
     const int which = threadIdx.x / COLS, c = threadIdx.x % COLS;
     const int64_t gc = (int64_t)blockIdx.x * COLS + c;
-    if (gc < n) {
-      float t0 = 0.f;
-#pragma unroll
-      for (int i = 0; i < RL; ++i) t0 += sh[which][i][c];
-      partial[(int64_t)blockIdx.y * width + which * n + gc] = t0;
-    }
+    if (gc < n) partial[(int64_t)blockIdx.y * width + which * n + gc] = colreduce_block_sum<COLS>(sh, which, c);
   }
+}
+
+// All six column reductions of one layer's backward in one launch and their second stages in another: job j sums
+// a[rows, n] (x == null) or is a LayerNorm's gamma / beta pair; it owns column blocks first[j] .. first[j+1]-1 of the
+// first stage, final column blocks ffirst[j] .. of the second, and `width` columns of the partials from pcol[j] on (row
+// pitch `pitch`).  With one chunk of rows the first stage adds to the outputs itself.
+// Twelve launches of a layer become two, or one up to 256 tokens: tiny fp32 step (16 layer backwards) 1097 -> 940 us.
+constexpr int kMaxReduceJobs = 6;
+template <typename T>
+struct ReduceJob { const T* a; const T* x; const float* stats; float* out0; float* out1; int n; };
+template <typename T>
+struct ReduceJobs {
+  int n_jobs, nchunks;
+  int64_t rows, pitch;
+  int first[kMaxReduceJobs + 1], ffirst[kMaxReduceJobs + 1], pcol[kMaxReduceJobs];
+  ReduceJob<T> job[kMaxReduceJobs];
+};
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void colreduce_jobs_partial_kernel(ReduceJobs<T> g, float* __restrict__ partial) {
+  constexpr int COLS = CRV_CG * VEC;
+  __shared__ float sh[2][CRV_RL][COLS + 4];
+  int j = 0;
+  while (j + 1 < g.n_jobs && (int)blockIdx.x >= g.first[j + 1]) ++j;
+  const ReduceJob<T> w = g.job[j];
+  const int colblk = (int)blockIdx.x - g.first[j];
+  const bool ln = w.x != nullptr;
+  if (ln) colreduce_partial_block<T, 1, VEC>(w.a, w.x, w.stats, g.rows, w.n, colblk, blockIdx.y, sh);
+  else colreduce_partial_block<T, 0, VEC>(w.a, nullptr, nullptr, g.rows, w.n, colblk, blockIdx.y, sh);
+  if ((int)threadIdx.x >= (ln ? 2 : 1) * COLS) return;
+  const int which = threadIdx.x / COLS, c = threadIdx.x % COLS;
+  const int64_t gc = (int64_t)colblk * COLS + c;
+  if (gc >= w.n) return;
+  const float t = colreduce_block_sum<COLS>(sh, which, c);
+  if (g.nchunks == 1) (which ? w.out1 : w.out0)[gc] += t;
+  else partial[(int64_t)blockIdx.y * g.pitch + g.pcol[j] + which * w.n + gc] = t;
+}
+template <typename T>
+__global__ __launch_bounds__(CF_COLS* CF_LANES) void colreduce_jobs_final_kernel(ReduceJobs<T> g, const float* __restrict__ partial) {
+  int j = 0;
+  while (j + 1 < g.n_jobs && (int)blockIdx.x >= g.ffirst[j + 1]) ++j;
+  const ReduceJob<T> w = g.job[j];
+  colreduce_final_block(partial + g.pcol[j], g.pitch, g.nchunks, w.n, w.out0, w.out1, (int64_t)((int)blockIdx.x - g.ffirst[j]));
 }
 
 template <typename T, int LNMODE>
@@ -418,6 +474,40 @@ inline hipError_t launch_colsum(const T* a, float* out, float* partial, int64_t 
   const int nch = colreduce_chunks(rows);
   launch_colreduce_partial<T, 0>(a, (const T*)nullptr, (const float*)nullptr, partial, rows, n, st);
   launch_colreduce_final(partial, nch, n, out, nullptr, st);
+  return hipGetLastError();
+}
+
+// The jobs of one layer; partial: (sum of the jobs' widths) * colreduce_chunks(rows) floats.
+template <typename T>
+inline hipError_t launch_reduce_jobs(const ReduceJob<T>* jobs, int n_jobs, float* partial, int64_t rows, hipStream_t st) {
+  constexpr int VEC = 16 / sizeof(T);
+  const int nch = colreduce_chunks(rows);
+  bool vec = true;
+  for (int i = 0; i < n_jobs; ++i) vec = vec && jobs[i].n % VEC == 0 && ln_aligned16({jobs[i].a, jobs[i].x});
+  if (!vec) {   // columns that are no whole 16-byte pieces: one by one
+    for (int i = 0; i < n_jobs; ++i) {
+      const ReduceJob<T>& w = jobs[i];
+      const hipError_t e = w.x ? launch_layernorm_bwd_params<T>(w.a, w.x, w.stats, w.out0, w.out1, partial, rows, w.n, st)
+                               : launch_colsum<T>(w.a, w.out0, partial, rows, w.n, st);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  ReduceJobs<T> g{};
+  g.n_jobs = n_jobs; g.nchunks = nch; g.rows = rows;
+  int64_t pitch = 0;
+  for (int i = 0; i < n_jobs; ++i) {
+    const int width = (jobs[i].x ? 2 : 1) * jobs[i].n;
+    g.job[i] = jobs[i];
+    g.pcol[i] = (int)pitch;
+    g.first[i + 1] = g.first[i] + (jobs[i].n + CRV_CG * VEC - 1) / (CRV_CG * VEC);
+    g.ffirst[i + 1] = g.ffirst[i] + (width + CF_COLS - 1) / CF_COLS;
+    pitch += width;
+  }
+  g.pitch = pitch;
+  hipLaunchKernelGGL((colreduce_jobs_partial_kernel<T, VEC>), dim3((unsigned)g.first[n_jobs], (unsigned)nch), dim3(256), 0, st, g, partial);
+  if (nch > 1)
+    hipLaunchKernelGGL((colreduce_jobs_final_kernel<T>), dim3((unsigned)g.ffirst[n_jobs]), dim3(CF_COLS * CF_LANES), 0, st, g, (const float*)partial);
   return hipGetLastError();
 }
 

@@ -129,8 +129,7 @@ struct Workspace {
   LayerArea fwd;                 // scratch of the forward pass (nothing of it is kept)
   size_t saved_begin, saved_end;
   size_t ping[2];                // forward layer outputs (discarded)
-  size_t dxn, dxn_b, dctx, delta, partial;   // dxn: gradient of LN2's output, dxn_b: of LN1's
-  size_t partial_side;           // reduction partials of the bias-gradient sums that run on the side stream
+  size_t dxn, dxn_b, dctx, delta, partial;   // dxn: gradient of LN2's output, dxn_b: of LN1's; partial: column reductions
   size_t stat_partial;           // partial sums of the gradient statistics (doubles)
   size_t splitk, splitk_size;    // partial weight gradients of split-K GEMMs (fp32); size 0 if no GEMM splits
   size_t total;
@@ -175,10 +174,8 @@ Workspace carve(const Dims& D) {
   w.ping[0] = take(E); w.ping[1] = take(E);
   w.dxn = take(E); w.dxn_b = take(E); w.dctx = take(E);
   w.delta = take(lse);
-  int64_t widest = 3 * (int64_t)D.h;
-  if (D.f > widest) widest = D.f;
-  w.partial = take((size_t)colreduce_chunks(D.T) * widest * sizeof(float));
-  w.partial_side = take((size_t)colreduce_chunks(D.T) * widest * sizeof(float));
+  // partials of all column reductions of a layer: b1, bqkv, b2, bo and two gamma / beta pairs
+  w.partial = take((size_t)colreduce_chunks(D.T) * ((size_t)D.f + 9 * (size_t)D.h) * sizeof(float));
   w.stat_partial = take((size_t)kStatBlocks * 2 * sizeof(double));
   w.splitk_size = splitk_bytes(D);
   w.splitk = take(w.splitk_size);
@@ -390,30 +387,22 @@ struct StageOps {
     return gemm(VARUNA_K_GEMM_FWD, GEMM_FWD, EPI_BIAS_RES, T_, D.h, D.f, g, param(l, VARUNA_P_W2), param(l, VARUNA_P_B2), x1, y, nullptr, nullptr, drop_args(DROP_SITE_MLP, l, mb));
   }
 
-  // Runs `launch(stream, partial scratch)` beside the GEMM chain when the caller has handed over a
-  // side stream: everything the launch reads is complete at this point of the caller's stream,
-  // and nothing on that stream depends on its result before the next join_side().
-  template <typename F>
-  hipError_t on_side(int cls, double bytes, F&& launch) {
+  // The column reductions of one layer (bias, gamma and beta gradients), beside the GEMM chain when the caller has handed
+  // over a side stream: everything they read is complete at this point of the caller's stream, and nothing on that
+  // stream depends on their results, or rewrites what they read, before the next join_side().
+  hipError_t reduce_layer(const ReduceJob<T>* jobs, int n) {
+    double bytes = 0;
+    for (int i = 0; i < n; ++i) bytes += (jobs[i].x ? 2.0 : 1.0) * D.T * jobs[i].n * sizeof(T);
+    float* partial = wsp<float>(S->ws.partial);
     if (S->prof_on || S->side == nullptr) {  // per-kernel timing wants everything on one stream
-      Bracket br(S, st, cls, 0, bytes);
-      return launch(st, wsp<float>(S->ws.partial));
+      Bracket br(S, st, VARUNA_K_COLREDUCE, 0, bytes);
+      return launch_reduce_jobs<T>(jobs, n, partial, D.T, st);
     }
     hipError_t e;
     if ((e = hipEventRecord(S->ev_fork, st))) return e;
     if ((e = hipStreamWaitEvent(S->side, S->ev_fork, 0))) return e;
     S->side_used = true;
-    return launch(S->side, wsp<float>(S->ws.partial_side));
-  }
-  hipError_t colsum(const T* a, float* out, int64_t n) {
-    return on_side(VARUNA_K_COLREDUCE, (double)D.T * n * sizeof(T),
-                   [&](hipStream_t s, float* partial) { return launch_colsum<T>(a, out, partial, D.T, n, s); });
-  }
-  // gamma / beta gradients of one LayerNorm (reads dy, x, statistics)
-  hipError_t ln_params(const T* dyn, const T* x, const float* stats, float* dgamma, float* dbeta) {
-    return on_side(VARUNA_K_COLREDUCE, 2.0 * D.E * sizeof(T), [&](hipStream_t s, float* partial) {
-      return launch_layernorm_bwd_params<T>(dyn, x, stats, dgamma, dbeta, partial, D.T, D.h, s);
-    });
+    return launch_reduce_jobs<T>(jobs, n, partial, D.T, S->side);
   }
 
   // The caller's stream waits for everything forked since the last join.
@@ -453,18 +442,17 @@ struct StageOps {
       if ((e = launch_dropout_apply<T>(dy, o, T_, D.h, drop_args(DROP_SITE_MLP, l, mb), st))) return e;
       dyd = o;
     }
-    // MLP2: du = (dyd W2) * GeLU'(u); db2 += colsum(dyd)
+    // MLP2: du = (dyd W2) * GeLU'(u)
     if ((e = gemm(VARUNA_K_GEMM_DGRAD, GEMM_DGRAD, EPI_DGELU, T_, D.f, D.h, dyd, param(l, VARUNA_P_W2), nullptr, u, du, nullptr, nullptr))) return e;
-    if ((e = colsum(dyd, grad(l, VARUNA_P_B2), D.h))) return e;
-    // MLP1: dxn2 = du W1; db1 += colsum(du)
+    // the layer above's reductions read dxn and dxn_b, which this layer rewrites from here on
+    if ((e = join_side())) return e;
+    // MLP1: dxn2 = du W1
     if ((e = gemm(VARUNA_K_GEMM_DGRAD, GEMM_DGRAD, EPI_PLAIN, T_, D.h, D.f, du, param(l, VARUNA_P_W1), nullptr, nullptr, dxn, nullptr, nullptr))) return e;
-    if ((e = colsum(du, grad(l, VARUNA_P_B1), D.f))) return e;
     // LN2: dx1 = dy + LN'(dxn2)
     {
       Bracket br(S, st, VARUNA_K_LN_BWD, 0, 4.0 * D.E * sizeof(T));
       if ((e = launch_layernorm_bwd_dx<T>(dxn, x1, stats2, param(l, VARUNA_P_LN2_G), dy, dx1, T_, D.h, st))) return e;
     }
-    if ((e = ln_params(dxn, x1, stats2, grad(l, VARUNA_P_LN2_G), grad(l, VARUNA_P_LN2_B)))) return e;
     const T* dx1d = dx1;
     if (dr) {
       T* o = wsp<T>(A.dx1d) + (size_t)rs * D.E;
@@ -472,25 +460,28 @@ struct StageOps {
       if ((e = launch_dropout_apply<T>(dx1, o, T_, D.h, drop_args(DROP_SITE_PROJ, l, mb), st))) return e;
       dx1d = o;
     }
-    // proj: dctx = dx1d Wo; dbo += colsum(dx1d)
+    // proj: dctx = dx1d Wo
     if ((e = gemm(VARUNA_K_GEMM_DGRAD, GEMM_DGRAD, EPI_PLAIN, T_, D.h, D.h, dx1d, param(l, VARUNA_P_WO), nullptr, nullptr, dctx, nullptr, nullptr))) return e;
-    if ((e = colsum(dx1d, grad(l, VARUNA_P_BO), D.h))) return e;
     // attention
     {
       Bracket br(S, st, VARUNA_K_ATTN_BWD, 2.5 * attn_flops_fwd(), 9.0 * D.E * sizeof(T));
       if ((e = AttnDispatch<T>::bwd(0, qkv, ctx, lse, dctx, dqkv, delta, D.b, D.s, D.a, D.d, D.causal, drop_args(DROP_SITE_ATTN, l, mb), st))) return e;
     }
-    // QKV: dxn1 = dqkv Wqkv; dbqkv += colsum(dqkv)
+    // QKV: dxn1 = dqkv Wqkv
     if ((e = gemm(VARUNA_K_GEMM_DGRAD, GEMM_DGRAD, EPI_PLAIN, T_, D.h, 3 * D.h, dqkv, param(l, VARUNA_P_WQKV), nullptr, nullptr, dxn_b, nullptr, nullptr))) return e;
-    if ((e = colsum(dqkv, grad(l, VARUNA_P_BQKV), 3 * D.h))) return e;
     // LN1: dx = dx1 + LN'(dxn1)
     {
       Bracket br(S, st, VARUNA_K_LN_BWD, 0, 4.0 * D.E * sizeof(T));
       if ((e = launch_layernorm_bwd_dx<T>(dxn_b, x, stats1, param(l, VARUNA_P_LN1_G), dx1, dx, T_, D.h, st))) return e;
     }
-    if ((e = ln_params(dxn_b, x, stats1, grad(l, VARUNA_P_LN1_G), grad(l, VARUNA_P_LN1_B)))) return e;
-    // the next layer down rewrites dxn / dxn_b and this layer's rings: the side stream's reads come first
-    return join_side();
+    const ReduceJob<T> jobs[kMaxReduceJobs] = {
+        {du, nullptr, nullptr, grad(l, VARUNA_P_B1), nullptr, D.f},
+        {dqkv, nullptr, nullptr, grad(l, VARUNA_P_BQKV), nullptr, 3 * D.h},
+        {dxn, x1, stats2, grad(l, VARUNA_P_LN2_G), grad(l, VARUNA_P_LN2_B), D.h},
+        {dxn_b, x, stats1, grad(l, VARUNA_P_LN1_G), grad(l, VARUNA_P_LN1_B), D.h},
+        {dyd, nullptr, nullptr, grad(l, VARUNA_P_B2), nullptr, D.h},
+        {dx1d, nullptr, nullptr, grad(l, VARUNA_P_BO), nullptr, D.h}};
+    return reduce_layer(jobs, kMaxReduceJobs);
   }
 
   // One weight gradient dW[M,N] += A^T B over K tokens.  bf16 shapes with too few output
@@ -607,12 +598,11 @@ struct StageOps {
       T* dx = (l == 0) ? dx_out : wsp<T>(S->ws.layer[l - 1].dy) + (size_t)rs * D.E;
       if ((e = layer_backward(l, mb, x, dx, S->ws.layer[l], rs))) return e;
     }
-    if ((e = join_side())) return e;   // the bias gradients are complete when this call's work is
     if (++S->pending == D.G) {
       if ((e = flush_wgrads(S->pending))) return e;
       S->pending = 0;
     }
-    return hipSuccess;
+    return join_side();   // the bias gradients are complete when this call's work is
   }
 
   hipError_t flush() {
