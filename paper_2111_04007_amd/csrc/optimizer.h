@@ -2,7 +2,9 @@
 // squares and number of non-finite entries: this GPU's share of the global gradient norm and
 // of the overflow flag that the stages of a pipeline synchronise) and a mixed-precision Adam
 // step (fp32 master weight, momentum and variance; parameter re-rounded to the stage's
-// storage type).  Both are single passes over flat buffers, bound by HBM.
+// storage type).  Both are single passes over flat buffers, bound by HBM.  Nothing the update touches is
+// used again before it has been evicted, so it bypasses the caches: 44 M parameters 251 -> 206 us (30 bytes each, 6.4 TB/s;
+// a large copy moves 4.9 TB/s here); the statistics with 8 loads in flight per thread 45 -> 37 us.
 #pragma once
 #include "common.h"
 
@@ -17,6 +19,7 @@ __global__ __launch_bounds__(256) void grad_stats_partial_kernel(const float* __
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
   unsigned bad = 0;
+#pragma unroll 8   // loads in flight
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
     const floatx4 v = reinterpret_cast<const floatx4*>(g)[i];
     const bool f0 = isfinite(v[0]), f1 = isfinite(v[1]), f2 = isfinite(v[2]), f3 = isfinite(v[3]);
@@ -90,8 +93,10 @@ __global__ __launch_bounds__(256) void adam_kernel(const float* __restrict__ g, 
   const size_t n4 = n / 4;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
-    const floatx4 g4 = reinterpret_cast<const floatx4*>(g)[i];
-    floatx4 w4 = reinterpret_cast<floatx4*>(w)[i], m4 = reinterpret_cast<floatx4*>(m)[i], v4 = reinterpret_cast<floatx4*>(v)[i];
+    const floatx4 g4 = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g) + i);
+    floatx4 w4 = __builtin_nontemporal_load(reinterpret_cast<floatx4*>(w) + i);
+    floatx4 m4 = __builtin_nontemporal_load(reinterpret_cast<floatx4*>(m) + i);
+    floatx4 v4 = __builtin_nontemporal_load(reinterpret_cast<floatx4*>(v) + i);
     Tx4 p4;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -100,9 +105,9 @@ __global__ __launch_bounds__(256) void adam_kernel(const float* __restrict__ g, 
       adam_one<T>(g4[e], wi, mi, vi, pi, a);
       w4[e] = wi; m4[e] = mi; v4[e] = vi; p4[e] = pi;
     }
-    reinterpret_cast<floatx4*>(w)[i] = w4;
-    reinterpret_cast<floatx4*>(m)[i] = m4;
-    reinterpret_cast<floatx4*>(v)[i] = v4;
+    __builtin_nontemporal_store(w4, reinterpret_cast<floatx4*>(w) + i);
+    __builtin_nontemporal_store(m4, reinterpret_cast<floatx4*>(m) + i);
+    __builtin_nontemporal_store(v4, reinterpret_cast<floatx4*>(v) + i);
     reinterpret_cast<Tx4*>(p)[i] = p4;
   }
   if (blockIdx.x == 0 && threadIdx.x < n - n4 * 4) {

@@ -217,9 +217,10 @@ struct varuna_stage {
 namespace {
 
 __global__ void fill_zero_f32_kernel(float* p, size_t n) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) p[i] = 0.f;
+  // (p is 256-byte aligned: the gradient buffer)
+  const size_t first = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = first; i < n / 4; i += stride) reinterpret_cast<floatx4*>(p)[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  if (first < n % 4) p[n - 1 - first] = 0.f;
 }
 
 // RAII-free profiling bracket: records start/stop events around one launch group.
