@@ -736,7 +736,8 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_group_kernel(DgGroup g, 
 //   12: as 5 with three stages of B and loads in every k-step   13: as 6 with that   14: as 7 with that
 //   15: 128x256, 8 waves, that schedule   16: 256x128, 8 waves, that schedule
 //   17: as 13 with the k-tile loop unrolled over the stage period   18: as 12 with that
-//   19, 20, 21: as 14, 15, 16 with that
+//   19: as 14 with that
+//   20: 128x256, 21: 256x128 with that, 4 waves
 //   22, 23: as 19, 18 for sizes that are no multiples of the tile (EDGE)
 // ---------------------------------------------------------------------------
 inline bool dg_variant_tile(int variant, GemmTile* t) {
@@ -754,7 +755,7 @@ inline bool dg_shape_ok(int variant, int64_t M, int64_t N, int64_t K, int64_t ld
   if (!dg_variant_tile(variant, &t)) return false;
   // operands are addressed with 32-bit byte offsets from their base (buffer loads)
   const int64_t a_bytes = (M > K ? M : K) * lda * 2, b_bytes = (N > K ? N : K) * ldb * 2;
-  if (variant >= 22) {   // EDGE: rows of both operands and of the output are whole 16-byte pieces; offsets below DG_OUTSIDE
+  if (variant == 22 || variant == 23) {   // EDGE: rows of both operands and of the output are whole 16-byte pieces; offsets below DG_OUTSIDE
     const int64_t pad = 2 * 256 * (lda > ldb ? lda : ldb);
     return lda % 8 == 0 && ldb % 8 == 0 && N % 8 == 0 && K >= 1 && ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) < (1ll << 31) &&
            a_bytes + pad < DG_OUTSIDE && b_bytes + pad < DG_OUTSIDE;
@@ -763,6 +764,11 @@ inline bool dg_shape_ok(int variant, int64_t M, int64_t N, int64_t K, int64_t ld
          (M / t.bm) * (N / t.bn) < (1ll << 31) && a_bytes < (1ll << 32) && b_bytes < (1ll << 32);
 }
 
+// The merged 128x256 and 256x128 tiles run on four waves (64x128 / 128x64 each: 6 fragment reads per 8 products), not on eight
+// of 64x64 (4 per 4): with eight the LDS moves 128 KB of fragments and 48 KB of new data per k-tile, 1400 clocks against
+// 1024 of products.  Eight against four waves on operands out of cache (us): forward 2048x3072x12288 186 / 169, 2048x12288x3072
+// 158 / 150; dgrad 2048x3072x9216 138 / 126; on 256x128 219 / 183, 167 / 153, 168 / 141.  (128x128 tiles on two waves of
+// 128x64: 3-15 % faster than on four with cached operands, 3-10 % slower otherwise.)
 // Picks between the 256x256 (one workgroup per CU) and 128x128 (two per CU) tiles by the
 // number of full-chip rounds each needs; 0 if neither fits the shape.  Sizes that are no multiples of 128 (64 for K)
 // take the EDGE form of the same two tiles, if their rows are whole 16-byte pieces and the product is larger than one
