@@ -289,13 +289,13 @@ __device__ __forceinline__ void dg_epilogue_bf16(floatx16 (&acc)[TM][TN], unsign
 // Dynamic LDS of one workgroup: the operand stages, or the epilogue's per-wave staging where that is larger.
 template <int BM, int BN, int WGM, int WGN, int MODE, int LS>
 constexpr size_t dg_smem_bytes() {
-  const size_t stages = (size_t)(LS >= 2 ? 2 * BM + 3 * BN : DG_STAGES * (BM + BN)) * DG_BK * 2;
+  const size_t stages = (size_t)(LS == 5 ? 3 * (BM + BN) : (LS >= 2 ? 2 * BM + 3 * BN : DG_STAGES * (BM + BN))) * DG_BK * 2;
   const size_t pass = (size_t)WGM * WGN * 32 * (BN / WGN) * 4;   // 32 rows x WN floats per wave
   const size_t epi = (MODE == EPI_ACCUM_F32 || MODE == EPI_STORE_F32) ? 2 * pass : pass;
   return stages > epi ? stages : epi;
 }
 
-// LS (load schedule): 0 = the loads of a k-tile go out in one run right after the barrier that
+// LS (load schedule; 2 and 4: in the body): 0 = the loads of a k-tile go out in one run right after the barrier that
 // frees their stage (from the upper half of the waves, or from both halves one k-step apart,
 // see below); 1 = every wave sends its share one load at a time between its products, spread
 // over the three k-steps that follow that barrier, so that no wave sits at the texture
@@ -375,7 +375,7 @@ __device__ __forceinline__ void dg_tile(
   // LDS map.  LS 0, 1: two stages of [A tile | B tile].  LS 2: two stages of A, then three of B.
   constexpr int A_STRIDE = (LS >= 2) ? BM * DG_BK : STAGE_ELEMS;
   constexpr int B_STRIDE = (LS >= 2) ? BN * DG_BK : STAGE_ELEMS;
-  constexpr int B_BASE = (LS >= 2) ? 2 * BM * DG_BK : BM * DG_BK;
+  constexpr int B_BASE = (LS >= 2) ? (LS == 5 ? 3 : 2) * BM * DG_BK : BM * DG_BK;
   // LS >= 2: which of a wave's loads (A's LA first, then B's LB) go out in the k-step after the barrier
   // ([0, C3)), and in k-steps 0, 1, 2 of the next tile ([C3, C0), [C0, C1), [C1, LA+LB)).
   constexpr int LA_ = DgLoader<BM, NI, A_KMAJOR, EDGE>::LPT, LB_ = DgLoader<BN, NI, B_KMAJOR, EDGE>::LPT;
@@ -398,6 +398,12 @@ __device__ __forceinline__ void dg_tile(
     // (a load whose descriptor covers zero bytes makes no memory request and may retire ahead of
     // older loads still in flight: counting outstanding loads is only valid among live ones)
     if (nk > 1) __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(N31)); else __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(0));
+  } else if constexpr (LS == 5) {
+    la.issue(a_stage(0), kt0, iw);   // tile 0, then tile 1 (past the end: zeros, as below)
+    lb.issue(b_stage(0), kt0, iw);
+    dg_static_for<LA_>([&](auto j_tag) { la.template issue_one<decltype(j_tag)::value>(a_stage(1), kt0 + 1, iw, nk > 1); });
+    dg_static_for<LB_>([&](auto j_tag) { lb.template issue_one<decltype(j_tag)::value>(b_stage(1), kt0 + 1, iw, nk > 1); });
+    if (counted(1)) __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(LA_ + LB_)); else __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(0));
   } else if constexpr (LS >= 2) {
     // A(0), B(0) whole, then B(1) whole and the loads of tile 1 that go out right after a barrier (all of
     // them A's): what the steady state has sent for tile 0's period by the time its k-step 0 starts.
@@ -552,6 +558,34 @@ __device__ __forceinline__ void dg_tile(
       __builtin_amdgcn_s_barrier();
       kstep(S1{}, nxt, nxtb, KS0{}, DgLoads<0, N3>{}, cur, kt0 + kt + 2, kt + 2 < nk, curb, kt0 + kt + 2, kt + 2 < nk);
     }
+  } else if constexpr (LS == 5) {
+    // Three stages of both operands: all loads of tile kt+2 go into the stage of tile kt-1, a quarter in every k-step.
+    constexpr int L1 = LT / 4, L2 = LT / 2, L3 = 3 * LT / 4;
+    auto ktile = [&](auto s_tag, int kt) {
+      constexpr int P = decltype(s_tag)::value, P1 = (P + 1) % 3, P2 = (P + 2) % 3;
+      bf16* ca = a_stage(P);
+      bf16* cb = b_stage(P);
+      bf16* fa2 = a_stage(P2);
+      bf16* fb2 = b_stage(P2);
+      const bool live = kt + 2 < nk;
+      kstep(S0{}, ca, cb, KS1{}, DgLoads<0, L1>{}, fa2, kt0 + kt + 2, live, fb2, kt0 + kt + 2, live);
+      kstep(S1{}, ca, cb, KS2{}, DgLoads<L1, L2>{}, fa2, kt0 + kt + 2, live, fb2, kt0 + kt + 2, live);
+      kstep(S0{}, ca, cb, KS3{}, DgLoads<L2, L3>{}, fa2, kt0 + kt + 2, live, fb2, kt0 + kt + 2, live);
+      // tile kt+1 must have landed; the L3 loads of tile kt+2 sent so far may be in flight (see the LS 2 loop)
+      if (counted(kt + 2)) __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(L3) & DG_WAIT_LGKM0);
+      else __builtin_amdgcn_s_waitcnt(DG_WAIT_VM0_LGKM0);
+      __builtin_amdgcn_s_barrier();
+      kstep(S1{}, a_stage(P1), b_stage(P1), KS0{}, DgLoads<L3, LT>{}, fa2, kt0 + kt + 2, live, fb2, kt0 + kt + 2, live);
+    };
+    using S2 = std::integral_constant<int, 2>;
+    int kt = 0;
+    for (; kt + 3 <= nk; kt += 3) {
+      ktile(S0{}, kt);
+      ktile(S1{}, kt + 1);
+      ktile(S2{}, kt + 2);
+    }
+    if (kt < nk) { ktile(S0{}, kt); ++kt; }
+    if (kt < nk) { ktile(S1{}, kt); ++kt; }
   } else {
     // One k-tile whose A stage AP (kt mod 2) and B stage BS (kt mod 3) are compile-time values.
     auto ktile = [&](auto ap_tag, auto bs_tag, int kt) {
@@ -737,7 +771,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_group_kernel(DgGroup g, 
 //   15: 128x256, 8 waves, that schedule   16: 256x128, 8 waves, that schedule
 //   17: as 13 with the k-tile loop unrolled over the stage period   18: as 12 with that
 //   19: as 14 with that
-//   20: 128x256, 21: 256x128 with that, 4 waves
+//   20: 128x256, 21: 256x128, 4 waves, three stages of both operands (LS 5)
 //   22, 23: as 19, 18 for sizes that are no multiples of the tile (EDGE)
 // ---------------------------------------------------------------------------
 inline bool dg_variant_tile(int variant, GemmTile* t) {
@@ -767,7 +801,9 @@ inline bool dg_shape_ok(int variant, int64_t M, int64_t N, int64_t K, int64_t ld
 // The merged 128x256 and 256x128 tiles run on four waves (64x128 / 128x64 each: 6 fragment reads per 8 products), not on eight
 // of 64x64 (4 per 4): with eight the LDS moves 128 KB of fragments and 48 KB of new data per k-tile, 1400 clocks against
 // 1024 of products.  Eight against four waves on operands out of cache (us): forward 2048x3072x12288 186 / 169, 2048x12288x3072
-// 158 / 150; dgrad 2048x3072x9216 138 / 126; on 256x128 219 / 183, 167 / 153, 168 / 141.  (128x128 tiles on two waves of
+// 158 / 150; dgrad 2048x3072x9216 138 / 126; on 256x128 219 / 183, 167 / 153, 168 / 141.  160 KB of LDS hold a third stage of
+// A as well (LS 5), which gives every load two k-tiles to arrive and the loop a period of three: again (us, forward / dgrad)
+// 169 / 174 -> 164 / 161 at 2048x3072x12288, 126 / 126 -> 123 / 119 at 2048x3072x9216, on 256x128 183 / 187 -> 170 / 161.  (128x128 tiles on two waves of
 // 128x64: 3-15 % faster than on four with cached operands, 3-10 % slower otherwise.)
 // Picks between the 256x256 (one workgroup per CU) and 128x128 (two per CU) tiles by the
 // number of full-chip rounds each needs; 0 if neither fits the shape.  Sizes that are no multiples of 128 (64 for K)

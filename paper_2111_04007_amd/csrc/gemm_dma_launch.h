@@ -28,7 +28,6 @@ inline hipError_t dg_launch_one(const bf16* a, int64_t lda, const bf16* b, int64
 template <bool AK, bool BK_, int MODE>
 inline hipError_t dg_launch_variant(int variant, const bf16* a, int64_t lda, const bf16* b, int64_t ldb,
                                     int64_t M, int64_t N, int64_t K, const EpiArgs<bf16>& epi, int splits, hipStream_t st) {
-  constexpr int op = AK ? (BK_ ? GEMM_FWD : GEMM_DGRAD) : GEMM_WGRAD;
   switch (variant) {
     case 5: return dg_launch_one<256, 256, 2, 4, AK, BK_, MODE>(a, lda, b, ldb, M, N, K, epi, splits, st);
     case 6: return dg_launch_one<256, 256, 2, 2, AK, BK_, MODE>(a, lda, b, ldb, M, N, K, epi, splits, st);
@@ -45,8 +44,8 @@ inline hipError_t dg_launch_variant(int variant, const bf16* a, int64_t lda, con
     case 17: return dg_launch_one<256, 256, 2, 2, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
     case 18: return dg_launch_one<256, 256, 2, 4, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
     case 19: return dg_launch_one<128, 128, 2, 2, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 20: return dg_launch_one<128, 256, 2, 2, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 21: return dg_launch_one<256, 128, 2, 2, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
+    case 20: return dg_launch_one<128, 256, 2, 2, AK, BK_, MODE, 5>(a, lda, b, ldb, M, N, K, epi, splits, st);
+    case 21: return dg_launch_one<256, 128, 2, 2, AK, BK_, MODE, 5>(a, lda, b, ldb, M, N, K, epi, splits, st);
     case 22: return dg_launch_one<128, 128, 2, 2, AK, BK_, MODE, 4, true>(a, lda, b, ldb, M, N, K, epi, splits, st);
     case 23: return dg_launch_one<256, 256, 2, 4, AK, BK_, MODE, 4, true>(a, lda, b, ldb, M, N, K, epi, splits, st);
     default: return hipErrorInvalidValue;
