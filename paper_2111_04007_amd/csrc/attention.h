@@ -28,9 +28,12 @@ hipError_t launch_attention_bwd_mfma_edge(const bf16* qkv, const bf16* ctx, cons
 inline bool attn_f32_supported(int d) { return d <= 128; }
 // A call of a few short rows ends sooner with one wave per row: a wave of the other form works through whole 32x32 tiles, 7-8 us
 // forward and 20-25 us backward for any call that leaves the chip idle.  Measured (us forward / backward, per row against
-// fp32 products; batch x length x heads x dim): 2x32x2x64 5.2 / 12 against 7.3 / 22, 2x64x2x64 6.8 / 19 against 7.8 / 23,
-// 1x32x16x64 5.2 / 12 against 7.4 / 22; but 2x96x2x64 9.1 / 29 against 8.2 / 24, 8x32x16x64 9.5 / 31 against 7.4 / 23.
-inline bool attn_few_rows(int b, int s, int heads) { return s <= 64 && (int64_t)b * heads * s <= 1024; }
+// fp32 products; batch x length x heads x dim): 2x32x2x64 5.2 / 12 against 7.3 / 22, 2x64x2x64 6.8 / 19 against 7.8 / 23
+// (forward inside a step, operands out of cache: 9.7 against 8.0), 1x32x16x64 5.2 / 12 against 7.4 / 22; but 2x96x2x64 9.1 /
+// 29 against 8.2 / 24, 8x32x16x64 9.5 / 31 against 7.4 / 23.
+inline bool attn_few_rows(int b, int s, int heads, bool backward) {
+  return s <= (backward ? 64 : 32) && (int64_t)b * heads * s <= 1024;
+}
 template <typename T>
 hipError_t launch_attention_fwd_f32(const T* qkv, T* ctx, float* lse, int b, int s, int heads, int d, int causal,
                                     const DropArgs& drop, hipStream_t st);

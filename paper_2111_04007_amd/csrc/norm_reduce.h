@@ -526,31 +526,47 @@ inline hipError_t launch_reduce_jobs(const ReduceJob<T>* jobs, int n_jobs, float
 }
 
 // out = dropout(in) with the mask of one site (backward of a residual-branch dropout: the
-// gradient that enters the branch's GEMMs and bias reduction).  One thread per 4 columns of a
-// row = one mask word.
-template <typename T>
+// gradient that enters the branch's GEMMs and bias reduction).  A thread takes 4 rows x 8 columns, two mask patches: one
+// generator call per 16 elements (a thread per row of a patch made one per 4, which bound the kernel) and 16-byte (fp32:
+// two 16-byte) accesses.  4096 x 1024 in bf16: 9.6 -> 5.8 us.
+template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void dropout_apply_kernel(const T* __restrict__ in, T* __restrict__ out, int64_t rows,
                                                             int64_t cols, DropArgs drop) {
-  const int64_t cpr = (cols + 3) / 4;  // column patches per row
-  const int64_t total = rows * cpr;
+  typedef T Tx8 __attribute__((ext_vector_type(8)));
+  const int64_t cpr = (cols + 7) / 8, total = (rows + 3) / 4 * cpr;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = i / cpr, cp = i % cpr;
-    const uint32_t w = drop_row_word(drop, (uint32_t)r, (uint32_t)cp);
-    const int64_t base = r * cols + cp * 4;
+    const int64_t rp = i / cpr, c0 = (i % cpr) * 8;
+    uint32_t w[2][4];
+    drop_patch(drop, (uint32_t)rp, (uint32_t)(c0 >> 2), w[0]);
+    drop_patch(drop, (uint32_t)rp, (uint32_t)(c0 >> 2) + 1, w[1]);
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (cp * 4 + e < cols)
-        out[base + e] = drop_keep(drop, w, e) ? from_f32<T>(to_f32(in[base + e]) * drop.scale) : from_f32<T>(0.f);
+    for (int r = 0; r < 4; ++r) {
+      if (rp * 4 + r >= rows) break;
+      const int64_t base = (rp * 4 + r) * cols + c0;
+      if constexpr (VEC) {
+        Tx8 v = *reinterpret_cast<const Tx8*>(in + base);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = drop_keep(drop, w[e >> 2][r], e & 3) ? from_f32<T>(to_f32((T)v[e]) * drop.scale) : from_f32<T>(0.f);
+        *reinterpret_cast<Tx8*>(out + base) = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (c0 + e < cols) out[base + e] = drop_keep(drop, w[e >> 2][r], e & 3) ? from_f32<T>(to_f32(in[base + e]) * drop.scale) : from_f32<T>(0.f);
+      }
+    }
   }
 }
 
 template <typename T>
 inline hipError_t launch_dropout_apply(const T* in, T* out, int64_t rows, int64_t cols, const DropArgs& drop, hipStream_t st) {
-  const int64_t total = rows * ((cols + 3) / 4);
+  const int64_t total = (rows + 3) / 4 * ((cols + 7) / 8);
   int64_t nblk = (total + 255) / 256;
   if (nblk > 16384) nblk = 16384;
   if (nblk < 1) nblk = 1;
-  hipLaunchKernelGGL((dropout_apply_kernel<T>), dim3((unsigned)nblk), dim3(256), 0, st, in, out, rows, cols, drop);
+  const uintptr_t align = 8 * sizeof(T) - 1;
+  if (cols % 8 == 0 && ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & align) == 0)
+    hipLaunchKernelGGL((dropout_apply_kernel<T, true>), dim3((unsigned)nblk), dim3(256), 0, st, in, out, rows, cols, drop);
+  else hipLaunchKernelGGL((dropout_apply_kernel<T, false>), dim3((unsigned)nblk), dim3(256), 0, st, in, out, rows, cols, drop);
   return hipGetLastError();
 }
 

@@ -275,17 +275,17 @@ template <> struct GemmDispatch<bf16> {
 
 // fp32.  variant 0: library's choice; -1: one wave per row (few rows, head dims above 128); 3: fp32 products.
 template <typename T> struct AttnDispatch {
-  static bool per_row(int variant, int b, int s, int a, int d) {
-    return variant == -1 || !attn_f32_supported(d) || (variant == 0 && attn_few_rows(b, s, a));
+  static bool per_row(int variant, int b, int s, int a, int d, bool backward) {
+    return variant == -1 || !attn_f32_supported(d) || (variant == 0 && attn_few_rows(b, s, a, backward));
   }
   static hipError_t fwd(int variant, const T* qkv, T* ctx, float* lse, int b, int s, int a, int d, int causal,
                         const DropArgs& drop, hipStream_t st) {
-    if (per_row(variant, b, s, a, d)) return launch_attention_fwd_simple<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
+    if (per_row(variant, b, s, a, d, false)) return launch_attention_fwd_simple<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
     return launch_attention_fwd_f32<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
   }
   static hipError_t bwd(int variant, const T* qkv, const T* ctx, const float* lse, const T* dctx, T* dqkv,
                         float* delta, int b, int s, int a, int d, int causal, const DropArgs& drop, hipStream_t st) {
-    if (per_row(variant, b, s, a, d)) return launch_attention_bwd_simple<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
+    if (per_row(variant, b, s, a, d, true)) return launch_attention_bwd_simple<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
     return launch_attention_bwd_f32<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
   }
 };
