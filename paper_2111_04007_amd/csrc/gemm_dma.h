@@ -887,11 +887,16 @@ inline int dg_wgrad_splits(int64_t M, int64_t N, int64_t K) {
 // or the whole rounds of 256x256 tiles its tiles need; one by one every product rounds up by itself.  With fewer tiles than
 // slots cutting the reductions (dg_wgrad_splits) fills the chip better.  Measured (us), one by one with their
 // split sums against one launch, the four matrices of a layer over 4096 tokens: 1920 wide 537 -> 422, 1024 wide 181 -> 125.
+// Whole steps with 8 stacked micro-batches (TFLOP/s, one by one / grouped): 1024 wide 624 / 642 and 3072 wide 833 / 887, both on
+// 256x256 tiles; on 128x128 tiles the mixture of matrices costs more of the L2 than the last rounds give once the reduction
+// is long: 1920 wide over 32768 tokens 806 / 758, so those stay one by one.
 inline int dg_group_choice(const DgJob* jobs, int n, int64_t K) {
   int64_t t5 = 0, t7 = 0;
-  bool plain5 = true, plain7 = true, edge = true;
+  bool plain5 = true, plain7 = true, edge = true, big_alone = true;
   for (int i = 0; i < n; ++i) {
     const int64_t M = jobs[i].M, N = jobs[i].N;
+    const int alone = dg_choose_variant(M, N, K, M, N);
+    big_alone = big_alone && (alone == 5 || alone == 23);
     plain5 = plain5 && dg_shape_ok(5, M, N, K, M, N);
     plain7 = plain7 && dg_shape_ok(7, M, N, K, M, N);
     edge = edge && dg_shape_ok(22, M, N, K, M, N);
@@ -901,7 +906,9 @@ inline int dg_group_choice(const DgJob* jobs, int n, int64_t K) {
   if (t7 < 512 || !(plain7 || edge)) return 0;
   const double cost7 = (double)t7 / 512.0 + 0.2;
   const double cost5 = (double)((t5 + 255) / 256) * 2.0 / 1.15 * (plain5 ? 1.0 : 1.05);
+  if (big_alone && t5 >= 16 * 256) return 0;   // whole rounds of 256x256 tiles either way
   if (cost5 <= cost7 && (plain5 || edge)) return plain5 ? 18 : 23;
+  if (K > 8192) return 0;
   return plain7 ? 19 : 22;
 }
 hipError_t launch_gemm_group(int variant, const DgJob* jobs, int n, int64_t K, hipStream_t st);   // gemm_wgrad.hip
