@@ -12,8 +12,12 @@
 //
 // What bounds it: the fp32 matrix rate once the chip is full, the serial products of one wave below that.  Measured against the
 // one-wave-per-row kernels (us; 2 x 500 tokens, 12 heads of 64, causal): forward 153 -> 26, backward 643 -> 82.
+//
+// A block that holds a result that is not finite works its rows out again one by one (attention_rows.h): what a masked token's
+// infinity or NaN did to rows that must not see it is undone.  The check takes 0.1 - 0.2 us of a kernel.
 #pragma once
 #include "attention.h"
+#include "attention_rows.h"
 #include "common.h"
 
 namespace varuna {
@@ -67,25 +71,34 @@ __device__ __forceinline__ void af_cols(float (&x)[16], const T* __restrict__ ba
     x[r] = row < rows ? v : 0.f;
   }
 }
-// acc[db][column of the tile][lane] += sum over the tile's 32 rows, weight w[r] for the lane's column of the result.  The tile
-// is read ahead (af_cols into `x`) up to D = 64; above, registers allow one 32-column block at a time.
-template <int D> struct AfTile { static constexpr bool AHEAD = D <= 64; float x[AHEAD ? D / 32 : 1][16]; };
-template <typename T, int D>
-__device__ __forceinline__ void af_ahead(AfTile<D>& t, const T* __restrict__ base, int64_t ld, int row0, int rows, int d, int half, int l32) {
-  if constexpr (AfTile<D>::AHEAD) {
+// acc[db][column of the tile][lane] += sum over the tile's 32 rows, weight w[r] for the lane's column of the result.  BUFS blocks of 32
+// columns of the tile are held at a time: all of them, read ahead of the scores (af_ahead), up to D = 64; above, registers
+// allow one, or two with the next one on its way during the products of one.  Taken by measurement (backward, us, against one
+// block): D = 96 all three in dQ 68.6 -> 62.4 (4 heads of 72, 200 tokens), D = 128 two in both 308 -> 285 (2 heads, 1000 tokens);
+// two blocks in the forward at D = 96 17.7 -> 21.8.
+template <int D, int BUFS = D / 32> struct AfTile { float x[BUFS][16]; };
+template <typename T, int D, int BUFS>
+__device__ __forceinline__ void af_ahead(AfTile<D, BUFS>& t, const T* __restrict__ base, int64_t ld, int row0, int rows, int d, int half, int l32) {
+  if constexpr (BUFS == D / 32) {
 #pragma unroll
     for (int db = 0; db < D / 32; ++db) af_cols<T>(t.x[db], base, ld, row0, rows, db, d, half, l32);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
-template <typename T, int D>
-__device__ __forceinline__ void af_weighted(floatx16 (&acc)[D / 32], AfTile<D>& t, const T* __restrict__ base, int64_t ld, int row0, int rows,
+template <typename T, int D, int BUFS>
+__device__ __forceinline__ void af_weighted(floatx16 (&acc)[D / 32], AfTile<D, BUFS>& t, const T* __restrict__ base, int64_t ld, int row0, int rows,
                                             int d, const floatx16& w, int half, int l32) {
+  constexpr bool AHEAD = BUFS == D / 32;
+  if constexpr (!AHEAD && BUFS == 2) af_cols<T>(t.x[0], base, ld, row0, rows, 0, d, half, l32);
 #pragma unroll
   for (int db = 0; db < D / 32; ++db) {
-    if constexpr (!AfTile<D>::AHEAD) af_cols<T>(t.x[0], base, ld, row0, rows, db, d, half, l32);
+    if constexpr (!AHEAD && BUFS == 1) af_cols<T>(t.x[0], base, ld, row0, rows, db, d, half, l32);
+    if constexpr (!AHEAD && BUFS == 2) {
+      if (db + 1 < D / 32) af_cols<T>(t.x[(db + 1) & 1], base, ld, row0, rows, db + 1, d, half, l32);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(t.x[AfTile<D>::AHEAD ? db : 0][r], w[r], acc[db], 0, 0, 0);
+    for (int r = 0; r < 16; ++r) acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(t.x[AHEAD ? db : db % BUFS][r], w[r], acc[db], 0, 0, 0);
   }
 }
 
@@ -116,10 +129,47 @@ __device__ __forceinline__ float af_get_sum(const float* sm, int row, int e) {
   return v;
 }
 
+// Arguments of the three kernels (the forward uses no dctx, dqkv and delta; the key side no ctx).
+template <typename T>
+struct AfArgs {
+  const T* qkv; T* ctx; float* lse;
+  const T* dctx; T* dqkv; float* delta;
+  int s, heads, d, causal;
+  DropArgs drop;
+};
+// Whether any thread of the block saw a result that is not finite (probe: ar_probe over what it stored); pad: the four unused words
+// behind a row of the partial results.
+__device__ __forceinline__ bool af_any(float* pad, float probe, int wave) {
+  const float mine = __ballot(!(probe == 0.f)) != 0 ? 1.f : 0.f;
+  if (ar_lane() == 0) pad[wave] = mine;
+  __syncthreads();
+  const floatx4 all = *reinterpret_cast<const floatx4*>(pad);
+  return __builtin_amdgcn_readfirstlane(all[0] + all[1] + all[2] + all[3] != 0.f);
+}
+// f(arguments, row, lane, first element of its head in qkv and in ctx, its index in the statistics) for the block's 32 rows, shared
+// out over the waves (attention_rows.h).  Everything is read anew from the argument segment: kept from the kernel's start for
+// this rare path it would cost the loops their registers.
+template <typename T, typename F>
+__device__ __forceinline__ void af_rows(int block, int wave, F&& f) {
+  auto seg = (const __attribute__((address_space(4))) AfArgs<T>*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(seg));
+  const AfArgs<T> a = *(const AfArgs<T>*)seg;
+  const int lane = ar_lane();
+  const int64_t head = blockIdx.x % a.heads, bi = blockIdx.x / a.heads, tok = bi * a.s * a.heads * a.d;
+  __threadfence();   // the results stored so far are in place in every wave before they are stored again
+  __syncthreads();
+  for (int row = block * 32 + wave; row < block * 32 + 32 && row < a.s; row += AF_WAVES)
+    f(a, row, lane, 3 * tok + head * a.d, tok + head * a.d, (bi * a.heads + head) * a.s);
+}
+
 // ctx and log-sum-exp (lse may be null).
 template <typename T, int D, bool VEC>
-__global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_fwd_kernel(const T* __restrict__ qkv, T* __restrict__ ctx, float* __restrict__ lse,
-                                                                       int s, int heads, int d, int causal, float scale_log2e, DropArgs drop) {
+__global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_fwd_kernel(AfArgs<T> args, float scale_log2e) {
+  const T* __restrict__ qkv = args.qkv;
+  T* __restrict__ ctx = args.ctx;
+  float* __restrict__ lse = args.lse;
+  const int s = args.s, heads = args.heads, d = args.d, causal = args.causal;
+  const DropArgs drop = args.drop;
   __shared__ __attribute__((aligned(16))) float so[AF_WAVES * 32 * (D + 4)];
   __shared__ float sml[2][AF_WAVES][32];
   const int tid = threadIdx.x, lane = tid % kWave, half = lane >> 5, l32 = lane & 31;
@@ -142,8 +192,8 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_fwd_kernel(const T* 
   };
   if (wave * 32 < end) load_k(wave * 32);
   for (int k0 = wave * 32; k0 < end; k0 += AF_WAVES * 32) {
-    AfTile<D> vt;
-    af_ahead<T, D>(vt, base + 2 * h, ld, k0, s, d, half, l32);
+    AfTile<D, D <= 64 ? D / 32 : 1> vt;
+    af_ahead<T>(vt, base + 2 * h, ld, k0, s, d, half, l32);
     floatx16 sc = af_dot<D>(kf, qf);
     if (k0 + AF_WAVES * 32 < end) load_k(k0 + AF_WAVES * 32);
     float mx = -INFINITY;
@@ -175,12 +225,13 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_fwd_kernel(const T* 
           if (!drop_keep(drop, w, e)) sc[4 * g + e] = 0.f;
       }
     }
-    af_weighted<T, D>(o, vt, base + 2 * h, ld, k0, s, d, sc, half, l32);
+    af_weighted<T>(o, vt, base + 2 * h, ld, k0, s, d, sc, half, l32);
   }
   l += __shfl_xor(l, 32, 64);
   af_put<D>(so, o, wave, half, l32);
   if (half == 0) { sml[0][wave][l32] = m; sml[1][wave][l32] = l; }
   __syncthreads();
+  float probe = 0.f;
   for (int i = tid; i < 32 * D; i += AF_WAVES * kWave) {
     const int row = i / D, e = i % D;
     if (q0 + row >= s || e >= d) continue;
@@ -194,17 +245,27 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_fwd_kernel(const T* 
       num += a * so[(w * 32 + row) * (D + 4) + e];
       den += a * sml[1][w][row];
     }
-    ctx[((int64_t)bi * s + q0 + row) * h + (int64_t)head * d + e] = from_f32<T>(num * ((drop.thr != 0 ? drop.scale : 1.0f) / den));
+    const float v = num * ((drop.thr != 0 ? drop.scale : 1.0f) / den);
+    probe = ar_probe(probe, v);
+    ctx[((int64_t)bi * s + q0 + row) * h + (int64_t)head * d + e] = from_f32<T>(v);
     if (lse && e == 0) lse[((int64_t)bi * heads + head) * s + q0 + row] = (mm + log2f(den)) * 0.6931471805599453f;
   }
+  if (af_any(so + D, probe, wave)) af_rows<T>((int)(gridDim.y - 1 - blockIdx.y), wave, [](const AfArgs<T>& a, int i, int ln, int64_t at3, int64_t at, int64_t stat) {
+    ar_fwd<T>(a.qkv + at3, a.ctx + at, a.lse, i, a.s, a.heads * a.d, a.d, a.causal, 1.0f / sqrtf((float)a.d), stat, a.drop, ln);
+  });
 }
 
 // dQ, and delta = rowsum(dO * O) for the key-side kernel.
 template <typename T, int D, bool VEC>
-__global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_bwd_dq_kernel(const T* __restrict__ qkv, const T* __restrict__ ctx,
-                                                                          const float* __restrict__ lse, const T* __restrict__ dctx,
-                                                                          T* __restrict__ dqkv, float* __restrict__ delta, int s, int heads,
-                                                                          int d, int causal, float scale, DropArgs drop) {
+__global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_bwd_dq_kernel(AfArgs<T> args, float scale) {
+  const T* __restrict__ qkv = args.qkv;
+  const T* __restrict__ ctx = args.ctx;
+  const T* __restrict__ dctx = args.dctx;
+  const float* __restrict__ lse = args.lse;
+  T* __restrict__ dqkv = args.dqkv;
+  float* __restrict__ delta = args.delta;
+  const int s = args.s, heads = args.heads, d = args.d, causal = args.causal;
+  const DropArgs drop = args.drop;
   __shared__ __attribute__((aligned(16))) float so[AF_WAVES * 32 * (D + 4)];
   const int tid = threadIdx.x, lane = tid % kWave, half = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -231,8 +292,8 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_bwd_dq_kernel(const 
   for (int k0 = wave * 32; k0 < end; k0 += AF_WAVES * 32) {
     const int key0 = k0 + l32, krow = key0 < s ? key0 : s - 1;
     af_row<T, D, VEC>(rf, base + h + (int64_t)krow * ld, half, d);
-    AfTile<D> kt;
-    af_ahead<T, D>(kt, base + h, ld, k0, s, d, half, l32);
+    AfTile<D, D <= 64 || (D == 96 && VEC) ? D / 32 : (D == 96 ? 1 : 2)> kt;
+    af_ahead<T>(kt, base + h, ld, k0, s, d, half, l32);
     const floatx16 sc = af_dot<D>(rf, qf);
     af_row<T, D, VEC>(rf, base + 2 * h + (int64_t)krow * ld, half, d);
     floatx16 ds = af_dot<D>(rf, gf);
@@ -250,22 +311,33 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_bwd_dq_kernel(const 
       const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, -l2));
       ds[r] = (key >= s || (causal && key > query)) ? 0.f : p * (ds[r] - dl);
     }
-    af_weighted<T, D>(dq, kt, base + h, ld, k0, s, d, ds, half, l32);
+    af_weighted<T>(dq, kt, base + h, ld, k0, s, d, ds, half, l32);
   }
   af_put<D>(so, dq, wave, half, l32);
   __syncthreads();
+  float probe = 0.f;
   for (int i = tid; i < 32 * D; i += AF_WAVES * kWave) {
     const int row = i / D, e = i % D;
-    if (q0 + row < s && e < d) dqkv[((int64_t)bi * s + q0 + row) * ld + (int64_t)head * d + e] = from_f32<T>(af_get_sum<D>(so, row, e) * scale);
+    if (q0 + row >= s || e >= d) continue;
+    const float v = af_get_sum<D>(so, row, e) * scale;
+    probe = ar_probe(probe, v);
+    dqkv[((int64_t)bi * s + q0 + row) * ld + (int64_t)head * d + e] = from_f32<T>(v);
   }
+  if (af_any(so + D, probe, wave)) af_rows<T>((int)(gridDim.y - 1 - blockIdx.y), wave, [](const AfArgs<T>& a, int i, int ln, int64_t at3, int64_t at, int64_t stat) {
+    ar_dq<T>(a.qkv + at3, a.ctx + at, a.dctx + at, a.lse, a.dqkv + at3, i, a.s, a.heads * a.d, a.d, a.causal, 1.0f / sqrtf((float)a.d), stat, a.drop, ln);
+  });
 }
 
 // dK and dV.
 template <typename T, int D, bool VEC>
-__global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_bwd_dkv_kernel(const T* __restrict__ qkv, const float* __restrict__ lse,
-                                                                           const T* __restrict__ dctx, const float* __restrict__ delta,
-                                                                           T* __restrict__ dqkv, int s, int heads, int d, int causal,
-                                                                           float scale, DropArgs drop) {
+__global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_bwd_dkv_kernel(AfArgs<T> args, float scale) {
+  const T* __restrict__ qkv = args.qkv;
+  const T* __restrict__ dctx = args.dctx;
+  const float* __restrict__ lse = args.lse;
+  const float* __restrict__ delta = args.delta;
+  T* __restrict__ dqkv = args.dqkv;
+  const int s = args.s, heads = args.heads, d = args.d, causal = args.causal;
+  const DropArgs drop = args.drop;
   __shared__ __attribute__((aligned(16))) float so[AF_WAVES * 32 * (D + 4)];
   const int tid = threadIdx.x, lane = tid % kWave, half = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -284,9 +356,9 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_bwd_dkv_kernel(const
   for (int q0 = (causal ? kb0 : 0) + wave * 32; q0 < s; q0 += AF_WAVES * 32) {
     const int qr = q0 + l32, qrow = qr < s ? qr : s - 1;
     af_row<T, D, VEC>(rf, base + (int64_t)qrow * ld, half, d);
-    AfTile<D> gt, qt;
-    af_ahead<T, D>(gt, gbase, h, q0, s, d, half, l32);
-    af_ahead<T, D>(qt, base, ld, q0, s, d, half, l32);
+    AfTile<D, D <= 64 ? D / 32 : (D == 96 ? 1 : 2)> gt, qt;
+    af_ahead<T>(gt, gbase, h, q0, s, d, half, l32);
+    af_ahead<T>(qt, base, ld, q0, s, d, half, l32);
     const floatx16 sc = af_dot<D>(rf, kf);
     af_row<T, D, VEC>(rf, gbase + (int64_t)qrow * h, half, d);
     const floatx16 dp = af_dot<D>(rf, vf);
@@ -304,29 +376,39 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_bwd_dkv_kernel(const
       pr[r] = p * f;
       ds[r] = in ? p * (dp[r] * f - delta[at]) : 0.f;
     }
-    af_weighted<T, D>(dv, gt, gbase, h, q0, s, d, pr, half, l32);
-    af_weighted<T, D>(dk, qt, base, ld, q0, s, d, ds, half, l32);
+    af_weighted<T>(dv, gt, gbase, h, q0, s, d, pr, half, l32);
+    af_weighted<T>(dk, qt, base, ld, q0, s, d, ds, half, l32);
   }
   af_put<D>(so, dk, wave, half, l32);
   __syncthreads();
+  float probe = 0.f;
   for (int i = tid; i < 32 * D; i += AF_WAVES * kWave) {
     const int row = i / D, e = i % D;
-    if (kb0 + row < s && e < d) dqkv[((int64_t)bi * s + kb0 + row) * ld + h + (int64_t)head * d + e] = from_f32<T>(af_get_sum<D>(so, row, e) * scale);
+    if (kb0 + row >= s || e >= d) continue;
+    const float v = af_get_sum<D>(so, row, e) * scale;
+    probe = ar_probe(probe, v);
+    dqkv[((int64_t)bi * s + kb0 + row) * ld + h + (int64_t)head * d + e] = from_f32<T>(v);
   }
   __syncthreads();
   af_put<D>(so, dv, wave, half, l32);
   __syncthreads();
   for (int i = tid; i < 32 * D; i += AF_WAVES * kWave) {
     const int row = i / D, e = i % D;
-    if (kb0 + row < s && e < d) dqkv[((int64_t)bi * s + kb0 + row) * ld + 2 * h + (int64_t)head * d + e] = from_f32<T>(af_get_sum<D>(so, row, e));
+    if (kb0 + row >= s || e >= d) continue;
+    const float v = af_get_sum<D>(so, row, e);
+    probe = ar_probe(probe, v);
+    dqkv[((int64_t)bi * s + kb0 + row) * ld + 2 * h + (int64_t)head * d + e] = from_f32<T>(v);
   }
+  if (af_any(so + D, probe, wave)) af_rows<T>((int)blockIdx.y, wave, [](const AfArgs<T>& a, int i, int ln, int64_t at3, int64_t at, int64_t stat) {
+    ar_dkv<T>(a.qkv + at3, a.dctx + at, a.lse, a.delta, a.dqkv + at3, i, a.s, a.heads * a.d, a.d, a.causal, 1.0f / sqrtf((float)a.d), stat, a.drop, ln);
+  });
 }
 
 template <typename T, int D, bool VEC>
 inline hipError_t af_fwd(const T* qkv, T* ctx, float* lse, int b, int s, int heads, int d, int causal, const DropArgs& drop, hipStream_t st) {
   const dim3 grid((unsigned)(heads * b), (unsigned)((s + 31) / 32));
-  hipLaunchKernelGGL((attn_f32_fwd_kernel<T, D, VEC>), grid, dim3(AF_WAVES * kWave), 0, st, qkv, ctx, lse, s, heads, d, causal,
-                     1.4426950408889634f / sqrtf((float)d), drop);
+  const AfArgs<T> a{qkv, ctx, lse, nullptr, nullptr, nullptr, s, heads, d, causal, drop};
+  hipLaunchKernelGGL((attn_f32_fwd_kernel<T, D, VEC>), grid, dim3(AF_WAVES * kWave), 0, st, a, 1.4426950408889634f / sqrtf((float)d));
   return hipGetLastError();
 }
 template <typename T, int D, bool VEC>
@@ -334,8 +416,9 @@ inline hipError_t af_bwd(const T* qkv, const T* ctx, const float* lse, const T* 
                          int causal, const DropArgs& drop, hipStream_t st) {
   const dim3 grid((unsigned)(heads * b), (unsigned)((s + 31) / 32)), block(AF_WAVES * kWave);
   const float scale = 1.0f / sqrtf((float)d);
-  hipLaunchKernelGGL((attn_f32_bwd_dq_kernel<T, D, VEC>), grid, block, 0, st, qkv, ctx, lse, dctx, dqkv, delta, s, heads, d, causal, scale, drop);
-  hipLaunchKernelGGL((attn_f32_bwd_dkv_kernel<T, D, VEC>), grid, block, 0, st, qkv, lse, dctx, delta, dqkv, s, heads, d, causal, scale, drop);
+  const AfArgs<T> a{qkv, const_cast<T*>(ctx), const_cast<float*>(lse), dctx, dqkv, delta, s, heads, d, causal, drop};
+  hipLaunchKernelGGL((attn_f32_bwd_dq_kernel<T, D, VEC>), grid, block, 0, st, a, scale);
+  hipLaunchKernelGGL((attn_f32_bwd_dkv_kernel<T, D, VEC>), grid, block, 0, st, a, scale);
   return hipGetLastError();
 }
 

@@ -4,6 +4,9 @@
 // is a multiple of 8, in the next D of {32, 64, 96, 128}.  qkv is [b*s, 3h] (Q | K | V column blocks, head j at
 // column j*D of each), ctx / dctx are [b*s, h], lse / delta are [b, heads, s] fp32.
 //
+// The EDGE form works out rows that are not finite again one by one (attention_rows.h), so that an infinity or NaN of a
+// masked token does not reach them.
+//
 // All three kernels keep two 64-row tiles in LDS (rows of D values, padded pitch)
 // and hold the other operands in registers.  Products use
 // v_mfma_f32_32x32x16_bf16 whose operand layout is: row operand lane L -> row
@@ -23,6 +26,7 @@
 //   backward dK/dV (per 128-key workgroup, 32 keys per wave; Q, dO tiles in LDS):
 //     S = Q K^T, dP = dO V^T ; dV^T += dO^T P ; dK^T += Q^T dS
 #pragma once
+#include "attention_rows.h"
 #include "common.h"
 
 namespace varuna {
@@ -165,6 +169,27 @@ __device__ __forceinline__ bf16x8 at_pack8_rest(const float* p, const bf16x8& hi
   return r;
 }
 
+// f(row, lane, head, sequence) for the marked rows of the wave's 32, by the whole wave (attention_rows.h).  What f needs is derived
+// anew: values of the kernel's start kept for this rare path would cost its loop registers.
+template <typename F>
+__device__ __forceinline__ void at_bad_rows(uint32_t bad, int first, int rows, int heads, F&& f) {
+  bad = __builtin_amdgcn_readfirstlane(bad);
+  if (bad == 0) return;
+  asm volatile("" : "+s"(heads));
+  const int lane = ar_lane();
+  for (int i = 0; i < 32 && first + i < rows; ++i)
+    if (bad >> i & 1) f(first + i, lane, (int)(blockIdx.x % heads), (int)(blockIdx.x / heads));
+}
+// The sum of ar_probe over a lane's accumulators.
+template <int D>
+__device__ __forceinline__ float at_probe(const floatx16 (&acc)[AttnCfg<D>::DB], float t) {
+#pragma unroll
+  for (int db = 0; db < AttnCfg<D>::DB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) t = ar_probe(t, acc[db][r]);
+  return t;
+}
+
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
@@ -185,7 +210,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
   const int cols = EDGE ? d : D, h = heads * cols;
   const int64_t ld = 3 * (int64_t)h;
   const bf16* base = qkv + (int64_t)bi * s * ld + head * cols;
-  const int q0 = qb * 128, qw = q0 + wave * 32;  // this wave's first query
+  const int q0 = qb * 128, qw = q0 + wave * 32, qw_s = __builtin_amdgcn_readfirstlane(qw);  // this wave's first query
   const int query = qw + (lane & 31);
 
   const int qrow = EDGE && query >= s ? s - 1 : query;   // queries past the end repeat the last one and are not stored
@@ -325,19 +350,25 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
   }
   l += __shfl_xor(l, 32, 64);
   const float inv = (DROP ? drop.scale : 1.0f) / l;
-  if (EDGE && query >= s) return;
-  if (lse && hf == 0) lse[((int64_t)bi * heads + head) * s + query] = (m + log2f(l)) * 0.6931471805599453f;
-  bf16* crow = ctx + ((int64_t)bi * s + query) * h + head * cols;
+  const uint32_t bad = EDGE ? ar_bad_rows(at_probe<D>(o, ar_probe(0.f, l))) : 0;   // rows that are not finite: below
+  if (!EDGE || (query < s && !(bad >> (ar_lane() & 31) & 1))) {
+    if (lse && hf == 0) lse[((int64_t)bi * heads + head) * s + query] = (m + log2f(l)) * 0.6931471805599453f;
+    bf16* crow = ctx + ((int64_t)bi * s + query) * h + head * cols;
 #pragma unroll
-  for (int db = 0; db < C::DB; ++db)
+    for (int db = 0; db < C::DB; ++db)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      if (EDGE && db * 32 + 8 * g >= cols) continue;
-      bf16x4 v;
+      for (int g = 0; g < 4; ++g) {
+        if (EDGE && db * 32 + 8 * g >= cols) continue;
+        bf16x4 v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = (bf16)(o[db][4 * g + e] * inv);
-      *reinterpret_cast<bf16x4*>(crow + db * 32 + 8 * g + 4 * hf) = v;
-    }
+        for (int e = 0; e < 4; ++e) v[e] = (bf16)(o[db][4 * g + e] * inv);
+        *reinterpret_cast<bf16x4*>(crow + db * 32 + 8 * g + 4 * hf) = v;
+      }
+  }
+  if constexpr (EDGE) at_bad_rows(bad, qw_s, s, heads, [&](int i, int ln, int hd, int b) {
+    const int64_t at = (int64_t)b * s * heads * d + hd * d;
+    ar_fwd<bf16>(qkv + 3 * at - 2 * hd * d, ctx + at, lse, i, s, heads * d, d, CAUSAL, 1.0f / sqrtf((float)d), ((int64_t)b * heads + hd) * s, drop, ln);
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -358,7 +389,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
   const int cols = EDGE ? d : D, h = heads * cols;
   const int64_t ld = 3 * (int64_t)h;
   const bf16* base = qkv + (int64_t)bi * s * ld + head * cols;
-  const int q0 = qb * 128, qw = q0 + wave * 32;
+  const int q0 = qb * 128, qw = q0 + wave * 32, qw_s = __builtin_amdgcn_readfirstlane(qw);
   const int query = qw + (lane & 31);
   const int qrow = EDGE && query >= s ? s - 1 : query;   // queries past the end repeat the last one and store nothing
   const int64_t orow = ((int64_t)bi * s + qrow) * h + head * cols;
@@ -485,18 +516,24 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
       }
     }
   }
-  if (EDGE && query >= s) return;
-  bf16* drow = dqkv + ((int64_t)bi * s + query) * ld + head * cols;
+  const uint32_t bad = EDGE ? ar_bad_rows(at_probe<D>(dq, 0.f)) : 0;
+  if (!EDGE || (query < s && !(bad >> (ar_lane() & 31) & 1))) {
+    bf16* drow = dqkv + ((int64_t)bi * s + query) * ld + head * cols;
 #pragma unroll
-  for (int db = 0; db < C::DB; ++db)
+    for (int db = 0; db < C::DB; ++db)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      if (EDGE && db * 32 + 8 * g >= cols) continue;
-      bf16x4 v;
+      for (int g = 0; g < 4; ++g) {
+        if (EDGE && db * 32 + 8 * g >= cols) continue;
+        bf16x4 v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = (bf16)(dq[db][4 * g + e] * scale);
-      *reinterpret_cast<bf16x4*>(drow + db * 32 + 8 * g + 4 * hf) = v;
-    }
+        for (int e = 0; e < 4; ++e) v[e] = (bf16)(dq[db][4 * g + e] * scale);
+        *reinterpret_cast<bf16x4*>(drow + db * 32 + 8 * g + 4 * hf) = v;
+      }
+  }
+  if constexpr (EDGE) at_bad_rows(bad, qw_s, s, heads, [&](int i, int ln, int hd, int b) {
+    const int64_t at = (int64_t)b * s * heads * d + hd * d, at3 = 3 * at - 2 * hd * d;
+    ar_dq<bf16>(qkv + at3, ctx + at, dctx + at, lse, dqkv + at3, i, s, heads * d, d, CAUSAL, scale, ((int64_t)b * heads + hd) * s, drop, ln);
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -520,7 +557,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
   const int64_t ld = 3 * (int64_t)h;
   const bf16* base = qkv + (int64_t)bi * s * ld + head * cols;
   const bf16* gbase = dctx + (int64_t)bi * s * h + head * cols;
-  const int kb0 = kblk * 128, kw = kb0 + wave * 32;  // this wave's first key
+  const int kb0 = kblk * 128, kw = kb0 + wave * 32, kw_s = __builtin_amdgcn_readfirstlane(kw);  // this wave's first key
   const int key = kw + (lane & 31);
   const int64_t sbase = ((int64_t)bi * heads + head) * s;
 
@@ -677,20 +714,26 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
   }
   at_mfma_settle();
   __builtin_amdgcn_sched_barrier(0);  // the reads of dK/dV below stay below the wait
-  if (EDGE && key >= s) return;
-  bf16* krow = dqkv + ((int64_t)bi * s + key) * ld + h + head * cols;
-  bf16* vrow = krow + h;
+  const uint32_t bad = EDGE ? ar_bad_rows(at_probe<D>(dk, at_probe<D>(dv, 0.f))) : 0;
+  if (!EDGE || (key < s && !(bad >> (ar_lane() & 31) & 1))) {
+    bf16* krow = dqkv + ((int64_t)bi * s + key) * ld + h + head * cols;
+    bf16* vrow = krow + h;
 #pragma unroll
-  for (int db = 0; db < C::DB; ++db)
+    for (int db = 0; db < C::DB; ++db)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      if (EDGE && db * 32 + 8 * g >= cols) continue;
-      bf16x4 a, c;
+      for (int g = 0; g < 4; ++g) {
+        if (EDGE && db * 32 + 8 * g >= cols) continue;
+        bf16x4 a, c;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { a[e] = (bf16)(dk[db][4 * g + e] * scale); c[e] = (bf16)dv[db][4 * g + e]; }
-      *reinterpret_cast<bf16x4*>(krow + db * 32 + 8 * g + 4 * hf) = a;
-      *reinterpret_cast<bf16x4*>(vrow + db * 32 + 8 * g + 4 * hf) = c;
-    }
+        for (int e = 0; e < 4; ++e) { a[e] = (bf16)(dk[db][4 * g + e] * scale); c[e] = (bf16)dv[db][4 * g + e]; }
+        *reinterpret_cast<bf16x4*>(krow + db * 32 + 8 * g + 4 * hf) = a;
+        *reinterpret_cast<bf16x4*>(vrow + db * 32 + 8 * g + 4 * hf) = c;
+      }
+  }
+  if constexpr (EDGE) at_bad_rows(bad, kw_s, s, heads, [&](int i, int ln, int hd, int b) {
+    const int64_t at = (int64_t)b * s * heads * d + hd * d, at3 = 3 * at - 2 * hd * d;
+    ar_dkv<bf16>(qkv + at3, dctx + at, lse, delta, dqkv + at3, i, s, heads * d, d, CAUSAL, scale, ((int64_t)b * heads + hd) * s, drop, ln);
+  });
 }
 
 }  // namespace varuna
