@@ -24,8 +24,9 @@ hipError_t launch_attention_fwd_mfma_edge(const bf16* qkv, bf16* ctx, float* lse
 hipError_t launch_attention_bwd_mfma_edge(const bf16* qkv, const bf16* ctx, const float* lse, const bf16* dctx, bf16* dqkv,
                                      float* delta, int b, int s, int heads, int d, int causal, const DropArgs& drop, hipStream_t st);
 
-// The tiled forms take (batch, head) as one grid dimension.
-inline bool attn_grid_ok(int b, int heads) { return (int64_t)b * heads < (1ll << 31); }
+// The tiled forms take (batch, head) as one grid dimension of 256-thread blocks, and a dimension holds less than 2^32 threads;
+// beyond, the per-row kernels (three dimensions) serve.
+inline bool attn_grid_ok(int b, int heads) { return (int64_t)b * heads < (1ll << 24); }
 // fp32 products on the matrix cores (attention_f32.h), head dims up to 128.
 inline bool attn_f32_supported(int d) { return d <= 128; }
 // A call of a few short rows ends sooner with one wave per row: a wave of the other form works through whole 32x32 tiles, 7-8 us
