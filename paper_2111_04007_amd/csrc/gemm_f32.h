@@ -196,6 +196,11 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * KS * kWave) void gemm_f32_k
   int logical = blockIdx.x;
   const int nblk = gridDim.x;
   if ((nblk & 7) == 0) logical = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+  if (gridDim.y > 1) {   // more than 2^22 tiles
+    const int64_t t = (int64_t)blockIdx.y * nblk + logical;
+    if (t >= (int64_t)tiles_m * tiles_n) return;
+    logical = (int)t;
+  }
   gf_tile<T, MODE, AK, BK, BM, BN, WM, WN, KS, BKT, VEC>(a, lda, b, ldb, M, N, K, tiles_m, tiles_n, epi, logical);
 }
 

@@ -11,7 +11,10 @@ inline hipError_t gf_launch_tile(bool vec, const T* a, int64_t lda, const T* b, 
                                  const EpiArgs<T>& epi, hipStream_t st) {
   const int64_t tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
   if (tm > (1 << 27) || tn > (1 << 27) || tm * tn >= (1ll << 31)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(tm * tn)), block((BM / WM) * (BN / WN) * KS * kWave);
+  // a grid dimension holds less than 2^32 threads: 2^22 blocks of up to 512, then a second one (blocks past the last tile end)
+  constexpr int64_t line = 1 << 22;
+  const int64_t tiles = tm * tn;
+  const dim3 grid((unsigned)(tiles < line ? tiles : line), (unsigned)((tiles + line - 1) / line)), block((BM / WM) * (BN / WN) * KS * kWave);
   if (vec) hipLaunchKernelGGL((gemm_f32_kernel<T, MODE, AK, BK, BM, BN, WM, WN, KS, BKT, true>), grid, block, 0, st, a, lda, b, ldb, M, N, K, (int)tm, (int)tn, epi);
   else hipLaunchKernelGGL((gemm_f32_kernel<T, MODE, AK, BK, BM, BN, WM, WN, KS, BKT, false>), grid, block, 0, st, a, lda, b, ldb, M, N, K, (int)tm, (int)tn, epi);
   return hipGetLastError();

@@ -24,3 +24,17 @@ def test_attention_with_more_than_2_24_heads(dtype, d):
     assert torch.equal(dqkv[:, 2 * h:], dctx)
     # dP - delta is the difference of two orders of one sum of d products: 2^-24 of it each, times values of a few units
     assert float(dqkv[:, :2 * h].abs().max()) <= 1e-4
+
+
+@pytest.mark.parametrize("dtype,M,N", [(torch.float32, (1 << 28) + 40, 1), (torch.bfloat16, (1 << 28) + 40, 1), (torch.float32, 3, (1 << 28) + 33)])
+def test_gemm_of_more_than_2_23_tiles(dtype, M, N):
+    """One-term products, so every output has one rounding: the tall and the wide side of 32x32 tiles."""
+    g = torch.Generator(device="cuda").manual_seed(2)
+    x, w, bias = (torch.empty(n, dtype=dtype, device="cuda").normal_(generator=g) for n in ((M, 1), (N, 1), (N,)))
+    out = torch.full((M, N), 7.0, dtype=dtype, device="cuda")
+    B.op_gemm(B.OP_FWD, 0, x, w, out, bias=bias, M=M, N=N, K=1)
+    for lo in range(0, max(M, N), 1 << 26):   # (the reference in pieces)
+        rows, cols = (slice(lo, lo + (1 << 26)), slice(None)) if M > N else (slice(None), slice(lo, lo + (1 << 26)))
+        want = torch.addcmul(bias[cols].float()[None], x[rows].float(), w[cols].float().t())
+        assert float((out[rows, cols].float() - want).abs().max()) <= (2.0 ** -18 if dtype == torch.float32 else 2.0 ** -4)
+        assert float((out[rows, cols].float() - want).norm() / want.norm()) <= (2.0 ** -22 if dtype == torch.float32 else 2.0 ** -8)
