@@ -276,29 +276,37 @@ __global__ __launch_bounds__(CR_COLS* CR_ROWLANES) void colreduce_partial_kernel
 // outputs per thread lane, the chunks over 8 groups of lanes (summed through LDS in a fixed order): the kernel lasts as
 // long as one thread's serial loads.
 constexpr int CF_COLS = 32, CF_LANES = 8;
+template <int COLS, int LANES>
 __device__ __forceinline__ void colreduce_final_block(const float* __restrict__ partial, int64_t pitch, int nchunks, int64_t n,
                                                       float* __restrict__ out0, float* __restrict__ out1, int64_t blk) {
-  __shared__ float sh[CF_LANES][CF_COLS];
-  const int c = threadIdx.x % CF_COLS, l = threadIdx.x / CF_COLS;
-  const int64_t width = out1 ? 2 * n : n, col = blk * CF_COLS + c;
+  __shared__ float sh[LANES][COLS];
+  const int c = threadIdx.x % COLS, l = threadIdx.x / COLS;
+  const int64_t width = out1 ? 2 * n : n, col = blk * COLS + c;
   float t = 0.f;
   if (col < width)
 #pragma unroll 4
-    for (int k = l; k < nchunks; k += CF_LANES) t += partial[(int64_t)k * pitch + col];
-  sh[l][c] = t;
-  __syncthreads();
-  if (l != 0 || col >= width) return;
+    for (int k = l; k < nchunks; k += LANES) t += partial[(int64_t)k * pitch + col];
+  if constexpr (LANES > 1) {
+    sh[l][c] = t;
+    __syncthreads();
+    if (l != 0) return;
 #pragma unroll
-  for (int i = 1; i < CF_LANES; ++i) t += sh[i][c];
+    for (int i = 1; i < LANES; ++i) t += sh[i][c];
+  }
+  if (col >= width) return;
   if (col < n) out0[col] += t; else out1[col - n] += t;
 }
-__global__ __launch_bounds__(CF_COLS* CF_LANES) void colreduce_final_kernel(const float* __restrict__ partial, int nchunks, int64_t n,
-                                                                            float* __restrict__ out0, float* __restrict__ out1) {
-  colreduce_final_block(partial, out1 ? 2 * n : n, nchunks, n, out0, out1, blockIdx.x);
+template <int COLS, int LANES>
+__global__ __launch_bounds__(COLS* LANES) void colreduce_final_kernel(const float* __restrict__ partial, int nchunks, int64_t n,
+                                                                      float* __restrict__ out0, float* __restrict__ out1) {
+  colreduce_final_block<COLS, LANES>(partial, out1 ? 2 * n : n, nchunks, n, out0, out1, blockIdx.x);
 }
 inline void launch_colreduce_final(const float* partial, int nchunks, int64_t n, float* out0, float* out1, hipStream_t st) {
   const int64_t width = out1 ? 2 * n : n;
-  hipLaunchKernelGGL(colreduce_final_kernel, dim3((unsigned)((width + CF_COLS - 1) / CF_COLS)), dim3(CF_COLS * CF_LANES), 0, st, partial, nchunks, n, out0, out1);
+  if (nchunks <= CF_LANES / 2)   // a thread per column: no lanes to spare on so few chunks (1 x 2^20 sums 23.4 -> 13.9 us for both stages)
+    hipLaunchKernelGGL((colreduce_final_kernel<256, 1>), dim3((unsigned)((width + 255) / 256)), dim3(256), 0, st, partial, nchunks, n, out0, out1);
+  else
+    hipLaunchKernelGGL((colreduce_final_kernel<CF_COLS, CF_LANES>), dim3((unsigned)((width + CF_COLS - 1) / CF_COLS)), dim3(CF_COLS * CF_LANES), 0, st, partial, nchunks, n, out0, out1);
 }
 
 template <typename T> constexpr int ln_vec() { return 16 / (int)sizeof(T); }
@@ -324,16 +332,19 @@ inline hipError_t launch_layernorm_fwd(const T* x, const T* gamma, const T* beta
   return hipGetLastError();
 }
 
-// The same partial column sums with 16-byte accesses.  HBM-bound, so what counts is how many loads are in flight: a block
-// takes 8 column groups of VEC columns (128-byte row segments) x 32 row lanes, which makes four times as many blocks
-// of the same number of partials as 32 groups x 8 row lanes did (480 for 4096 x 1920).  Measured there: gamma / beta
-// sums 16.1 -> 8.7 us (31 MB, mostly from the caches), their second stage 6.7 -> 3.2 us.
+// The same partial column sums with 16-byte accesses.  HBM-bound, so what counts is how many loads are in flight.  A block takes
+// 8 column groups of VEC columns (128-byte row segments) x 32 row lanes, or 32 groups x 8 row lanes: a quarter of the blocks, for
+// the same number of partials, with longer row segments.  The wide form serves what it fills the chip with (2 blocks per CU; 3
+// for the gamma / beta sums, which read twice as much per block).  Measured, narrow / wide (us, both stages or the whole backward):
+// sums in bf16 1024 x 32768 14.2 / 13.2, 16384 x 8192 44.5 / 41.4, fp32 512 x 32768 14.1 / 12.8, but 16384 x 256 fp32 backward
+// 20.3 / 21.7; LayerNorm backward in bf16 4096 x 1920 20.9 / 36.4, 16384 x 1920 58.6 / 65.7, 16384 x 8192 360 / 338, fp32
+// 4096 x 1024 19.2 / 23.5, 16384 x 8192 825 / 794.  Of few rows the narrow form leaves most row lanes idle: 1 x 2^20 23.3 / 17.7.
+// Rows of 256 KB and more are taken one at a time, not four: fp32 512 x 131072 47.1 -> 39.8.
 constexpr int CRV_CG = 8, CRV_RL = 32;   // column groups and row lanes of a block
-template <typename T, int LNMODE, int VEC>
+template <typename T, int LNMODE, int VEC, int CG, int RL, int UNROLL = 4>
 __device__ __forceinline__ void colreduce_partial_block(
     const T* __restrict__ a, const T* __restrict__ x, const float* __restrict__ stats, int64_t rows, int64_t n, int64_t colblk,
-    int64_t chunk, float (&sh)[2][CRV_RL][CRV_CG * VEC + 4]) {
-  constexpr int CG = CRV_CG, RL = CRV_RL;
+    int64_t chunk, float (&sh)[2][RL][CG * VEC + 4]) {
   const int cg = threadIdx.x % CG, rl = threadIdx.x / CG;
   const int64_t col = (colblk * CG + cg) * VEC;
   const int64_t r0 = chunk * CR_CHUNK;
@@ -342,7 +353,7 @@ __device__ __forceinline__ void colreduce_partial_block(
 #pragma unroll
   for (int i = 0; i < VEC; ++i) { s0[i] = 0.f; s1[i] = 0.f; }
   if (col < n) {
-#pragma unroll 4
+#pragma unroll UNROLL
     for (int t = rl; t < nr; t += RL) {
       float v[VEC];
       VecLoad<T, VEC>::load(a + (r0 + t) * n + col, v);
@@ -363,26 +374,26 @@ __device__ __forceinline__ void colreduce_partial_block(
   __syncthreads();
 }
 // Sum number c of the block (LNMODE: first the columns' dy * xhat, then their dy).
-template <int COLS>
-__device__ __forceinline__ float colreduce_block_sum(const float (&sh)[2][CRV_RL][COLS + 4], int which, int c) {
+template <int COLS, int RL>
+__device__ __forceinline__ float colreduce_block_sum(const float (&sh)[2][RL][COLS + 4], int which, int c) {
   float t = 0.f;
 #pragma unroll
-  for (int i = 0; i < CRV_RL; ++i) t += sh[which][i][c];
+  for (int i = 0; i < RL; ++i) t += sh[which][i][c];
   return t;
 }
 
-template <typename T, int LNMODE, int VEC>
+template <typename T, int LNMODE, int VEC, int CG, int RL, int UNROLL>
 __global__ __launch_bounds__(256) void colreduce_partial_vec_kernel(
     const T* __restrict__ a, const T* __restrict__ x, const float* __restrict__ stats,
     float* __restrict__ partial, int64_t rows, int64_t n) {
-  constexpr int COLS = CRV_CG * VEC;
-  __shared__ float sh[2][CRV_RL][COLS + 4];
-  colreduce_partial_block<T, LNMODE, VEC>(a, x, stats, rows, n, blockIdx.x, blockIdx.y, sh);
+  constexpr int COLS = CG * VEC;
+  __shared__ float sh[2][RL][COLS + 4];
+  colreduce_partial_block<T, LNMODE, VEC, CG, RL, UNROLL>(a, x, stats, rows, n, blockIdx.x, blockIdx.y, sh);
   const int64_t width = LNMODE ? 2 * n : n;
-  if (threadIdx.x < (LNMODE ? 2 : 1) * COLS) {
-    const int which = threadIdx.x / COLS, c = threadIdx.x % COLS;
+  for (int t = threadIdx.x; t < (LNMODE ? 2 : 1) * COLS; t += 256) {
+    const int which = t / COLS, c = t % COLS;
     const int64_t gc = (int64_t)blockIdx.x * COLS + c;
-    if (gc < n) partial[(int64_t)blockIdx.y * width + which * n + gc] = colreduce_block_sum<COLS>(sh, which, c);
+    if (gc < n) partial[(int64_t)blockIdx.y * width + which * n + gc] = colreduce_block_sum<COLS, RL>(sh, which, c);
   }
 }
 
@@ -410,13 +421,13 @@ __global__ __launch_bounds__(256) void colreduce_jobs_partial_kernel(ReduceJobs<
   const ReduceJob<T> w = g.job[j];
   const int colblk = (int)blockIdx.x - g.first[j];
   const bool ln = w.x != nullptr;
-  if (ln) colreduce_partial_block<T, 1, VEC>(w.a, w.x, w.stats, g.rows, w.n, colblk, blockIdx.y, sh);
-  else colreduce_partial_block<T, 0, VEC>(w.a, nullptr, nullptr, g.rows, w.n, colblk, blockIdx.y, sh);
+  if (ln) colreduce_partial_block<T, 1, VEC, CRV_CG, CRV_RL>(w.a, w.x, w.stats, g.rows, w.n, colblk, blockIdx.y, sh);
+  else colreduce_partial_block<T, 0, VEC, CRV_CG, CRV_RL>(w.a, nullptr, nullptr, g.rows, w.n, colblk, blockIdx.y, sh);
   if ((int)threadIdx.x >= (ln ? 2 : 1) * COLS) return;
   const int which = threadIdx.x / COLS, c = threadIdx.x % COLS;
   const int64_t gc = (int64_t)colblk * COLS + c;
   if (gc >= w.n) return;
-  const float t = colreduce_block_sum<COLS>(sh, which, c);
+  const float t = colreduce_block_sum<COLS, CRV_RL>(sh, which, c);
   if (g.nchunks == 1) (which ? w.out1 : w.out0)[gc] += t;
   else partial[(int64_t)blockIdx.y * g.pitch + g.pcol[j] + which * w.n + gc] = t;
 }
@@ -425,7 +436,7 @@ __global__ __launch_bounds__(CF_COLS* CF_LANES) void colreduce_jobs_final_kernel
   int j = 0;
   while (j + 1 < g.n_jobs && (int)blockIdx.x >= g.ffirst[j + 1]) ++j;
   const ReduceJob<T> w = g.job[j];
-  colreduce_final_block(partial + g.pcol[j], g.pitch, g.nchunks, w.n, w.out0, w.out1, (int64_t)((int)blockIdx.x - g.ffirst[j]));
+  colreduce_final_block<CF_COLS, CF_LANES>(partial + g.pcol[j], g.pitch, g.nchunks, w.n, w.out0, w.out1, (int64_t)((int)blockIdx.x - g.ffirst[j]));
 }
 
 template <typename T, int LNMODE>
@@ -435,8 +446,15 @@ inline void launch_colreduce_partial(const T* a, const T* x, const float* stats,
   constexpr int VEC = 16 / sizeof(T);
   const bool aligned = (reinterpret_cast<uintptr_t>(a) % 16 == 0) && (x == nullptr || reinterpret_cast<uintptr_t>(x) % 16 == 0);
   if (n % VEC == 0 && aligned) {
-    dim3 g((unsigned)((n + 8 * VEC - 1) / (8 * VEC)), (unsigned)nch);
-    hipLaunchKernelGGL((colreduce_partial_vec_kernel<T, LNMODE, VEC>), g, dim3(256), 0, st, a, x, stats, partial, rows, n);
+    const int64_t wide = (n + CRV_RL * VEC - 1) / (CRV_RL * VEC);
+    if (wide * nch >= (LNMODE ? 768 : 512)) {
+      dim3 g((unsigned)wide, (unsigned)nch);
+      if (n * (int64_t)sizeof(T) >= (1 << 18)) hipLaunchKernelGGL((colreduce_partial_vec_kernel<T, LNMODE, VEC, CRV_RL, CRV_CG, 1>), g, dim3(256), 0, st, a, x, stats, partial, rows, n);
+      else hipLaunchKernelGGL((colreduce_partial_vec_kernel<T, LNMODE, VEC, CRV_RL, CRV_CG, 4>), g, dim3(256), 0, st, a, x, stats, partial, rows, n);
+    } else {
+      dim3 g((unsigned)((n + CRV_CG * VEC - 1) / (CRV_CG * VEC)), (unsigned)nch);
+      hipLaunchKernelGGL((colreduce_partial_vec_kernel<T, LNMODE, VEC, CRV_CG, CRV_RL, 4>), g, dim3(256), 0, st, a, x, stats, partial, rows, n);
+    }
   } else {
     dim3 g((unsigned)((n + CR_COLS - 1) / CR_COLS), (unsigned)nch);
     hipLaunchKernelGGL((colreduce_partial_kernel<T, LNMODE>), g, dim3(CR_COLS * CR_ROWLANES), 0, st, a, x, stats, partial, rows, n);

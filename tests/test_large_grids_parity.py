@@ -38,3 +38,13 @@ def test_gemm_of_more_than_2_23_tiles(dtype, M, N):
         want = torch.addcmul(bias[cols].float()[None], x[rows].float(), w[cols].float().t())
         assert float((out[rows, cols].float() - want).abs().max()) <= (2.0 ** -18 if dtype == torch.float32 else 2.0 ** -4)
         assert float((out[rows, cols].float() - want).norm() / want.norm()) <= (2.0 ** -22 if dtype == torch.float32 else 2.0 ** -8)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_colsum_of_more_than_2_29_columns(dtype):
+    n = (1 << 30) + 256 if dtype == torch.bfloat16 else (1 << 29) + 128
+    a = torch.empty((1, n), dtype=dtype, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(3))
+    out = torch.ones(n, device="cuda")
+    B.op_colsum(a, out, torch.empty(B.colreduce_scratch_bytes(1, n) // 4, device="cuda"))
+    for lo in range(0, n, 1 << 27):   # one addition
+        assert torch.equal(out[lo:lo + (1 << 27)], a[0, lo:lo + (1 << 27)].float() + 1.0)
