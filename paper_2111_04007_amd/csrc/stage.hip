@@ -291,17 +291,17 @@ template <typename T> struct AttnDispatch {
 };
 
 template <> struct AttnDispatch<bf16> {
-  // variant 0: library's choice; -1: one wave per row; 1: MFMA kernels on whole tiles; 2: their EDGE form; 3: fp32 products
-  // (what the two cannot address, up to head dim 128).  The EDGE form takes
-  // what the whole tiles do not (any length, head dims that are multiples of 8 up to 128): against the simple kernels, which
+  // variant 0: library's choice; 1: MFMA kernels on whole tiles (refused where they do not fit); 2: their EDGE form; 3: fp32
+  // products (what the two cannot address, up to head dim 128); everything else, and 2 and 3 where they do not take the
+  // shape: one wave per row.  The EDGE form takes what the whole tiles do not (any length, head dims that are multiples of 8 up to 128): against the simple kernels, which
   // read their operands element by element, 594 -> 29 us forward and 2409 -> 98 us backward at 2 x 1000 tokens, 25 heads of 64.
   static int choose(int variant, int b, int s, int a, int d, bool aligned) {
     if (variant == 0 && !attn_mfma_supported(s, d) && !attn_grid_ok(b, a)) return -1;
     if (variant == 0) return attn_mfma_supported(s, d) ? 1 : (attn_edge_supported(d) && aligned ? 2 : (attn_f32_supported(d) ? 3 : -1));
-    if ((variant == 1 && !attn_mfma_supported(s, d)) || (variant == 2 && !(attn_edge_supported(d) && aligned)) ||
-        (variant == 3 && !attn_f32_supported(d)))
-      return 0;
-    return variant;
+    if (variant == 1) return attn_mfma_supported(s, d) ? 1 : 0;
+    if (variant == 2) return attn_edge_supported(d) && aligned && attn_grid_ok(b, a) ? 2 : -1;
+    if (variant == 3) return attn_f32_supported(d) && attn_grid_ok(b, a) ? 3 : -1;
+    return -1;
   }
   static hipError_t fwd(int variant, const bf16* qkv, bf16* ctx, float* lse, int b, int s, int a, int d, int causal,
                         const DropArgs& drop, hipStream_t st) {

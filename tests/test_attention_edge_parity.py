@@ -66,3 +66,16 @@ def test_dropout_edge(s, d, causal):
     st, ys, dxs = U.gpu_stage_step(cfg, params, xs, dys, seed=9)
     U.compare_step(cfg, st, ys, dxs, U.oracle_stage_step(cfg, params, xs, dys, seed=9), label=f"s={s} d={d}")
     st.close()
+
+
+@pytest.mark.parametrize("variant,d", [(2, 20), (2, 136), (3, 136), (7, 64)])
+def test_other_forms_leave_shapes_they_do_not_take_to_the_row_kernels(variant, d):
+    b, s, heads = 1, 37, 2
+    qkv, dctx = rnd((b * s, 3 * heads * d), "bf16", 7), rnd((b * s, heads * d), "bf16", 8)
+    got = []
+    for v in (variant, -1):
+        ctx, dqkv, lse = torch.empty_like(dctx), torch.empty_like(qkv), torch.empty(b * heads * s, device="cuda")
+        B.op_attention_fwd(qkv, ctx, lse, b, s, heads, d, 1, variant=v)
+        B.op_attention_bwd(qkv, ctx, lse, dctx, dqkv, torch.empty_like(lse), b, s, heads, d, 1, variant=v)
+        got.append((ctx, lse, dqkv))
+    assert all(torch.equal(x, y) for x, y in zip(*got))
