@@ -241,7 +241,7 @@ varuna_status_t varuna_stage_debug_saved_region(const varuna_stage_t* st, size_t
  * the stage calls use for forward / dgrad / wgrad products on 256x256 and on 128x128 tiles; 0
  * restores the library's choice.  Naming a 128x128 configuration for forward or dgrad also turns
  * off the library's merging of 128x128 tile pairs into one 128x256 / 256x128 tile (configurations
- * 15 / 16) for products of 257..512 such tiles.  Process-wide, not thread-safe, for same-process
+ * 20 / 21), naming one for wgrad its grouping of several weight gradients into one launch.  Process-wide, not thread-safe, for same-process
  * A/B timing only: results of every configuration agree to rounding but not bit for bit. */
 varuna_status_t varuna_debug_set_gemm_kernels(int32_t fwd256, int32_t dgrad256, int32_t wgrad256,
                                               int32_t fwd128, int32_t dgrad128, int32_t wgrad128);
@@ -250,6 +250,9 @@ varuna_status_t varuna_debug_set_gemm_kernels(int32_t fwd256, int32_t dgrad256, 
  * a `variant` number of varuna_op_gemm, -1 for the fp32-product kernel (rows that are not whole
  * 16-byte pieces, or a single tile of a ragged shape), -2 for an invalid argument. */
 int32_t varuna_debug_gemm_choice(int32_t op, int64_t M, int64_t N, int64_t K);
+/* Host only: the configuration (18, 19, 22 or 23) on which the weight gradients of n_layers (1 to 4) consecutive
+ * bf16 layers over `tokens` stacked tokens run as one launch, 0 if they run one by one, -2 for an invalid argument. */
+int32_t varuna_debug_wgrad_group_choice(int32_t n_layers, int64_t hidden, int64_t mlp, int64_t tokens);
 
 /* ---- per-kernel timing (HIP events on the caller's stream) -------------- */
 

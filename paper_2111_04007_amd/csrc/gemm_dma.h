@@ -833,7 +833,7 @@ inline int dg_choose_variant(int64_t M, int64_t N, int64_t K, int64_t lda, int64
 // load schedule, and so does wgrad (both operands read transposed); all of them with the k-tile
 // loop unrolled over the stage period, which removes the address arithmetic from the loop and was
 // worth 4.4 % of the C5 step and 1.4-2.6 % of the smaller stages' in same-process A/B.
-struct DgFlavours { int fwd256 = 17, bwd256 = 18, fwd128 = 19, dgrad128 = 19, wgrad128 = 19, wgrad256 = 18; bool pair128 = true; };
+struct DgFlavours { int fwd256 = 17, bwd256 = 18, fwd128 = 19, dgrad128 = 19, wgrad128 = 19, wgrad256 = 18; bool pair128 = true, group = true; };
 inline DgFlavours& dg_flavours() { static DgFlavours f; return f; }   // tuning hook: varuna_debug_set_gemm_kernels
 inline int dg_flavour(int tile_variant, int op) {
   const DgFlavours& f = dg_flavours();
@@ -891,6 +891,7 @@ inline int dg_wgrad_splits(int64_t M, int64_t N, int64_t K) {
 // 256x256 tiles; on 128x128 tiles the mixture of matrices costs more of the L2 than the last rounds give once the reduction
 // is long: 1920 wide over 32768 tokens 806 / 758, so those stay one by one.
 inline int dg_group_choice(const DgJob* jobs, int n, int64_t K) {
+  if (!dg_flavours().group) return 0;   // a named weight-gradient configuration runs one by one
   int64_t t5 = 0, t7 = 0;
   bool plain5 = true, plain7 = true, edge = true, big_alone = true;
   for (int i = 0; i < n; ++i) {

@@ -1025,6 +1025,7 @@ varuna_status_t varuna_debug_set_gemm_kernels(int32_t fwd256, int32_t dgrad256, 
   f.fwd256 = fwd256 ? fwd256 : d.fwd256; f.bwd256 = dgrad256 ? dgrad256 : d.bwd256; f.wgrad256 = wgrad256 ? wgrad256 : d.wgrad256;
   f.fwd128 = fwd128 ? fwd128 : d.fwd128; f.dgrad128 = dgrad128 ? dgrad128 : d.dgrad128; f.wgrad128 = wgrad128 ? wgrad128 : d.wgrad128;
   f.pair128 = fwd128 == 0 && dgrad128 == 0;   // naming a 128x128 configuration also turns the merging of tile pairs off
+  f.group = wgrad256 == 0 && wgrad128 == 0;
   return VARUNA_OK;
 }
 
@@ -1033,6 +1034,18 @@ int32_t varuna_debug_gemm_choice(int32_t op, int64_t M, int64_t N, int64_t K) {
   const int64_t lda = (op == GEMM_WGRAD) ? M : K, ldb = (op == GEMM_FWD) ? K : N;
   const int v = (N % 8 == 0) ? dg_pick(op, M, N, K, lda, ldb) : 0;
   return v == 0 ? -1 : v;
+}
+
+int32_t varuna_debug_wgrad_group_choice(int32_t n_layers, int64_t hidden, int64_t mlp, int64_t tokens) {
+  if (n_layers < 1 || n_layers > kMaxGroupJobs / 4 || hidden < 1 || mlp < 1 || hidden > (1 << 20) || mlp > (1 << 22) || tokens < 1 || tokens > (1ll << 30))
+    return -2;
+  const int h = (int)hidden, f = (int)mlp;
+  DgJob jobs[kMaxGroupJobs];
+  for (int l = 0; l < n_layers; ++l) {
+    const int mn[4][2] = {{h, f}, {f, h}, {h, h}, {3 * h, h}};
+    for (int i = 0; i < 4; ++i) jobs[4 * l + i] = {nullptr, nullptr, nullptr, mn[i][0], mn[i][1]};
+  }
+  return dg_group_choice(jobs, 4 * n_layers, tokens);
 }
 
 varuna_status_t varuna_probe_mfma_rate(const void* operands, int64_t n_elems, int32_t waves_per_simd, int32_t pattern,

@@ -170,3 +170,17 @@ def test_gemm_kernel_choice_for_the_named_stage_shapes():
     assert B.debug_gemm_choice(DGRAD, T, h, 3 * h) == 19
     assert B.debug_gemm_choice(FWD, 100, 128, 64) == -1            # ragged: the plain kernel
     assert B.debug_gemm_choice(7, 128, 128, 64) == -2
+
+
+def test_named_weight_gradient_kernels_turn_the_grouped_launch_off():
+    """A named configuration is what a step's weight gradients run on, so they may not go into a launch that has its own."""
+    h, f, tokens = 1024, 4096, 4096
+    assert B.debug_wgrad_group_choice(1, h, f, tokens) > 0 and B.debug_wgrad_group_choice(0, h, f, tokens) == -2
+    try:
+        for kw in ({"wgrad256": 12}, {"wgrad128": 14}):
+            B.debug_set_gemm_kernels(**kw)
+            assert B.debug_wgrad_group_choice(1, h, f, tokens) == 0
+        B.debug_set_gemm_kernels(fwd256=12)
+        assert B.debug_wgrad_group_choice(1, h, f, tokens) > 0
+    finally:
+        B.debug_set_gemm_kernels()
