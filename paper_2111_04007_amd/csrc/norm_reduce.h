@@ -126,7 +126,8 @@ __global__ __launch_bounds__(LN_ROWS_PER_BLOCK* kWave) void layernorm_bwd_dx_ker
 // from memory once: rows of up to NC * 64 * VEC elements.
 template <typename T, int VEC> struct RawVec { typedef T type __attribute__((ext_vector_type(VEC))); };
 
-template <typename T, int VEC, int NC>
+// EARLY: gamma and beta are fetched with the row, on their way during the reductions; it pays with their registers.
+template <typename T, int VEC, int NC, bool EARLY>
 __global__ __launch_bounds__(LN_ROWS_PER_BLOCK* kWave) void layernorm_fwd_cached_kernel(
     const T* __restrict__ x, const T* __restrict__ gamma, const T* __restrict__ beta,
     T* __restrict__ y, float* __restrict__ stats, int64_t rows, int h, float eps) {
@@ -135,10 +136,9 @@ __global__ __launch_bounds__(LN_ROWS_PER_BLOCK* kWave) void layernorm_fwd_cached
   const int64_t row = (int64_t)blockIdx.x * LN_ROWS_PER_BLOCK + threadIdx.x / kWave;
   if (row >= rows) return;
   const T* xr = x + row * h;
-  constexpr bool EARLY = NC <= 8;   // (longer rows leave no registers for it)
   Raw xc[NC], gc[EARLY ? NC : 1], bc[EARLY ? NC : 1];
   float s = 0.f;
-  if constexpr (EARLY) {   // gamma and beta on their way during the reductions
+  if constexpr (EARLY) {
 #pragma unroll
     for (int it = 0; it < NC; ++it) {
       const int j = (it * kWave + lane) * VEC;
@@ -323,9 +323,17 @@ inline hipError_t launch_layernorm_fwd(const T* x, const T* gamma, const T* beta
   constexpr int V = ln_vec<T>();
   if (h % V == 0 && ln_aligned16({x, gamma, beta, y})) {
     const int nv = (h / V + kWave - 1) / kWave;  // 16-byte vectors per lane
-    if (nv <= 4) hipLaunchKernelGGL((layernorm_fwd_cached_kernel<T, V, 4>), grid, block, 0, st, x, gamma, beta, y, stats, rows, h, eps);
-    else if (nv <= 8) hipLaunchKernelGGL((layernorm_fwd_cached_kernel<T, V, 8>), grid, block, 0, st, x, gamma, beta, y, stats, rows, h, eps);
-    else if (nv <= 16) hipLaunchKernelGGL((layernorm_fwd_cached_kernel<T, V, 16>), grid, block, 0, st, x, gamma, beta, y, stats, rows, h, eps);
+    // EARLY up to 8 vectors (beyond, registers run out), unless a row is one vector per lane (it then costs more waves than it
+    // hides), or the rows are one round of the chip without it and two with it (5 to 8 vectors: 3 blocks of 4 rows per CU with
+    // it, 5 in bf16 and 7 in fp32 without).  Measured, without / with (kernel us, row just written): bf16 512 x 4096 9.1 / 6.2,
+    // 1000 x 1920 6.0 / 5.4, 16384 x 4096 48.0 / 42.7, but 16384 x 256 8.6 / 9.8, 4096 x 3072 11.7 / 12.4, fp32 4096 x 1536
+    // 10.6 / 11.5.  (fp32 held to 128 registers for a fourth block spills: 16384 x 2048 49.0 / 58.8.)
+    const bool early = nv >= 2 && !(nv > 4 && rows > 3072 && rows <= (sizeof(T) == 2 ? 5120 : 7168));
+#define VARUNA_LNF(NC_, E_) hipLaunchKernelGGL((layernorm_fwd_cached_kernel<T, V, NC_, E_>), grid, block, 0, st, x, gamma, beta, y, stats, rows, h, eps)
+    if (nv <= 4) { if (early) VARUNA_LNF(4, true); else VARUNA_LNF(4, false); }
+    else if (nv <= 8) { if (early) VARUNA_LNF(8, true); else VARUNA_LNF(8, false); }
+    else if (nv <= 16) VARUNA_LNF(16, false);
+#undef VARUNA_LNF
     else hipLaunchKernelGGL((layernorm_fwd_kernel<T, V>), grid, block, 0, st, x, gamma, beta, y, stats, rows, h, eps);
   } else
     hipLaunchKernelGGL((layernorm_fwd_kernel<T, 1>), grid, block, 0, st, x, gamma, beta, y, stats, rows, h, eps);
