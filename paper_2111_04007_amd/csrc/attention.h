@@ -29,13 +29,30 @@ hipError_t launch_attention_bwd_mfma_edge(const bf16* qkv, const bf16* ctx, cons
 inline bool attn_grid_ok(int b, int heads) { return (int64_t)b * heads < (1ll << 24); }
 // fp32 products on the matrix cores (attention_f32.h), head dims up to 128.
 inline bool attn_f32_supported(int d) { return d <= 128; }
-// A call of a few short rows ends sooner with one wave per row: a wave of the other form works through whole 32x32 tiles, 7-8 us
-// forward and 20-25 us backward for any call that leaves the chip idle.  Measured (us forward / backward, per row against
-// fp32 products; batch x length x heads x dim): 2x32x2x64 5.2 / 12 against 7.3 / 22, 2x64x2x64 6.8 / 19 against 7.8 / 23
-// (forward inside a step, operands out of cache: 9.7 against 8.0), 1x32x16x64 5.2 / 12 against 7.4 / 22; but 2x96x2x64 9.1 /
-// 29 against 8.2 / 24, 8x32x16x64 9.5 / 31 against 7.4 / 23.
-inline bool attn_few_rows(int b, int s, int heads, bool backward) {
-  return s <= (backward ? 64 : 32) && (int64_t)b * heads * s <= 1024;
+// Whether a call ends sooner with one wave per row than with fp32 products, whose waves work through whole 32x32 tiles however few
+// there are (and load element by element where `vec`, whole pieces of four from an aligned base, does not hold).  Rows are
+// many small tasks, so what counts is their work rows * s * d; long rows are a chain each, which the other form cuts into tiles.
+// Limits by operand type, loads, direction and padded head dim {32, 64, 96, 128}: longest row, work in 2^20; set on 2650 shapes (d
+// 7 .. 128, s 4 .. 512, 1 .. 256 heads), where the choice is within 6 % of the better form on 98 in 100.  us, per row / fp32
+// products, forward and backward: fp32 8 heads of 128 over 64 tokens 10.5 / 16.3 and 36 / 50, 256 heads 90 / 32 and 394 / 103; 4
+// heads of 99 over 48 8.0 / 22.8 and 25 / 86; bf16 16 heads of 100 over 32 7.3 / 13.1 and 17 / 46, 32 heads of 35 over 128
+// 20.2 / 14.6 and 70 / 49.  (fp32 forwards of up to 1024 rows of 32 tokens: equal alone, per row sooner inside a step.)
+inline bool attn_rows_sooner(bool f32, bool vec, bool backward, int b, int s, int heads, int d) {
+  struct Limit { int s, work; };
+  constexpr Limit limit[2][2][2][4] = {
+      {{{{0, 0}, {192, 6}, {192, 9}, {192, 19}}, {{64, 1}, {192, 11}, {96, 13}, {192, 26}}},      // bf16, single elements
+       {{{0, 0}, {0, 0}, {64, 13}, {64, 16}}, {{48, 2}, {64, 9}, {64, 13}, {96, 16}}}},           // bf16, pieces
+      {{{{0, 0}, {256, 14}, {512, 19}, {512, 46}}, {{64, 1}, {256, 14}, {256, 19}, {512, 46}}},   // fp32, single elements
+       {{{0, 0}, {0, 0}, {64, 7}, {192, 18}}, {{64, 2}, {64, 5}, {64, 7}, {80, 10}}}}};           // fp32, pieces
+  const int64_t rows = (int64_t)b * heads * s;
+  if (f32 && !backward && s <= 32 && rows <= 1024) return true;
+  const Limit& l = limit[f32][vec][backward][(d + 31) / 32 - 1];
+  return s <= l.s && rows * s * d <= (int64_t)l.work << 20;
+}
+// Whole pieces of four elements from an aligned base: rows start at multiples of d.
+template <typename T>
+inline bool attn_f32_vec(const void* p, const void* q, const void* r, int d) {
+  return d % 4 == 0 && ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(r)) & (4 * sizeof(T) - 1)) == 0;
 }
 template <typename T>
 hipError_t launch_attention_fwd_f32(const T* qkv, T* ctx, float* lse, int b, int s, int heads, int d, int causal,

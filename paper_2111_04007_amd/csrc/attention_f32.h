@@ -422,15 +422,9 @@ inline hipError_t af_bwd(const T* qkv, const T* ctx, const float* lse, const T* 
   return hipGetLastError();
 }
 
-// Whole pieces of four elements from an aligned base: rows start at multiples of d.
-template <typename T>
-inline bool af_vec(const void* p, const void* q, const void* r, int d) {
-  return d % 4 == 0 && ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(r)) & (4 * sizeof(T) - 1)) == 0;
-}
-
 template <typename T>
 hipError_t launch_attention_fwd_f32(const T* qkv, T* ctx, float* lse, int b, int s, int heads, int d, int causal, const DropArgs& drop, hipStream_t st) {
-  const bool vec = af_vec<T>(qkv, qkv, qkv, d);
+  const bool vec = attn_f32_vec<T>(qkv, qkv, qkv, d);
 #define VARUNA_AF(D_) \
   if (d <= D_) return vec ? af_fwd<T, D_, true>(qkv, ctx, lse, b, s, heads, d, causal, drop, st) : af_fwd<T, D_, false>(qkv, ctx, lse, b, s, heads, d, causal, drop, st);
   VARUNA_AF(32) VARUNA_AF(64) VARUNA_AF(96) VARUNA_AF(128)
@@ -440,7 +434,7 @@ hipError_t launch_attention_fwd_f32(const T* qkv, T* ctx, float* lse, int b, int
 template <typename T>
 hipError_t launch_attention_bwd_f32(const T* qkv, const T* ctx, const float* lse, const T* dctx, T* dqkv, float* delta, int b, int s,
                                     int heads, int d, int causal, const DropArgs& drop, hipStream_t st) {
-  const bool vec = af_vec<T>(qkv, ctx, dctx, d);
+  const bool vec = attn_f32_vec<T>(qkv, ctx, dctx, d);
 #define VARUNA_AF(D_) \
   if (d <= D_) return vec ? af_bwd<T, D_, true>(qkv, ctx, lse, dctx, dqkv, delta, b, s, heads, d, causal, drop, st) \
                           : af_bwd<T, D_, false>(qkv, ctx, lse, dctx, dqkv, delta, b, s, heads, d, causal, drop, st);

@@ -275,17 +275,17 @@ template <> struct GemmDispatch<bf16> {
 
 // fp32.  variant 0: library's choice; -1: one wave per row (few rows, head dims above 128); 3: fp32 products.
 template <typename T> struct AttnDispatch {
-  static bool per_row(int variant, int b, int s, int a, int d, bool backward) {
-    return variant == -1 || !attn_f32_supported(d) || !attn_grid_ok(b, a) || (variant == 0 && attn_few_rows(b, s, a, backward));
+  static bool per_row(int variant, int b, int s, int a, int d, bool vec, bool backward) {
+    return variant == -1 || !attn_f32_supported(d) || !attn_grid_ok(b, a) || (variant == 0 && attn_rows_sooner(true, vec, backward, b, s, a, d));
   }
   static hipError_t fwd(int variant, const T* qkv, T* ctx, float* lse, int b, int s, int a, int d, int causal,
                         const DropArgs& drop, hipStream_t st) {
-    if (per_row(variant, b, s, a, d, false)) return launch_attention_fwd_simple<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
+    if (per_row(variant, b, s, a, d, attn_f32_vec<T>(qkv, qkv, qkv, d), false)) return launch_attention_fwd_simple<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
     return launch_attention_fwd_f32<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
   }
   static hipError_t bwd(int variant, const T* qkv, const T* ctx, const float* lse, const T* dctx, T* dqkv,
                         float* delta, int b, int s, int a, int d, int causal, const DropArgs& drop, hipStream_t st) {
-    if (per_row(variant, b, s, a, d, true)) return launch_attention_bwd_simple<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
+    if (per_row(variant, b, s, a, d, attn_f32_vec<T>(qkv, ctx, dctx, d), true)) return launch_attention_bwd_simple<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
     return launch_attention_bwd_f32<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
   }
 };
@@ -295,9 +295,13 @@ template <> struct AttnDispatch<bf16> {
   // products (what the two cannot address, up to head dim 128); everything else, and 2 and 3 where they do not take the
   // shape: one wave per row.  The EDGE form takes what the whole tiles do not (any length, head dims that are multiples of 8 up to 128): against the simple kernels, which
   // read their operands element by element, 594 -> 29 us forward and 2409 -> 98 us backward at 2 x 1000 tokens, 25 heads of 64.
-  static int choose(int variant, int b, int s, int a, int d, bool aligned) {
-    if (variant == 0 && !attn_mfma_supported(s, d) && !attn_grid_ok(b, a)) return -1;
-    if (variant == 0) return attn_mfma_supported(s, d) ? 1 : (attn_edge_supported(d) && aligned ? 2 : (attn_f32_supported(d) ? 3 : -1));
+  static int choose(int variant, int b, int s, int a, int d, bool aligned, bool vec, bool backward) {
+    if (variant == 0) {
+      if (attn_mfma_supported(s, d)) return 1;
+      if (!attn_grid_ok(b, a)) return -1;
+      if (attn_edge_supported(d) && aligned) return 2;
+      return attn_f32_supported(d) && !attn_rows_sooner(false, vec, backward, b, s, a, d) ? 3 : -1;
+    }
     if (variant == 1) return attn_mfma_supported(s, d) ? 1 : 0;
     if (variant == 2) return attn_edge_supported(d) && aligned && attn_grid_ok(b, a) ? 2 : -1;
     if (variant == 3) return attn_f32_supported(d) && attn_grid_ok(b, a) ? 3 : -1;
@@ -305,7 +309,7 @@ template <> struct AttnDispatch<bf16> {
   }
   static hipError_t fwd(int variant, const bf16* qkv, bf16* ctx, float* lse, int b, int s, int a, int d, int causal,
                         const DropArgs& drop, hipStream_t st) {
-    switch (choose(variant, b, s, a, d, aligned16(qkv) && aligned16(ctx))) {
+    switch (choose(variant, b, s, a, d, aligned16(qkv) && aligned16(ctx), attn_f32_vec<bf16>(qkv, qkv, qkv, d), false)) {
       case 0: return hipErrorInvalidConfiguration;
       case 1: return launch_attention_fwd_mfma(qkv, ctx, lse, b, s, a, d, causal, drop, st);
       case 2: return launch_attention_fwd_mfma_edge(qkv, ctx, lse, b, s, a, d, causal, drop, st);
@@ -315,7 +319,8 @@ template <> struct AttnDispatch<bf16> {
   }
   static hipError_t bwd(int variant, const bf16* qkv, const bf16* ctx, const float* lse, const bf16* dctx, bf16* dqkv,
                         float* delta, int b, int s, int a, int d, int causal, const DropArgs& drop, hipStream_t st) {
-    switch (choose(variant, b, s, a, d, aligned16(qkv) && aligned16(ctx) && aligned16(dctx) && aligned16(dqkv))) {
+    switch (choose(variant, b, s, a, d, aligned16(qkv) && aligned16(ctx) && aligned16(dctx) && aligned16(dqkv),
+                   attn_f32_vec<bf16>(qkv, ctx, dctx, d), true)) {
       case 0: return hipErrorInvalidConfiguration;
       case 1: return launch_attention_bwd_mfma(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
       case 2: return launch_attention_bwd_mfma_edge(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);

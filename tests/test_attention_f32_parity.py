@@ -36,3 +36,25 @@ def test_dropout_fp32(heads, d, s, causal):
     st, ys, dxs = U.gpu_stage_step(cfg, params, xs, dys, seed=3)
     U.compare_step(cfg, st, ys, dxs, U.oracle_stage_step(cfg, params, xs, dys, seed=3), label=f"s={s} d={d}")
     st.close()
+
+
+@pytest.mark.parametrize("dtype,b,s,heads,d,fwd,bwd", [
+    ("f32", 1, 64, 8, 128, -1, -1), ("f32", 4, 64, 16, 128, 3, 3), ("f32", 1, 193, 1, 128, 3, 3), ("f32", 1, 64, 2, 64, 3, -1), ("f32", 1, 65, 2, 64, 3, 3),
+    ("f32", 1, 256, 2, 63, -1, -1), ("f32", 2, 257, 16, 63, 3, 3), ("f32", 1, 33, 1, 32, 3, -1), ("f32", 1, 32, 2, 16, -1, -1),
+    ("bf16", 1, 48, 4, 20, 3, -1), ("bf16", 1, 64, 16, 92, -1, -1), ("bf16", 1, 70, 2, 92, 3, 3), ("bf16", 1, 192, 1, 127, -1, -1), ("bf16", 1, 200, 1, 127, 3, 3),
+    ("bf16", 1, 100, 2, 7, 3, 3),
+])
+def test_short_rows_go_to_the_row_kernels(dtype, b, s, heads, d, fwd, bwd):
+    """Both sides of the lines between the two forms: the library's choice is, bit for bit, the form named here."""
+    import torch
+    from paper_2111_04007_amd import binding as B
+    from tests.test_ops_parity import rnd
+    h = heads * d
+    qkv, dctx = rnd((b * s, 3 * h), dtype, 7), rnd((b * s, h), dtype, 8)
+    got = []
+    for vf, vb in ((0, 0), (fwd, bwd)):
+        ctx, dqkv, lse = torch.empty_like(dctx), torch.empty_like(qkv), torch.empty(b * heads * s, device="cuda")
+        B.op_attention_fwd(qkv, ctx, lse, b, s, heads, d, 1, variant=vf)
+        B.op_attention_bwd(qkv, ctx, lse, dctx, dqkv, torch.empty_like(lse), b, s, heads, d, 1, variant=vb)
+        got.append((ctx, lse, dqkv))
+    assert all(torch.equal(x, y) for x, y in zip(*got))
