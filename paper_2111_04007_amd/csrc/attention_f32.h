@@ -22,6 +22,11 @@
 
 namespace varuna {
 
+// e^x.  Its argument is a score minus a maximum or log-sum-exp in one rounding (the fma), with the factor log2(e) only then: folded
+// into the scale it would add its rounding to the whole score, and another one to the log-sum-exp (up to twice the error of
+// dV where softmax rows are peaked).
+__device__ __forceinline__ float af_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.4426950408889634f); }
+
 // k-values 8g + 4*half .. +3 of one row of d columns for every group g; zeros past the end of the row.  (Here and below what
 // lies outside is loaded from an element inside and replaced, so that no branch keeps a load from going out early.)
 template <typename T, int D, bool VEC>
@@ -164,7 +169,7 @@ __device__ __forceinline__ void af_rows(int block, int wave, F&& f) {
 
 // ctx and log-sum-exp (lse may be null).
 template <typename T, int D, bool VEC>
-__global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_fwd_kernel(AfArgs<T> args, float scale_log2e) {
+__global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_fwd_kernel(AfArgs<T> args, float scale) {
   const T* __restrict__ qkv = args.qkv;
   T* __restrict__ ctx = args.ctx;
   float* __restrict__ lse = args.lse;
@@ -204,7 +209,7 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_fwd_kernel(AfArgs<T>
       mx = fmaxf(mx, sc[r]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m, mx * scale_log2e), alpha = __builtin_amdgcn_exp2f(m - m_new);
+    const float m_new = fmaxf(m, mx * scale), alpha = af_exp(m - m_new);
     m = m_new;
     l *= alpha;
 #pragma unroll
@@ -213,7 +218,7 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_fwd_kernel(AfArgs<T>
       for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      sc[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, -m));
+      sc[r] = af_exp(__builtin_fmaf(sc[r], scale, -m));
       l += sc[r];   // the softmax is normalised before the dropout
     }
     if (drop.thr != 0) {
@@ -232,23 +237,39 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_fwd_kernel(AfArgs<T>
   if (half == 0) { sml[0][wave][l32] = m; sml[1][wave][l32] = l; }
   __syncthreads();
   float probe = 0.f;
-  for (int i = tid; i < 32 * D; i += AF_WAVES * kWave) {
-    const int row = i / D, e = i % D;
+  const bool whole = d % 4 == 0 && (reinterpret_cast<uintptr_t>(ctx) & (4 * sizeof(T) - 1)) == 0;
+  for (int i = tid; i < 32 * D / 4; i += AF_WAVES * kWave) {   // four columns at a time: the weights are a row's
+    const int row = i / (D / 4), e = i % (D / 4) * 4;
     if (q0 + row >= s || e >= d) continue;
     float mm = sml[0][0][row];
 #pragma unroll
     for (int w = 1; w < AF_WAVES; ++w) mm = fmaxf(mm, sml[0][w][row]);
-    float num = 0.f, den = 0.f;
+    floatx4 num = {0.f, 0.f, 0.f, 0.f};
+    float den = 0.f;
 #pragma unroll
     for (int w = 0; w < AF_WAVES; ++w) {   // a wave without a tile: m = -inf, weight 0
-      const float a = __builtin_amdgcn_exp2f(sml[0][w][row] - mm);
-      num += a * so[(w * 32 + row) * (D + 4) + e];
+      const float a = af_exp(sml[0][w][row] - mm);
+      const floatx4 x = *reinterpret_cast<const floatx4*>(so + (w * 32 + row) * (D + 4) + e);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) num[j] += a * x[j];
       den += a * sml[1][w][row];
     }
-    const float v = num * ((drop.thr != 0 ? drop.scale : 1.0f) / den);
-    probe = ar_probe(probe, v);
-    ctx[((int64_t)bi * s + q0 + row) * h + (int64_t)head * d + e] = from_f32<T>(v);
-    if (lse && e == 0) lse[((int64_t)bi * heads + head) * s + q0 + row] = (mm + log2f(den)) * 0.6931471805599453f;
+    const float inv = (drop.thr != 0 ? drop.scale : 1.0f) / den;
+    typedef T Tx4 __attribute__((ext_vector_type(4)));
+    Tx4 out;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (e + j < d) probe = ar_probe(probe, num[j] * inv);
+      out[j] = from_f32<T>(num[j] * inv);
+    }
+    T* to = ctx + ((int64_t)bi * s + q0 + row) * h + (int64_t)head * d + e;
+    if (whole) *reinterpret_cast<Tx4*>(to) = out;
+    else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (e + j < d) to[j] = out[j];
+    }
+    if (lse && e == 0) lse[((int64_t)bi * heads + head) * s + q0 + row] = mm + logf(den);
   }
   if (af_any(so + D, probe, wave)) af_rows<T>((int)(gridDim.y - 1 - blockIdx.y), wave, [](const AfArgs<T>& a, int i, int ln, int64_t at3, int64_t at, int64_t stat) {
     ar_fwd<T>(a.qkv + at3, a.ctx + at, a.lse, i, a.s, a.heads * a.d, a.d, a.causal, 1.0f / sqrtf((float)a.d), stat, a.drop, ln);
@@ -285,7 +306,7 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_bwd_dq_kernel(AfArgs
     for (int i = 0; i < 4; ++i) dl = fmaf(gf[g][i], rf[g][i], dl);
   dl += __shfl_xor(dl, 32, 64);
   if (wave == 0 && half == 0 && query < s) delta[sbase + query] = dl;
-  const float scale_log2e = scale * 1.4426950408889634f, l2 = lse[sbase + qrow] * 1.4426950408889634f;
+  const float l = lse[sbase + qrow];
   floatx16 dq[D / 32];
   af_zero<D>(dq);
   const int end = causal && q0 + 32 < s ? q0 + 32 : s;
@@ -308,7 +329,7 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_bwd_dq_kernel(AfArgs
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int key = k0 + 8 * (r >> 2) + 4 * half + (r & 3);
-      const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, -l2));
+      const float p = af_exp(__builtin_fmaf(sc[r], scale, -l));
       ds[r] = (key >= s || (causal && key > query)) ? 0.f : p * (ds[r] - dl);
     }
     af_weighted<T>(dq, kt, base + h, ld, k0, s, d, ds, half, l32);
@@ -349,7 +370,6 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_bwd_dkv_kernel(AfArg
   floatx4 kf[D / 8], vf[D / 8], rf[D / 8];
   af_row<T, D, VEC>(kf, base + h + (int64_t)krow * ld, half, d);
   af_row<T, D, VEC>(vf, base + 2 * h + (int64_t)krow * ld, half, d);
-  const float scale_log2e = scale * 1.4426950408889634f;
   floatx16 dk[D / 32], dv[D / 32];
   af_zero<D>(dk);
   af_zero<D>(dv);
@@ -368,7 +388,7 @@ __global__ __launch_bounds__(AF_WAVES* kWave) void attn_f32_bwd_dkv_kernel(AfArg
       const int q = q0 + 8 * (r >> 2) + 4 * half + (r & 3);
       const bool in = q < s && !(causal && q < key);
       const int64_t at = sbase + (q < s ? q : s - 1);
-      const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, -lse[at] * 1.4426950408889634f));
+      const float e = af_exp(__builtin_fmaf(sc[r], scale, -lse[at]));
       const float p = in ? e : 0.f;
       float f = 1.0f;
       if (drop.thr != 0 && in)
@@ -408,7 +428,7 @@ template <typename T, int D, bool VEC>
 inline hipError_t af_fwd(const T* qkv, T* ctx, float* lse, int b, int s, int heads, int d, int causal, const DropArgs& drop, hipStream_t st) {
   const dim3 grid((unsigned)(heads * b), (unsigned)((s + 31) / 32));
   const AfArgs<T> a{qkv, ctx, lse, nullptr, nullptr, nullptr, s, heads, d, causal, drop};
-  hipLaunchKernelGGL((attn_f32_fwd_kernel<T, D, VEC>), grid, dim3(AF_WAVES * kWave), 0, st, a, 1.4426950408889634f / sqrtf((float)d));
+  hipLaunchKernelGGL((attn_f32_fwd_kernel<T, D, VEC>), grid, dim3(AF_WAVES * kWave), 0, st, a, 1.0f / sqrtf((float)d));
   return hipGetLastError();
 }
 template <typename T, int D, bool VEC>

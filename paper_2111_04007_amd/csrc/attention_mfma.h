@@ -352,7 +352,11 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
   const float inv = (DROP ? drop.scale : 1.0f) / l;
   const uint32_t bad = EDGE ? ar_bad_rows(at_probe<D>(o, ar_probe(0.f, l))) : 0;   // rows that are not finite: below
   if (!EDGE || (query < s && !(bad >> (ar_lane() & 31) & 1))) {
-    if (lse && hf == 0) lse[((int64_t)bi * heads + head) * s + query] = (m + log2f(l)) * 0.6931471805599453f;
+    if (lse && hf == 0) {
+      float& out = lse[((int64_t)bi * heads + head) * s + query];
+      if constexpr (EDGE) out = (float)(((double)m + (double)log2f(l)) * 0.69314718055994531);   // one rounding, as the natural logarithm of a row kernel
+      else out = (m + log2f(l)) * 0.6931471805599453f;
+    }
     bf16* crow = ctx + ((int64_t)bi * s + query) * h + head * cols;
 #pragma unroll
     for (int db = 0; db < C::DB; ++db)

@@ -37,10 +37,32 @@ __device__ __forceinline__ uint32_t ar_bad_rows(float probe) {
   return (uint32_t)b | (uint32_t)(b >> 32);
 }
 
+// f(e) for every element of a row, in the order in which the fp32 matrix products add them (attention_f32.h: k-values 8g + i, then
+// 8g + 4 + i, one fma each).  A score is then the same to the bit in either form.  It has to be: the rounding of a long score is in
+// the forward's log-sum-exp as well, and cancels in the backward's probability only if both computed the same (rows peaked on
+// one key, forward on one form and backward on the other: twice the error of dV).  bf16 rows, whose results are rounded to 2^-9, keep
+// the plain order, which their loads like better (2-5 % of the backward).
+template <typename T, typename F>
+__device__ __forceinline__ void ar_elements(int d, F&& f) {
+  if constexpr (sizeof(T) == 2) {
+    for (int e = 0; e < d; ++e) f(e);
+    return;
+  }
+  int e = 0;
+  for (; e + 8 <= d; e += 8) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { f(e + i); f(e + 4 + i); }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (e + i < d) f(e + i);
+    if (e + 4 + i < d) f(e + 4 + i);
+  }
+}
 template <typename T>
 __device__ __forceinline__ float ar_dot(const T* __restrict__ a, const T* __restrict__ b, int d) {
   float dot = 0.f;
-  for (int e = 0; e < d; ++e) dot = fmaf(to_f32(a[e]), to_f32(b[e]), dot);
+  ar_elements<T>(d, [&](int e) { dot = fmaf(to_f32(a[e]), to_f32(b[e]), dot); });
   return dot;
 }
 

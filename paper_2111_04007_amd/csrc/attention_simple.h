@@ -6,6 +6,7 @@
 // qkv is [b*s, 3h]: Q at column j*d, K at h + j*d, V at 2h + j*d for head j.
 #pragma once
 #include "attention.h"
+#include "attention_rows.h"
 #include "common.h"
 
 namespace varuna {
@@ -35,7 +36,7 @@ __global__ void attention_fwd_simple_kernel(const T* __restrict__ qkv, T* __rest
   for (int k = lane; k < nk; k += kWave) {
     const T* krow = base + (int64_t)k * ld + h + j * d;
     float dot = 0.f;
-    for (int e = 0; e < d; ++e) dot = fmaf(q[e], to_f32(krow[e]), dot);
+    ar_elements<T>(d, [&](int e) { dot = fmaf(q[e], to_f32(krow[e]), dot); });
     dot *= scale;
     p[k] = dot;
     mx = fmaxf(mx, dot);
@@ -100,10 +101,10 @@ __global__ void attention_bwd_dq_simple_kernel(const T* __restrict__ qkv, const 
     const T* krow = base + (int64_t)k * ld + h + j * d;
     const T* vrow = krow + h;
     float dot = 0.f, dp = 0.f;
-    for (int e = 0; e < d; ++e) {
+    ar_elements<T>(d, [&](int e) {
       dot = fmaf(q[e], to_f32(krow[e]), dot);
       dp = fmaf(go[e], to_f32(vrow[e]), dp);
-    }
+    });
     float pr = expf(dot * scale - l);
     if (drop.thr != 0)
       dp = drop_keep(drop, drop_row_word(drop, (uint32_t)sidx, (uint32_t)k >> 2), k & 3) ? dp * drop.scale : 0.f;
@@ -151,10 +152,10 @@ __global__ void attention_bwd_dkv_simple_kernel(const T* __restrict__ qkv,
     const T* qrow = base + (int64_t)i * ld + j * d;
     const T* grow = dctx + ((int64_t)bi * s + i) * h + j * d;
     float dot = 0.f, dp = 0.f;
-    for (int e = 0; e < d; ++e) {
+    ar_elements<T>(d, [&](int e) {
       dot = fmaf(to_f32(qrow[e]), kk[e], dot);
       dp = fmaf(to_f32(grow[e]), vv[e], dp);
-    }
+    });
     float pr = expf(dot * scale - lse[sbase + i]);
     float f = 1.0f;
     if (drop.thr != 0)

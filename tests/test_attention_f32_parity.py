@@ -58,3 +58,37 @@ def test_short_rows_go_to_the_row_kernels(dtype, b, s, heads, d, fwd, bwd):
         B.op_attention_bwd(qkv, ctx, lse, dctx, dqkv, torch.empty_like(lse), b, s, heads, d, 1, variant=vb)
         got.append((ctx, lse, dqkv))
     assert all(torch.equal(x, y) for x, y in zip(*got))
+
+
+@pytest.mark.parametrize("dtype,variant,b,s,heads,d,causal,peak", [
+    ("f32", 3, 2, 130, 4, 112, 0, 4), ("f32", 3, 2, 130, 4, 112, 0, 16), ("f32", 3, 1, 90, 2, 80, 1, 16), ("f32", 3, 2, 333, 3, 40, 1, 4),
+    ("f32", 3, 1, 1500, 1, 64, 1, 16), ("f32", 0, 2, 130, 4, 112, 0, 16), ("f32", 0, 2, 64, 2, 64, 1, 16), ("bf16", 2, 2, 333, 3, 40, 1, 4), ("bf16", 2, 1, 1000, 2, 72, 1, 1),
+])
+def test_no_further_from_64_bits_than_the_row_kernels(dtype, variant, b, s, heads, d, causal, peak):
+    """Softmax rows flat and peaked (queries `peak` times as long).  Both forms round scores, exponents and sums in fp32; their errors
+    are samples of the same size, 15 % apart at most on these many values.  The log-sum-exp may differ
+    by the rounding of the scale (2^-24 of the score, a constant of d and the form) and of the result (2^-24 / sqrt(3)).  Variant 0
+    mixes the forms: forward and backward of one call choose by themselves."""
+    import torch
+    from paper_2111_04007_amd import binding as B
+    from tests.test_ops_parity import DT, rnd
+    h = heads * d
+    qkv, dctx = rnd((b * s, 3 * h), "f32", 11), rnd((b * s, h), dtype, 12)
+    qkv[:, :h] *= peak
+    qkv = qkv.to(DT[dtype])
+    x = qkv.double().requires_grad_(True)
+    q, k, v = (t.reshape(b, s, heads, d).transpose(1, 2).contiguous() for t in x.split(h, 1))
+    sc = torch.matmul(q, k.transpose(2, 3).contiguous()) / d ** 0.5
+    if causal:
+        sc = sc.masked_fill(torch.ones(s, s, dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+    want = torch.matmul(sc.softmax(-1), v).transpose(1, 2).reshape(-1, h)
+    dwant, = torch.autograd.grad(want, x, dctx.double())
+    errs = []
+    for vn in (variant, -1):
+        ctx, dqkv, lse = torch.empty_like(dctx), torch.empty_like(qkv), torch.empty(b * heads * s, device="cuda")
+        B.op_attention_fwd(qkv, ctx, lse, b, s, heads, d, causal, variant=vn)
+        B.op_attention_bwd(qkv, ctx, lse, dctx, dqkv, torch.empty_like(lse), b, s, heads, d, causal, variant=vn)
+        pairs = [(ctx, want.detach()), (lse, sc.detach().logsumexp(-1).reshape(-1))] + [(dqkv[:, i * h:(i + 1) * h], dwant[:, i * h:(i + 1) * h]) for i in range(3)]
+        errs.append([float((g.double() - w).norm() / w.norm()) for g, w in pairs])
+    for i, (new, row) in enumerate(zip(*errs)):
+        assert new <= max(1.15 * row, 2.0 ** -24 * 1.6 if i == 1 else 0.0), (("ctx", "lse", "dq", "dk", "dv")[i], new, row)
