@@ -79,3 +79,9 @@ def test_other_forms_leave_shapes_they_do_not_take_to_the_row_kernels(variant, d
         B.op_attention_bwd(qkv, ctx, lse, dctx, dqkv, torch.empty_like(lse), b, s, heads, d, 1, variant=v)
         got.append((ctx, lse, dqkv))
     assert all(torch.equal(x, y) for x, y in zip(*got))
+
+
+@pytest.mark.parametrize("b,s,heads,d,causal", [(1, 500, 2, 64, 0), (1, 333, 1, 128, 1), (1, 390, 1, 40, 0), (1, 450, 2, 72, 1)])
+def test_attention_edge_rising_row_maxima(b, s, heads, d, causal):
+    """Both branches of the thresholded rescale after the first block, as for the whole tiles."""
+    run_attention_case("bf16", b, s, heads, d, causal, variant=2, seed=70 + d, key_ramp=(0.5, 4.0))

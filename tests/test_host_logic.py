@@ -168,7 +168,7 @@ def test_gemm_kernel_choice_for_the_named_stage_shapes():
     assert B.debug_gemm_choice(FWD, T, h, h) == 19                 # 256 tiles: one workgroup per CU
     assert B.debug_gemm_choice(FWD, T, 3 * h, h) == 17             # 192 256x256 tiles: one round
     assert B.debug_gemm_choice(DGRAD, T, h, 3 * h) == 19
-    assert B.debug_gemm_choice(FWD, 100, 128, 64) == -1            # ragged: the plain kernel
+    assert B.debug_gemm_choice(FWD, 100, 128, 64) == -1            # one ragged tile: the fp32-product kernel
     assert B.debug_gemm_choice(7, 128, 128, 64) == -2
 
 
@@ -184,3 +184,20 @@ def test_named_weight_gradient_kernels_turn_the_grouped_launch_off():
         assert B.debug_wgrad_group_choice(1, h, f, tokens) > 0
     finally:
         B.debug_set_gemm_kernels()
+
+
+def test_gemm_kernel_choice_for_ragged_shapes():
+    """Sizes that are no multiples of the tiles: 128x128 (22) or 256x256 (23) ragged tiles, the fp32-product kernel where rows are not
+    whole 16-byte pieces."""
+    FWD, DGRAD, WGRAD = 0, 1, 2
+    T, h, f = 2000, 1600, 6400
+    assert B.debug_gemm_choice(FWD, T, h, h) == 22 and B.debug_gemm_choice(DGRAD, T, h, f) == 22 and B.debug_gemm_choice(WGRAD, h, h, T) == 22
+    assert B.debug_gemm_choice(FWD, T, f, h) == 23 and B.debug_gemm_choice(DGRAD, T, f, h) == 23 and B.debug_gemm_choice(WGRAD, f, h, T) == 23
+    assert B.debug_gemm_choice(FWD, T, h, h + 1) == -1 and B.debug_gemm_choice(DGRAD, T, h + 4, h) == -1 and B.debug_gemm_choice(WGRAD, h + 4, h, T) == -1
+
+
+def test_weight_gradient_group_choice():
+    assert [B.debug_wgrad_group_choice(*a) for a in ((4, 1024, 4096, 128), (1, 1024, 4096, 4096), (1, 960, 3840, 192), (2, 768, 3072, 1000))] == [18, 19, 22, 23]
+    assert B.debug_wgrad_group_choice(1, 512, 2048, 128) == 0          # fewer tiles than slots: split sums instead
+    assert B.debug_wgrad_group_choice(2, 8192, 32768, 4096) == 0       # thousands of 256x256 tiles: nothing to gain
+    assert B.debug_wgrad_group_choice(4, 1920, 7680, 4096) == 19 and B.debug_wgrad_group_choice(4, 1920, 7680, 32768) == 0
