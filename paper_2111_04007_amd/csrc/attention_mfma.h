@@ -109,9 +109,11 @@ __device__ __forceinline__ bf16x8 at_tr_frag(const bf16* tile, int r0, int col_b
 // SIMD the dK/dV kernel spreads over both halves of the register file, and left to itself the
 // compiler keeps these long-lived accumulators in the ordinary half and copies all 16
 // registers across around every product.  The product is opaque to the compiler here, so the
-// wait states a later read of the result needs are inserted by hand (at_mfma_settle).
+// wait states around it are inserted by hand: two between an operand's last VALU write and the product (a conversion or
+// register move may stand directly before it; the product then multiplied what the register held before, now and then:
+// dK of d = 32 with dropout up to infinity), and those a later read of the result needs (at_mfma_settle).
 __device__ __forceinline__ void at_mfma_acc(floatx16& acc, const bf16x8& a, const bf16x8& b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+  asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 __device__ __forceinline__ void at_mfma_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 

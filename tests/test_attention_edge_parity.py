@@ -68,6 +68,20 @@ def test_dropout_edge(s, d, causal):
     st.close()
 
 
+@pytest.mark.parametrize("s,causal", [(220, False), (220, True), (333, False)])
+def test_dropout_edge_many_heads_of_32(s, causal):
+    """Enough waves for products to follow their operands' conversions without a gap: what dK multiplied before the last
+    conversion had landed was an fp32 number's lower half, up to 1e38."""
+    cfg = synth.StageConfig("edge-dropout-32", 1, 704, 22, s, 6, 1, 704, causal, "bf16", 0.02, seed=90 + s, dropout_p=0.1)
+    params = synth.make_params(cfg, perturb=0.05)
+    xs, dys = synth.make_activations(cfg, 1)
+    want = U.oracle_stage_step(cfg, params, xs, dys, seed=9)
+    for _ in range(3):
+        st, ys, dxs = U.gpu_stage_step(cfg, params, xs, dys, seed=9)
+        U.compare_step(cfg, st, ys, dxs, want, label=f"s={s}")
+        st.close()
+
+
 @pytest.mark.parametrize("variant,d", [(2, 20), (2, 136), (3, 136), (7, 64)])
 def test_other_forms_leave_shapes_they_do_not_take_to_the_row_kernels(variant, d):
     b, s, heads = 1, 37, 2
