@@ -241,8 +241,8 @@ varuna_status_t varuna_stage_debug_saved_region(const varuna_stage_t* st, size_t
  * the stage calls use for forward / dgrad / wgrad products on 256x256 and on 128x128 tiles; 0
  * restores the library's choice.  Naming a 128x128 configuration for forward or dgrad also turns
  * off the library's merging of 128x128 tile pairs into one 128x256 / 256x128 tile (configurations
- * 20 / 21), naming one for wgrad its grouping of several weight gradients into one launch.  Process-wide, not thread-safe, for same-process
- * A/B timing only: results of every configuration agree to rounding but not bit for bit. */
+ * 20 / 21), naming one for wgrad its grouping of several weight gradients into one launch.  Process-wide, not
+ * thread-safe, for same-process A/B timing only: results of every configuration agree to rounding but not bit for bit. */
 varuna_status_t varuna_debug_set_gemm_kernels(int32_t fwd256, int32_t dgrad256, int32_t wgrad256,
                                               int32_t fwd128, int32_t dgrad128, int32_t wgrad128);
 /* Host only (no GPU call): the kernel configuration the library picks for a bf16 product of

@@ -1,6 +1,6 @@
 // bf16 MFMA GEMM for gfx950: operands go from global memory straight into LDS
 // (buffer_load_dwordx4 ... lds, no register staging) into stages of 64 k (two per
-// operand, or two of A and three of B: template parameter LS), and MFMA fragments
+// operand, two of A and three of B, or three of both: template parameter LS), and MFMA fragments
 // are software-pipelined in registers across k-steps and across k-tiles, with one
 // workgroup barrier per k-tile.
 //
@@ -295,7 +295,7 @@ constexpr size_t dg_smem_bytes() {
   return stages > epi ? stages : epi;
 }
 
-// LS (load schedule; 2 and 4: in the body): 0 = the loads of a k-tile go out in one run right after the barrier that
+// LS (load schedule; 2, 4 and 5, with three stages of B or of both operands: in the body): 0 = the loads of a k-tile go out in one run right after the barrier that
 // frees their stage (from the upper half of the waves, or from both halves one k-step apart,
 // see below); 1 = every wave sends its share one load at a time between its products, spread
 // over the three k-steps that follow that barrier, so that no wave sits at the texture
@@ -372,11 +372,11 @@ __device__ __forceinline__ void dg_tile(
   // Whether the loads of this workgroup's k-tile `kt` retire in order, so that a wait may count them: it exists, and
   // none of its loads lies outside the operand as a whole (a partly filled k-tile's may).
   auto counted = [&](int kt) { return kt < nk && (!EDGE || k_tail == DG_BK || kt0 + kt != nkt - 1); };
-  // LDS map.  LS 0, 1: two stages of [A tile | B tile].  LS 2: two stages of A, then three of B.
+  // LDS map.  LS 0, 1: two stages of [A tile | B tile].  LS 2, 4: two stages of A, then three of B.  LS 5: three of A, three of B.
   constexpr int A_STRIDE = (LS >= 2) ? BM * DG_BK : STAGE_ELEMS;
   constexpr int B_STRIDE = (LS >= 2) ? BN * DG_BK : STAGE_ELEMS;
   constexpr int B_BASE = (LS >= 2) ? (LS == 5 ? 3 : 2) * BM * DG_BK : BM * DG_BK;
-  // LS >= 2: which of a wave's loads (A's LA first, then B's LB) go out in the k-step after the barrier
+  // LS 2, 4: which of a wave's loads (A's LA first, then B's LB) go out in the k-step after the barrier
   // ([0, C3)), and in k-steps 0, 1, 2 of the next tile ([C3, C0), [C0, C1), [C1, LA+LB)).
   constexpr int LA_ = DgLoader<BM, NI, A_KMAJOR, EDGE>::LPT, LB_ = DgLoader<BN, NI, B_KMAJOR, EDGE>::LPT;
   // (Halves of A right after the barrier and in k-step 0, halves of B in k-steps 1 and 2; sending all of A
@@ -801,14 +801,15 @@ inline bool dg_shape_ok(int variant, int64_t M, int64_t N, int64_t K, int64_t ld
 // The merged 128x256 and 256x128 tiles run on four waves (64x128 / 128x64 each: 6 fragment reads per 8 products), not on eight
 // of 64x64 (4 per 4): with eight the LDS moves 128 KB of fragments and 48 KB of new data per k-tile, 1400 clocks against
 // 1024 of products.  Eight against four waves on operands out of cache (us): forward 2048x3072x12288 186 / 169, 2048x12288x3072
-// 158 / 150; dgrad 2048x3072x9216 138 / 126; on 256x128 219 / 183, 167 / 153, 168 / 141.  160 KB of LDS hold a third stage of
-// A as well (LS 5), which gives every load two k-tiles to arrive and the loop a period of three: again (us, forward / dgrad)
+// 158 / 150; dgrad 2048x3072x9216 138 / 126; on 256x128 219 / 183, 167 / 153, 168 / 141.  The LDS (160 KB) holds a third stage
+// of A as well (LS 5: 144 KB), which gives every load two k-tiles to arrive and the loop a period of three: again (us, forward / dgrad)
 // 169 / 174 -> 164 / 161 at 2048x3072x12288, 126 / 126 -> 123 / 119 at 2048x3072x9216, on 256x128 183 / 187 -> 170 / 161.  (128x128 tiles on two waves of
 // 128x64: 3-15 % faster than on four with cached operands, 3-10 % slower otherwise.)
 // Picks between the 256x256 (one workgroup per CU) and 128x128 (two per CU) tiles by the
 // number of full-chip rounds each needs; 0 if neither fits the shape.  Sizes that are no multiples of 128 (64 for K)
 // take the EDGE form of the same two tiles, if their rows are whole 16-byte pieces and the product is larger than one
-// tile (of a single one the fp32-product kernel makes 16 small workgroups; both take the launch's time).  Against that
+// tile (of a single one the fp32-product kernel makes 16 small workgroups: up to 512 deep both take the launch's time,
+// 8.6 us; at long reductions the EDGE tile is the faster, 64x64x1024 13.2 / 8.8, 100x128x8192 84 / 38).  Against that
 // kernel (us, forward / dgrad / wgrad): 2000x1600x1600 184 / 161 / 147 -> 18 / 18 / 22 on 128x128 (34 on 256x256),
 // 2000x6400x1600 495 / 481 / 509 -> 42 / 43 / 54 on 256x256 (50 on 128x128).  At sizes both forms take the plain one is
 // 1-5 % faster.
@@ -844,9 +845,10 @@ inline int dg_flavour(int tile_variant, int op) {
 
 // The library's choice for one product.  On top of the tile size and its kernel configuration:
 // two 128x128 workgroups on a CU are bound by the CU's path from L2 (64 B per clock), so forward
-// and dgrad products may run on 128x256 (else 256x128) tiles of 8 waves instead, one per CU: a pair
-// of tiles that shares one operand panel through LDS, a quarter less L2->LDS traffic, measured 8 %
-// faster per product.  The merged tiles come in whole rounds of one per CU.  A 128x128 workgroup alone
+// and dgrad products may run on 128x256 (else 256x128) tiles of 4 waves instead, one per CU: a pair
+// of tiles that shares one operand panel through LDS, a quarter less L2->LDS traffic.  (The 0.92 below was
+// measured with the eight-wave, two-stage form of these tiles; the present one, configurations 20 and 21,
+// is 4-17 % faster still, so the rule may take them too seldom.)  The merged tiles come in whole rounds of one per CU.  A 128x128 workgroup alone
 // on a CU runs at nearly twice the speed (0.55 of a full round's time for a product of at most 256
 // tiles), one CU holding two makes the round a full one, and beyond 512 tiles the slots refill as
 // they drain; in units of one full round of 512 tiles the two cost 0.55 / 1 / (tiles / 512) and
@@ -885,11 +887,15 @@ inline int dg_wgrad_splits(int64_t M, int64_t N, int64_t K) {
 // Whether `n` weight gradients over K (all four of a layer, of several layers) run as one launch, and on which kernel
 // configuration (18, 19, 22, 23; 0: one by one).  In units of a full-chip round of 128x128 tiles a group takes its tiles / 512,
 // or the whole rounds of 256x256 tiles its tiles need; one by one every product rounds up by itself.  With fewer tiles than
-// slots cutting the reductions (dg_wgrad_splits) fills the chip better.  Measured (us), one by one with their
-// split sums against one launch, the four matrices of a layer over 4096 tokens: 1920 wide 537 -> 422, 1024 wide 181 -> 125.
-// Whole steps with 8 stacked micro-batches (TFLOP/s, one by one / grouped): 1024 wide 624 / 642 and 3072 wide 833 / 887, both on
-// 256x256 tiles; on 128x128 tiles the mixture of matrices costs more of the L2 than the last rounds give once the reduction
-// is long: 1920 wide over 32768 tokens 806 / 758, so those stay one by one.
+// slots cutting the reductions (dg_wgrad_splits) fills the chip better.  A group of 4096 and more 256x256 tiles whose matrices
+// all prefer them alone stays one by one: at 8192 wide every matrix is whole rounds by itself and the group gains nothing; at
+// widths where they are not (5120: 6.25, 6.25, 1.56 and 4.69 rounds) it would save a round or two, which is not taken.
+// On 128x128 tiles over more than 8192 tokens the mixture of matrices costs more of the L2 than the last rounds give.
+// Measured, one by one with their split sums / one launch, us of all weight gradients (4096 tokens unless given): one layer
+// 1024 wide 197 / 126, 1920 wide 526 / 413, four layers of them 821 / 388 and 2063 / 1714, one and four layers 3072 wide over
+// 2048 tokens 594 / 512 and 2358 / 1853; of 530 groups 576 to 7168 wide, 1 to 4 layers, 512 to 32768 tokens, none is more than 2 %
+// slower than one by one.  Whole steps with 8 stacked micro-batches (TFLOP/s): 1024 wide 624 / 642 and 3072 wide 833 / 887, both
+// on 256x256 tiles; 1920 wide over 32768 tokens on 128x128 tiles 806 / 758.
 inline int dg_group_choice(const DgJob* jobs, int n, int64_t K) {
   if (!dg_flavours().group) return 0;   // a named weight-gradient configuration runs one by one
   int64_t t5 = 0, t7 = 0;
@@ -907,7 +913,7 @@ inline int dg_group_choice(const DgJob* jobs, int n, int64_t K) {
   if (t7 < 512 || !(plain7 || edge)) return 0;
   const double cost7 = (double)t7 / 512.0 + 0.2;
   const double cost5 = (double)((t5 + 255) / 256) * 2.0 / 1.15 * (plain5 ? 1.0 : 1.05);
-  if (big_alone && t5 >= 16 * 256) return 0;   // whole rounds of 256x256 tiles either way
+  if (big_alone && t5 >= 16 * 256) return 0;
   if (cost5 <= cost7 && (plain5 || edge)) return plain5 ? 18 : 23;
   if (K > 8192) return 0;
   return plain7 ? 19 : 22;
