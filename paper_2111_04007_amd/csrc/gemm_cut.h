@@ -1,0 +1,418 @@
+// GEMM of fp32 accuracy on the bf16 matrix cores: acc[m,n] = sum_k A(m,k) * B(n,k), any M, N, K.
+//   AK: A(m,k) = a[m*lda + k]   else A(m,k) = a[k*lda + m];   BK likewise for B(n,k) = b[n*ldb + k] / b[k*ldb + n]
+// It takes the bf16 operands whose rows are not whole 16-byte pieces (the direct-to-LDS kernels cannot address them), and those fp32
+// products where it is faster than the fp32 matrix instructions of gemm_f32.h (gc_kind).
+//
+// An fp32 operand is cut into three bf16 pieces, x = x1 + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1), x3 = the rest: 24 bits of
+// mantissa in pieces of 8, nothing is left over.  Of the nine piece products the six that reach 2^-18 of the whole are summed in
+// fp32 (x1y1, x1y2, x2y1, x2y2, x1y3, x3y1); the others are below 2^-26, a quarter of the rounding of one fp32 product, and x1y1
+// has a sum of its own: a sum rounds relative to its size.  Error against 64 bits (K = 768 / 3072 / 2048, 1 / 4 waves per tile):
+// 1.6e-7 / 1.6e-7 / 2.7e-7 where fp32 products gave 1.9e-7 / 3.6e-7 / 8.1e-7.  A bf16 operand is its own only piece.
+//
+// What bounds it: fp32, the vector instructions that cut (seven per element and wave) beside products at the rate real data
+// sustains; bf16, the path from L2 (16 KB per 64x64x64 block).  Every wave works alone, on its own steps of the reduction: no
+// barrier until the sums meet, and the cutting of one step issues between the products of the step before.  Reading the
+// operands straight into registers instead (32 rows of 32 bytes per instruction) took 1.2 to 3 times as long: one cache line per
+// clock; sharing cut tiles through LDS between waves was equal at 2048^3 and slower below.  Measured (us, before / now):
+// bf16 [4001,3001] over 3001 1527 / 275, 1001^3 72 / 15, 301^3 9.3 / 4.6; fp32 [1000,768] over 3072 67 / 51, 2048^3 184 / 147,
+// 1024^3 30 / 24, [512,512] over 2048 19 / 16.
+#pragma once
+#include "common.h"
+#include "gemm_epilogue.h"
+
+namespace varuna {
+
+template <typename T> struct GcPieces { static constexpr int N = 1; };
+template <> struct GcPieces<float> { static constexpr int N = 3; };
+
+typedef uint32_t gc_words __attribute__((ext_vector_type(4)));
+
+// Eight consecutive k of one row as the operand of a 32x32x16 product, in NP pieces.
+template <typename T> struct GcFrag { bf16x8 p[GcPieces<T>::N]; };
+
+__device__ __forceinline__ GcFrag<bf16> gc_cut(const bf16 (&x)[8]) {
+  GcFrag<bf16> f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) f.p[0][e] = x[e];
+  return f;
+}
+__device__ __forceinline__ GcFrag<float> gc_cut(const float (&x)[8]) {
+  gc_words h, m, l;   // two pieces per word
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    const bf16x2 hp = {(bf16)x[e], (bf16)x[e + 1]};
+    uint32_t hw = __builtin_bit_cast(uint32_t, hp);
+    asm("" : "+v"(hw));   // (seen through, the first half is converted a second time)
+    const float y0 = x[e] - __builtin_bit_cast(float, hw << 16), y1 = x[e + 1] - __builtin_bit_cast(float, hw & 0xffff0000u);
+    const bf16x2 mp = {(bf16)y0, (bf16)y1};
+    uint32_t mw = __builtin_bit_cast(uint32_t, mp);
+    asm("" : "+v"(mw));
+    const float z0 = y0 - __builtin_bit_cast(float, mw << 16), z1 = y1 - __builtin_bit_cast(float, mw & 0xffff0000u);
+    h[e / 2] = hw;
+    m[e / 2] = mw;
+    l[e / 2] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, z1), __builtin_bit_cast(uint32_t, z0), 0x07060302u);   // upper halves: exact
+  }
+  GcFrag<float> f;
+  f.p[0] = __builtin_bit_cast(bf16x8, h); f.p[1] = __builtin_bit_cast(bf16x8, m); f.p[2] = __builtin_bit_cast(bf16x8, l);
+  return f;
+}
+
+// One operand of a wave: NB blocks of 32 rows, steps of 64 bytes of k (fp32: 16 k, bf16: 32).  A step goes from memory into registers in
+// whole 16-byte pieces (rows of 64 bytes, or k-rows of all the rows), through the wave's own part of LDS and back in the layout
+// of a product's operand: lane l holds row l % 32 of every block and k 8 * (l / 32) .. +7 of a 16-k group.  KMAJOR: block i, row r is
+// row 32 i + r of the tile, 16-byte pieces XOR-permuted by row / 4 so that a read's 16 rows fall into different banks; else row
+// NB r + i, so that a lane's rows are neighbours.
+template <typename T, int NB, bool KMAJOR>
+struct GcOperand {
+  static constexpr int EPP = 16 / sizeof(T), KST = 4 * EPP, ROWS = 32 * NB, PIECES = ROWS * 4 / kWave;   // pieces of a lane per step
+  static constexpr int BYTES = ROWS * 64, PPK = ROWS / EPP;   // n-major: pieces of a k-row
+  typedef T Piece __attribute__((ext_vector_type(EPP), aligned(sizeof(T))));   // (element-aligned is enough)
+  typedef T PieceA __attribute__((ext_vector_type(EPP)));
+  struct Raw { PieceA v[PIECES]; };
+  struct Group { T v[NB][8]; };   // a 16-k group of every block
+  const T* p[PIECES];      // this lane's pieces of step 0
+  int64_t kpitch;          // elements from one k to the next
+
+  static __device__ __forceinline__ int row(int i, int r) { return KMAJOR ? 32 * i + r : NB * r + i; }
+  static __device__ __forceinline__ int piece_line(int q, int lane) { return KMAJOR ? q * 16 + lane / 4 : q * (kWave / PPK) + lane / PPK; }   // row, or k
+  static __device__ __forceinline__ int piece_elem(int q, int lane) {   // first k of the piece, or first row
+    if constexpr (KMAJOR) return ((lane & 3) ^ (piece_line(q, lane) >> 2 & 3)) * EPP;
+    else return lane % PPK * EPP;
+  }
+  __device__ __forceinline__ void init(const T* __restrict__ g, int64_t ld, int64_t row0, int64_t rows, int lane) {
+    kpitch = KMAJOR ? 1 : ld;
+#pragma unroll
+    for (int q = 0; q < PIECES; ++q) {   // rows past the end repeat the last one, or what follows it in memory (nothing of them is stored)
+      int64_t r = row0 + (KMAJOR ? piece_line(q, lane) : piece_elem(q, lane));
+      r = r < rows ? r : rows - 1;
+      p[q] = KMAJOR ? g + r * ld + piece_elem(q, lane) : g + piece_line(q, lane) * ld + r;
+    }
+  }
+  __device__ __forceinline__ void load(Raw& x, int64_t k) const {
+#pragma unroll
+    for (int q = 0; q < PIECES; ++q) x.v[q] = *reinterpret_cast<const Piece*>(p[q] + k * kpitch);
+  }
+  // The last steps: k past the end reads as zero, and no piece runs over its k-row.
+  __device__ __forceinline__ void load_last(Raw& x, int64_t k, int64_t K, int64_t row0, int64_t rows, int lane) const {
+#pragma unroll
+    for (int q = 0; q < PIECES; ++q)
+#pragma unroll
+      for (int e = 0; e < EPP; ++e) {
+        T v = (T)0.f;
+        if constexpr (KMAJOR) {
+          if (k + piece_elem(q, lane) + e < K) v = p[q][k + e];
+        } else {
+          const int64_t r = row0 + piece_elem(q, lane), last = r < rows ? rows - 1 - r : 0;
+          if (k + piece_line(q, lane) < K) v = p[q][k * kpitch + (e < last ? e : last)];
+        }
+        x.v[q][e] = v;
+      }
+  }
+  __device__ __forceinline__ void put(const Raw& x, char* lds, int lane) const {
+#pragma unroll
+    for (int q = 0; q < PIECES; ++q) *reinterpret_cast<PieceA*>(lds + (q * kWave + lane) * 16) = x.v[q];
+  }
+  // Group c of the step.
+  __device__ __forceinline__ void get(Group& g, const char* lds, int c, int lane) const {
+    const int half = lane >> 5, r = lane & 31;
+    if constexpr (KMAJOR) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int q = 0; q < 8 / EPP; ++q) {
+          const int piece = (c * 16 + 8 * half) / EPP + q;
+          *reinterpret_cast<PieceA*>(&g.v[i][q * EPP]) = *reinterpret_cast<const PieceA*>(lds + (i * 32 + r) * 64 + ((piece ^ (r >> 2 & 3)) * 16));
+        }
+    } else {
+      typedef T Rows __attribute__((ext_vector_type(NB)));
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const T* s = reinterpret_cast<const T*>(lds) + (c * 16 + 8 * half + e) * ROWS + NB * r;
+        if constexpr (NB == 1) g.v[0][e] = *s;
+        else {
+          const Rows t = *reinterpret_cast<const Rows*>(s);
+#pragma unroll
+          for (int i = 0; i < NB; ++i) g.v[i][e] = t[i];
+        }
+      }
+    }
+  }
+};
+
+// One 32x32 block over the steps of wave `ks`, with fp32 products from memory: for sums whose pieces are no good.  An infinity, or a value
+// that rounds to one, has NaN as its rest; below 2^-109 the last pieces underflow, which only shows where all of a block is small.
+template <typename T, bool AK, bool BK>
+__device__ __attribute__((noinline)) floatx16 gc_exact_block(const T* a, const T* b, int64_t lda, int64_t ldb, int64_t K, int ks, int nks, int step) {
+  const int half = (threadIdx.x % kWave) >> 5;   // a, b: this lane's row
+  floatx16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  for (int64_t s = (int64_t)ks * step; s < K; s += step * nks)
+    for (int64_t kk = s; kk < s + step && kk < K; kk += 2) {
+      const int64_t k = kk + half;
+      float x = 0.f, y = 0.f;
+      if (k < K) {
+        x = to_f32(AK ? a[k] : a[k * lda]);
+        y = to_f32(BK ? b[k] : b[k * ldb]);
+      }
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc, 0, 0, 0);
+    }
+  return acc;
+}
+
+// LDS accesses of one wave are served in order; this keeps the compiler from exchanging one lane's write with another's read.
+__device__ __forceinline__ void gc_wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int V> struct GcInt { static constexpr int v = V; };
+
+// One workgroup: a 32 TM x 32 TN tile; its KS waves take every KS-th step of k of the whole tile.
+template <typename T, int MODE, bool AK, bool BK, int TM, int TN, int KS>
+struct GcTile {
+  static constexpr int BM = 32 * TM, BN = 32 * TN, NT = KS * kWave, NP = GcPieces<T>::N;
+  using OA = GcOperand<T, TM, AK>;
+  using OB = GcOperand<T, TN, BK>;
+  static constexpr int KST = OA::KST, GROUPS = KST / 16, STAGE = OA::BYTES + OB::BYTES;
+  static constexpr size_t RED = KS > 1 ? sizeof(float) * KS * TM * TN * 1024 : 0, RING = (size_t)KS * 2 * STAGE, SMEM = RED > RING ? RED : RING;
+
+  static __device__ __forceinline__ void run(const T* __restrict__ a, int64_t lda, const T* __restrict__ b, int64_t ldb, int64_t M,
+                                             int64_t N, int64_t K, int tiles_m, int tiles_n, const EpiArgs<T>& epi, int logical, float* red) {
+    const int tid = threadIdx.x, lane = tid % kWave, half = lane >> 5, l32 = lane & 31;
+    const int ks = __builtin_amdgcn_readfirstlane(tid / kWave);
+
+    // Logical tile -> output tile, in groups of 8 tile rows.
+    const int width = 8 * tiles_n, grp = logical / width, first_m = grp * 8;
+    const int gsize = tiles_m - first_m < 8 ? tiles_m - first_m : 8;
+    const int64_t m0 = (int64_t)(first_m + (logical % width) % gsize) * BM, n0 = (int64_t)((logical % width) / gsize) * BN;
+
+    // The products of the first pieces are summed by themselves: a sum rounds relative to its size, and the other terms are small.
+    floatx16 acc[TM][TN], low[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = low[i][j][r] = 0.f;
+
+    OA oa;
+    OB ob;
+    oa.init(a, lda, m0, M, lane);
+    ob.init(b, ldb, n0, N, lane);
+    char* ring = reinterpret_cast<char*>(red) + ks * 2 * STAGE;   // this wave's two stages
+    typename OA::Raw ra[2];
+    typename OB::Raw rb[2];
+    GcFrag<T> fa[2][GROUPS][TM], fb[2][GROUPS][TN];
+    const int64_t steps = (K + KST - 1) / KST, mine = steps > ks ? (steps - ks + KS - 1) / KS : 0;   // this wave's: ks, ks + KS, ...
+    // Whole steps: no piece of them reaches past the end of its operand (a piece of a ragged k-row may run into the rows after it).
+    const int64_t over_a = AK || M % OA::EPP == 0 ? 0 : (OA::EPP - 2 + M) / M, over_b = BK || N % OB::EPP == 0 ? 0 : (OB::EPP - 2 + N) / N;
+    const int64_t over = over_a > over_b ? over_a : over_b;
+    const int64_t whole = K > over ? (K - over) / KST : 0, full = whole > ks ? (whole - ks + KS - 1) / KS : 0;
+    auto load = [&](auto set, int64_t t) {
+      constexpr int S = decltype(set)::v;
+      const int64_t k = (t * KS + ks) * KST;
+      if (t < full) {
+        oa.load(ra[S], k);
+        ob.load(rb[S], k);
+      } else if (t < mine) {
+        oa.load_last(ra[S], k, K, m0, M, lane);
+        ob.load_last(rb[S], k, K, n0, N, lane);
+      }
+    };
+    auto put = [&](auto set) {
+      constexpr int S = decltype(set)::v;
+      oa.put(ra[S], ring + S * STAGE, lane);
+      ob.put(rb[S], ring + S * STAGE + OA::BYTES, lane);
+    };
+    auto cut = [&](auto set) {   // a step in LDS becomes operands
+      constexpr int S = decltype(set)::v;
+#pragma unroll
+      for (int c = 0; c < GROUPS; ++c) {
+        typename OA::Group ga;
+        typename OB::Group gb;
+        oa.get(ga, ring + S * STAGE, c, lane);
+        ob.get(gb, ring + S * STAGE + OA::BYTES, c, lane);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[S][c][i] = gc_cut(ga.v[i]);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[S][c][j] = gc_cut(gb.v[j]);
+      }
+    };
+    auto products = [&](auto set) {
+      constexpr int S = decltype(set)::v;
+#pragma unroll
+      for (int c = 0; c < GROUPS; ++c)
+#pragma unroll
+        for (int s = NP - 1; s >= 0; --s)   // pieces p + q = s
+#pragma unroll
+          for (int p = 0; p <= s; ++p)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int j = 0; j < TN; ++j) {
+                floatx16& d = s ? low[i][j] : acc[i][j];
+                d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[S][c][i].p[p], fb[S][c][j].p[s - p], d, 0, 0, 0);
+              }
+    };
+    // Phase t: the products of step t, the cutting of step t + 1, step t + 2 into LDS, the loads of step t + 4.
+    auto phase = [&](auto set, int64_t t, auto fast) {
+      constexpr int S = decltype(set)::v;
+      if constexpr (decltype(fast)::v) {
+        put(set);
+        oa.load(ra[S], ((t + 4) * KS + ks) * KST);
+        ob.load(rb[S], ((t + 4) * KS + ks) * KST);
+      } else {
+        if (t + 2 < mine) put(set);
+        load(set, t + 4);
+      }
+      gc_wave_order();   // (and left alone, the compiler sinks the loads to where they are needed)
+      if (decltype(fast)::v || t + 1 < mine) cut(GcInt<1 - S>{});
+      products(set);
+      if constexpr (NP > 1 && decltype(fast)::v) {
+        __builtin_amdgcn_sched_group_barrier(0x100, 64, 0);
+#pragma unroll
+        for (int i = 0; i < 6 * TM * TN; ++i) {   // one product, then what issues in its shadow
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, TM * TN > 1 ? 8 : 15, 0);
+        }
+      }
+      gc_wave_order();
+    };
+    int64_t t = 0;
+    if (full > 5) {   // (no branch between here and the loop: at a join the compiler waits for every load)
+      auto fetch = [&](auto set, int64_t u) {
+        oa.load(ra[decltype(set)::v], (u * KS + ks) * KST);
+        ob.load(rb[decltype(set)::v], (u * KS + ks) * KST);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      fetch(GcInt<0>{}, 0);
+      fetch(GcInt<1>{}, 1);
+      put(GcInt<0>{});
+      fetch(GcInt<0>{}, 2);
+      put(GcInt<1>{});
+      fetch(GcInt<1>{}, 3);
+      gc_wave_order();
+      cut(GcInt<0>{});
+      do {
+        phase(GcInt<0>{}, t, GcInt<1>{});
+        phase(GcInt<1>{}, t + 1, GcInt<1>{});
+        t += 2;
+      } while (t + 5 < full);
+    } else if (mine > 0) {
+      load(GcInt<0>{}, 0);
+      load(GcInt<1>{}, 1);
+      put(GcInt<0>{});
+      load(GcInt<0>{}, 2);
+      if (mine > 1) put(GcInt<1>{});
+      load(GcInt<1>{}, 3);
+      gc_wave_order();
+      cut(GcInt<0>{});
+    }
+    for (; t < mine; t += 2) {
+      phase(GcInt<0>{}, t, GcInt<0>{});
+      if (t + 1 < mine) phase(GcInt<1>{}, t + 1, GcInt<0>{});
+    }
+
+    if constexpr (NP > 1) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j];
+      uint32_t mx = 0;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const uint32_t v = __builtin_bit_cast(uint32_t, (float)acc[i][j][r]) & 0x7fffffffu;
+            mx = v > mx ? v : mx;
+          }
+      const bool inexact = __ballot(mx >= 0x7f800000u) != 0 ||                              // something is not finite
+                           (__ballot(mx >= (67u << 23)) == 0 && __ballot(mx != 0) != 0);    // all below 2^-60
+      if (__builtin_expect(inexact, 0)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            const int64_t m = m0 + OA::row(i, l32), n = n0 + OB::row(j, l32);
+            const int64_t mr = m < M ? m : M - 1, nr = n < N ? n : N - 1;
+            acc[i][j] = gc_exact_block<T, AK, BK>(a + mr * (AK ? lda : 1), b + nr * (BK ? ldb : 1), lda, ldb, K, ks, KS, KST);
+          }
+      }
+    }
+
+    // acc[i][j][r] is row 8*(r/4) + 4*half + r%4, column l32 of its 32x32 block.
+    auto emit = [&](int i, int j, int r, float v) {
+      const int64_t m = m0 + OA::row(i, 8 * (r >> 2) + 4 * half + (r & 3)), n = n0 + OB::row(j, l32);
+      if (m < M && n < N) epilogue_store<T, MODE>(epi, m, n, v);
+    };
+    if constexpr (KS == 1) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) emit(i, j, r, acc[i][j][r]);
+    } else {
+      __syncthreads();   // (the sums lie where the waves' stages were)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) red[((ks * TM * TN + i * TN + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+      __syncthreads();
+      constexpr int RPW = 16 / KS;   // every wave finishes its share of the rows
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int q = 0; q < RPW; ++q)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            const int r = ks * RPW + q;
+            float v = 0.f;
+#pragma unroll
+            for (int w = 0; w < KS; ++w) v += red[((w * TM * TN + i * TN + j) * 16 + r) * 64 + lane];
+            emit(i, j, r, v);
+          }
+    }
+  }
+};
+
+// Workgroup -> tile: consecutive workgroups go round the 8 XCDs; every XCD gets a contiguous range of tiles, walked in
+// groups of 8 tile rows (the panels it touches stay in its L2).
+template <typename T, int MODE, bool AK, bool BK, int TM, int TN, int KS>
+__global__ __launch_bounds__(KS * kWave) void gemm_cut_kernel(const T* __restrict__ a, int64_t lda, const T* __restrict__ b, int64_t ldb,
+                                                              int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n, EpiArgs<T> epi) {
+  extern __shared__ __attribute__((aligned(16))) float gc_smem[];
+  int logical = blockIdx.x;
+  const int nblk = gridDim.x;
+  if ((nblk & 7) == 0) logical = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+  if (gridDim.y > 1) {   // more than 2^22 tiles
+    const int64_t t = (int64_t)blockIdx.y * nblk + logical;
+    if (t >= (int64_t)tiles_m * tiles_n) return;
+    logical = (int)t;
+  }
+  GcTile<T, MODE, AK, BK, TM, TN, KS>::run(a, lda, b, ldb, M, N, K, tiles_m, tiles_n, epi, logical, gc_smem);
+}
+
+// Which kernel a product takes: tile of 32 or 64 rows and columns and the number of waves that share it, or the fp32 products of gemm_f32.h.
+//   bf16: as many waves as keep the chip's 1024 SIMDs busy.  Measured (us, 32x32 on 8 waves / 32x32 on 4 / 64x64 on 4 / 64x64 on 1):
+//   301^3 4.6 / 5.3 / 9.2 / 16, [2001,131] over 601 7.5 / 7.5 / 10 / 18, [701,701] over 6001 50 / 46 / 47 / 59, 1001^3 18 / 17 / 15 / 22,
+//   [4001,3001] over 3001 562 / 643 / 318 / 275.
+//   fp32 (32x32 on 8 waves / 64x64 on 4 / 64x64 on 1 / fp32 products) from K = 1024 on: one round of 32x32 tiles, [512,512] over 2048
+//   16 / 32 / 89 / 19 and 300x300 over 1200 11 / 22 / 58 / 12.5; from two thirds of a round of 64x64 tiles, 1024^3 38 / 24 / 54 / 30,
+//   1500^3 137 / 87 / 90 / 98, 2048^3 235 / 167 / 147 / 184.  A shorter reduction does not pay for the sums' way through LDS:
+//   [1000,768] over 768 26 / 20 / 43 / 20, transposed operands 29 / 24 / 54 / 20; and over 128 (one step per wave) a stage of
+//   128x128 products took 4.9 us instead of 4.4.
+enum GcKind : int { GC_NONE = 0, GC_32_8 = 1, GC_32_4 = 2, GC_64_4 = 3, GC_64_1 = 4 };
+inline GcKind gc_kind(bool is_f32, int64_t tiles32, int64_t tiles64, int64_t K) {
+  if (is_f32 && K < 1024) return GC_NONE;
+  if (tiles32 <= 256) return GC_32_8;
+  if (!is_f32) return tiles32 <= 512 ? GC_32_4 : tiles64 <= 1024 ? GC_64_4 : GC_64_1;
+  return tiles64 < 170 ? GC_NONE : tiles64 < 768 ? GC_64_4 : GC_64_1;
+}
+
+}  // namespace varuna

@@ -1,9 +1,8 @@
 // GEMM with fp32 products and fp32 accumulation on the matrix cores (v_mfma_f32_32x32x2_f32):
 //   acc[m,n] = sum_k A(m,k) * B(n,k)
 //   AK: A(m,k) = a[m*lda + k]   else A(m,k) = a[k*lda + m];   BK likewise for B(n,k) = b[n*ldb + k] / b[k*ldb + n]
-// It serves the fp32 path (the 1e-5 tolerance rules out reduced-precision products) and the bf16 shapes the
-// bf16 MFMA kernels cannot address (rows that are not whole 16-byte pieces); bf16 operands are widened on the
-// way into LDS, so their products are exact.  Any M, N, K; every global access is bounds-checked.
+// It serves the fp32 path (the 1e-5 tolerance rules out reduced-precision products) where products of bf16 pieces (gemm_cut.h) are
+// no faster: short reductions.  Any M, N, K; every global access is bounds-checked.
 //
 // What bounds it: the fp32 matrix rate, 256 FLOP per clock and CU (157 TFLOP/s nominal, the rate a large library
 // product reaches here); a product of a 32x32 block takes 64 clocks for two LDS words per lane, so neither LDS

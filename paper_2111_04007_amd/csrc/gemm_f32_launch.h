@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "gemm_cut.h"
 #include "gemm_f32.h"
 
 namespace varuna {
@@ -20,14 +21,38 @@ inline hipError_t gf_launch_tile(bool vec, const T* a, int64_t lda, const T* b, 
   return hipGetLastError();
 }
 
+template <typename T, int MODE, bool AK, bool BK, int TM, int TN, int KS>
+inline hipError_t gc_launch(const T* a, int64_t lda, const T* b, int64_t ldb, int64_t M, int64_t N, int64_t K, const EpiArgs<T>& epi, hipStream_t st) {
+  using G = GcTile<T, MODE, AK, BK, TM, TN, KS>;
+  auto kern = gemm_cut_kernel<T, MODE, AK, BK, TM, TN, KS>;
+  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::SMEM);
+  if (attr_err != hipSuccess) return attr_err;
+  const int64_t tm = (M + G::BM - 1) / G::BM, tn = (N + G::BN - 1) / G::BN, tiles = tm * tn;
+  if (tm > (1 << 27) || tn > (1 << 27) || tiles >= (1ll << 31)) return hipErrorInvalidValue;
+  constexpr int64_t line = 1 << 22;   // (a grid dimension as below)
+  const dim3 grid((unsigned)(tiles < line ? tiles : line), (unsigned)((tiles + line - 1) / line));
+  hipLaunchKernelGGL(kern, grid, dim3(G::NT), G::SMEM, st, a, lda, b, ldb, M, N, K, (int)tm, (int)tn, epi);
+  return hipGetLastError();
+}
+
 template <typename T, int MODE, bool AK, bool BK>
 inline hipError_t gf_launch(const T* a, int64_t lda, const T* b, int64_t ldb, int64_t M, int64_t N, int64_t K,
                             const EpiArgs<T>& epi, hipStream_t st) {
-  // whole pieces of four along the contiguous direction of both operands, from an aligned base
-  const uintptr_t align = 4 * sizeof(T) - 1;
-  const bool vec = ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & align) == 0 && lda % 4 == 0 && ldb % 4 == 0;
-  if (gf_small_tile(gf_tiles(M, N, 32), gf_tiles(M, N, 64))) return gf_launch_tile<T, MODE, AK, BK, 32, 32, 32, 32, 8, 128>(vec, a, lda, b, ldb, M, N, K, epi, st);
-  return gf_launch_tile<T, MODE, AK, BK, 64, 64, 32, 32, 1, 64>(vec, a, lda, b, ldb, M, N, K, epi, st);
+  const int64_t t32 = gf_tiles(M, N, 32), t64 = gf_tiles(M, N, 64);
+  switch (gc_kind(sizeof(T) == 4, t32, t64, K)) {
+    case GC_32_8: return gc_launch<T, MODE, AK, BK, 1, 1, 8>(a, lda, b, ldb, M, N, K, epi, st);
+    case GC_64_4: return gc_launch<T, MODE, AK, BK, 2, 2, 4>(a, lda, b, ldb, M, N, K, epi, st);
+    case GC_64_1: return gc_launch<T, MODE, AK, BK, 2, 2, 1>(a, lda, b, ldb, M, N, K, epi, st);
+    case GC_32_4: if constexpr (sizeof(T) == 2) return gc_launch<T, MODE, AK, BK, 1, 1, 4>(a, lda, b, ldb, M, N, K, epi, st); break;
+    case GC_NONE: break;
+  }
+  if constexpr (sizeof(T) == 4) {
+    // whole pieces of four along the contiguous direction of both operands, from an aligned base
+    const bool vec = ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 15) == 0 && lda % 4 == 0 && ldb % 4 == 0;
+    if (gf_small_tile(t32, t64)) return gf_launch_tile<T, MODE, AK, BK, 32, 32, 32, 32, 8, 128>(vec, a, lda, b, ldb, M, N, K, epi, st);
+    return gf_launch_tile<T, MODE, AK, BK, 64, 64, 32, 32, 1, 64>(vec, a, lda, b, ldb, M, N, K, epi, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 template <typename T>

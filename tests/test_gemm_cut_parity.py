@@ -1,0 +1,81 @@
+"""Products on bf16 pieces: edges of steps, pieces and tiles, accuracy of an fp32 product, values at the ends of the range."""
+import pytest
+import torch
+
+from paper_2111_04007_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DT = {"f32": torch.float32, "bf16": torch.bfloat16}
+
+
+def rnd(shape, dtype, seed, std=1.0):
+    return torch.empty(shape, dtype=torch.float32, device="cuda").normal_(0, std, generator=torch.Generator(device="cuda").manual_seed(seed)).to(DT[dtype])
+
+
+def product(op, a, b, M, N, K, dtype):
+    """The plain product of every layout: out, and the same in 64 bits."""
+    if op == 0:
+        bias = torch.zeros(N, dtype=DT[dtype], device="cuda")
+        out = torch.full((M, N), 7.0, dtype=DT[dtype], device="cuda")
+        B.op_gemm(op, 0, a, b, out, bias=bias, M=M, N=N, K=K)
+        return out, a.double() @ b.double().t()
+    if op == 1:
+        out = torch.full((M, N), 7.0, dtype=DT[dtype], device="cuda")
+        B.op_gemm(op, 0, a, b, out, M=M, N=N, K=K)
+        return out, a.double() @ b.double()
+    out = torch.zeros(M, N, device="cuda")
+    B.op_gemm(op, 0, a, b, out, M=M, N=N, K=K)
+    return out, a.double().t() @ b.double()
+
+
+def operands(op, dtype, M, N, K, seed=1):
+    a, b = {0: ((M, K), (N, K)), 1: ((M, K), (K, N)), 2: ((K, M), (K, N))}[op]
+    return rnd(a, dtype, seed), rnd(b, dtype, seed + 1)
+
+
+# a tile of each kind (32 on 8 waves, 32 on 4, 64 on 4, 64 on 1) with remainders of tile, 16-byte piece, step and share of the steps
+SHAPES = [(1, 1, 1), (3, 2, 9), (33, 31, 17), (65, 7, 33), (63, 65, 1040), (41, 3, 1151), (31, 33, 255), (1, 257, 130), (481, 499, 161), (801, 803, 1025), (834, 833, 1089),
+          (1000, 768, 1100), (1793, 1801, 1031), (2113, 2049, 67)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("op", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_every_remainder(dtype, op, M, N, K):
+    """fp32 sums in several parts: 2e-7 and 5e-8 per root of K; a bf16 output adds its rounding (2^-9 / sqrt(3) and a margin)."""
+    out, want = product(op, *operands(op, dtype, M, N, K), M, N, K, dtype)
+    tol = 2.5e-3 if dtype == "bf16" and op < 2 else 2e-7 + 5e-8 * K ** 0.5
+    assert float((out.double() - want).norm() / want.norm()) <= tol
+    rows = (out.double() - want).norm(dim=1) / want.norm() * M ** 0.5
+    assert float(rows.max()) <= 12 * tol   # no row or tile of its own error
+
+
+@pytest.mark.parametrize("op", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(96, 70, 200), (96, 70, 1100), (1024, 1024, 1024), (2048, 2048, 1024)])
+@pytest.mark.parametrize("scale", [1e-36, 1e-30, 1e30])
+def test_small_and_large_values(op, M, N, K, scale):
+    """Values whose last pieces would underflow, and large ones, keep the accuracy of an fp32 product (the products stay normal numbers)."""
+    a, b = operands(op, "f32", M, N, K)
+    a *= scale
+    b *= min(1.0, 1e4 / scale) if scale > 1 else 1.0
+    out, want = product(op, a, b, M, N, K, "f32")
+    assert float((out.double() - want).norm() / want.norm()) <= 2e-7 + 5e-8 * K ** 0.5
+
+
+@pytest.mark.parametrize("op", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(70, 65, 90), (70, 65, 1090), (1024, 1024, 1024), (2048, 2048, 1024)])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), torch.finfo(torch.float32).max, torch.finfo(torch.float32).min])
+def test_values_at_the_end_of_the_range(op, M, N, K, value):
+    """One such value reaches exactly its row or column, as in fp32 products: zeros of the other operand included."""
+    a, b = operands(op, "f32", M, N, K)
+    (a if op == 2 else a.t())[K // 2, M // 3] = value
+    (b.t() if op == 0 else b)[K // 2, N // 4] = 0.0
+    (b.t() if op == 0 else b)[K // 2, N // 2] = 2.0 ** -20
+    out, want = product(op, a, b, M, N, K, "f32")
+    want = want.float()   # rounds to infinity beyond the range; 64-bit products of finite values stay finite
+    assert torch.equal(torch.isnan(out), torch.isnan(want)) and torch.equal(torch.isinf(out), torch.isinf(want))
+    fin = torch.isfinite(want)
+    assert torch.equal(out[~fin & ~torch.isnan(want)], want[~fin & ~torch.isnan(want)])
+    rest = torch.arange(M, device="cuda") != M // 3
+    d = (out[rest].double() - want[rest].double()).norm() / want[rest].double().norm()
+    assert float(d) <= 2e-7 + 5e-8 * K ** 0.5
