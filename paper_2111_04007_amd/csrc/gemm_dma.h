@@ -171,7 +171,7 @@ template <int N> __device__ __forceinline__ void dg_settle_all(DgFragReg<false, 
 }
 
 // Fragment reader: the 8 consecutive k-values KS*16 + (lane/32)*8 .. of row lane%32 of fragment number IDX
-// (32 rows each) of the wave's sub-tile, whose first row is wave_base (a multiple of 64).  Fragment number
+// (32 rows each) of the wave's sub-tile, whose first row is wave_base (a multiple of 32).  Fragment number
 // and k-step are compile-time values: in the hand-issued forms whatever part of the address they contribute
 // additively goes into the instruction's offset field instead of into an address computation.
 template <int ROWS, bool KMAJOR, bool HAND>
@@ -253,11 +253,13 @@ struct DgInterleaveMask {
 
 // bf16 epilogue of one wave's (TM*32) x WN sub-tile whose first output is (row0, col0), through a
 // private LDS buffer of 32 rows x WN floats.  acc[i][j][r] is row m = lane%32 of the 32x32 block,
-// column n = 8*(r/4) + 4*(lane/32) + r%4.
-template <int MODE, int TM, int TN, int WN, bool EDGE>
+// column n = 8*(r/4) + 4*(lane/32) + r%4.  Columns WN of the sub-tile from block J0 on (32 or a multiple of 64 at a time).
+template <int MODE, int TM, int TN, int WN, bool EDGE, int J0 = 0>
 __device__ __forceinline__ void dg_epilogue_bf16(floatx16 (&acc)[TM][TN], unsigned char* buf, const EpiArgs<bf16>& epi,
                                                  int64_t row0, int64_t col0, int lane, int64_t rows, int64_t cols) {
   constexpr int ROWB = WN * 4;              // bytes per staged fp32 row
+  static_assert(WN == 32 || WN % 64 == 0, "whole groups of 8 or 16 chunks");
+  constexpr int SW = WN == 32 ? 7 : 15;     // chunks are XOR-permuted within groups of SW + 1
   constexpr int LPR = WN / 8;               // lanes per output row (8 columns each)
   constexpr int RPI = 64 / LPR;             // rows per store instruction
   const int frow = lane & 31, fchunk = lane >> 5;
@@ -265,22 +267,22 @@ __device__ __forceinline__ void dg_epilogue_bf16(floatx16 (&acc)[TM][TN], unsign
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < WN / 32; ++j)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int c = j * 8 + g * 2 + fchunk;
-        floatx4 v = {acc[i][j][g * 4 + 0], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]};
-        *reinterpret_cast<floatx4*>(buf + frow * ROWB + (((c & ~15) | ((c ^ frow) & 15)) << 4)) = v;
+        floatx4 v = {acc[i][J0 + j][g * 4 + 0], acc[i][J0 + j][g * 4 + 1], acc[i][J0 + j][g * 4 + 2], acc[i][J0 + j][g * 4 + 3]};
+        *reinterpret_cast<floatx4*>(buf + frow * ROWB + (((c & ~SW) | ((c ^ frow) & SW)) << 4)) = v;
       }
     __builtin_amdgcn_s_waitcnt(DG_WAIT_LGKM0);  // own writes landed (the buffer is private to the wave)
 #pragma unroll
     for (int sub = 0; sub < 32 / RPI; ++sub) {
       const int r = sub * RPI + rrow, c0 = rcol / 4;
-      const floatx4 lo = *reinterpret_cast<const floatx4*>(buf + r * ROWB + (((c0 & ~15) | ((c0 ^ r) & 15)) << 4));
-      const floatx4 hi = *reinterpret_cast<const floatx4*>(buf + r * ROWB + ((((c0 + 1) & ~15) | (((c0 + 1) ^ r) & 15)) << 4));
+      const floatx4 lo = *reinterpret_cast<const floatx4*>(buf + r * ROWB + (((c0 & ~SW) | ((c0 ^ r) & SW)) << 4));
+      const floatx4 hi = *reinterpret_cast<const floatx4*>(buf + r * ROWB + ((((c0 + 1) & ~SW) | (((c0 + 1) ^ r) & SW)) << 4));
       float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      if (!EDGE || (row0 + i * 32 + r < rows && col0 + rcol < cols))   // (cols is a multiple of 8)
-        gemm_epilogue8<MODE>(epi, row0 + i * 32 + r, col0 + rcol, v);
+      if (!EDGE || (row0 + i * 32 + r < rows && col0 + J0 * 32 + rcol < cols))   // (cols is a multiple of 8)
+        gemm_epilogue8<MODE>(epi, row0 + i * 32 + r, col0 + J0 * 32 + rcol, v);
     }
     __builtin_amdgcn_s_waitcnt(DG_WAIT_LGKM0);  // reads done before the next pass overwrites
   }
@@ -311,8 +313,8 @@ __device__ __forceinline__ void dg_tile(
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = WN / 32;
   // the epilogues swizzle 16-byte chunks of a staged fp32 row by the low four bits of the row
-  // number, which needs rows of whole groups of 16 chunks
-  static_assert(WM % 32 == 0 && WN % 64 == 0, "wave sub-tile: rows in 32s, columns in 64s");
+  // number, which needs rows of whole groups of 16 chunks (sub-tiles 96 wide are staged as 64 and 32)
+  static_assert(WM % 32 == 0 && (WN % 64 == 0 || (WN == 96 && A_KMAJOR && B_KMAJOR)), "wave sub-tile: rows in 32s, columns in 64s or 96");
   constexpr int STAGE_ELEMS = (BM + BN) * DG_BK;
   extern __shared__ __attribute__((aligned(16))) unsigned char dg_smem[];
   bf16* smem = reinterpret_cast<bf16*>(dg_smem);  // [2][A tile | B tile]
@@ -428,7 +430,7 @@ __device__ __forceinline__ void dg_tile(
 
   DgFragReg<A_KMAJOR, HAND> fa[2][TM];
   DgFragReg<B_KMAJOR, HAND> fb[2][TN];
-  static_assert(WM % 64 == 0 && WN % 64 == 0, "the fragment readers take a wave's first row as a multiple of 64");
+  static_assert(WM % 32 == 0 && WN % 32 == 0, "the fragment readers take a wave's first row as a multiple of 32");
   using KS0 = std::integral_constant<int, 0>;
   using KS1 = std::integral_constant<int, 1>;
   using KS2 = std::integral_constant<int, 2>;
@@ -724,7 +726,12 @@ __device__ __forceinline__ void dg_tile(
     static_assert(NW * 32 * WN * 4 <= dg_smem_bytes<BM, BN, WGM, WGN, MODE, LS>(), "epilogue staging must fit the workgroup's LDS");
     __builtin_amdgcn_s_waitcnt(DG_WAIT_VM0_LGKM0);
     __builtin_amdgcn_s_barrier();             // every wave is done with the operand stages
-    dg_epilogue_bf16<MODE, TM, TN, WN, EDGE>(acc, dg_smem + wave * (32 * WN * 4), epi, m0 + wm * WM, n0 + wn * WN, lane, rows, cols);
+    if constexpr (WN % 64 == 0) {
+      dg_epilogue_bf16<MODE, TM, TN, WN, EDGE>(acc, dg_smem + wave * (32 * WN * 4), epi, m0 + wm * WM, n0 + wn * WN, lane, rows, cols);
+    } else {
+      dg_epilogue_bf16<MODE, TM, TN, 64, EDGE>(acc, dg_smem + wave * (32 * WN * 4), epi, m0 + wm * WM, n0 + wn * WN, lane, rows, cols);
+      dg_epilogue_bf16<MODE, TM, TN, 32, EDGE, 2>(acc, dg_smem + wave * (32 * WN * 4), epi, m0 + wm * WM, n0 + wn * WN, lane, rows, cols);
+    }
   }
 }
 
@@ -771,7 +778,8 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_group_kernel(DgGroup g, 
 //   15: 128x256, 8 waves, that schedule   16: 256x128, 8 waves, that schedule
 //   17: as 13 with the k-tile loop unrolled over the stage period   18: as 12 with that
 //   19: as 14 with that
-//   20: 128x256, 21: 256x128, 4 waves, three stages of both operands (LS 5)
+//   20: 128x256, 21: 256x128, 4 waves, three stages of both operands (LS 5); a forward product on 20 takes tiles of 128x192 where
+//     dg_narrow says so
 //   22, 23: as 19, 18 for sizes that are no multiples of the tile (EDGE)
 // ---------------------------------------------------------------------------
 inline bool dg_variant_tile(int variant, GemmTile* t) {
@@ -865,6 +873,16 @@ inline int dg_pick(int op, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t
     }
   }
   return dg_flavour(tile, op);
+}
+
+// Whether a forward product on merged tiles takes them 192 wide: where the 256-wide ones leave a quarter of the chip idle.  Per round of
+// 256 workgroups they cost 0.75 of the area and 1.04 for the larger share of loads.
+// Measured, 256 wide / 192 wide (us, operands out of cache): 2048x3072x3072 51 / 45, 2048x3072x12288 167 / 156, 1024x6144x2048 29.0 / 26.4,
+// 4096x1536x1536 28.6 / 25.4; a stage of three such layers forward 3307 -> 3219.
+inline bool dg_narrow(int64_t M, int64_t N) {
+  if (M % 128 != 0 || N % 192 != 0) return false;
+  const int64_t wide = (M / 128) * ((N + 255) / 256), narrow = (M / 128) * (N / 192);
+  return 0.75 * 1.04 * (double)((narrow + 255) / 256) < (double)((wide + 255) / 256);
 }
 
 // Split-K for weight-gradient GEMMs whose output has too few tiles to fill the chip: the
