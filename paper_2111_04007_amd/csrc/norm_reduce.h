@@ -187,12 +187,12 @@ __global__ __launch_bounds__(LN_ROWS_PER_BLOCK* kWave) void layernorm_fwd_cached
 
 // (The residual row fetched ahead of the reductions as well was measured: 10.6 -> 13.6 us at 4096 x 1920.)
 template <typename T, int VEC, int NC>
-__global__ __launch_bounds__(LN_ROWS_PER_BLOCK* kWave) void layernorm_bwd_dx_cached_kernel(
+__device__ __forceinline__ void layernorm_bwd_dx_block(
     const T* __restrict__ dy, const T* __restrict__ x, const float* __restrict__ stats,
-    const T* __restrict__ gamma, const T* __restrict__ res, T* __restrict__ dx, int64_t rows, int h) {
+    const T* __restrict__ gamma, const T* __restrict__ res, T* __restrict__ dx, int64_t rows, int h, int64_t block) {
   typedef typename RawVec<T, VEC>::type Raw;
   const int lane = threadIdx.x % kWave;
-  const int64_t row = (int64_t)blockIdx.x * LN_ROWS_PER_BLOCK + threadIdx.x / kWave;
+  const int64_t row = block * LN_ROWS_PER_BLOCK + threadIdx.x / kWave;
   if (row >= rows) return;
   const float mean = stats[row], rstd = stats[rows + row];
   const T* xr = x + row * h;
@@ -231,6 +231,13 @@ __global__ __launch_bounds__(LN_ROWS_PER_BLOCK* kWave) void layernorm_bwd_dx_cac
       *reinterpret_cast<Raw*>(dxr + j) = o;
     }
   }
+}
+
+template <typename T, int VEC, int NC>
+__global__ __launch_bounds__(LN_ROWS_PER_BLOCK* kWave) void layernorm_bwd_dx_cached_kernel(
+    const T* __restrict__ dy, const T* __restrict__ x, const float* __restrict__ stats,
+    const T* __restrict__ gamma, const T* __restrict__ res, T* __restrict__ dx, int64_t rows, int h) {
+  layernorm_bwd_dx_block<T, VEC, NC>(dy, x, stats, gamma, res, dx, rows, h, blockIdx.x);
 }
 
 // Stage 1 of a column reduction over rows [chunk*CR_CHUNK, +CR_CHUNK).
@@ -421,23 +428,41 @@ struct ReduceJobs {
   ReduceJob<T> job[kMaxReduceJobs];
 };
 template <typename T, int VEC>
-__global__ __launch_bounds__(256) void colreduce_jobs_partial_kernel(ReduceJobs<T> g, float* __restrict__ partial) {
+__device__ __forceinline__ void colreduce_jobs_block(const ReduceJobs<T>& g, float* __restrict__ partial, int blk, int chunk) {
   constexpr int COLS = CRV_CG * VEC;
   __shared__ float sh[2][CRV_RL][COLS + 4];
   int j = 0;
-  while (j + 1 < g.n_jobs && (int)blockIdx.x >= g.first[j + 1]) ++j;
+  while (j + 1 < g.n_jobs && blk >= g.first[j + 1]) ++j;
   const ReduceJob<T> w = g.job[j];
-  const int colblk = (int)blockIdx.x - g.first[j];
+  const int colblk = blk - g.first[j];
   const bool ln = w.x != nullptr;
-  if (ln) colreduce_partial_block<T, 1, VEC, CRV_CG, CRV_RL>(w.a, w.x, w.stats, g.rows, w.n, colblk, blockIdx.y, sh);
-  else colreduce_partial_block<T, 0, VEC, CRV_CG, CRV_RL>(w.a, nullptr, nullptr, g.rows, w.n, colblk, blockIdx.y, sh);
+  if (ln) colreduce_partial_block<T, 1, VEC, CRV_CG, CRV_RL>(w.a, w.x, w.stats, g.rows, w.n, colblk, chunk, sh);
+  else colreduce_partial_block<T, 0, VEC, CRV_CG, CRV_RL>(w.a, nullptr, nullptr, g.rows, w.n, colblk, chunk, sh);
   if ((int)threadIdx.x >= (ln ? 2 : 1) * COLS) return;
   const int which = threadIdx.x / COLS, c = threadIdx.x % COLS;
   const int64_t gc = (int64_t)colblk * COLS + c;
   if (gc >= w.n) return;
   const float t = colreduce_block_sum<COLS, CRV_RL>(sh, which, c);
   if (g.nchunks == 1) (which ? w.out1 : w.out0)[gc] += t;
-  else partial[(int64_t)blockIdx.y * g.pitch + g.pcol[j] + which * w.n + gc] = t;
+  else partial[(int64_t)chunk * g.pitch + g.pcol[j] + which * w.n + gc] = t;
+}
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void colreduce_jobs_partial_kernel(ReduceJobs<T> g, float* __restrict__ partial) {
+  colreduce_jobs_block<T, VEC>(g, partial, blockIdx.x, blockIdx.y);
+}
+
+// The first stage of some column reductions and a LayerNorm backward's dx in one launch: neither reads what the other writes, each alone
+// is a launch of a few microseconds that hardly fills the chip, and for the LayerNorm's own gamma / beta sums both read the same rows.
+// The reductions' blocks (the longer ones) come first.
+template <typename T>
+struct LnBwdDx { const T* dy; const T* x; const float* stats; const T* gamma; const T* res; T* dx; int64_t rows; int h; };
+template <typename T, int VEC, int NC>
+__global__ __launch_bounds__(256) void layernorm_bwd_jobs_kernel(LnBwdDx<T> d, ReduceJobs<T> g, float* __restrict__ partial) {
+  static_assert(LN_ROWS_PER_BLOCK * kWave == 256, "one block size for both");
+  const int per = g.first[g.n_jobs];
+  const int64_t dx_block = (int64_t)blockIdx.x - (int64_t)per * g.nchunks;
+  if (dx_block < 0) colreduce_jobs_block<T, VEC>(g, partial, (int)(blockIdx.x % per), (int)(blockIdx.x / per));
+  else layernorm_bwd_dx_block<T, VEC, NC>(d.dy, d.x, d.stats, d.gamma, d.res, d.dx, d.rows, d.h, dx_block);
 }
 template <typename T>
 __global__ __launch_bounds__(CF_COLS* CF_LANES) void colreduce_jobs_final_kernel(ReduceJobs<T> g, const float* __restrict__ partial) {
@@ -499,16 +524,6 @@ inline hipError_t launch_layernorm_bwd_params(const T* dy, const T* x, const flo
   return hipGetLastError();
 }
 
-// dx plus the gamma/beta gradient accumulation (three launches).
-template <typename T>
-inline hipError_t launch_layernorm_bwd(const T* dy, const T* x, const float* stats, const T* gamma,
-                                       const T* res, T* dx, float* dgamma, float* dbeta,
-                                       float* partial, int64_t rows, int h, hipStream_t st) {
-  hipError_t e = launch_layernorm_bwd_dx<T>(dy, x, stats, gamma, res, dx, rows, h, st);
-  if (e != hipSuccess) return e;
-  return launch_layernorm_bwd_params<T>(dy, x, stats, dgamma, dbeta, partial, rows, h, st);
-}
-
 template <typename T>
 inline hipError_t launch_colsum(const T* a, float* out, float* partial, int64_t rows, int64_t n, hipStream_t st) {
   const int nch = colreduce_chunks(rows);
@@ -517,24 +532,15 @@ inline hipError_t launch_colsum(const T* a, float* out, float* partial, int64_t 
   return hipGetLastError();
 }
 
-// The jobs of one layer; partial: (sum of the jobs' widths) * colreduce_chunks(rows) floats.
+// The job table of some column reductions over the same rows; false where their columns are no whole 16-byte pieces.
 template <typename T>
-inline hipError_t launch_reduce_jobs(const ReduceJob<T>* jobs, int n_jobs, float* partial, int64_t rows, hipStream_t st) {
+inline bool make_reduce_jobs(ReduceJobs<T>* out, const ReduceJob<T>* jobs, int n_jobs, int64_t rows) {
   constexpr int VEC = 16 / sizeof(T);
-  const int nch = colreduce_chunks(rows);
-  bool vec = true;
-  for (int i = 0; i < n_jobs; ++i) vec = vec && jobs[i].n % VEC == 0 && ln_aligned16({jobs[i].a, jobs[i].x});
-  if (!vec) {   // columns that are no whole 16-byte pieces: one by one
-    for (int i = 0; i < n_jobs; ++i) {
-      const ReduceJob<T>& w = jobs[i];
-      const hipError_t e = w.x ? launch_layernorm_bwd_params<T>(w.a, w.x, w.stats, w.out0, w.out1, partial, rows, w.n, st)
-                               : launch_colsum<T>(w.a, w.out0, partial, rows, w.n, st);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  ReduceJobs<T> g{};
-  g.n_jobs = n_jobs; g.nchunks = nch; g.rows = rows;
+  for (int i = 0; i < n_jobs; ++i)
+    if (jobs[i].n % VEC != 0 || !ln_aligned16({jobs[i].a, jobs[i].x})) return false;
+  ReduceJobs<T>& g = *out;
+  g = ReduceJobs<T>{};
+  g.n_jobs = n_jobs; g.nchunks = colreduce_chunks(rows); g.rows = rows;
   int64_t pitch = 0;
   for (int i = 0; i < n_jobs; ++i) {
     const int width = (jobs[i].x ? 2 : 1) * jobs[i].n;
@@ -545,10 +551,66 @@ inline hipError_t launch_reduce_jobs(const ReduceJob<T>* jobs, int n_jobs, float
     pitch += width;
   }
   g.pitch = pitch;
-  hipLaunchKernelGGL((colreduce_jobs_partial_kernel<T, VEC>), dim3((unsigned)g.first[n_jobs], (unsigned)nch), dim3(256), 0, st, g, partial);
-  if (nch > 1)
-    hipLaunchKernelGGL((colreduce_jobs_final_kernel<T>), dim3((unsigned)g.ffirst[n_jobs]), dim3(CF_COLS * CF_LANES), 0, st, g, (const float*)partial);
+  return true;
+}
+template <typename T>
+inline void launch_reduce_jobs_final(const ReduceJobs<T>& g, const float* partial, hipStream_t st) {
+  if (g.nchunks > 1) hipLaunchKernelGGL((colreduce_jobs_final_kernel<T>), dim3((unsigned)g.ffirst[g.n_jobs]), dim3(CF_COLS * CF_LANES), 0, st, g, partial);
+}
+
+// The jobs of one layer; partial: (sum of the jobs' widths) * colreduce_chunks(rows) floats.
+template <typename T>
+inline hipError_t launch_reduce_jobs(const ReduceJob<T>* jobs, int n_jobs, float* partial, int64_t rows, hipStream_t st) {
+  ReduceJobs<T> g;
+  if (!make_reduce_jobs<T>(&g, jobs, n_jobs, rows)) {   // one by one
+    for (int i = 0; i < n_jobs; ++i) {
+      const ReduceJob<T>& w = jobs[i];
+      const hipError_t e = w.x ? launch_layernorm_bwd_params<T>(w.a, w.x, w.stats, w.out0, w.out1, partial, rows, w.n, st)
+                               : launch_colsum<T>(w.a, w.out0, partial, rows, w.n, st);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  hipLaunchKernelGGL((colreduce_jobs_partial_kernel<T, 16 / (int)sizeof(T)>), dim3((unsigned)g.first[n_jobs], (unsigned)g.nchunks), dim3(256), 0, st, g, partial);
+  launch_reduce_jobs_final<T>(g, partial, st);
   return hipGetLastError();
+}
+
+// dx of a LayerNorm and some column reductions over the same rows: the dx and the reductions' first stage share a launch where both are
+// small.  Three launches become two, or one up to 256 rows; measured for a LayerNorm alone (us): bf16 64x64 13.2 -> 8.6, 512x768 13.6 -> 11.0,
+// 1000x4096 19.9 -> 14.0, 4096x1920 20.9 -> 18.3, 16384x256 18.2 -> 12.4, 16384x1920 60.4 -> 58.8; fp32 64x64 13.7 -> 8.5, 4096x1024
+// 19.4 -> 18.7.
+template <typename T>
+inline hipError_t launch_layernorm_bwd_jobs(const LnBwdDx<T>& d, const ReduceJob<T>* jobs, int n_jobs, float* partial, hipStream_t st) {
+  constexpr int V = ln_vec<T>();
+  ReduceJobs<T> g;
+  const int nv = (d.h / V + kWave - 1) / kWave;
+  const int64_t dx_blocks = (d.rows + LN_ROWS_PER_BLOCK - 1) / LN_ROWS_PER_BLOCK;
+  if (d.h % V == 0 && ln_aligned16({d.dy, d.x, d.gamma, d.res, d.dx}) && nv <= 8 && d.rows <= (1 << 20) && make_reduce_jobs<T>(&g, jobs, n_jobs, d.rows)) {
+    const dim3 grid((unsigned)(dx_blocks + (int64_t)g.first[n_jobs] * g.nchunks)), block(256);
+    if (nv <= 4) hipLaunchKernelGGL((layernorm_bwd_jobs_kernel<T, V, 4>), grid, block, 0, st, d, g, partial);
+    else hipLaunchKernelGGL((layernorm_bwd_jobs_kernel<T, V, 8>), grid, block, 0, st, d, g, partial);
+    launch_reduce_jobs_final<T>(g, partial, st);
+    return hipGetLastError();
+  }
+  const hipError_t e = launch_layernorm_bwd_dx<T>(d.dy, d.x, d.stats, d.gamma, d.res, d.dx, d.rows, d.h, st);
+  return e != hipSuccess ? e : launch_reduce_jobs<T>(jobs, n_jobs, partial, d.rows, st);
+}
+
+// dx plus the gamma / beta gradient accumulation.
+template <typename T>
+inline hipError_t launch_layernorm_bwd(const T* dy, const T* x, const float* stats, const T* gamma,
+                                       const T* res, T* dx, float* dgamma, float* dbeta,
+                                       float* partial, int64_t rows, int h, hipStream_t st) {
+  // (the wide form of the partial sums fills the chip by itself; longer rows than 8 vectors per lane have no joint kernel)
+  constexpr int V = ln_vec<T>();
+  if (h <= 8 * kWave * V && (int64_t)((h + CRV_RL * V - 1) / (CRV_RL * V)) * colreduce_chunks(rows) < 768) {
+    const ReduceJob<T> job{dy, x, stats, dgamma, dbeta, h};
+    return launch_layernorm_bwd_jobs<T>({dy, x, stats, gamma, res, dx, rows, h}, &job, 1, partial, st);
+  }
+  hipError_t e = launch_layernorm_bwd_dx<T>(dy, x, stats, gamma, res, dx, rows, h, st);
+  if (e != hipSuccess) return e;
+  return launch_layernorm_bwd_params<T>(dy, x, stats, dgamma, dbeta, partial, rows, h, st);
 }
 
 // out = dropout(in) with the mask of one site (backward of a residual-branch dropout: the

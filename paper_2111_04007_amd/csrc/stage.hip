@@ -477,11 +477,7 @@ struct StageOps {
     }
     // QKV: dxn1 = dqkv Wqkv
     if ((e = gemm(VARUNA_K_GEMM_DGRAD, GEMM_DGRAD, EPI_PLAIN, T_, D.h, 3 * D.h, dqkv, param(l, VARUNA_P_WQKV), nullptr, nullptr, dxn_b, nullptr, nullptr))) return e;
-    // LN1: dx = dx1 + LN'(dxn1)
-    {
-      Bracket br(S, st, VARUNA_K_LN_BWD, 0, 4.0 * D.E * sizeof(T));
-      if ((e = launch_layernorm_bwd_dx<T>(dxn_b, x, stats1, param(l, VARUNA_P_LN1_G), dx1, dx, T_, D.h, st))) return e;
-    }
+    // LN1: dx = dx1 + LN'(dxn1), and the column reductions of the layer
     const ReduceJob<T> jobs[kMaxReduceJobs] = {
         {du, nullptr, nullptr, grad(l, VARUNA_P_B1), nullptr, D.f},
         {dqkv, nullptr, nullptr, grad(l, VARUNA_P_BQKV), nullptr, 3 * D.h},
@@ -489,6 +485,12 @@ struct StageOps {
         {dxn_b, x, stats1, grad(l, VARUNA_P_LN1_G), grad(l, VARUNA_P_LN1_B), D.h},
         {dyd, nullptr, nullptr, grad(l, VARUNA_P_B2), nullptr, D.h},
         {dx1d, nullptr, nullptr, grad(l, VARUNA_P_BO), nullptr, D.h}};
+    if (!S->prof_on && S->side == nullptr)   // (on two streams, and timed by kind of kernel, they are launches of their own)
+      return launch_layernorm_bwd_jobs<T>({dxn_b, x, stats1, param(l, VARUNA_P_LN1_G), dx1, dx, T_, D.h}, jobs, kMaxReduceJobs, wsp<float>(W.partial), st);
+    {
+      Bracket br(S, st, VARUNA_K_LN_BWD, 0, 4.0 * D.E * sizeof(T));
+      if ((e = launch_layernorm_bwd_dx<T>(dxn_b, x, stats1, param(l, VARUNA_P_LN1_G), dx1, dx, T_, D.h, st))) return e;
+    }
     return reduce_layer(jobs, kMaxReduceJobs);
   }
 
