@@ -338,6 +338,7 @@ struct StageOps {
   varuna_stage* S;
   hipStream_t st;
   const Dims& D;
+  const T* top_dy = nullptr;   // the upstream gradient of the call in progress, where it is not in the top layer's ring
   StageOps(varuna_stage* s_, hipStream_t st_) : S(s_), st(st_), D(s_->D) {}
 
   const T* param(int l, int which) const {
@@ -366,8 +367,9 @@ struct StageOps {
   }
 
   // One layer forward.  rs: ring slot of the wgrad operands (xn1, ctx, xn2, g).
-  // save: also store stats, lse, u.  skip_mlp2: stop after GeLU.
-  hipError_t layer_forward(int l, int mb, const T* x, T* y, const LayerArea& A, int rs, bool save, bool skip_mlp2) {
+  // save: also store stats, lse, u.  skip_mlp2: stop after GeLU.  x_in: where x still has to be taken from (its first reader,
+  // the LayerNorm, stores it to x), or null.
+  hipError_t layer_forward(int l, int mb, T* x, T* y, const LayerArea& A, int rs, bool save, bool skip_mlp2, const T* x_in) {
     hipError_t e;
     const int64_t T_ = D.T;
     T* xn1 = wsp<T>(A.xn1) + (size_t)rs * D.E; T* qkv = wsp<T>(A.qkv); T* ctx = wsp<T>(A.ctx) + (size_t)rs * D.E;
@@ -378,7 +380,7 @@ struct StageOps {
     float* lse = save ? wsp<float>(A.lse) : nullptr;
     {
       Bracket br(S, st, VARUNA_K_LN_FWD, 0, 2.0 * D.E * sizeof(T));
-      if ((e = launch_layernorm_fwd<T>(x, param(l, VARUNA_P_LN1_G), param(l, VARUNA_P_LN1_B), xn1, stats1, T_, D.h, D.eps, st))) return e;
+      if ((e = launch_layernorm_fwd<T>(x_in ? x_in : x, param(l, VARUNA_P_LN1_G), param(l, VARUNA_P_LN1_B), xn1, stats1, T_, D.h, D.eps, st, x_in ? x : nullptr))) return e;
     }
     if ((e = gemm(VARUNA_K_GEMM_FWD, GEMM_FWD, EPI_BIAS, T_, 3 * D.h, D.h, xn1, param(l, VARUNA_P_WQKV), param(l, VARUNA_P_BQKV), nullptr, qkv, nullptr, nullptr))) return e;
     {
@@ -434,7 +436,7 @@ struct StageOps {
     const T* x1 = wsp<T>(A.x1); const T* u = wsp<T>(A.u);
     const float* stats1 = wsp<float>(A.stats1); const float* stats2 = wsp<float>(A.stats2);
     const float* lse = wsp<float>(A.lse);
-    const T* dy = wsp<T>(A.dy) + (size_t)rs * D.E;
+    const T* dy = l == D.L - 1 && top_dy ? top_dy : wsp<T>(A.dy) + (size_t)rs * D.E;
     T* du = wsp<T>(A.du) + (size_t)rs * D.F; T* dx1 = wsp<T>(A.dx1) + (size_t)rs * D.E;
     T* dqkv = wsp<T>(A.dqkv) + (size_t)rs * 3 * D.E;
     T* dxn = wsp<T>(W.dxn); T* dxn_b = wsp<T>(W.dxn_b); T* dctx = wsp<T>(W.dctx);
@@ -527,7 +529,8 @@ struct StageOps {
       int n = 0;
       for (int l = top; l >= 0 && l > top - kMaxGroupJobs / 4; --l) {
         const LayerArea& A = S->ws.layer[l];
-        jobs[n++] = {wsp<T>(A.dyd), wsp<T>(A.g), grad(l, VARUNA_P_W2), D.h, D.f};
+        const T* dyd = l == D.L - 1 && top_dy && D.drop_thr == 0 ? top_dy : wsp<T>(A.dyd);
+        jobs[n++] = {dyd, wsp<T>(A.g), grad(l, VARUNA_P_W2), D.h, D.f};
         jobs[n++] = {wsp<T>(A.du), wsp<T>(A.xn2), grad(l, VARUNA_P_W1), D.f, D.h};
         jobs[n++] = {wsp<T>(A.dx1d), wsp<T>(A.ctx), grad(l, VARUNA_P_WO), D.h, D.h};
         jobs[n++] = {wsp<T>(A.dqkv), wsp<T>(A.xn1), grad(l, VARUNA_P_WQKV), 3 * D.h, D.h};
@@ -560,34 +563,29 @@ struct StageOps {
 
   T* slot(int mb) const { return reinterpret_cast<T*>(S->boundary) + (size_t)mb * D.E; }
 
-  hipError_t store_boundary(int mb, const T* x_in) {
-    if (x_in == slot(mb)) return hipSuccess;
-    Bracket br(S, st, VARUNA_K_OTHER, 0, 2.0 * D.E * sizeof(T));
-    return hipMemcpyAsync(slot(mb), x_in, (size_t)D.E * sizeof(T), hipMemcpyDeviceToDevice, st);
-  }
-
-  // Forward that keeps nothing but the boundary slot: every layer reuses the forward scratch.
+  // Forward that keeps nothing but the boundary slot (x_in goes there): every layer reuses the forward scratch.
   hipError_t forward(int mb, const T* x_in, T* y_out) {
     hipError_t e;
-    if ((e = store_boundary(mb, x_in))) return e;
-    const T* x = slot(mb);
+    T* x = slot(mb);
+    if (x_in == x) x_in = nullptr;
     for (int l = 0; l < D.L; ++l) {
       T* y = (l == D.L - 1) ? y_out : wsp<T>(S->ws.ping[l & 1]);
-      if ((e = layer_forward(l, mb, x, y, S->ws.fwd, 0, false, false))) return e;
+      if ((e = layer_forward(l, mb, x, y, S->ws.fwd, 0, false, false, l == 0 ? x_in : nullptr))) return e;
       x = y;
     }
     return hipSuccess;
   }
 
-  // Recompute from the boundary slot into the per-layer areas, ring slot rs.  With y_out
+  // Recompute from the boundary slot (with x_in: after storing it there) into the per-layer areas, ring slot rs.  With y_out
   // the stage output is produced too (the debug hook wants it; the backward pass does not).
-  hipError_t recompute(int mb, T* y_out, int rs) {
+  hipError_t recompute(int mb, const T* x_in, T* y_out, int rs) {
     hipError_t e;
-    const T* x = slot(mb);
+    T* x = slot(mb);
+    if (x_in == x) x_in = nullptr;
     for (int l = 0; l < D.L; ++l) {
       const bool last = (l == D.L - 1);
       T* y = last ? y_out : wsp<T>(S->ws.layer[l].y);
-      if ((e = layer_forward(l, mb, x, y, S->ws.layer[l], rs, true, last && y_out == nullptr))) return e;
+      if ((e = layer_forward(l, mb, x, y, S->ws.layer[l], rs, true, last && y_out == nullptr, l == 0 ? x_in : nullptr))) return e;
       x = y;
     }
     return hipSuccess;
@@ -598,10 +596,17 @@ struct StageOps {
   hipError_t backward(int mb, const T* dy_in, T* dx_out, bool recompute_first) {
     hipError_t e;
     const int rs = S->pending;
-    if (recompute_first && (e = recompute(mb, nullptr, rs))) return e;
-    {  // the upstream gradient joins the top layer's dy ring
+    if (recompute_first && (e = recompute(mb, nullptr, nullptr, rs))) return e;
+    // The upstream gradient joins the top layer's dy ring.  Where this call also issues the weight gradients, so that nothing reads the
+    // ring after it, the caller's buffer serves as it is, unless dx_out (rewritten before the last reader) overlaps it.
+    const size_t bytes = (size_t)D.E * sizeof(T);
+    const char* d0 = reinterpret_cast<const char*>(dy_in);
+    const char* o0 = reinterpret_cast<const char*>(dx_out);
+    const bool in_place = D.G == 1 && aligned16(dy_in) && (d0 + bytes <= o0 || o0 + bytes <= d0);
+    top_dy = in_place ? dy_in : nullptr;
+    if (!in_place) {
       Bracket br(S, st, VARUNA_K_OTHER, 0, 2.0 * D.E * sizeof(T));
-      if ((e = hipMemcpyAsync(wsp<T>(S->ws.layer[D.L - 1].dy) + (size_t)rs * D.E, dy_in, (size_t)D.E * sizeof(T), hipMemcpyDeviceToDevice, st))) return e;
+      if ((e = hipMemcpyAsync(wsp<T>(S->ws.layer[D.L - 1].dy) + (size_t)rs * D.E, dy_in, bytes, hipMemcpyDeviceToDevice, st))) return e;
     }
     for (int l = D.L - 1; l >= 0; --l) {
       const T* x = (l == 0) ? slot(mb) : wsp<T>(S->ws.layer[l - 1].y);
@@ -645,12 +650,10 @@ varuna_status_t keep_forward(varuna_stage_t* st, int32_t mb, const void* x_in, v
   st->kept_mb = -1;
   if (st->D.dtype == VARUNA_F32) {
     StageOps<float> ops(st, s);
-    e = ops.store_boundary(mb, static_cast<const float*>(x_in));
-    if (e == hipSuccess) e = ops.recompute(mb, static_cast<float*>(y_out), st->pending);
+    e = ops.recompute(mb, static_cast<const float*>(x_in), static_cast<float*>(y_out), st->pending);
   } else {
     StageOps<bf16> ops(st, s);
-    e = ops.store_boundary(mb, static_cast<const bf16*>(x_in));
-    if (e == hipSuccess) e = ops.recompute(mb, static_cast<bf16*>(y_out), st->pending);
+    e = ops.recompute(mb, static_cast<const bf16*>(x_in), static_cast<bf16*>(y_out), st->pending);
   }
   if ((rc = hip_result(e, what))) return rc;
   st->forwarded[mb] = 1;
