@@ -66,15 +66,14 @@ __global__ void attention_fwd_simple_kernel(const T* __restrict__ qkv, T* __rest
 // Per query row i: delta_i = sum_e dctx_ie ctx_ie; dS_ik = P_ik (dctx_i.V_k - delta_i);
 // dQ_i = scale * sum_k dS_ik K_k.  Writes delta for the key-side kernel.
 template <typename T>
-__global__ void attention_bwd_dq_simple_kernel(const T* __restrict__ qkv, const T* __restrict__ ctx,
+__device__ __forceinline__ void attention_bwd_dq_simple_block(const T* __restrict__ qkv, const T* __restrict__ ctx,
                                                const float* __restrict__ lse,
                                                const T* __restrict__ dctx, T* __restrict__ dqkv,
                                                float* __restrict__ delta, int s, int heads, int d,
-                                               int causal, float scale, DropArgs drop) {
-  extern __shared__ float smem[];
+                                               int causal, float scale, const DropArgs& drop, float* smem, int block) {
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int nw = blockDim.x / kWave;
-  const int i = blockIdx.x * nw + wave;
+  const int i = block * nw + wave;
   const int j = blockIdx.y, bi = blockIdx.z;
   if (i >= s) return;
   const int h = heads * d;
@@ -120,18 +119,17 @@ __global__ void attention_bwd_dq_simple_kernel(const T* __restrict__ qkv, const 
   }
 }
 
-// Per key row k: dV_k = sum_i P_ik dctx_i; dK_k = scale * sum_i dS_ik Q_i (i >= k if causal).
-template <typename T>
-__global__ void attention_bwd_dkv_simple_kernel(const T* __restrict__ qkv,
+// Per key row k: dV_k = sum_i P_ik dctx_i; dK_k = scale * sum_i dS_ik Q_i (i >= k if causal).  OWN: delta of a query is summed here.
+template <typename T, bool OWN>
+__device__ __forceinline__ void attention_bwd_dkv_simple_block(const T* __restrict__ qkv, const T* __restrict__ ctx,
                                                 const float* __restrict__ lse,
                                                 const T* __restrict__ dctx,
                                                 const float* __restrict__ delta,
                                                 T* __restrict__ dqkv, int s, int heads, int d,
-                                                int causal, float scale, DropArgs drop) {
-  extern __shared__ float smem[];
+                                                int causal, float scale, const DropArgs& drop, float* smem, int block) {
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int nw = blockDim.x / kWave;
-  const int k = blockIdx.x * nw + wave;
+  const int k = block * nw + wave;
   const int j = blockIdx.y, bi = blockIdx.z;
   if (k >= s) return;
   const int h = heads * d;
@@ -151,17 +149,29 @@ __global__ void attention_bwd_dkv_simple_kernel(const T* __restrict__ qkv,
   for (int i = i0 + lane; i < s; i += kWave) {
     const T* qrow = base + (int64_t)i * ld + j * d;
     const T* grow = dctx + ((int64_t)bi * s + i) * h + j * d;
-    float dot = 0.f, dp = 0.f;
-    ar_elements<T>(d, [&](int e) {
-      dot = fmaf(to_f32(qrow[e]), kk[e], dot);
-      dp = fmaf(to_f32(grow[e]), vv[e], dp);
-    });
+    float dot = 0.f, dp = 0.f, dl = 0.f;
+    if constexpr (OWN) {
+      const T* crow = ctx + ((int64_t)bi * s + i) * h + j * d;
+      float d4[4] = {0.f, 0.f, 0.f, 0.f};   // (in four parts: the other kernel's sum runs over the lanes)
+      ar_elements<T>(d, [&](int e) {
+        dot = fmaf(to_f32(qrow[e]), kk[e], dot);
+        dp = fmaf(to_f32(grow[e]), vv[e], dp);
+        d4[e & 3] = fmaf(to_f32(grow[e]), to_f32(crow[e]), d4[e & 3]);
+      });
+      dl = (d4[0] + d4[1]) + (d4[2] + d4[3]);
+    } else {
+      ar_elements<T>(d, [&](int e) {
+        dot = fmaf(to_f32(qrow[e]), kk[e], dot);
+        dp = fmaf(to_f32(grow[e]), vv[e], dp);
+      });
+      dl = delta[sbase + i];
+    }
     float pr = expf(dot * scale - lse[sbase + i]);
     float f = 1.0f;
     if (drop.thr != 0)
       f = drop_keep(drop, drop_row_word(drop, (uint32_t)(sbase + i), (uint32_t)k >> 2), k & 3) ? drop.scale : 0.f;
     pp[i] = pr * f;
-    ds[i] = pr * (dp * f - delta[sbase + i]);
+    ds[i] = pr * (dp * f - dl);
   }
   __builtin_amdgcn_wave_barrier();
   T* dk = dqkv + ((int64_t)bi * s + k) * ld + h + j * d;
@@ -177,6 +187,31 @@ __global__ void attention_bwd_dkv_simple_kernel(const T* __restrict__ qkv,
     dk[e] = from_f32<T>(ak * scale);
     dv[e] = from_f32<T>(av);
   }
+}
+
+template <typename T>
+__global__ void attention_bwd_dq_simple_kernel(const T* __restrict__ qkv, const T* __restrict__ ctx, const float* __restrict__ lse,
+                                               const T* __restrict__ dctx, T* __restrict__ dqkv, float* __restrict__ delta, int s,
+                                               int heads, int d, int causal, float scale, DropArgs drop) {
+  extern __shared__ float smem[];
+  attention_bwd_dq_simple_block<T>(qkv, ctx, lse, dctx, dqkv, delta, s, heads, d, causal, scale, drop, smem, blockIdx.x);
+}
+template <typename T>
+__global__ void attention_bwd_dkv_simple_kernel(const T* __restrict__ qkv, const float* __restrict__ lse, const T* __restrict__ dctx,
+                                                const float* __restrict__ delta, T* __restrict__ dqkv, int s, int heads, int d,
+                                                int causal, float scale, DropArgs drop) {
+  extern __shared__ float smem[];
+  attention_bwd_dkv_simple_block<T, false>(qkv, nullptr, lse, dctx, delta, dqkv, s, heads, d, causal, scale, drop, smem, blockIdx.x);
+}
+// Both in one launch, the key rows (the longer ones) first; they sum delta themselves, as the query rows' is not there yet.
+template <typename T>
+__global__ void attention_bwd_joint_simple_kernel(const T* __restrict__ qkv, const T* __restrict__ ctx, const float* __restrict__ lse,
+                                                  const T* __restrict__ dctx, T* __restrict__ dqkv, float* __restrict__ delta, int s,
+                                                  int heads, int d, int causal, float scale, DropArgs drop) {
+  extern __shared__ float smem[];
+  const int half = gridDim.x / 2;
+  if ((int)blockIdx.x < half) attention_bwd_dkv_simple_block<T, true>(qkv, ctx, lse, dctx, nullptr, dqkv, s, heads, d, causal, scale, drop, smem, blockIdx.x);
+  else attention_bwd_dq_simple_block<T>(qkv, ctx, lse, dctx, dqkv, delta, s, heads, d, causal, scale, drop, smem, blockIdx.x - half);
 }
 
 // Waves per block such that the per-wave LDS rows fit the default 64 KB limit.
@@ -203,6 +238,17 @@ hipError_t launch_attention_bwd_simple(const T* qkv, const T* ctx, const float* 
                                               const T* dctx, T* dqkv, float* delta, int b, int s,
                                               int heads, int d, int causal, const DropArgs& drop, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)d);
+  // Few rows: both sides are resident at once, and one launch ends when the key side does; with more rows the key side's third sum
+  // counts.  Measured, two launches / one (us): fp32 256 rows 19.6 / 13.8, 512 of 128 35.8 / 25.6, 1024 of 64 20.2 / 18.8; bf16 (converted
+  // element by element) 256 rows 14.7 / 12.1, 512 of 128 29.6 / 26.6, but 768 of 96 19.5 / 22.2.
+  if ((int64_t)b * heads * s <= (sizeof(T) == 4 ? 1024 : 512)) {
+    const int nw = ats_waves((size_t)(2 * d + 2 * s) * sizeof(float));
+    if (nw == 0) return hipErrorInvalidValue;
+    const size_t sm = (size_t)nw * (2 * d + 2 * s) * sizeof(float);
+    dim3 grid((unsigned)(2 * ((s + nw - 1) / nw)), (unsigned)heads, (unsigned)b);
+    hipLaunchKernelGGL((attention_bwd_joint_simple_kernel<T>), grid, dim3(nw * kWave), sm, st, qkv, ctx, lse, dctx, dqkv, delta, s, heads, d, causal, scale, drop);
+    return hipGetLastError();
+  }
   {
     const int nw = ats_waves((size_t)(2 * d + s) * sizeof(float));
     if (nw == 0) return hipErrorInvalidValue;
