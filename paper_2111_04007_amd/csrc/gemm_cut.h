@@ -1,7 +1,7 @@
 // GEMM of fp32 accuracy on the bf16 matrix cores: acc[m,n] = sum_k A(m,k) * B(n,k), any M, N, K.
 //   AK: A(m,k) = a[m*lda + k]   else A(m,k) = a[k*lda + m];   BK likewise for B(n,k) = b[n*ldb + k] / b[k*ldb + n]
-// It takes the bf16 operands whose rows are not whole 16-byte pieces (the direct-to-LDS kernels cannot address them), and those fp32
-// products where it is faster than the fp32 matrix instructions of gemm_f32.h (gc_kind).
+// It takes the bf16 operands whose rows are not whole 16-byte pieces (the direct-to-LDS kernels cannot address them), bf16 products of few
+// tiles (dg_cut_sooner), and those fp32 products where it is faster than the fp32 matrix instructions of gemm_f32.h (gc_kind).
 //
 // An fp32 operand is cut into three bf16 pieces, x = x1 + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1), x3 = the rest: 24 bits of
 // mantissa in pieces of 8, nothing is left over.  Of the nine piece products the six that reach 2^-18 of the whole are summed in
@@ -19,6 +19,7 @@
 #pragma once
 #include "common.h"
 #include "gemm_epilogue.h"
+#include "gemm_f32.h"
 
 namespace varuna {
 
@@ -396,6 +397,22 @@ __global__ __launch_bounds__(KS * kWave) void gemm_cut_kernel(const T* __restric
     logical = (int)t;
   }
   GcTile<T, MODE, AK, BK, TM, TN, KS>::run(a, lda, b, ldb, M, N, K, tiles_m, tiles_n, epi, logical, gc_smem);
+}
+
+// The jobs of gemm_f32_group_kernel.
+template <typename T, int TM, int TN, int KS>
+__global__ __launch_bounds__(KS * kWave) void gemm_cut_group_kernel(GfGroup<T> g) {
+  extern __shared__ __attribute__((aligned(16))) float gc_smem[];
+  using G = GcTile<T, EPI_ACCUM_F32, false, false, TM, TN, KS>;
+  int j = 0;
+  while (j + 1 < g.n && (int)blockIdx.x >= g.first[j + 1]) ++j;
+  const WgradJob<T>& w = g.job[j];
+  const int local = (int)blockIdx.x - g.first[j], nblk = g.first[j + 1] - g.first[j];
+  const int logical = (local & 7) * (nblk >> 3) + (local >> 3);
+  const int tiles_m = (w.M + G::BM - 1) / G::BM, tiles_n = (w.N + G::BN - 1) / G::BN;
+  if (logical >= tiles_m * tiles_n) return;
+  const EpiArgs<T> epi{nullptr, nullptr, nullptr, nullptr, w.out, w.N, DropArgs{}, 0};
+  G::run(w.a, w.M, w.b, w.N, w.M, w.N, g.K, tiles_m, tiles_n, epi, logical, gc_smem);
 }
 
 // Which kernel a product takes: tile of 32 or 64 rows and columns and the number of waves that share it, or the fp32 products of gemm_f32.h.

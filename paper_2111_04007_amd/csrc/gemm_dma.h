@@ -851,7 +851,18 @@ inline int dg_flavour(int tile_variant, int op) {
   return tile_variant;
 }
 
-// The library's choice for one product.  On top of the tile size and its kernel configuration:
+// Whether a product of so few 128x128 tiles that most CUs would stay idle ends sooner on the small tiles of gemm_cut.h, whose waves share
+// the reduction.  Measured back to back, this kernel / those (us, forward, dgrad, wgrad): 512x512 over 512 6.8 / 4.3, 6.3 / 5.2, 7.9 / 6.6,
+// over 1024 8.9 / 5.0, 8.8 / 6.3, 10.6 / 8.2, over 4096 36 / 17 (wgrad); 512x1024 over 512 7.0 / 5.5, 6.4 / 6.5, 8.1 / 8.3, over 1024 9.4 / 7.4, 9.6 / 8.7, 13.6 / 12.1;
+// 1024^2 over 1024 12.3 / 11.3, 12.2 / 11.1, 14.0 / 18.3 and over 4096 1.4, 1.6 and 1.2 times as fast; at 96 tiles always slower.
+inline bool dg_cut_sooner(int op, int64_t M, int64_t N, int64_t K) {
+  const int64_t t7 = ((M + 127) / 128) * ((N + 127) / 128);
+  if (t7 <= 18) return true;
+  if (t7 <= 32) return op == GEMM_FWD || K >= (op == GEMM_WGRAD ? 2048 : 1024);
+  return t7 <= 64 && K >= (op == GEMM_WGRAD ? 4096 : 1536);
+}
+
+// The library's choice for one product (0: the kernels of gemm_cut.h).  On top of the tile size and its kernel configuration:
 // two 128x128 workgroups on a CU are bound by the CU's path from L2 (64 B per clock), so forward
 // and dgrad products may run on 128x256 (else 256x128) tiles of 4 waves instead, one per CU: a pair
 // of tiles that shares one operand panel through LDS, a quarter less L2->LDS traffic.  (The 0.92 below was
@@ -862,6 +873,7 @@ inline int dg_flavour(int tile_variant, int op) {
 // they drain; in units of one full round of 512 tiles the two cost 0.55 / 1 / (tiles / 512) and
 // 0.92 * ceil(tiles / 2 / 256).
 inline int dg_pick(int op, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
+  if (dg_cut_sooner(op, M, N, K)) return 0;
   const int tile = dg_choose_variant(M, N, K, lda, ldb);
   if (tile == 7 && op != GEMM_WGRAD && dg_flavours().pair128) {
     const int64_t t = (M / 128) * (N / 128);

@@ -245,5 +245,7 @@ hipError_t launch_gemm_f32(int op, int mode, const T* a, const T* b, int64_t M, 
 // `n` weight gradients over K (all of a layer, of several layers), in one launch of gemm_f32.hip.  One by one against one launch:
 // two layers 128 wide over 128 tokens 8 x 3.9 against 6.5 us, one layer 768 wide over 1000 tokens 206 against 164 us.
 hipError_t launch_gemm_f32_group(const WgradJob<float>* jobs, int n, int64_t K, hipStream_t st);
+// The same on bf16 operands (products of gemm_cut.h), in gemm_f32_bf16.hip.
+hipError_t launch_gemm_cut_group(const WgradJob<bf16>* jobs, int n, int64_t K, hipStream_t st);
 
 }  // namespace varuna

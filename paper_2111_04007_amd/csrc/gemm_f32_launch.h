@@ -71,8 +71,9 @@ hipError_t launch_gemm_f32(int op, int mode, const T* a, const T* b, int64_t M, 
   return hipErrorInvalidValue;
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int KS, int BKT, bool VEC>
-inline hipError_t gf_launch_group(const WgradJob<T>* jobs, int n, int64_t K, hipStream_t st) {
+// f(table, workgroups) for up to kMaxGroupJobs jobs at a time, tiles of BM x BN.
+template <typename T, int BM, int BN, typename F>
+inline hipError_t gf_for_groups(const WgradJob<T>* jobs, int n, int64_t K, F&& f) {
   for (int i0 = 0; i0 < n; i0 += kMaxGroupJobs) {
     GfGroup<T> g{};
     g.n = n - i0 < kMaxGroupJobs ? n - i0 : kMaxGroupJobs;
@@ -85,9 +86,25 @@ inline hipError_t gf_launch_group(const WgradJob<T>* jobs, int n, int64_t K, hip
       if (blocks >= (1ll << 31)) return hipErrorInvalidValue;
     }
     g.first[g.n] = (int)blocks;
-    hipLaunchKernelGGL((gemm_f32_group_kernel<T, BM, BN, WM, WN, KS, BKT, VEC>), dim3((unsigned)blocks), dim3((BM / WM) * (BN / WN) * KS * kWave), 0, st, g);
+    f(g, (unsigned)blocks);
   }
   return hipGetLastError();
+}
+template <typename T, int BM, int BN, int WM, int WN, int KS, int BKT, bool VEC>
+inline hipError_t gf_launch_group(const WgradJob<T>* jobs, int n, int64_t K, hipStream_t st) {
+  return gf_for_groups<T, BM, BN>(jobs, n, K, [&](const GfGroup<T>& g, unsigned blocks) {
+    hipLaunchKernelGGL((gemm_f32_group_kernel<T, BM, BN, WM, WN, KS, BKT, VEC>), dim3(blocks), dim3((BM / WM) * (BN / WN) * KS * kWave), 0, st, g);
+  });
+}
+template <typename T, int TM, int TN, int KS>
+inline hipError_t gc_launch_group(const WgradJob<T>* jobs, int n, int64_t K, hipStream_t st) {
+  using G = GcTile<T, EPI_ACCUM_F32, false, false, TM, TN, KS>;
+  auto kern = gemm_cut_group_kernel<T, TM, TN, KS>;
+  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::SMEM);
+  if (attr_err != hipSuccess) return attr_err;
+  return gf_for_groups<T, G::BM, G::BN>(jobs, n, K, [&](const GfGroup<T>& g, unsigned blocks) {
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(G::NT), G::SMEM, st, g);
+  });
 }
 
 }  // namespace varuna

@@ -185,6 +185,12 @@ Workspace carve(const Dims& D) {
 
 constexpr int kMaxEvents = 4096;
 
+// Weight gradients of at most this many 128x128 tiles in all share a launch of the small tiles of gemm_cut.h; one by one each of them is a
+// launch that leaves most CUs idle, or two where its reduction is split.  Whole steps of two micro-batches, one by one / one launch (us):
+// 128 wide over 2048 tokens 441 / 389, 256 wide over 512 459 / 406, two layers of that (96 tiles) 838 / 773, 384 wide (108) over 512
+// 458 / 445 and over 2048 574 / 559; 512 wide (192) over 256 384 / 394, over 1000 686 / 707.
+constexpr int kCutGroupTiles = 128;
+
 }  // namespace
 
 struct varuna_stage {
@@ -508,7 +514,7 @@ struct StageOps {
         {
           EpiArgs<T> ea{nullptr, nullptr, nullptr, nullptr, part, N, DropArgs{}, M * N};
           Bracket br(S, st, VARUNA_K_GEMM_WGRAD, 2.0 * M * N * K, (double)(M * K + N * K) * sizeof(T) + (double)M * N * 4.0 * splits);
-          if ((e = GemmDispatch<T>::run(GEMM_WGRAD, EPI_STORE_F32, 0, M, N, K, a, b, ea, st, splits))) return e;
+          if ((e = GemmDispatch<T>::run(GEMM_WGRAD, EPI_STORE_F32, dg_flavour(dg_choose_variant(M, N, K, M, N), GEMM_WGRAD), M, N, K, a, b, ea, st, splits))) return e;
         }
         Bracket br(S, st, VARUNA_K_OTHER, 0, (double)M * N * 4.0 * (splits + 2));
         return launch_splitk_reduce(part, splits, M * N, dw, st);
@@ -548,6 +554,13 @@ struct StageOps {
         if (v != 0) {
           Bracket br(S, st, VARUNA_K_GEMM_WGRAD, flops, bytes);
           if ((e = launch_gemm_group(v, jobs, n, K, st))) return e;
+          continue;
+        }
+        int64_t tiles = 0;
+        for (int i = 0; i < n; ++i) tiles += gf_tiles(jobs[i].M, jobs[i].N, 128);
+        if (tiles <= kCutGroupTiles) {
+          Bracket br(S, st, VARUNA_K_GEMM_WGRAD, flops, bytes);
+          if ((e = launch_gemm_cut_group(jobs, n, K, st))) return e;
           continue;
         }
       } else {
