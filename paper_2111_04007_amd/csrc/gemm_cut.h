@@ -419,16 +419,19 @@ __global__ __launch_bounds__(KS * kWave) void gemm_cut_group_kernel(GfGroup<T> g
 //   bf16: as many waves as keep the chip's 1024 SIMDs busy.  Measured (us, 32x32 on 8 waves / 32x32 on 4 / 64x64 on 4 / 64x64 on 1):
 //   301^3 4.6 / 5.3 / 9.2 / 16, [2001,131] over 601 7.5 / 7.5 / 10 / 18, [701,701] over 6001 50 / 46 / 47 / 59, 1001^3 18 / 17 / 15 / 22,
 //   [4001,3001] over 3001 562 / 643 / 318 / 275.
-//   fp32 (32x32 on 8 waves / 64x64 on 4 / 64x64 on 1 / fp32 products) from K = 1024 on: one round of 32x32 tiles, [512,512] over 2048
-//   16 / 32 / 89 / 19 and 300x300 over 1200 11 / 22 / 58 / 12.5; from two thirds of a round of 64x64 tiles, 1024^3 38 / 24 / 54 / 30,
+//   fp32 rows that are not whole 16-byte pieces, by the same rule (fp32 products loaded such operands element by element; us, those / now,
+//   forward, dgrad, wgrad): 301x303 over 301 8.7 / 5.3, 8.1 / 6.0, 8.7 / 6.9, 513x515 over 301 13.5 / 7.6, 11.7 / 8.4, 11.9 / 9.1,
+//   1001x1003 over 201 14.9 / 12.1, 13.3 / 12.3, 17.4 / 15.8 and over 1003 46 / 26, 45 / 24, 51 / 28, 2001x1901 over 301 57 / 34, 50 / 28, 55 / 42.
+//   fp32 in whole pieces (32x32 on 8 waves / 64x64 on 4 / 64x64 on 1 / fp32 products) from K = 1024 on: one round of 32x32 tiles, [512,512] over
+//   2048 16 / 32 / 89 / 19 and 300x300 over 1200 11 / 22 / 58 / 12.5; from two thirds of a round of 64x64 tiles, 1024^3 38 / 24 / 54 / 30,
 //   1500^3 137 / 87 / 90 / 98, 2048^3 235 / 167 / 147 / 184.  A shorter reduction does not pay for the sums' way through LDS:
-//   [1000,768] over 768 26 / 20 / 43 / 20, transposed operands 29 / 24 / 54 / 20; and over 128 (one step per wave) a stage of
-//   128x128 products took 4.9 us instead of 4.4.
+//   [1000,768] over 768 26 / 20 / 43 / 20, transposed operands 29 / 24 / 54 / 20, 256x256 over 512 6.2 / 13 / 31 / 6.6, transposed
+//   7.0 / 15 / 34 / 6.8, 128x512 over 128 4.2 / 8.2 / 17 / 3.8.
 enum GcKind : int { GC_NONE = 0, GC_32_8 = 1, GC_32_4 = 2, GC_64_4 = 3, GC_64_1 = 4 };
-inline GcKind gc_kind(bool is_f32, int64_t tiles32, int64_t tiles64, int64_t K) {
-  if (is_f32 && K < 1024) return GC_NONE;
+inline GcKind gc_kind(bool f32_pieces, int64_t tiles32, int64_t tiles64, int64_t K) {
+  if (f32_pieces && K < 1024) return GC_NONE;
   if (tiles32 <= 256) return GC_32_8;
-  if (!is_f32) return tiles32 <= 512 ? GC_32_4 : tiles64 <= 1024 ? GC_64_4 : GC_64_1;
+  if (!f32_pieces) return tiles32 <= 512 ? GC_32_4 : tiles64 <= 768 ? GC_64_4 : GC_64_1;
   return tiles64 < 170 ? GC_NONE : tiles64 < 768 ? GC_64_4 : GC_64_1;
 }
 

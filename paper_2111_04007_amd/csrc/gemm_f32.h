@@ -2,7 +2,7 @@
 //   acc[m,n] = sum_k A(m,k) * B(n,k)
 //   AK: A(m,k) = a[m*lda + k]   else A(m,k) = a[k*lda + m];   BK likewise for B(n,k) = b[n*ldb + k] / b[k*ldb + n]
 // It serves the fp32 path (the 1e-5 tolerance rules out reduced-precision products) where products of bf16 pieces (gemm_cut.h) are
-// no faster: short reductions.  Any M, N, K; every global access is bounds-checked.
+// no faster: short reductions over whole 16-byte pieces.  Any M, N, K of that kind; every global access is bounds-checked.
 //
 // What bounds it: the fp32 matrix rate, 256 FLOP per clock and CU (157 TFLOP/s nominal, the rate a large library
 // product reaches here); a product of a 32x32 block takes 64 clocks for two LDS words per lane, so neither LDS
@@ -28,9 +28,9 @@ struct GfTile {
 };
 
 // Staging of one operand tile: global -> registers -> LDS, four consecutive elements of the contiguous direction
-// at a time.  VEC: one 16-byte (bf16: 8-byte) load per piece, which needs an aligned base, a leading dimension and a
-// contiguous extent that are multiples of 4; otherwise element by element.  Outside the matrix: zeros.
-template <typename T, int ROWS, int BKT, bool KMAJOR, bool VEC, int NT>
+// at a time, which needs an aligned base, a leading dimension and a contiguous extent that are multiples of 4 (others go to
+// gemm_cut.h).  Outside the matrix: zeros.
+template <typename T, int ROWS, int BKT, bool KMAJOR, int NT>
 struct GfLoader {
   static constexpr int PIECES = ROWS * BKT / 4, PPT = PIECES / NT;
   static_assert(PIECES % NT == 0, "tile / threads mismatch");
@@ -47,16 +47,10 @@ struct GfLoader {
       const int64_t left = KMAJOR ? K - k : rows - row;   // elements of the contiguous direction from here on
       const T* p = g + (KMAJOR ? row * ld + k : k * ld + row);
       floatx4 x = {0.f, 0.f, 0.f, 0.f};
-      if constexpr (VEC) {
-        if (line_ok && left > 0) {
-          const Tx4 t = *reinterpret_cast<const Tx4*>(p);
+      if (line_ok && left > 0) {
+        const Tx4 t = *reinterpret_cast<const Tx4*>(p);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = to_f32((T)t[e]);
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (line_ok && left > e) x[e] = to_f32(p[e]);
+        for (int e = 0; e < 4; ++e) x[e] = to_f32((T)t[e]);
       }
       v[i] = x;
     }
@@ -82,7 +76,7 @@ __device__ __forceinline__ floatx4 gf_frag(const float* lds, int row, int kg, in
 }
 
 // One workgroup: a BM x BN tile on (BM / WM) * (BN / WN) * KS waves, one stage of BKT k in LDS, the next in registers.
-template <typename T, int MODE, bool AK, bool BK, int BM, int BN, int WM, int WN, int KS, int BKT, bool VEC>
+template <typename T, int MODE, bool AK, bool BK, int BM, int BN, int WM, int WN, int KS, int BKT>
 __device__ __forceinline__ void gf_tile(
     const T* __restrict__ a, int64_t lda, const T* __restrict__ b, int64_t ldb, int64_t M, int64_t N, int64_t K,
     int tiles_m, int tiles_n, const EpiArgs<T>& epi, int logical) {
@@ -109,8 +103,8 @@ __device__ __forceinline__ void gf_tile(
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  GfLoader<T, BM, BKT, AK, VEC, NT> la;
-  GfLoader<T, BN, BKT, BK, VEC, NT> lb;
+  GfLoader<T, BM, BKT, AK, NT> la;
+  GfLoader<T, BN, BKT, BK, NT> lb;
   const int64_t nst = (K + BKT - 1) / BKT;
   la.load(a, lda, m0, M, 0, K, tid);
   lb.load(b, ldb, n0, N, 0, K, tid);
@@ -188,7 +182,7 @@ __device__ __forceinline__ void gf_tile(
 
 // Workgroup -> tile: consecutive workgroups go round the 8 XCDs; every XCD gets a contiguous range of tiles, walked in
 // groups of 8 tile rows (the panels it touches stay in its L2).
-template <typename T, int MODE, bool AK, bool BK, int BM, int BN, int WM, int WN, int KS, int BKT, bool VEC>
+template <typename T, int MODE, bool AK, bool BK, int BM, int BN, int WM, int WN, int KS, int BKT>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * KS * kWave) void gemm_f32_kernel(
     const T* __restrict__ a, int64_t lda, const T* __restrict__ b, int64_t ldb, int64_t M, int64_t N, int64_t K,
     int tiles_m, int tiles_n, EpiArgs<T> epi) {
@@ -200,7 +194,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * KS * kWave) void gemm_f32_k
     if (t >= (int64_t)tiles_m * tiles_n) return;
     logical = (int)t;
   }
-  gf_tile<T, MODE, AK, BK, BM, BN, WM, WN, KS, BKT, VEC>(a, lda, b, ldb, M, N, K, tiles_m, tiles_n, epi, logical);
+  gf_tile<T, MODE, AK, BK, BM, BN, WM, WN, KS, BKT>(a, lda, b, ldb, M, N, K, tiles_m, tiles_n, epi, logical);
 }
 
 // Several weight gradients out[M,N] += a[K,M]^T b[K,N] over the same K in one launch: the products of a small stage are a few
@@ -213,7 +207,7 @@ struct GfGroup {
   int first[kMaxGroupJobs + 1];
   WgradJob<T> job[kMaxGroupJobs];
 };
-template <typename T, int BM, int BN, int WM, int WN, int KS, int BKT, bool VEC>
+template <typename T, int BM, int BN, int WM, int WN, int KS, int BKT>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * KS * kWave) void gemm_f32_group_kernel(GfGroup<T> g) {
   int j = 0;
   while (j + 1 < g.n && (int)blockIdx.x >= g.first[j + 1]) ++j;
@@ -223,7 +217,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * KS * kWave) void gemm_f32_g
   const int tiles_m = (w.M + BM - 1) / BM, tiles_n = (w.N + BN - 1) / BN;
   if (logical >= tiles_m * tiles_n) return;
   const EpiArgs<T> epi{nullptr, nullptr, nullptr, nullptr, w.out, w.N, DropArgs{}, 0};
-  gf_tile<T, EPI_ACCUM_F32, false, false, BM, BN, WM, WN, KS, BKT, VEC>(w.a, w.M, w.b, w.N, w.M, w.N, g.K, tiles_m, tiles_n, epi, logical);
+  gf_tile<T, EPI_ACCUM_F32, false, false, BM, BN, WM, WN, KS, BKT>(w.a, w.M, w.b, w.N, w.M, w.N, g.K, tiles_m, tiles_n, epi, logical);
 }
 
 // Output tile of a product: 64x64 (4 waves of 32x32) or 32x32 (8 waves, each an eighth of every stage's k-range).
