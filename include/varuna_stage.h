@@ -241,14 +241,15 @@ varuna_status_t varuna_stage_debug_saved_region(const varuna_stage_t* st, size_t
  * the stage calls use for forward / dgrad / wgrad products on 256x256 and on 128x128 tiles; 0
  * restores the library's choice.  Naming a 128x128 configuration for forward or dgrad also turns
  * off the library's merging of 128x128 tile pairs into one 128x256 / 256x128 tile (configurations
- * 20 / 21), naming one for wgrad its grouping of several weight gradients into one launch.  Process-wide, not
+ * 20 / 21), naming one for wgrad its grouping of several weight gradients into one launch; a product of few tiles, which
+ * the library gives to smaller tiles (-1), then runs on 128x128 tiles too.  Process-wide, not
  * thread-safe, for same-process A/B timing only: results of every configuration agree to rounding but not bit for bit. */
 varuna_status_t varuna_debug_set_gemm_kernels(int32_t fwd256, int32_t dgrad256, int32_t wgrad256,
                                               int32_t fwd128, int32_t dgrad128, int32_t wgrad128);
 /* Host only (no GPU call): the kernel configuration the library picks for a bf16 product of
  * contiguous, 16-byte aligned operands, op as in varuna_op_gemm (0 forward, 1 dgrad, 2 wgrad):
- * a `variant` number of varuna_op_gemm, -1 for the fp32-product kernel (rows that are not whole
- * 16-byte pieces, or a single tile of a ragged shape), -2 for an invalid argument. */
+ * a `variant` number of varuna_op_gemm, -1 for the kernels on small tiles whose waves share the reduction (rows that are
+ * not whole 16-byte pieces, and products of few 128x128 tiles), -2 for an invalid argument. */
 int32_t varuna_debug_gemm_choice(int32_t op, int64_t M, int64_t N, int64_t K);
 /* Host only: the configuration (18, 19, 22 or 23) on which the weight gradients of n_layers (1 to 4) consecutive
  * bf16 layers over `tokens` stacked tokens run as one launch, 0 if they run one by one, -2 for an invalid argument. */

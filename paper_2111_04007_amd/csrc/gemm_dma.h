@@ -771,7 +771,7 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_group_kernel(DgGroup g, 
 }
 
 // ---------------------------------------------------------------------------
-// host side.  Variant ids (0 is "the library's choice", -1 the fp32-product kernel):
+// host side.  Variant ids (0 is "the library's choice", -1 the kernels of gemm_cut.h):
 //   5: 256x256 tile, 8 waves   6: 256x256, 4 waves   7: 128x128, 4 waves   8: 256x128, 4 waves
 //   9: as 5 with the spread load schedule   10: as 7 with the spread load schedule   11: as 6 with it
 //   12: as 5 with three stages of B and loads in every k-step   13: as 6 with that   14: as 7 with that
@@ -816,9 +816,8 @@ inline bool dg_shape_ok(int variant, int64_t M, int64_t N, int64_t K, int64_t ld
 // Picks between the 256x256 (one workgroup per CU) and 128x128 (two per CU) tiles by the
 // number of full-chip rounds each needs; 0 if neither fits the shape.  Sizes that are no multiples of 128 (64 for K)
 // take the EDGE form of the same two tiles, if their rows are whole 16-byte pieces and the product is larger than one
-// tile (of a single one the fp32-product kernel makes 16 small workgroups: up to 512 deep both take the launch's time,
-// 8.6 us; at long reductions the EDGE tile is the faster, 64x64x1024 13.2 / 8.8, 100x128x8192 84 / 38).  Against that
-// kernel (us, forward / dgrad / wgrad): 2000x1600x1600 184 / 161 / 147 -> 18 / 18 / 22 on 128x128 (34 on 256x256),
+// tile (which gemm_cut.h cuts into 16 or more workgroups; so it does with products of few tiles, dg_cut_sooner).  Against
+// fp32 products (us, forward / dgrad / wgrad): 2000x1600x1600 184 / 161 / 147 -> 18 / 18 / 22 on 128x128 (34 on 256x256),
 // 2000x6400x1600 495 / 481 / 509 -> 42 / 43 / 54 on 256x256 (50 on 128x128).  At sizes both forms take the plain one is
 // 1-5 % faster.
 inline int dg_choose_variant(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
@@ -842,7 +841,7 @@ inline int dg_choose_variant(int64_t M, int64_t N, int64_t K, int64_t lda, int64
 // load schedule, and so does wgrad (both operands read transposed); all of them with the k-tile
 // loop unrolled over the stage period, which removes the address arithmetic from the loop and was
 // worth 4.4 % of the C5 step and 1.4-2.6 % of the smaller stages' in same-process A/B.
-struct DgFlavours { int fwd256 = 17, bwd256 = 18, fwd128 = 19, dgrad128 = 19, wgrad128 = 19, wgrad256 = 18; bool pair128 = true, group = true; };
+struct DgFlavours { int fwd256 = 17, bwd256 = 18, fwd128 = 19, dgrad128 = 19, wgrad128 = 19, wgrad256 = 18; bool pair128 = true, group = true, small[3] = {true, true, true}; };
 inline DgFlavours& dg_flavours() { static DgFlavours f; return f; }   // tuning hook: varuna_debug_set_gemm_kernels
 inline int dg_flavour(int tile_variant, int op) {
   const DgFlavours& f = dg_flavours();
@@ -873,7 +872,7 @@ inline bool dg_cut_sooner(int op, int64_t M, int64_t N, int64_t K) {
 // they drain; in units of one full round of 512 tiles the two cost 0.55 / 1 / (tiles / 512) and
 // 0.92 * ceil(tiles / 2 / 256).
 inline int dg_pick(int op, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
-  if (dg_cut_sooner(op, M, N, K)) return 0;
+  if (dg_flavours().small[op] && dg_cut_sooner(op, M, N, K)) return 0;   // (a named 128x128 configuration is what runs)
   const int tile = dg_choose_variant(M, N, K, lda, ldb);
   if (tile == 7 && op != GEMM_WGRAD && dg_flavours().pair128) {
     const int64_t t = (M / 128) * (N / 128);

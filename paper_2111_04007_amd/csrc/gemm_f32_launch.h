@@ -1,4 +1,4 @@
-// Launches of the fp32-product GEMM kernels; included by one translation unit per operand type.
+// Launches of the GEMM kernels with fp32 products and on bf16 pieces; included by one translation unit per operand type.
 #pragma once
 #include <hip/hip_runtime.h>
 

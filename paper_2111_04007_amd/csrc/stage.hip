@@ -258,7 +258,7 @@ template <> struct GemmDispatch<float> {
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 template <> struct GemmDispatch<bf16> {
-  // variant 0: library's choice; -1: force the fp32-product kernel; >0: that MFMA configuration
+  // variant 0: library's choice; -1: force the kernels of gemm_cut.h; >0: that MFMA configuration
   static hipError_t run(int op, int mode, int variant, int64_t M, int64_t N, int64_t K, const bf16* a,
                         const bf16* b, const EpiArgs<bf16>& e, hipStream_t s, int splits = 1) {
     const int64_t lda = (op == GEMM_WGRAD) ? M : K;
@@ -558,7 +558,7 @@ struct StageOps {
         }
         int64_t tiles = 0;
         for (int i = 0; i < n; ++i) tiles += gf_tiles(jobs[i].M, jobs[i].N, 128);
-        if (tiles <= kCutGroupTiles) {
+        if (tiles <= kCutGroupTiles && dg_flavours().group) {
           Bracket br(S, st, VARUNA_K_GEMM_WGRAD, flops, bytes);
           if ((e = launch_gemm_cut_group(jobs, n, K, st))) return e;
           continue;
@@ -1050,6 +1050,7 @@ varuna_status_t varuna_debug_set_gemm_kernels(int32_t fwd256, int32_t dgrad256, 
   f.fwd128 = fwd128 ? fwd128 : d.fwd128; f.dgrad128 = dgrad128 ? dgrad128 : d.dgrad128; f.wgrad128 = wgrad128 ? wgrad128 : d.wgrad128;
   f.pair128 = fwd128 == 0 && dgrad128 == 0;   // naming a 128x128 configuration also turns the merging of tile pairs off
   f.group = wgrad256 == 0 && wgrad128 == 0;
+  f.small[GEMM_FWD] = fwd128 == 0; f.small[GEMM_DGRAD] = dgrad128 == 0; f.small[GEMM_WGRAD] = wgrad128 == 0;
   return VARUNA_OK;
 }
 
