@@ -82,10 +82,13 @@ struct GcOperand {
   }
   __device__ __forceinline__ void init(const T* __restrict__ g, int64_t ld, int64_t row0, int64_t rows, int lane) {
     kpitch = KMAJOR ? 1 : ld;
+    // Rows past the end (nothing of them is stored) repeat the last one, or the last whole piece of a k-row; of a k-row that does not end
+    // with a whole piece they are the last row and what follows it in memory, which `over` in GcTile keeps inside the operand.
+    const int64_t end = KMAJOR || rows % EPP != 0 ? rows - 1 : rows - EPP;
 #pragma unroll
-    for (int q = 0; q < PIECES; ++q) {   // rows past the end repeat the last one, or what follows it in memory (nothing of them is stored)
+    for (int q = 0; q < PIECES; ++q) {
       int64_t r = row0 + (KMAJOR ? piece_line(q, lane) : piece_elem(q, lane));
-      r = r < rows ? r : rows - 1;
+      r = r < rows ? r : end;
       p[q] = KMAJOR ? g + r * ld + piece_elem(q, lane) : g + piece_line(q, lane) * ld + r;
     }
   }
