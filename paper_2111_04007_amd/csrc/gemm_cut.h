@@ -9,7 +9,7 @@
 // has a sum of its own: a sum rounds relative to its size.  Error against 64 bits (K = 768 / 3072 / 2048, 1 / 4 waves per tile):
 // 1.6e-7 / 1.6e-7 / 2.7e-7 where fp32 products gave 1.9e-7 / 3.6e-7 / 8.1e-7.  A bf16 operand is its own only piece.
 //
-// What bounds it: fp32, the vector instructions that cut (seven per element and wave) beside products at the rate real data
+// What bounds it: fp32, the vector instructions that cut (seven and a half per element and wave) beside products at the rate real data
 // sustains; bf16, the path from L2 (16 KB per 64x64x64 block).  Every wave works alone, on its own steps of the reduction: no
 // barrier until the sums meet, and the cutting of one step issues between the products of the step before.  Reading the
 // operands straight into registers instead (32 rows of 32 bytes per instruction) took 1.2 to 3 times as long: one cache line per
@@ -31,13 +31,14 @@ typedef uint32_t gc_words __attribute__((ext_vector_type(4)));
 // Eight consecutive k of one row as the operand of a 32x32x16 product, in NP pieces.
 template <typename T> struct GcFrag { bf16x8 p[GcPieces<T>::N]; };
 
-__device__ __forceinline__ GcFrag<bf16> gc_cut(const bf16 (&x)[8]) {
+__device__ __forceinline__ GcFrag<bf16> gc_cut(const bf16 (&x)[8], uint32_t&) {
   GcFrag<bf16> f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) f.p[0][e] = x[e];
   return f;
 }
-__device__ __forceinline__ GcFrag<float> gc_cut(const float (&x)[8]) {
+// lost: every bit of the rests is or-ed into it; the lower 16 are what the third pieces leave out (gc_exact_block).
+__device__ __forceinline__ GcFrag<float> gc_cut(const float (&x)[8], uint32_t& lost) {
   gc_words h, m, l;   // two pieces per word
 #pragma unroll
   for (int e = 0; e < 8; e += 2) {
@@ -51,7 +52,9 @@ __device__ __forceinline__ GcFrag<float> gc_cut(const float (&x)[8]) {
     const float z0 = y0 - __builtin_bit_cast(float, mw << 16), z1 = y1 - __builtin_bit_cast(float, mw & 0xffff0000u);
     h[e / 2] = hw;
     m[e / 2] = mw;
-    l[e / 2] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, z1), __builtin_bit_cast(uint32_t, z0), 0x07060302u);   // upper halves: exact
+    const uint32_t zw0 = __builtin_bit_cast(uint32_t, z0), zw1 = __builtin_bit_cast(uint32_t, z1);
+    l[e / 2] = __builtin_amdgcn_perm(zw1, zw0, 0x07060302u);   // upper halves: all there is from 2^-109 on
+    lost |= zw0 | zw1;
   }
   GcFrag<float> f;
   f.p[0] = __builtin_bit_cast(bf16x8, h); f.p[1] = __builtin_bit_cast(bf16x8, m); f.p[2] = __builtin_bit_cast(bf16x8, l);
@@ -144,23 +147,40 @@ struct GcOperand {
 };
 
 // One 32x32 block over the steps of wave `ks`, with fp32 products from memory: for sums whose pieces are no good.  An infinity, or a value
-// that rounds to one, has NaN as its rest; below 2^-109 the last pieces underflow, which only shows where all of a block is small.
-template <typename T, bool AK, bool BK>
-__device__ __attribute__((noinline)) floatx16 gc_exact_block(const T* a, const T* b, int64_t lda, int64_t ldb, int64_t K, int ks, int nks, int step) {
-  const int half = (threadIdx.x % kWave) >> 5;   // a, b: this lane's row
+// that rounds to one, has NaN as its rest.  Below 2^-109 a value's last bits lie below the smallest bf16, 2^-133 (the matrix cores keep
+// bf16 and fp32 denormals): one such operand is enough, as its sums may be as large as any.  And sums of products below 2^-100 reach
+// into the denormals with their small terms.  Measured: 2048^3 125 us, with one such row in A 400 (as long as with every row
+// such, since all of a round wait for its tiles), 1024^3 23 and 53; the notice taken of it costs 1 to 4 % of a product.
+template <bool KMAJOR>
+__device__ __forceinline__ void gc_exact_load(float (&x)[8], const float* p, int64_t ld, int64_t k, int64_t K) {   // p: this lane's row
+  typedef float Four __attribute__((ext_vector_type(4), aligned(4)));
+  if (KMAJOR && k + 8 <= K) {
+    const Four lo = *reinterpret_cast<const Four*>(p + k), hi = *reinterpret_cast<const Four*>(p + k + 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { x[e] = lo[e]; x[4 + e] = hi[e]; }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int64_t kr = k + e < K ? k + e : K - 1;   // (no branch: the loads are in flight together)
+      const float v = KMAJOR ? p[kr] : p[kr * ld];
+      x[e] = k + e < K ? v : 0.f;
+    }
+  }
+}
+template <bool AK, bool BK>
+__device__ __attribute__((noinline)) floatx16 gc_exact_block(const float* a, const float* b, int64_t lda, int64_t ldb, int64_t K, int ks, int nks) {
+  constexpr int step = 16;
+  const int half = (threadIdx.x % kWave) >> 5;
   floatx16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  for (int64_t s = (int64_t)ks * step; s < K; s += step * nks)
-    for (int64_t kk = s; kk < s + step && kk < K; kk += 2) {
-      const int64_t k = kk + half;
-      float x = 0.f, y = 0.f;
-      if (k < K) {
-        x = to_f32(AK ? a[k] : a[k * lda]);
-        y = to_f32(BK ? b[k] : b[k * ldb]);
-      }
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc, 0, 0, 0);
-    }
+  for (int64_t s = (int64_t)ks * step; s < K; s += step * nks) {
+    float x[8], y[8];   // half 0 has the first eight k of a step, half 1 the others
+    gc_exact_load<AK>(x, a, lda, s + 8 * half, K);
+    gc_exact_load<BK>(y, b, ldb, s + 8 * half, K);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], acc, 0, 0, 0);
+  }
   return acc;
 }
 
@@ -208,6 +228,7 @@ struct GcTile {
     typename OA::Raw ra[2];
     typename OB::Raw rb[2];
     GcFrag<T> fa[2][GROUPS][TM], fb[2][GROUPS][TN];
+    uint32_t lost = 0;
     const int64_t steps = (K + KST - 1) / KST, mine = steps > ks ? (steps - ks + KS - 1) / KS : 0;   // this wave's: ks, ks + KS, ...
     // Whole steps: no piece of them reaches past the end of its operand (a piece of a ragged k-row may run into the rows after it).
     const int64_t over_a = AK || M % OA::EPP == 0 ? 0 : (OA::EPP - 2 + M) / M, over_b = BK || N % OB::EPP == 0 ? 0 : (OB::EPP - 2 + N) / N;
@@ -238,9 +259,9 @@ struct GcTile {
         oa.get(ga, ring + S * STAGE, c, lane);
         ob.get(gb, ring + S * STAGE + OA::BYTES, c, lane);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[S][c][i] = gc_cut(ga.v[i]);
+        for (int i = 0; i < TM; ++i) fa[S][c][i] = gc_cut(ga.v[i], lost);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) fb[S][c][j] = gc_cut(gb.v[j]);
+        for (int j = 0; j < TN; ++j) fb[S][c][j] = gc_cut(gb.v[j], lost);
       }
     };
     auto products = [&](auto set) {
@@ -278,7 +299,7 @@ struct GcTile {
 #pragma unroll
         for (int i = 0; i < 6 * TM * TN; ++i) {   // one product, then what issues in its shadow
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x002, TM * TN > 1 ? 8 : 15, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, TM * TN > 1 ? 9 : 16, 0);
         }
       }
       gc_wave_order();
@@ -323,7 +344,7 @@ struct GcTile {
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j];
-      uint32_t mx = 0;
+      uint32_t mx = 0, mn = ~0u;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -332,9 +353,10 @@ struct GcTile {
           for (int r = 0; r < 16; ++r) {
             const uint32_t v = __builtin_bit_cast(uint32_t, (float)acc[i][j][r]) & 0x7fffffffu;
             mx = v > mx ? v : mx;
+            mn = v - 1 < mn ? v - 1 : mn;   // (a sum of zero does not count)
           }
-      const bool inexact = __ballot(mx >= 0x7f800000u) != 0 ||                              // something is not finite
-                           (__ballot(mx >= (67u << 23)) == 0 && __ballot(mx != 0) != 0);    // all below 2^-60
+      // something is not finite, an operand had more bits than its pieces, or a sum is below 2^-100
+      const bool inexact = __ballot(mx >= 0x7f800000u || (lost & 0xffffu) != 0 || mn < (27u << 23)) != 0;
       if (__builtin_expect(inexact, 0)) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -342,7 +364,8 @@ struct GcTile {
           for (int j = 0; j < TN; ++j) {
             const int64_t m = m0 + OA::row(i, l32), n = n0 + OB::row(j, l32);
             const int64_t mr = m < M ? m : M - 1, nr = n < N ? n : N - 1;
-            acc[i][j] = gc_exact_block<T, AK, BK>(a + mr * (AK ? lda : 1), b + nr * (BK ? ldb : 1), lda, ldb, K, ks, KS, KST);
+            static_assert(KST == 16, "the steps of gc_exact_block");
+            acc[i][j] = gc_exact_block<AK, BK>(a + mr * (AK ? lda : 1), b + nr * (BK ? ldb : 1), lda, ldb, K, ks, KS);
           }
       }
     }

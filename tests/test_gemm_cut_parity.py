@@ -79,3 +79,27 @@ def test_values_at_the_end_of_the_range(op, M, N, K, value):
     rest = torch.arange(M, device="cuda") != M // 3
     d = (out[rest].double() - want[rest].double()).norm() / want[rest].double().norm()
     assert float(d) <= 2e-7 + 5e-8 * K ** 0.5
+
+
+@pytest.mark.parametrize("op", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(70, 65, 90), (70, 65, 1090), (512, 512, 2048), (1024, 1024, 1024), (2048, 2048, 1024)])
+@pytest.mark.parametrize("place", ["row", "column", "pair", "small times large"])
+def test_small_values_beside_others(op, M, N, K, place):
+    """Values whose last bits no bf16 holds, in tiles whose sums are ordinary: one row, one column, one k of both operands, one whole operand.
+    Every row and every column keeps the error of an fp32 product, relative to itself."""
+    a, b = operands(op, "f32", M, N, K)
+    at, bt = (a.t() if op == 2 else a), (b if op == 0 else b.t())   # [M, K], [N, K]
+    if place == "row":
+        at[M // 3] *= 1e-36
+    elif place == "column":
+        bt[N // 2] *= 1e-37
+    elif place == "pair":
+        at[:, K // 2] *= 1e-36
+        bt[:, K // 2] *= 1e37
+    else:
+        a *= 1e-36
+        b *= 1e30
+    out, want = product(op, a, b, M, N, K, "f32")
+    d = out.double() - want
+    for dim in (0, 1):
+        assert float((d.norm(dim=dim) / want.norm(dim=dim)).max()) <= 2e-7 + 5e-8 * K ** 0.5
