@@ -17,6 +17,8 @@
 // bf16 [4001,3001] over 3001 1527 / 275, 1001^3 72 / 15, 301^3 9.3 / 4.6; fp32 [1000,768] over 3072 67 / 51, 2048^3 184 / 147,
 // 1024^3 30 / 24, [512,512] over 2048 19 / 16.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 #include "gemm_epilogue.h"
 #include "gemm_f32.h"
@@ -31,12 +33,7 @@ typedef uint32_t gc_words __attribute__((ext_vector_type(4)));
 // Eight consecutive k of one row as the operand of a 32x32x16 product, in NP pieces.
 template <typename T> struct GcFrag { bf16x8 p[GcPieces<T>::N]; };
 
-__device__ __forceinline__ GcFrag<bf16> gc_cut(const bf16 (&x)[8], uint32_t&) {
-  GcFrag<bf16> f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) f.p[0][e] = x[e];
-  return f;
-}
+__device__ __forceinline__ GcFrag<bf16> gc_cut(const gc_words& x, uint32_t&) { return {{__builtin_bit_cast(bf16x8, x)}}; }
 // lost: every bit of the rests is or-ed into it; the lower 16 are what the third pieces leave out (gc_exact_block).
 __device__ __forceinline__ GcFrag<float> gc_cut(const float (&x)[8], uint32_t& lost) {
   gc_words h, m, l;   // two pieces per word
@@ -70,10 +67,12 @@ template <typename T, int NB, bool KMAJOR>
 struct GcOperand {
   static constexpr int EPP = 16 / sizeof(T), KST = 4 * EPP, ROWS = 32 * NB, PIECES = ROWS * 4 / kWave;   // pieces of a lane per step
   static constexpr int BYTES = ROWS * 64, PPK = ROWS / EPP;   // n-major: pieces of a k-row
-  typedef T Piece __attribute__((ext_vector_type(EPP), aligned(sizeof(T))));   // (element-aligned is enough)
-  typedef T PieceA __attribute__((ext_vector_type(EPP)));
+  // bf16 elements are held two per word throughout: as elements the compiler gives each a register of its own.
+  typedef std::conditional_t<sizeof(T) == 4, float, uint32_t> Word;
+  typedef Word Piece __attribute__((ext_vector_type(4), aligned(sizeof(T))));   // (element-aligned is enough)
+  typedef Word PieceA __attribute__((ext_vector_type(4)));
   struct Raw { PieceA v[PIECES]; };
-  struct Group { T v[NB][8]; };   // a 16-k group of every block
+  struct Group { std::conditional_t<sizeof(T) == 4, float[8], gc_words> v[NB]; };   // a 16-k group of every block
   const T* p[PIECES];      // this lane's pieces of step 0
   int64_t kpitch;          // elements from one k to the next
 
@@ -102,18 +101,21 @@ struct GcOperand {
   // The last steps: k past the end reads as zero, and no piece runs over its k-row.
   __device__ __forceinline__ void load_last(Raw& x, int64_t k, int64_t K, int64_t row0, int64_t rows, int lane) const {
 #pragma unroll
-    for (int q = 0; q < PIECES; ++q)
+    for (int q = 0; q < PIECES; ++q) {
+      const int64_t left = K - k - (KMAJOR ? piece_elem(q, lane) : piece_line(q, lane));   // k from the piece's first on
+      const int64_t r = row0 + piece_elem(q, lane), last = r < rows ? rows - 1 - r : 0;
+      const T* base = p[q] + (KMAJOR || left > 0 ? k : k + left - 1) * kpitch;             // n-major: past the end the last k-row
+      auto element = [&](int e) -> T {
+        if constexpr (KMAJOR) return e < left ? base[e] : (T)0.f;
+        const T v = base[e < last ? e : last];   // (no branch, and a piece at a time: all at once took the registers of a second wave)
+        return left > 0 ? v : (T)0.f;
+      };
+      T t __attribute__((ext_vector_type(EPP)));
 #pragma unroll
-      for (int e = 0; e < EPP; ++e) {
-        T v = (T)0.f;
-        if constexpr (KMAJOR) {
-          if (k + piece_elem(q, lane) + e < K) v = p[q][k + e];
-        } else {
-          const int64_t r = row0 + piece_elem(q, lane), last = r < rows ? rows - 1 - r : 0;
-          if (k + piece_line(q, lane) < K) v = p[q][k * kpitch + (e < last ? e : last)];
-        }
-        x.v[q][e] = v;
-      }
+      for (int e = 0; e < EPP; ++e) t[e] = element(e);
+      x.v[q] = __builtin_bit_cast(PieceA, t);
+      if constexpr (!KMAJOR) __builtin_amdgcn_sched_barrier(0);
+    }
   }
   __device__ __forceinline__ void put(const Raw& x, char* lds, int lane) const {
 #pragma unroll
@@ -128,18 +130,34 @@ struct GcOperand {
 #pragma unroll
         for (int q = 0; q < 8 / EPP; ++q) {
           const int piece = (c * 16 + 8 * half) / EPP + q;
-          *reinterpret_cast<PieceA*>(&g.v[i][q * EPP]) = *reinterpret_cast<const PieceA*>(lds + (i * 32 + r) * 64 + ((piece ^ (r >> 2 & 3)) * 16));
+          reinterpret_cast<PieceA*>(&g.v[i])[q] = *reinterpret_cast<const PieceA*>(lds + (i * 32 + r) * 64 + ((piece ^ (r >> 2 & 3)) * 16));
         }
     } else {
-      typedef T Rows __attribute__((ext_vector_type(NB)));
+      const T* s = reinterpret_cast<const T*>(lds) + (c * 16 + 8 * half) * ROWS + NB * r;
+      if constexpr (sizeof(T) == 4) {
+        typedef float Rows __attribute__((ext_vector_type(NB)));
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const T* s = reinterpret_cast<const T*>(lds) + (c * 16 + 8 * half + e) * ROWS + NB * r;
-        if constexpr (NB == 1) g.v[0][e] = *s;
-        else {
-          const Rows t = *reinterpret_cast<const Rows*>(s);
+        for (int e = 0; e < 8; ++e) {
+          if constexpr (NB == 1) g.v[0][e] = s[e * ROWS];
+          else {
+            const Rows t = *reinterpret_cast<const Rows*>(s + e * ROWS);
 #pragma unroll
-          for (int i = 0; i < NB; ++i) g.v[i][e] = t[i];
+            for (int i = 0; i < NB; ++i) g.v[i][e] = t[i];
+          }
+        }
+      } else {
+        static_assert(NB <= 2, "a word holds the rows of a lane");
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const T* s0 = s + 2 * w * ROWS;
+          const T* s1 = s0 + ROWS;
+          if constexpr (NB == 1) {
+            g.v[0][w] = *reinterpret_cast<const uint16_t*>(s0) | (uint32_t)*reinterpret_cast<const uint16_t*>(s1) << 16;
+          } else {
+            const uint32_t t0 = *reinterpret_cast<const uint32_t*>(s0), t1 = *reinterpret_cast<const uint32_t*>(s1);
+            g.v[0][w] = __builtin_amdgcn_perm(t1, t0, 0x05040100u);
+            g.v[1][w] = __builtin_amdgcn_perm(t1, t0, 0x07060302u);
+          }
         }
       }
     }
@@ -196,6 +214,7 @@ template <int V> struct GcInt { static constexpr int v = V; };
 template <typename T, int MODE, bool AK, bool BK, int TM, int TN, int KS>
 struct GcTile {
   static constexpr int BM = 32 * TM, BN = 32 * TN, NT = KS * kWave, NP = GcPieces<T>::N;
+  static constexpr bool PARTS = NP == 1 && (MODE == EPI_ACCUM_F32 || MODE == EPI_STORE_F32);
   using OA = GcOperand<T, TM, AK>;
   using OB = GcOperand<T, TN, BK>;
   static constexpr int KST = OA::KST, GROUPS = KST / 16, STAGE = OA::BYTES + OB::BYTES;
@@ -211,7 +230,10 @@ struct GcTile {
     const int gsize = tiles_m - first_m < 8 ? tiles_m - first_m : 8;
     const int64_t m0 = (int64_t)(first_m + (logical % width) % gsize) * BM, n0 = (int64_t)((logical % width) / gsize) * BN;
 
-    // The products of the first pieces are summed by themselves: a sum rounds relative to its size, and the other terms are small.
+    // Two sums, as a sum rounds relative to its size.  fp32: the products of the first pieces by themselves, the other terms are small.
+    // bf16 where the result is fp32: acc takes four steps (eight products), low all before them.  (As one sum a weight gradient over
+    // K = 1000 / 2000 / 4000 was 1.9e-7 / 2.7e-7 / 3.9e-7 off on one wave, in fp32 products 0.9e-7 / 1.2e-7 / 1.7e-7, in two 0.8e-7 /
+    // 1.0e-7 / 1.2e-7.  A bf16 result rounds by 2e-3: one sum is enough there, and leaves two waves their registers.)
     floatx16 acc[TM][TN], low[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -292,6 +314,17 @@ struct GcTile {
         load(set, t + 4);
       }
       gc_wave_order();   // (and left alone, the compiler sinks the loads to where they are needed)
+      if constexpr (PARTS && S == 0) {
+        if ((t & 2) == 0 || mine <= 16)   // (a short reduction: every two steps)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+              low[i][j] += acc[i][j];
+#pragma unroll
+              for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            }
+      }
       if (decltype(fast)::v || t + 1 < mine) cut(GcInt<1 - S>{});
       products(set);
       if constexpr (NP > 1 && decltype(fast)::v) {
@@ -339,11 +372,13 @@ struct GcTile {
       if (t + 1 < mine) phase(GcInt<1>{}, t + 1, GcInt<0>{});
     }
 
-    if constexpr (NP > 1) {
+    if constexpr (NP > 1 || PARTS) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j];
+    }
+    if constexpr (NP > 1) {
       uint32_t mx = 0, mn = ~0u;
 #pragma unroll
       for (int i = 0; i < TM; ++i)

@@ -103,3 +103,16 @@ def test_small_values_beside_others(op, M, N, K, place):
     d = out.double() - want
     for dim in (0, 1):
         assert float((d.norm(dim=dim) / want.norm(dim=dim)).max()) <= 2e-7 + 5e-8 * K ** 0.5
+
+
+@pytest.mark.parametrize("M,N,K", [(1801, 1801, 1000), (1801, 1801, 2000), (2049, 1601, 4000), (1201, 1101, 2000), (601, 601, 1000), (301, 255, 3000), (1801, 1801, 300), (1801, 1801, 129)])
+@pytest.mark.parametrize("signs", ["both", "one"])
+def test_error_of_a_bf16_weight_gradient(M, N, K, signs):
+    """fp32 sums of exact products, on every kind of tile: no further from 64 bits than sums in fp32 products, whose measured errors stand
+    here (values of both signs, which err more); a quarter as much again is allowed for, the error of a seed's values differs by a tenth."""
+    a, b = operands(2, "bf16", M, N, K)
+    if signs == "one":
+        a, b = a.abs(), b.abs()
+    out, want = product(2, a, b, M, N, K, "bf16")
+    fp32_products = {129: 0.56e-7, 300: 0.70e-7, 1000: 0.92e-7, 2000: 1.20e-7, 3000: 1.46e-7, 4000: 1.69e-7}[K]
+    assert float((out.double() - want).norm() / want.norm()) <= 1.25 * fp32_products
