@@ -778,8 +778,8 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_group_kernel(DgGroup g, 
 //   15: 128x256, 8 waves, that schedule   16: 256x128, 8 waves, that schedule
 //   17: as 13 with the k-tile loop unrolled over the stage period   18: as 12 with that
 //   19: as 14 with that
-//   20: 128x256, 21: 256x128, 4 waves, three stages of both operands (LS 5); a forward product on 20 takes tiles of 128x192 where
-//     dg_narrow says so
+//   20: 128x256, 21: 256x128, 4 waves, three stages of both operands (LS 5)
+//   24: 128x192 in that form, forward only; the library takes it in place of 20 where dg_narrow says so
 //   22, 23: as 19, 18 for sizes that are no multiples of the tile (EDGE)
 // ---------------------------------------------------------------------------
 inline bool dg_variant_tile(int variant, GemmTile* t) {
@@ -788,6 +788,7 @@ inline bool dg_variant_tile(int variant, GemmTile* t) {
     case 7: case 10: case 14: case 19: case 22: *t = {128, 128}; return true;
     case 8: case 16: case 21: *t = {256, 128}; return true;
     case 15: case 20: *t = {128, 256}; return true;
+    case 24: *t = {128, 192}; return true;
     default: return false;
   }
 }
@@ -886,7 +887,7 @@ inline int dg_pick(int op, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t
   return dg_flavour(tile, op);
 }
 
-// Whether a forward product on merged tiles takes them 192 wide: where the 256-wide ones leave a quarter of the chip idle.  Per round of
+// Whether a forward product that dg_pick gives to merged tiles (20) takes them 192 wide (24): where the 256-wide ones leave a quarter of the chip idle.  Per round of
 // 256 workgroups they cost 0.75 of the area and 1.04 for the larger share of loads.
 // Measured, 256 wide / 192 wide (us, operands out of cache): 2048x3072x3072 51 / 45, 2048x3072x12288 167 / 156, 1024x6144x2048 29.0 / 26.4,
 // 4096x1536x1536 28.6 / 25.4; a stage of three such layers forward 3307 -> 3219.

@@ -44,13 +44,12 @@ inline hipError_t dg_launch_variant(int variant, const bf16* a, int64_t lda, con
     case 17: return dg_launch_one<256, 256, 2, 2, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
     case 18: return dg_launch_one<256, 256, 2, 4, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
     case 19: return dg_launch_one<128, 128, 2, 2, AK, BK_, MODE, 4>(a, lda, b, ldb, M, N, K, epi, splits, st);
-    case 20:
-      if constexpr (AK && BK_)
-        if (dg_narrow(M, N)) return dg_launch_one<128, 192, 2, 2, AK, BK_, MODE, 5>(a, lda, b, ldb, M, N, K, epi, splits, st);
-      return dg_launch_one<128, 256, 2, 2, AK, BK_, MODE, 5>(a, lda, b, ldb, M, N, K, epi, splits, st);
+    case 20: return dg_launch_one<128, 256, 2, 2, AK, BK_, MODE, 5>(a, lda, b, ldb, M, N, K, epi, splits, st);
     case 21: return dg_launch_one<256, 128, 2, 2, AK, BK_, MODE, 5>(a, lda, b, ldb, M, N, K, epi, splits, st);
     case 22: return dg_launch_one<128, 128, 2, 2, AK, BK_, MODE, 4, true>(a, lda, b, ldb, M, N, K, epi, splits, st);
     case 23: return dg_launch_one<256, 256, 2, 4, AK, BK_, MODE, 4, true>(a, lda, b, ldb, M, N, K, epi, splits, st);
+    case 24:
+      if constexpr (AK && BK_) return dg_launch_one<128, 192, 2, 2, AK, BK_, MODE, 5>(a, lda, b, ldb, M, N, K, epi, splits, st);
     default: return hipErrorInvalidValue;
   }
 }

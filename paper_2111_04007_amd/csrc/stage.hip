@@ -271,13 +271,14 @@ template <> struct GemmDispatch<bf16> {
       if (v == 0) v = -1;
     }
     if (v >= 5) {
-      if (!ptr_ok || !dg_shape_ok(v, M, N, K, lda, ldb)) return hipErrorInvalidConfiguration;
+      if (!ptr_ok || !dg_shape_ok(v, M, N, K, lda, ldb) || (v == 24 && op != GEMM_FWD)) return hipErrorInvalidConfiguration;
       return launch_gemm_dma(op, mode, v, a, lda, b, ldb, M, N, K, e, s, splits);
     }
     if (splits != 1 || v != -1) return hipErrorInvalidConfiguration;
     return launch_gemm_f32<bf16>(op, mode, a, b, M, N, K, e, s);
   }
 };
+      if (v == 20 && op == GEMM_FWD && dg_narrow(M, N)) v = 24;
 
 // fp32.  variant 0: library's choice; -1: one wave per row (few or short rows, head dims above 128); else fp32 products.
 template <typename T> struct AttnDispatch {
