@@ -253,7 +253,8 @@ varuna_status_t varuna_debug_set_gemm_kernels(int32_t fwd256, int32_t dgrad256, 
  * not whole 16-byte pieces, and products of few 128x128 tiles), -2 for an invalid argument. */
 int32_t varuna_debug_gemm_choice(int32_t op, int64_t M, int64_t N, int64_t K);
 /* Host only: the configuration (18, 19, 22 or 23) on which the weight gradients of n_layers (1 to 4) consecutive
- * bf16 layers over `tokens` stacked tokens run as one launch, 0 if they run one by one, -2 for an invalid argument. */
+ * bf16 layers over `tokens` stacked tokens (16-byte aligned) run as one launch, -1 if they share one launch of the small tiles
+ * (at most 128 tiles of 128x128 in all; more layers than that run one by one), 0 if they run one by one, -2 for an invalid argument. */
 int32_t varuna_debug_wgrad_group_choice(int32_t n_layers, int64_t hidden, int64_t mlp, int64_t tokens);
 
 /* ---- per-kernel timing (HIP events on the caller's stream) -------------- */

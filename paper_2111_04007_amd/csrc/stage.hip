@@ -191,6 +191,15 @@ constexpr int kMaxEvents = 4096;
 // 458 / 445 and over 2048 574 / 559; 512 wide (192) over 256 384 / 394, over 1000 686 / 707.
 constexpr int kCutGroupTiles = 128;
 
+// How `n` bf16 weight gradients over K run: one launch on a configuration of gemm_dma.h (aligned operands), one of the small tiles (-1), or one by one (0).
+int wgrad_group_choice(const DgJob* jobs, int n, int64_t K, bool aligned) {
+  const int v = aligned ? dg_group_choice(jobs, n, K) : 0;
+  if (v != 0 || !dg_flavours().group) return v;
+  int64_t tiles = 0;
+  for (int i = 0; i < n; ++i) tiles += gf_tiles(jobs[i].M, jobs[i].N, 128);
+  return tiles <= kCutGroupTiles ? -1 : 0;
+}
+
 }  // namespace
 
 struct varuna_stage {
@@ -551,7 +560,7 @@ struct StageOps {
         bytes += ((double)jobs[i].M + jobs[i].N) * K * sizeof(T) + 8.0 * mn;
       }
       if constexpr (std::is_same<T, bf16>::value) {
-        const int v = aligned ? dg_group_choice(jobs, n, K) : 0;
+        const int v = wgrad_group_choice(jobs, n, K, aligned);
         if (v != 0) {
           Bracket br(S, st, VARUNA_K_GEMM_WGRAD, flops, bytes);
           if ((e = launch_gemm_group(v, jobs, n, K, st))) return e;
@@ -1071,7 +1080,7 @@ int32_t varuna_debug_wgrad_group_choice(int32_t n_layers, int64_t hidden, int64_
     const int mn[4][2] = {{h, f}, {f, h}, {h, h}, {3 * h, h}};
     for (int i = 0; i < 4; ++i) jobs[4 * l + i] = {nullptr, nullptr, nullptr, mn[i][0], mn[i][1]};
   }
-  return dg_group_choice(jobs, 4 * n_layers, tokens);
+  return wgrad_group_choice(jobs, 4 * n_layers, tokens, true);
 }
 
 varuna_status_t varuna_probe_mfma_rate(const void* operands, int64_t n_elems, int32_t waves_per_simd, int32_t pattern,

@@ -201,3 +201,14 @@ def test_weight_gradient_group_choice():
     assert B.debug_wgrad_group_choice(1, 512, 2048, 128) == 0          # fewer tiles than slots: split sums instead
     assert B.debug_wgrad_group_choice(2, 8192, 32768, 4096) == 0       # thousands of 256x256 tiles: nothing to gain
     assert B.debug_wgrad_group_choice(4, 1920, 7680, 4096) == 19 and B.debug_wgrad_group_choice(4, 1920, 7680, 32768) == 0
+
+
+def test_weight_gradients_of_a_small_stage_share_a_launch_of_the_small_tiles():
+    """Up to 128 tiles of 128x128 in all, counted with their ragged ones, and not where a weight-gradient configuration is named."""
+    for layers, h, f, want in ((1, 64, 256, -1), (4, 64, 256, -1), (2, 256, 1024, -1), (3, 256, 1024, 0), (1, 384, 1536, -1), (1, 385, 1536, 0), (1, 512, 2048, 0), (1, 385, 1152, -1), (1, 385, 1153, 0)):
+        assert B.debug_wgrad_group_choice(layers, h, f, 512) == want, (layers, h, f)
+    try:
+        B.debug_set_gemm_kernels(wgrad128=14)
+        assert B.debug_wgrad_group_choice(2, 256, 1024, 512) == 0
+    finally:
+        B.debug_set_gemm_kernels()
