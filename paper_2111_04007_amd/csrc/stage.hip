@@ -278,6 +278,7 @@ template <> struct GemmDispatch<bf16> {
     if (v == 0) {
       v = ptr_ok ? dg_pick(op, M, N, K, lda, ldb) : -1;
       if (v == 0) v = -1;
+      if (v == 20 && op == GEMM_FWD && dg_narrow(M, N)) v = 24;
     }
     if (v >= 5) {
       if (!ptr_ok || !dg_shape_ok(v, M, N, K, lda, ldb) || (v == 24 && op != GEMM_FWD)) return hipErrorInvalidConfiguration;
@@ -287,7 +288,6 @@ template <> struct GemmDispatch<bf16> {
     return launch_gemm_f32<bf16>(op, mode, a, b, M, N, K, e, s);
   }
 };
-      if (v == 20 && op == GEMM_FWD && dg_narrow(M, N)) v = 24;
 
 // fp32.  variant 0: library's choice; -1: one wave per row (few or short rows, head dims above 128); else fp32 products.
 template <typename T> struct AttnDispatch {
@@ -563,14 +563,7 @@ struct StageOps {
         const int v = wgrad_group_choice(jobs, n, K, aligned);
         if (v != 0) {
           Bracket br(S, st, VARUNA_K_GEMM_WGRAD, flops, bytes);
-          if ((e = launch_gemm_group(v, jobs, n, K, st))) return e;
-          continue;
-        }
-        int64_t tiles = 0;
-        for (int i = 0; i < n; ++i) tiles += gf_tiles(jobs[i].M, jobs[i].N, 128);
-        if (tiles <= kCutGroupTiles && dg_flavours().group) {
-          Bracket br(S, st, VARUNA_K_GEMM_WGRAD, flops, bytes);
-          if ((e = launch_gemm_cut_group(jobs, n, K, st))) return e;
+          if ((e = v > 0 ? launch_gemm_group(v, jobs, n, K, st) : launch_gemm_cut_group(jobs, n, K, st))) return e;
           continue;
         }
       } else {
