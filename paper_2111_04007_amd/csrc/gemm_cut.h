@@ -4,18 +4,23 @@
 // tiles (dg_cut_sooner), and those fp32 products where it is faster than the fp32 matrix instructions of gemm_f32.h (gc_kind).
 //
 // An fp32 operand is cut into three bf16 pieces, x = x1 + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1), x3 = the rest: 24 bits of
-// mantissa in pieces of 8, nothing is left over.  Of the nine piece products the six that reach 2^-18 of the whole are summed in
-// fp32 (x1y1, x1y2, x2y1, x2y2, x1y3, x3y1); the others are below 2^-26, a quarter of the rounding of one fp32 product, and x1y1
-// has a sum of its own: a sum rounds relative to its size.  Error against 64 bits (K = 768 / 3072 / 2048, 1 / 4 waves per tile):
-// 1.6e-7 / 1.6e-7 / 2.7e-7 where fp32 products gave 1.9e-7 / 3.6e-7 / 8.1e-7.  A bf16 operand is its own only piece.
+// mantissa in pieces of 8, nothing is left over.  Of the nine piece products six are summed in fp32 (x1y1, x1y2, x2y1, x2y2, x1y3, x3y1),
+// x1y1 in a sum of its own: a sum rounds relative to its size.  x2y3 + x3y2 reach 2^-24 of a product at worst, half a unit of an fp32
+// result (near 1.004 times 1.004; a tenth of that on average, of either sign), and x3y3 2^-34.  Where single products show, in
+// reductions of up to five steps of each wave and in the last steps of longer ones, those two are summed as well: K = 1 is then off by one
+// rounding, as an fp32 product is (6.0e-8 at most; with six 8.8e-8).  In the pipelined loop they would take 8 to 13 % of the time
+// ([1000,768] over 3072 43 -> 48 us, 2048^3 123 -> 140) and change no result beyond its rounding: operands within 1e-5 of that worst place
+// over K = 200 / 300 / 1024 / 3072 are 3.7e-8 / 2.9e-8 / 5.0e-8 / 3.9e-8 from 64 bits with six as with eight, in fp32 products
+// 2.1e-7 / 2.5e-7 / 2.8e-7 / 1.1e-7.  N(0,1) operands, fp32 products / this (K = 33, 301, 1024, 3072, 2048 on one wave): 8.2e-8 / 4.9e-8,
+// 1.3e-7 / 7.1e-8, 5.7e-7 / 9.8e-8, 3.6e-7 / 1.6e-7, 8.1e-7 / 2.7e-7.  A bf16 operand is its own only piece.
 //
 // What bounds it: fp32, the vector instructions that cut (seven and a half per element and wave) beside products at the rate real data
 // sustains; bf16, the path from L2 (16 KB per 64x64x64 block).  Every wave works alone, on its own steps of the reduction: no
 // barrier until the sums meet, and the cutting of one step issues between the products of the step before.  Reading the
 // operands straight into registers instead (32 rows of 32 bytes per instruction) took 1.2 to 3 times as long: one cache line per
-// clock; sharing cut tiles through LDS between waves was equal at 2048^3 and slower below.  Measured (us, before / now):
-// bf16 [4001,3001] over 3001 1527 / 275, 1001^3 72 / 15, 301^3 9.3 / 4.6; fp32 [1000,768] over 3072 67 / 51, 2048^3 184 / 147,
-// 1024^3 30 / 24, [512,512] over 2048 19 / 16.
+// clock; sharing cut tiles through LDS between waves was equal at 2048^3 and slower below.  Measured (us, fp32 products / this):
+// bf16 [4001,3001] over 3001 1527 / 275, 1001^3 72 / 15, 301^3 9.3 / 4.6; fp32 [1000,768] over 3072 57 / 44, 2048^3 154 / 120,
+// 1024^3 27 / 22, [512,512] over 2048 17.5 / 14.4.
 #pragma once
 #include <type_traits>
 
@@ -286,14 +291,15 @@ struct GcTile {
         for (int j = 0; j < TN; ++j) fb[S][c][j] = gc_cut(gb.v[j], lost);
       }
     };
-    auto products = [&](auto set) {
+    auto products = [&](auto set, auto fast) {
       constexpr int S = decltype(set)::v;
+      constexpr int LAST = NP > 1 && !decltype(fast)::v ? NP : NP - 1;
 #pragma unroll
       for (int c = 0; c < GROUPS; ++c)
 #pragma unroll
-        for (int s = NP - 1; s >= 0; --s)   // pieces p + q = s
+        for (int s = LAST; s >= 0; --s)   // pieces p + q = s
 #pragma unroll
-          for (int p = 0; p <= s; ++p)
+          for (int p = s < NP ? 0 : s - NP + 1; p <= s && p < NP; ++p)
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -326,7 +332,7 @@ struct GcTile {
             }
       }
       if (decltype(fast)::v || t + 1 < mine) cut(GcInt<1 - S>{});
-      products(set);
+      products(set, fast);
       if constexpr (NP > 1 && decltype(fast)::v) {
         __builtin_amdgcn_sched_group_barrier(0x100, 64, 0);
 #pragma unroll

@@ -116,3 +116,19 @@ def test_error_of_a_bf16_weight_gradient(M, N, K, signs):
     out, want = product(2, a, b, M, N, K, "bf16")
     fp32_products = {129: 0.56e-7, 300: 0.70e-7, 1000: 0.92e-7, 2000: 1.20e-7, 3000: 1.46e-7, 4000: 1.69e-7}[K]
     assert float((out.double() - want).norm() / want.norm()) <= 1.25 * fp32_products
+
+
+@pytest.mark.parametrize("op", [0, 1, 2])
+@pytest.mark.parametrize("values", ["normal", "clustered"])
+@pytest.mark.parametrize("K", [1, 2, 3, 16, 33])
+def test_single_products_of_a_short_reduction(op, values, K):
+    """Short sums show the rounding of their products.  1.0040206 * 1.0038986 has the largest terms of middle and last pieces, 2^-24 of the
+    product; of K terms of one sign a result in fp32 is off by half a unit for each of its K roundings, and by no more."""
+    M, N = 63, 65
+    a, b = operands(op, "f32", M, N, K)
+    if values == "clustered":
+        a, b = (c * (1 + 1e-5 * x.clamp(-1, 1)) for c, x in ((1.0040206, a), (1.0038986, b)))
+    else:
+        a, b = a.abs(), b.abs()
+    out, want = product(op, a, b, M, N, K, "f32")
+    assert float(((out.double() - want).abs() / want).max()) <= 2.0 ** -24 * (K + 2.0 ** -8)   # (what is left out is below 2^-33)
