@@ -491,7 +491,11 @@ __global__ __launch_bounds__(KS * kWave) void gemm_cut_group_kernel(GfGroup<T> g
 //   1001x1003 over 201 14.9 / 12.1, 13.3 / 12.3, 17.4 / 15.8 and over 1003 46 / 26, 45 / 24, 51 / 28, 2001x1901 over 301 57 / 34, 50 / 28, 55 / 42.
 //   fp32 in whole pieces (32x32 on 8 waves / 64x64 on 4 / 64x64 on 1 / fp32 products) from K = 1024 on: one round of 32x32 tiles, [512,512] over
 //   2048 16 / 32 / 89 / 19 and 300x300 over 1200 11 / 22 / 58 / 12.5; from two thirds of a round of 64x64 tiles, 1024^3 38 / 24 / 54 / 30,
-//   1500^3 137 / 87 / 90 / 98, 2048^3 235 / 167 / 147 / 184.  A shorter reduction does not pay for the sums' way through LDS:
+//   1500^3 137 / 87 / 90 / 98, 2048^3 235 / 167 / 147 / 184.  64x64 on 4 waves come in whole rounds of 256, so they pay where the fp32
+//   products' own rounds (gf_small_tile, there on 32x32 tiles four times finer) take 3.5 times the tile area per round, 4 times
+//   below K = 1280 (fp32 products / 64x64 on 4, forward, dgrad, wgrad): at 3 times, 500x2304 over 1024 33 / 40, 32 / 38, 35 / 43 and over 2048
+//   60 / 65, 58 / 63, 63 / 69; at 3.6, 1024x2304 over 1024 59 / 61, 58 / 58, 60 / 66, over 1280 73 / 72, 72 / 69, 75 / 76 and over 2048
+//   114 / 101, 109 / 98, 111 / 105; at 4, 1000x1600 over 1024 42 / 40, 42 / 38, 47 / 44.  A shorter reduction does not pay for the sums' way through LDS:
 //   [1000,768] over 768 26 / 20 / 43 / 20, transposed operands 29 / 24 / 54 / 20, 256x256 over 512 6.2 / 13 / 31 / 6.6, transposed
 //   7.0 / 15 / 34 / 6.8, 128x512 over 128 4.2 / 8.2 / 17 / 3.8.
 enum GcKind : int { GC_NONE = 0, GC_32_8 = 1, GC_32_4 = 2, GC_64_4 = 3, GC_64_1 = 4 };
@@ -499,7 +503,10 @@ inline GcKind gc_kind(bool f32_pieces, int64_t tiles32, int64_t tiles64, int64_t
   if (f32_pieces && K < 1024) return GC_NONE;
   if (tiles32 <= 256) return GC_32_8;
   if (!f32_pieces) return tiles32 <= 512 ? GC_32_4 : tiles64 <= 768 ? GC_64_4 : GC_64_1;
-  return tiles64 < 170 ? GC_NONE : tiles64 < 768 ? GC_64_4 : GC_64_1;
+  if (tiles64 >= 768) return GC_64_1;
+  const double r32 = (double)((tiles32 + 255) / 256), r64 = (double)((tiles64 + 255) / 256);
+  const double fp32 = gf_small_tile(tiles32, tiles64) ? 1.2 * r32 : 4.0 * r64;
+  return tiles64 >= 170 && fp32 >= (K < 1280 ? 4.0 : 3.5) * r64 ? GC_64_4 : GC_NONE;
 }
 
 }  // namespace varuna

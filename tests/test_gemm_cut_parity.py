@@ -132,3 +132,10 @@ def test_single_products_of_a_short_reduction(op, values, K):
         a, b = a.abs(), b.abs()
     out, want = product(op, a, b, M, N, K, "f32")
     assert float(((out.double() - want).abs() / want).max()) <= 2.0 ** -24 * (K + 2.0 ** -8)   # (what is left out is below 2^-33)
+
+
+@pytest.mark.parametrize("op", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(500, 2304, 1280), (1024, 1152, 1024), (1000, 1600, 1024), (1000, 768, 1276), (1000, 768, 1280), (1000, 3068, 1024), (1000, 3072, 1024)])
+def test_whole_pieces_on_either_side_of_the_limits(op, M, N, K):
+    out, want = product(op, *operands(op, "f32", M, N, K), M, N, K, "f32")
+    assert float((out.double() - want).norm() / want.norm()) <= 2e-7 + 5e-8 * K ** 0.5   # as in every remainder
