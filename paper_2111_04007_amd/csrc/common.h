@@ -129,28 +129,46 @@ struct EpiArgs {
   int64_t split_stride;  // EPI_STORE_F32: elements between the partial results of consecutive splits
 };
 
-// One output element.
+// What one output element reads: the bias of its column, and its own place.  (Read for several elements before the first of them is
+// stored: a store may alias the next element's read for all the compiler knows, and one by one they wait for memory in turn.)
 template <typename T, int MODE>
-__device__ __forceinline__ void epilogue_store(const EpiArgs<T>& e, int64_t m, int64_t n, float acc) {
+__device__ __forceinline__ float epilogue_bias(const EpiArgs<T>& e, int64_t n) {
+  return MODE == EPI_BIAS || MODE == EPI_BIAS_GELU || MODE == EPI_BIAS_RES ? to_f32(e.bias[n]) : 0.f;
+}
+template <typename T, int MODE>
+__device__ __forceinline__ float epilogue_fetch(const EpiArgs<T>& e, int64_t m, int64_t n) {
+  const int64_t idx = m * e.ldc + n;
+  if (MODE == EPI_BIAS_RES || MODE == EPI_DGELU) return to_f32(e.aux_in[idx]);
+  if (MODE == EPI_ACCUM_F32 || MODE == EPI_STORE_F32) return e.out_f32[idx];
+  return 0.f;
+}
+
+// One output element; bias and old: of epilogue_bias and epilogue_fetch.
+template <typename T, int MODE>
+__device__ __forceinline__ void epilogue_store(const EpiArgs<T>& e, int64_t m, int64_t n, float acc, float bias, float old) {
   const int64_t idx = m * e.ldc + n;
   if (MODE == EPI_BIAS) {
-    e.out[idx] = from_f32<T>(acc + to_f32(e.bias[n]));
+    e.out[idx] = from_f32<T>(acc + bias);
   } else if (MODE == EPI_BIAS_GELU) {
-    float u = acc + to_f32(e.bias[n]);
+    float u = acc + bias;
     if (e.aux_out) e.aux_out[idx] = from_f32<T>(u);
     e.out[idx] = from_f32<T>(gelu_tanh_f(u));
   } else if (MODE == EPI_BIAS_RES) {
-    float v = acc + to_f32(e.bias[n]);
+    float v = acc + bias;
     if (e.drop.thr != 0)
       v = drop_keep(e.drop, drop_row_word(e.drop, (uint32_t)m, (uint32_t)(n >> 2)), (int)(n & 3)) ? v * e.drop.scale : 0.f;
-    e.out[idx] = from_f32<T>(v + to_f32(e.aux_in[idx]));
+    e.out[idx] = from_f32<T>(v + old);
   } else if (MODE == EPI_DGELU) {
-    e.out[idx] = from_f32<T>(acc * gelu_tanh_grad_f(to_f32(e.aux_in[idx])));
+    e.out[idx] = from_f32<T>(acc * gelu_tanh_grad_f(old));
   } else if (MODE == EPI_PLAIN) {
     e.out[idx] = from_f32<T>(acc);
   } else {
-    e.out_f32[idx] += acc;
+    e.out_f32[idx] = old + acc;
   }
+}
+template <typename T, int MODE>
+__device__ __forceinline__ void epilogue_store(const EpiArgs<T>& e, int64_t m, int64_t n, float acc) {
+  epilogue_store<T, MODE>(e, m, n, acc, epilogue_bias<T, MODE>(e, n), epilogue_fetch<T, MODE>(e, m, n));
 }
 
 }  // namespace varuna

@@ -412,18 +412,43 @@ struct GcTile {
     }
 
     // acc[i][j][r] is row 8*(r/4) + 4*half + r%4, column l32 of its 32x32 block.
-    auto emit = [&](int i, int j, int r, float v) {
-      const int64_t m = m0 + OA::row(i, 8 * (r >> 2) + 4 * half + (r & 3)), n = n0 + OB::row(j, l32);
-      if (m < M && n < N) epilogue_store<T, MODE>(epi, m, n, v);
+    auto row_of = [&](int i, int r) { return m0 + OA::row(i, 8 * (r >> 2) + 4 * half + (r & 3)); };
+    auto fetch_old = [&](int i, int j, int r) {   // (past the end the last row or column)
+      const int64_t m = row_of(i, r), n = n0 + OB::row(j, l32);
+      return epilogue_fetch<T, MODE>(epi, m < M ? m : M - 1, n < N ? n : N - 1);
+    };
+    float bias[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int64_t n = n0 + OB::row(j, l32);
+      bias[j] = epilogue_bias<T, MODE>(epi, n < N ? n : N - 1);
+    }
+    auto emit = [&](int i, int j, int r, float v, float old) {
+      const int64_t m = row_of(i, r), n = n0 + OB::row(j, l32);
+      if (m < M && n < N) epilogue_store<T, MODE>(epi, m, n, v, bias[j], old);
     };
     if constexpr (KS == 1) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i) {
+        float old[16][TN];
 #pragma unroll
         for (int r = 0; r < 16; ++r)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) emit(i, j, r, acc[i][j][r]);
+          for (int j = 0; j < TN; ++j) old[r][j] = fetch_old(i, j, r);
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) emit(i, j, r, acc[i][j][r], old[r][j]);
+      }
     } else {
+      constexpr int RPW = 16 / KS;   // every wave finishes its share of the rows
+      float old[TM][RPW][TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int q = 0; q < RPW; ++q)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) old[i][q][j] = fetch_old(i, j, ks * RPW + q);
       __syncthreads();   // (the sums lie where the waves' stages were)
 #pragma unroll
       for (int i = 0; i < TM; ++i)
@@ -432,7 +457,6 @@ struct GcTile {
 #pragma unroll
           for (int r = 0; r < 16; ++r) red[((ks * TM * TN + i * TN + j) * 16 + r) * 64 + lane] = acc[i][j][r];
       __syncthreads();
-      constexpr int RPW = 16 / KS;   // every wave finishes its share of the rows
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -443,7 +467,7 @@ struct GcTile {
             float v = 0.f;
 #pragma unroll
             for (int w = 0; w < KS; ++w) v += red[((w * TM * TN + i * TN + j) * 16 + r) * 64 + lane];
-            emit(i, j, r, v);
+            emit(i, j, r, v, old[i][q][j]);
           }
     }
   }
