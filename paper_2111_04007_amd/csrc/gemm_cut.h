@@ -5,22 +5,21 @@
 //
 // An fp32 operand is cut into three bf16 pieces, x = x1 + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1), x3 = the rest: 24 bits of
 // mantissa in pieces of 8, nothing is left over.  Of the nine piece products six are summed in fp32 (x1y1, x1y2, x2y1, x2y2, x1y3, x3y1),
-// x1y1 in a sum of its own: a sum rounds relative to its size.  x2y3 + x3y2 reach 2^-24 of a product at worst, half a unit of an fp32
-// result (near 1.004 times 1.004; a tenth of that on average, of either sign), and x3y3 2^-34.  Where single products show, in
-// reductions of up to five steps of each wave and in the last steps of longer ones, those two are summed as well: K = 1 is then off by one
-// rounding, as an fp32 product is (6.0e-8 at most; with six 8.8e-8).  In the pipelined loop they would take 8 to 13 % of the time
-// ([1000,768] over 3072 43 -> 48 us, 2048^3 123 -> 140) and change no result beyond its rounding: operands within 1e-5 of that worst place
-// over K = 200 / 300 / 1024 / 3072 are 3.7e-8 / 2.9e-8 / 5.0e-8 / 3.9e-8 from 64 bits with six as with eight, in fp32 products
-// 2.1e-7 / 2.5e-7 / 2.8e-7 / 1.1e-7.  N(0,1) operands, fp32 products / this (K = 33, 301, 1024, 3072, 2048 on one wave): 8.2e-8 / 4.9e-8,
-// 1.3e-7 / 7.1e-8, 5.7e-7 / 9.8e-8, 3.6e-7 / 1.6e-7, 8.1e-7 / 2.7e-7.  A bf16 operand is its own only piece.
+// x1y1 in a sum of its own: a sum rounds relative to its size.  Left out are x2y3 + x3y2, at worst 2^-24 of a product, half a unit of an fp32
+// result (near 1.004 times 1.004; a tenth of that on average, of either sign), and x3y3, 2^-34.  A single product shows that (8.8e-8 off
+// where an fp32 product is 6.0e-8), a sum of 128 and more, the shortest that comes here, does not: operands within 1e-5 of that worst
+// place over K = 200 / 300 / 1024 / 3072 are 3.7e-8 / 2.9e-8 / 5.0e-8 / 3.9e-8 from 64 bits with these six as with eight of the products, in
+// fp32 products 2.1e-7 / 2.5e-7 / 2.8e-7 / 1.1e-7; eight take 8 to 13 % longer ([1000,768] over 3072 43 -> 48 us, 2048^3 123 -> 140).
+// N(0,1) operands, fp32 products / this (K = 301, 1024, 3072, 2048 on one wave): 1.3e-7 / 7.1e-8, 5.7e-7 / 9.8e-8, 3.6e-7 / 1.6e-7,
+// 8.1e-7 / 2.7e-7.  A bf16 operand is its own only piece.
 //
 // What bounds it: fp32, the vector instructions that cut (seven and a half per element and wave) beside products at the rate real data
 // sustains; bf16, the path from L2 (16 KB per 64x64x64 block).  Every wave works alone, on its own steps of the reduction: no
 // barrier until the sums meet, and the cutting of one step issues between the products of the step before.  Reading the
 // operands straight into registers instead (32 rows of 32 bytes per instruction) took 1.2 to 3 times as long: one cache line per
 // clock; sharing cut tiles through LDS between waves was equal at 2048^3 and slower below.  Measured (us, fp32 products / this):
-// bf16 [4001,3001] over 3001 1527 / 275, 1001^3 72 / 15, 301^3 9.3 / 4.6; fp32 [1000,768] over 3072 57 / 44, 2048^3 154 / 120,
-// 1024^3 27 / 22, [512,512] over 2048 17.5 / 14.4.
+// bf16 [4001,3001] over 3001 1515 / 246, 1001^3 65 / 12, 301^3 8.9 / 4.3; fp32 [1000,768] over 3072 57 / 44, 2048^3 154 / 120,
+// 1024^3 27 / 21, [512,512] over 2048 17.3 / 14.2.
 #pragma once
 #include <type_traits>
 
@@ -291,15 +290,14 @@ struct GcTile {
         for (int j = 0; j < TN; ++j) fb[S][c][j] = gc_cut(gb.v[j], lost);
       }
     };
-    auto products = [&](auto set, auto fast) {
+    auto products = [&](auto set) {
       constexpr int S = decltype(set)::v;
-      constexpr int LAST = NP > 1 && !decltype(fast)::v ? NP : NP - 1;
 #pragma unroll
       for (int c = 0; c < GROUPS; ++c)
 #pragma unroll
-        for (int s = LAST; s >= 0; --s)   // pieces p + q = s
+        for (int s = NP - 1; s >= 0; --s)   // pieces p + q = s
 #pragma unroll
-          for (int p = s < NP ? 0 : s - NP + 1; p <= s && p < NP; ++p)
+          for (int p = 0; p <= s; ++p)
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -332,7 +330,7 @@ struct GcTile {
             }
       }
       if (decltype(fast)::v || t + 1 < mine) cut(GcInt<1 - S>{});
-      products(set, fast);
+      products(set);
       if constexpr (NP > 1 && decltype(fast)::v) {
         __builtin_amdgcn_sched_group_barrier(0x100, 64, 0);
 #pragma unroll
@@ -510,9 +508,13 @@ __global__ __launch_bounds__(KS * kWave) void gemm_cut_group_kernel(GfGroup<T> g
 //   bf16: as many waves as keep the chip's 1024 SIMDs busy.  Measured (us, 32x32 on 8 waves / 32x32 on 4 / 64x64 on 4 / 64x64 on 1):
 //   301^3 4.6 / 5.3 / 9.2 / 16, [2001,131] over 601 7.5 / 7.5 / 10 / 18, [701,701] over 6001 50 / 46 / 47 / 59, 1001^3 18 / 17 / 15 / 22,
 //   [4001,3001] over 3001 562 / 643 / 318 / 275.
-//   fp32 rows that are not whole 16-byte pieces, by the same rule (fp32 products loaded such operands element by element; us, those / now,
-//   forward, dgrad, wgrad): 301x303 over 301 8.7 / 5.3, 8.1 / 6.0, 8.7 / 6.9, 513x515 over 301 13.5 / 7.6, 11.7 / 8.4, 11.9 / 9.1,
-//   1001x1003 over 201 14.9 / 12.1, 13.3 / 12.3, 17.4 / 15.8 and over 1003 46 / 26, 45 / 24, 51 / 28, 2001x1901 over 301 57 / 34, 50 / 28, 55 / 42.
+//   A reduction of one or two steps leaves waves that share it idle: beyond one round such tiles go to one wave (64x64 on 4 / on 1, forward,
+//   dgrad, wgrad: 1550x1273 over 33 6.9 / 7.2, 12 / 7.6, 16 / 11).  (In that range a weight gradient on fewer tiles, over fewer than 64 tokens, was
+//   0.2 to 1.4 us shorter in fp32 products: 301x303 over 33 5.0 / 5.3, 701x1001 over 49 7.6 / 8.8.)
+//   fp32 rows that are not whole 16-byte pieces, by the same rule from K = 128 on (fp32 products load such operands element by element; us,
+//   those / this, forward, dgrad, wgrad): 301x303 over 301 8.4 / 5.2, 7.8 / 5.6, 8.3 / 6.3, 513x515 over 301 13.0 / 7.5, 11.2 / 7.7, 11.1 / 8.2,
+//   1001x1003 over 201 13.8 / 11.3, 12.4 / 11.4, 16.9 / 12.5 and over 1003 39 / 24, 39 / 22, 47 / 23, 3001x3003 over 129 63 / 52, 56 / 46, 63 / 56;
+//   but 3001x3003 over 33 28 / 45, 25 / 30, 36 / 68, 1729x355 over 65 7.4 / 8.6, 6.8 / 8.3, 7.6 / 11.7, 301x303 over 97 4.6 / 4.5, 4.6 / 4.9, 5.0 / 5.7.
 //   fp32 in whole pieces (32x32 on 8 waves / 64x64 on 4 / 64x64 on 1 / fp32 products) from K = 1024 on: one round of 32x32 tiles, [512,512] over
 //   2048 16 / 32 / 89 / 19 and 300x300 over 1200 11 / 22 / 58 / 12.5; from two thirds of a round of 64x64 tiles, 1024^3 38 / 24 / 54 / 30,
 //   1500^3 137 / 87 / 90 / 98, 2048^3 235 / 167 / 147 / 184.  64x64 on 4 waves come in whole rounds of 256, so they pay where the fp32
@@ -523,14 +525,14 @@ __global__ __launch_bounds__(KS * kWave) void gemm_cut_group_kernel(GfGroup<T> g
 //   [1000,768] over 768 26 / 20 / 43 / 20, transposed operands 29 / 24 / 54 / 20, 256x256 over 512 6.2 / 13 / 31 / 6.6, transposed
 //   7.0 / 15 / 34 / 6.8, 128x512 over 128 4.2 / 8.2 / 17 / 3.8.
 enum GcKind : int { GC_NONE = 0, GC_32_8 = 1, GC_32_4 = 2, GC_64_4 = 3, GC_64_1 = 4 };
-inline GcKind gc_kind(bool f32_pieces, int64_t tiles32, int64_t tiles64, int64_t K) {
-  if (f32_pieces && K < 1024) return GC_NONE;
+inline GcKind gc_kind(bool fp32, bool pieces, int64_t tiles32, int64_t tiles64, int64_t K) {
+  if (fp32 && K < (pieces ? 1024 : 128)) return GC_NONE;
   if (tiles32 <= 256) return GC_32_8;
-  if (!f32_pieces) return tiles32 <= 512 ? GC_32_4 : tiles64 <= 768 ? GC_64_4 : GC_64_1;
+  if (!fp32 || !pieces) return tiles32 <= 512 ? GC_32_4 : tiles64 <= (K <= 64 ? 256 : 768) ? GC_64_4 : GC_64_1;
   if (tiles64 >= 768) return GC_64_1;
   const double r32 = (double)((tiles32 + 255) / 256), r64 = (double)((tiles64 + 255) / 256);
-  const double fp32 = gf_small_tile(tiles32, tiles64) ? 1.2 * r32 : 4.0 * r64;
-  return tiles64 >= 170 && fp32 >= (K < 1280 ? 4.0 : 3.5) * r64 ? GC_64_4 : GC_NONE;
+  const double area = gf_small_tile(tiles32, tiles64) ? 1.2 * r32 : 4.0 * r64;
+  return tiles64 >= 170 && area >= (K < 1280 ? 4.0 : 3.5) * r64 ? GC_64_4 : GC_NONE;
 }
 
 }  // namespace varuna

@@ -1,8 +1,8 @@
 // GEMM with fp32 products and fp32 accumulation on the matrix cores (v_mfma_f32_32x32x2_f32):
 //   acc[m,n] = sum_k A(m,k) * B(n,k)
 //   AK: A(m,k) = a[m*lda + k]   else A(m,k) = a[k*lda + m];   BK likewise for B(n,k) = b[n*ldb + k] / b[k*ldb + n]
-// It serves the fp32 path (the 1e-5 tolerance rules out reduced-precision products) where products of bf16 pieces (gemm_cut.h) are
-// no faster: short reductions over whole 16-byte pieces.  Any M, N, K of that kind; every global access is bounds-checked.
+// It serves the fp32 path where products of bf16 pieces (gemm_cut.h) are no faster: short reductions, below K = 1024 over whole 16-byte
+// pieces and below 128 over others (gc_kind).  Any M, N, K; every global access is bounds-checked.
 //
 // What bounds it: the fp32 matrix rate, 256 FLOP per clock and CU (157 TFLOP/s nominal, the rate a large library
 // product reaches here); a product of a 32x32 block takes 64 clocks for two LDS words per lane, so neither LDS
@@ -10,8 +10,7 @@
 // filling 1024 SIMDs: KS waves of a workgroup share an output tile and take every stage's k-range in KS parts,
 // summed through LDS in a fixed order at the end, so a 32x32 tile still occupies all four SIMDs of its CU, and
 // stages are long (64 or 128 k), which leaves a load's latency the products of the resident workgroups.  Measured
-// against the vector-ALU kernel before it (us): [1000,768] over 3072 377 -> 62 (75 TFLOP/s), [128,128] over 512
-// 60 -> 5, and 2048^3 at 111 TFLOP/s.
+// against the vector-ALU kernel before it (us): [128,128] over 512 60 -> 5; [1000,768] over 768 takes 20, and 2048^3 ran at 111 TFLOP/s.
 #pragma once
 #include "common.h"
 #include "gemm_epilogue.h"
@@ -28,15 +27,14 @@ struct GfTile {
 };
 
 // Staging of one operand tile: global -> registers -> LDS, four consecutive elements of the contiguous direction
-// at a time, which needs an aligned base, a leading dimension and a contiguous extent that are multiples of 4 (others go to
-// gemm_cut.h).  Outside the matrix: zeros.
-template <typename T, int ROWS, int BKT, bool KMAJOR, int NT>
+// at a time.  VEC: one 16-byte load per piece, which needs an aligned base, a leading dimension and a contiguous extent that are
+// multiples of 4; otherwise element by element.  Outside the matrix: zeros.
+template <int ROWS, int BKT, bool KMAJOR, bool VEC, int NT>
 struct GfLoader {
   static constexpr int PIECES = ROWS * BKT / 4, PPT = PIECES / NT;
   static_assert(PIECES % NT == 0, "tile / threads mismatch");
-  typedef T Tx4 __attribute__((ext_vector_type(4)));
   floatx4 v[PPT];
-  __device__ __forceinline__ void load(const T* __restrict__ g, int64_t ld, int64_t row0, int64_t rows, int64_t k0, int64_t K, int tid) {
+  __device__ __forceinline__ void load(const float* __restrict__ g, int64_t ld, int64_t row0, int64_t rows, int64_t k0, int64_t K, int tid) {
 #pragma unroll
     for (int i = 0; i < PPT; ++i) {
       const int id = tid + i * NT;
@@ -45,12 +43,14 @@ struct GfLoader {
       const int64_t row = row0 + (KMAJOR ? line : c), k = k0 + (KMAJOR ? c : line);
       const bool line_ok = KMAJOR ? row < rows : k < K;
       const int64_t left = KMAJOR ? K - k : rows - row;   // elements of the contiguous direction from here on
-      const T* p = g + (KMAJOR ? row * ld + k : k * ld + row);
+      const float* p = g + (KMAJOR ? row * ld + k : k * ld + row);
       floatx4 x = {0.f, 0.f, 0.f, 0.f};
-      if (line_ok && left > 0) {
-        const Tx4 t = *reinterpret_cast<const Tx4*>(p);
+      if constexpr (VEC) {
+        if (line_ok && left > 0) x = *reinterpret_cast<const floatx4*>(p);
+      } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = to_f32((T)t[e]);
+        for (int e = 0; e < 4; ++e)
+          if (line_ok && left > e) x[e] = p[e];
       }
       v[i] = x;
     }
@@ -76,10 +76,10 @@ __device__ __forceinline__ floatx4 gf_frag(const float* lds, int row, int kg, in
 }
 
 // One workgroup: a BM x BN tile on (BM / WM) * (BN / WN) * KS waves, one stage of BKT k in LDS, the next in registers.
-template <typename T, int MODE, bool AK, bool BK, int BM, int BN, int WM, int WN, int KS, int BKT>
+template <int MODE, bool AK, bool BK, int BM, int BN, int WM, int WN, int KS, int BKT, bool VEC>
 __device__ __forceinline__ void gf_tile(
-    const T* __restrict__ a, int64_t lda, const T* __restrict__ b, int64_t ldb, int64_t M, int64_t N, int64_t K,
-    int tiles_m, int tiles_n, const EpiArgs<T>& epi, int logical) {
+    const float* __restrict__ a, int64_t lda, const float* __restrict__ b, int64_t ldb, int64_t M, int64_t N, int64_t K,
+    int tiles_m, int tiles_n, const EpiArgs<float>& epi, int logical) {
   constexpr int NW = (BM / WM) * (BN / WN) * KS, NT = NW * kWave;
   constexpr int TM = WM / 32, TN = WN / 32;
   constexpr int AE = GfTile<BM, BKT, AK>::ELEMS, BE = GfTile<BN, BKT, BK>::ELEMS;
@@ -103,8 +103,8 @@ __device__ __forceinline__ void gf_tile(
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  GfLoader<T, BM, BKT, AK, NT> la;
-  GfLoader<T, BN, BKT, BK, NT> lb;
+  GfLoader<BM, BKT, AK, VEC, NT> la;
+  GfLoader<BN, BKT, BK, VEC, NT> lb;
   const int64_t nst = (K + BKT - 1) / BKT;
   la.load(a, lda, m0, M, 0, K, tid);
   lb.load(b, ldb, n0, N, 0, K, tid);
@@ -146,7 +146,7 @@ __device__ __forceinline__ void gf_tile(
   const int64_t mb = m0 + wm * WM, nb = n0 + wn * WN;
   auto put = [&](int i, int j, int r, float v) {
     const int64_t m = mb + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3), n = nb + j * 32 + l32;
-    if (m < M && n < N) epilogue_store<T, MODE>(epi, m, n, v);
+    if (m < M && n < N) epilogue_store<float, MODE>(epi, m, n, v);
   };
   if constexpr (KS == 1) {
 #pragma unroll
@@ -182,10 +182,10 @@ __device__ __forceinline__ void gf_tile(
 
 // Workgroup -> tile: consecutive workgroups go round the 8 XCDs; every XCD gets a contiguous range of tiles, walked in
 // groups of 8 tile rows (the panels it touches stay in its L2).
-template <typename T, int MODE, bool AK, bool BK, int BM, int BN, int WM, int WN, int KS, int BKT>
+template <int MODE, bool AK, bool BK, int BM, int BN, int WM, int WN, int KS, int BKT, bool VEC>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * KS * kWave) void gemm_f32_kernel(
-    const T* __restrict__ a, int64_t lda, const T* __restrict__ b, int64_t ldb, int64_t M, int64_t N, int64_t K,
-    int tiles_m, int tiles_n, EpiArgs<T> epi) {
+    const float* __restrict__ a, int64_t lda, const float* __restrict__ b, int64_t ldb, int64_t M, int64_t N, int64_t K,
+    int tiles_m, int tiles_n, EpiArgs<float> epi) {
   int logical = blockIdx.x;
   const int nblk = gridDim.x;
   if ((nblk & 7) == 0) logical = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
@@ -194,7 +194,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * KS * kWave) void gemm_f32_k
     if (t >= (int64_t)tiles_m * tiles_n) return;
     logical = (int)t;
   }
-  gf_tile<T, MODE, AK, BK, BM, BN, WM, WN, KS, BKT>(a, lda, b, ldb, M, N, K, tiles_m, tiles_n, epi, logical);
+  gf_tile<MODE, AK, BK, BM, BN, WM, WN, KS, BKT, VEC>(a, lda, b, ldb, M, N, K, tiles_m, tiles_n, epi, logical);
 }
 
 // Several weight gradients out[M,N] += a[K,M]^T b[K,N] over the same K in one launch: the products of a small stage are a few
@@ -207,17 +207,17 @@ struct GfGroup {
   int first[kMaxGroupJobs + 1];
   WgradJob<T> job[kMaxGroupJobs];
 };
-template <typename T, int BM, int BN, int WM, int WN, int KS, int BKT>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * KS * kWave) void gemm_f32_group_kernel(GfGroup<T> g) {
+template <int BM, int BN, int WM, int WN, int KS, int BKT, bool VEC>
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * KS * kWave) void gemm_f32_group_kernel(GfGroup<float> g) {
   int j = 0;
   while (j + 1 < g.n && (int)blockIdx.x >= g.first[j + 1]) ++j;
-  const WgradJob<T>& w = g.job[j];
+  const WgradJob<float>& w = g.job[j];
   const int local = (int)blockIdx.x - g.first[j], nblk = g.first[j + 1] - g.first[j];
   const int logical = (local & 7) * (nblk >> 3) + (local >> 3);
   const int tiles_m = (w.M + BM - 1) / BM, tiles_n = (w.N + BN - 1) / BN;
   if (logical >= tiles_m * tiles_n) return;
-  const EpiArgs<T> epi{nullptr, nullptr, nullptr, nullptr, w.out, w.N, DropArgs{}, 0};
-  gf_tile<T, EPI_ACCUM_F32, false, false, BM, BN, WM, WN, KS, BKT>(w.a, w.M, w.b, w.N, w.M, w.N, g.K, tiles_m, tiles_n, epi, logical);
+  const EpiArgs<float> epi{nullptr, nullptr, nullptr, nullptr, w.out, w.N, DropArgs{}, 0};
+  gf_tile<EPI_ACCUM_F32, false, false, BM, BN, WM, WN, KS, BKT, VEC>(w.a, w.M, w.b, w.N, w.M, w.N, g.K, tiles_m, tiles_n, epi, logical);
 }
 
 // Output tile of a product: 64x64 (4 waves of 32x32) or 32x32 (8 waves, each an eighth of every stage's k-range).

@@ -12,9 +12,10 @@ hipError_t launch_gemm_f32_group(const WgradJob<float>* jobs, int n, int64_t K, 
     t64 += gf_tiles(jobs[i].M, jobs[i].N, 64);
     vec = vec && ((reinterpret_cast<uintptr_t>(jobs[i].a) | reinterpret_cast<uintptr_t>(jobs[i].b)) & 15) == 0 && jobs[i].M % 4 == 0 && jobs[i].N % 4 == 0;
   }
-  if (!vec) return t32 <= 512 ? gc_launch_group<float, 1, 1, 4>(jobs, n, K, st) : gc_launch_group<float, 2, 2, 4>(jobs, n, K, st);
-  if (gf_small_tile(t32, t64)) return gf_launch_group<float, 32, 32, 32, 32, 8, 128>(jobs, n, K, st);
-  return gf_launch_group<float, 64, 64, 32, 32, 1, 64>(jobs, n, K, st);
+  if (!vec && K >= 128) return t32 <= 512 ? gc_launch_group<float, 1, 1, 4>(jobs, n, K, st) : gc_launch_group<float, 2, 2, 4>(jobs, n, K, st);
+  if (gf_small_tile(t32, t64))
+    return vec ? gf_launch_group<32, 32, 32, 32, 8, 128, true>(jobs, n, K, st) : gf_launch_group<32, 32, 32, 32, 8, 128, false>(jobs, n, K, st);
+  return vec ? gf_launch_group<64, 64, 32, 32, 1, 64, true>(jobs, n, K, st) : gf_launch_group<64, 64, 32, 32, 1, 64, false>(jobs, n, K, st);
 }
 
 }  // namespace varuna

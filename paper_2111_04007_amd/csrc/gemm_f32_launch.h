@@ -7,16 +7,17 @@
 
 namespace varuna {
 
-template <typename T, int MODE, bool AK, bool BK, int BM, int BN, int WM, int WN, int KS, int BKT>
-inline hipError_t gf_launch_tile(const T* a, int64_t lda, const T* b, int64_t ldb, int64_t M, int64_t N, int64_t K,
-                                 const EpiArgs<T>& epi, hipStream_t st) {
+template <int MODE, bool AK, bool BK, int BM, int BN, int WM, int WN, int KS, int BKT>
+inline hipError_t gf_launch_tile(bool vec, const float* a, int64_t lda, const float* b, int64_t ldb, int64_t M, int64_t N, int64_t K,
+                                 const EpiArgs<float>& epi, hipStream_t st) {
   const int64_t tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
   if (tm > (1 << 27) || tn > (1 << 27) || tm * tn >= (1ll << 31)) return hipErrorInvalidValue;
   // a grid dimension holds less than 2^32 threads: 2^22 blocks of up to 512, then a second one (blocks past the last tile end)
   constexpr int64_t line = 1 << 22;
   const int64_t tiles = tm * tn;
   const dim3 grid((unsigned)(tiles < line ? tiles : line), (unsigned)((tiles + line - 1) / line)), block((BM / WM) * (BN / WN) * KS * kWave);
-  hipLaunchKernelGGL((gemm_f32_kernel<T, MODE, AK, BK, BM, BN, WM, WN, KS, BKT>), grid, block, 0, st, a, lda, b, ldb, M, N, K, (int)tm, (int)tn, epi);
+  if (vec) hipLaunchKernelGGL((gemm_f32_kernel<MODE, AK, BK, BM, BN, WM, WN, KS, BKT, true>), grid, block, 0, st, a, lda, b, ldb, M, N, K, (int)tm, (int)tn, epi);
+  else hipLaunchKernelGGL((gemm_f32_kernel<MODE, AK, BK, BM, BN, WM, WN, KS, BKT, false>), grid, block, 0, st, a, lda, b, ldb, M, N, K, (int)tm, (int)tn, epi);
   return hipGetLastError();
 }
 
@@ -39,8 +40,8 @@ inline hipError_t gf_launch(const T* a, int64_t lda, const T* b, int64_t ldb, in
                             const EpiArgs<T>& epi, hipStream_t st) {
   const int64_t t32 = gf_tiles(M, N, 32), t64 = gf_tiles(M, N, 64);
   // whole pieces of four along the contiguous direction of both operands, from an aligned base
-  const bool vec = sizeof(T) == 4 && ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 15) == 0 && lda % 4 == 0 && ldb % 4 == 0;
-  switch (gc_kind(vec, t32, t64, K)) {
+  const bool vec = ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 15) == 0 && lda % 4 == 0 && ldb % 4 == 0;
+  switch (gc_kind(sizeof(T) == 4, vec, t32, t64, K)) {
     case GC_32_8: return gc_launch<T, MODE, AK, BK, 1, 1, 8>(a, lda, b, ldb, M, N, K, epi, st);
     case GC_32_4: return gc_launch<T, MODE, AK, BK, 1, 1, 4>(a, lda, b, ldb, M, N, K, epi, st);
     case GC_64_4: return gc_launch<T, MODE, AK, BK, 2, 2, 4>(a, lda, b, ldb, M, N, K, epi, st);
@@ -48,8 +49,8 @@ inline hipError_t gf_launch(const T* a, int64_t lda, const T* b, int64_t ldb, in
     case GC_NONE: break;
   }
   if constexpr (sizeof(T) == 4) {
-    if (gf_small_tile(t32, t64)) return gf_launch_tile<T, MODE, AK, BK, 32, 32, 32, 32, 8, 128>(a, lda, b, ldb, M, N, K, epi, st);
-    return gf_launch_tile<T, MODE, AK, BK, 64, 64, 32, 32, 1, 64>(a, lda, b, ldb, M, N, K, epi, st);
+    if (gf_small_tile(t32, t64)) return gf_launch_tile<MODE, AK, BK, 32, 32, 32, 32, 8, 128>(vec, a, lda, b, ldb, M, N, K, epi, st);
+    return gf_launch_tile<MODE, AK, BK, 64, 64, 32, 32, 1, 64>(vec, a, lda, b, ldb, M, N, K, epi, st);
   }
   return hipErrorInvalidValue;
 }
@@ -89,10 +90,10 @@ inline hipError_t gf_for_groups(const WgradJob<T>* jobs, int n, int64_t K, F&& f
   }
   return hipGetLastError();
 }
-template <typename T, int BM, int BN, int WM, int WN, int KS, int BKT>
-inline hipError_t gf_launch_group(const WgradJob<T>* jobs, int n, int64_t K, hipStream_t st) {
-  return gf_for_groups<T, BM, BN>(jobs, n, K, [&](const GfGroup<T>& g, unsigned blocks) {
-    hipLaunchKernelGGL((gemm_f32_group_kernel<T, BM, BN, WM, WN, KS, BKT>), dim3(blocks), dim3((BM / WM) * (BN / WN) * KS * kWave), 0, st, g);
+template <int BM, int BN, int WM, int WN, int KS, int BKT, bool VEC>
+inline hipError_t gf_launch_group(const WgradJob<float>* jobs, int n, int64_t K, hipStream_t st) {
+  return gf_for_groups<float, BM, BN>(jobs, n, K, [&](const GfGroup<float>& g, unsigned blocks) {
+    hipLaunchKernelGGL((gemm_f32_group_kernel<BM, BN, WM, WN, KS, BKT, VEC>), dim3(blocks), dim3((BM / WM) * (BN / WN) * KS * kWave), 0, st, g);
   });
 }
 template <typename T, int TM, int TN, int KS>
