@@ -79,6 +79,11 @@ def test_values_at_the_end_of_the_range(op, M, N, K, value):
     rest = torch.arange(M, device="cuda") != M // 3
     d = (out[rest].double() - want[rest].double()).norm() / want[rest].double().norm()
     assert float(d) <= 2e-7 + 5e-8 * K ** 0.5
+    # the row itself, element by element: an fp32 sum of K terms is off by at most K half units of the sum of their sizes
+    ad, bd = (a.double().t() if op == 2 else a.double()), (b.double().t() if op == 0 else b.double())
+    size = ad[M // 3].abs() @ bd.abs()
+    off = (out[M // 3].double() - want[M // 3].double()).abs()
+    assert bool((off <= K * 2.0 ** -24 * size)[fin[M // 3]].all())
 
 
 @pytest.mark.parametrize("op", [0, 1, 2])

@@ -168,7 +168,7 @@ def test_gemm_kernel_choice_for_the_named_stage_shapes():
     assert B.debug_gemm_choice(FWD, T, h, h) == 19                 # 256 tiles: one workgroup per CU
     assert B.debug_gemm_choice(FWD, T, 3 * h, h) == 17             # 192 256x256 tiles: one round
     assert B.debug_gemm_choice(DGRAD, T, h, 3 * h) == 19
-    assert B.debug_gemm_choice(FWD, 100, 128, 64) == -1            # one ragged tile: the fp32-product kernel
+    assert B.debug_gemm_choice(FWD, 100, 128, 64) == -1            # one ragged tile: the small tiles
     assert B.debug_gemm_choice(7, 128, 128, 64) == -2
 
 
@@ -187,8 +187,8 @@ def test_named_weight_gradient_kernels_turn_the_grouped_launch_off():
 
 
 def test_gemm_kernel_choice_for_ragged_shapes():
-    """Sizes that are no multiples of the tiles: 128x128 (22) or 256x256 (23) ragged tiles, the fp32-product kernel where rows are not
-    whole 16-byte pieces."""
+    """Sizes that are no multiples of the tiles: 128x128 (22) or 256x256 (23) ragged tiles, small tiles on any addresses where rows are
+    not whole 16-byte pieces."""
     FWD, DGRAD, WGRAD = 0, 1, 2
     T, h, f = 2000, 1600, 6400
     assert B.debug_gemm_choice(FWD, T, h, h) == 22 and B.debug_gemm_choice(DGRAD, T, h, f) == 22 and B.debug_gemm_choice(WGRAD, h, h, T) == 22

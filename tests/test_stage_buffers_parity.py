@@ -1,5 +1,6 @@
 """Where a call's tensors lie: the boundary slot itself, addresses that are not whole 16-byte pieces, one buffer for the upstream and the
-input gradient.  Every placement gives the bits of separate, aligned buffers."""
+input gradient, or two that overlap in part.  Every placement gives the bits of separate, aligned buffers, in the calls that recompute and
+in those that keep, with and without a second stream."""
 import pytest
 import torch
 
@@ -9,7 +10,7 @@ from paper_2111_04007_amd.synth import StageConfig
 pytestmark = pytest.mark.gpu
 
 
-def step(c, place, dropout):
+def step(c, place, dropout, keep=False):
     dt = torch.float32 if c.dtype == "f32" else torch.bfloat16
     T, h = c.micro_batch * c.seq_len, c.hidden
     g = torch.Generator(device="cuda").manual_seed(3)
@@ -31,23 +32,40 @@ def step(c, place, dropout):
 
     for m, (x, dy) in enumerate(data):
         x, dy, y = at(x), at(dy), torch.empty(T, h, dtype=dt, device="cuda")
-        st.forward(m, x, y)
-        x.fill_(float("nan"))   # the slot holds it now
-        dx = dy if place == "same" else torch.empty_like(y)
-        st.backward_recompute(m, dy, dx)
-        if place != "same":
-            dy.fill_(float("nan"))   # in order on the stream: the call has read it
+        if place == "slot":
+            x = st.boundary_slot(m).copy_(x)
+        (st.forward_keep if keep else st.forward)(m, x, y)
+        if place != "slot":
+            x.fill_(float("nan"))   # the slot holds it now
+        dx = torch.empty_like(y)
+        if place == "same":
+            dx = dy
+        elif place == "overlap":   # dx starts a token (whole 16-byte pieces in every case) after dy, or before it
+            both = torch.empty((T + 1) * h, dtype=dt, device="cuda")
+            dy = both[m * h:m * h + T * h].view(T, h).copy_(dy)
+            dx = both[(1 - m) * h:(1 - m) * h + T * h].view(T, h)
+        (st.backward_stored if keep else st.backward_recompute)(m, dy, dx)
         ys.append(y)
         dxs.append(dx.clone())
+        if place not in ("same", "overlap"):
+            dy.fill_(float("nan"))   # in order on the stream: the call has read it
     st.grad_flush()
     return torch.stack(ys), torch.stack(dxs), st.grads.clone()
 
 
-@pytest.mark.parametrize("place", ["misaligned", "same", "side"])
+@pytest.mark.parametrize("place", ["misaligned", "same", "side", "slot", "overlap"])
 @pytest.mark.parametrize("dtype,h,heads,s,group,dropout", [("f32", 128, 2, 64, 1, 0.0), ("f32", 60, 3, 33, 1, 0.0), ("bf16", 256, 4, 128, 1, 0.0),
                                                            ("bf16", 256, 4, 128, 2, 0.0), ("bf16", 256, 4, 128, 1, 0.1), ("bf16", 200, 5, 70, 1, 0.0)])
 @pytest.mark.parametrize("layers", [1, 2])
 def test_placement(place, dtype, h, heads, s, group, dropout, layers):
     c = StageConfig("case", layers, h, heads, s, 2, 2, 4 * h, True, dtype, wgrad_group=group, dropout_p=dropout)
     for a, b in zip(step(c, "apart", dropout), step(c, place, dropout)):
+        assert bool(torch.isfinite(a.float()).all()) and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("place", ["misaligned", "same", "side", "slot", "overlap"])
+@pytest.mark.parametrize("dtype,h,heads,s,group,dropout", [("f32", 60, 3, 33, 1, 0.0), ("bf16", 256, 4, 128, 1, 0.1), ("bf16", 256, 4, 128, 2, 0.0), ("bf16", 200, 5, 70, 1, 0.0)])
+def test_placement_of_kept_forwards(place, dtype, h, heads, s, group, dropout):
+    c = StageConfig("case", 2, h, heads, s, 2, 2, 4 * h, True, dtype, wgrad_group=group, dropout_p=dropout)
+    for a, b in zip(step(c, "apart", dropout), step(c, place, dropout, keep=True)):
         assert bool(torch.isfinite(a.float()).all()) and torch.equal(a, b)
