@@ -113,7 +113,8 @@ varuna_status_t varuna_stage_create(const varuna_stage_config_t* cfg, const void
 
 /* Stage forward for micro-batch slot mb (0 <= mb < M): copies x_in [T,h] into
  * boundary slot mb (skipped when x_in is that slot), runs the L layers, writes
- * the stage output y_out [T,h].  Nothing else is kept. */
+ * the stage output y_out [T,h].  Nothing else is kept.  x_in is read by kernels, as every tensor of these calls is: it has to lie
+ * in memory that the GPU of hip_stream can read. */
 varuna_status_t varuna_stage_forward(varuna_stage_t* st, int32_t mb, const void* x_in /*device*/,
                                      void* y_out /*device*/, void* hip_stream);
 
@@ -123,7 +124,9 @@ varuna_status_t varuna_stage_forward(varuna_stage_t* st, int32_t mb, const void*
  * this micro-batch's parameter gradients into grads_f32 (the four matrix gradients
  * per layer possibly deferred, see varuna_stage_grad_flush).  Requires a forward of
  * slot mb since that slot was last consumed (else VARUNA_ESTATE).  Calls for
- * different slots may be interleaved with forwards in any order. */
+ * different slots may be interleaved with forwards in any order.  dy_in is read where it lies by kernels up to the last of the
+ * call, also by those on the side stream (which hip_stream waits for), so it may be overwritten by work that follows on
+ * hip_stream but not by another stream before that; dx_out may be dy_in or overlap it. */
 varuna_status_t varuna_stage_backward_recompute(varuna_stage_t* st, int32_t mb,
                                                 const void* dy_in /*device*/,
                                                 void* dx_out /*device*/, void* hip_stream);

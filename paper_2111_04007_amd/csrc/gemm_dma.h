@@ -855,6 +855,10 @@ inline int dg_flavour(int tile_variant, int op) {
 // the reduction.  Measured back to back, this kernel / those (us, forward, dgrad, wgrad): 512x512 over 512 6.8 / 4.3, 6.3 / 5.2, 7.9 / 6.6,
 // over 1024 8.9 / 5.0, 8.8 / 6.3, 10.6 / 8.2, over 4096 36 / 17 (wgrad); 512x1024 over 512 7.0 / 5.5, 6.4 / 6.5, 8.1 / 8.3, over 1024 9.4 / 7.4, 9.6 / 8.7, 13.6 / 12.1;
 // 1024^2 over 1024 12.3 / 11.3, 12.2 / 11.1, 14.0 / 18.3 and over 4096 1.4, 1.6 and 1.2 times as fast; at 96 tiles always slower.
+// The lines are those of operands in cache and keep off where the two are close there (1024^2 over 1024 on a later measurement 8.9 / 10.1,
+// 8.8 / 9.4, 11.0 / 14.9).  With operands out of cache the small tiles are ahead further up in forward and dgrad: 1024^2 over 1024
+// 15.9 / 12.1, 15.5 / 11.2 (wgrad 17.9 / 19.0), 1024^2 over 512 10.4 / 9.3, 9.7 / 8.8 (12.3 / 15.5), 512x1024 over 1024 as wgrad 17.5 / 13.4.
+// A reduction of 8 or 16 is up to 1.2 us longer on them in dgrad and wgrad (128x128 over 16 3.8 / 4.4, 3.6 / 4.9).
 inline bool dg_cut_sooner(int op, int64_t M, int64_t N, int64_t K) {
   const int64_t t7 = ((M + 127) / 128) * ((N + 127) / 128);
   if (t7 <= 18) return true;

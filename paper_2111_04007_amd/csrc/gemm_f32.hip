@@ -4,6 +4,9 @@ namespace varuna {
 
 template hipError_t launch_gemm_f32<float>(int, int, const float*, const float*, int64_t, int64_t, int64_t, const EpiArgs<float>&, hipStream_t);
 
+// Odd rows: from 128 tokens on as launch_gemm_cut_group, below in fp32 products (gc_kind).  Micro-batches of whole steps (us, 32x32 on 4
+// waves / 64x64 on 4 / 64x64 on 1 / fp32 products): 66 wide over 2048 tokens 279 / 293 / 352 / 299, 258 wide (783 tiles) over 512 401 / 413 / 414 / 453, 390 wide
+// (2041) over 8192 2180 / 2169 / 2220 / 3401, 774 wide (7250) over 512 895 / 892 / 849 / 1131.
 hipError_t launch_gemm_f32_group(const WgradJob<float>* jobs, int n, int64_t K, hipStream_t st) {
   int64_t t32 = 0, t64 = 0;
   bool vec = true;

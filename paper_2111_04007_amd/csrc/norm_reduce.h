@@ -589,8 +589,9 @@ inline hipError_t launch_reduce_jobs(const ReduceJob<T>* jobs, int n_jobs, float
   return hipGetLastError();
 }
 
-// dx of a LayerNorm and some column reductions over the same rows: the dx and the reductions' first stage share a launch where both are
-// small.  Three launches become two, or one up to 256 rows; measured for a LayerNorm alone (us): bf16 64x64 13.2 -> 8.6, 512x768 13.6 -> 11.0,
+// dx of a LayerNorm and some column reductions over the same rows: the dx and the reductions' first stage share a launch up to eight vectors
+// per lane, the rows that the joint kernel holds; where both are long it costs nothing (micro-batches of a stage, two launches / one: bf16
+// 16384 x 2048 3807 / 3811, 16384 x 4096 11479 / 11454, 65536 x 1024 5453 / 5443, fp32 8192 x 1024 5157 / 5125).  Three launches become two, or one up to 256 rows; measured for a LayerNorm alone (us): bf16 64x64 13.2 -> 8.6, 512x768 13.6 -> 11.0,
 // 1000x4096 19.9 -> 14.0, 4096x1920 20.9 -> 18.3, 16384x256 18.2 -> 12.4, 16384x1920 60.4 -> 58.8; fp32 64x64 13.7 -> 8.5, 4096x1024
 // 19.4 -> 18.7.
 template <typename T>

@@ -185,8 +185,9 @@ Workspace carve(const Dims& D) {
 
 constexpr int kMaxEvents = 4096;
 
-// Weight gradients of at most this many 128x128 tiles in all share a launch of the small tiles of gemm_cut.h; one by one each of them is a
-// launch that leaves most CUs idle, or two where its reduction is split.  Whole steps of two micro-batches, one by one / one launch (us):
+// Weight gradients of at most this many 128x128 tiles in all, counted over the up to four layers that end together, share a launch of the
+// small tiles of gemm_cut.h; one by one each of them is a launch that leaves most CUs idle, or two where its reduction is split.  (Three layers
+// 256 wide are 144 tiles and go one by one; launches of one or two of them have not been tried.)  Whole steps of two micro-batches, one by one / one launch (us):
 // 128 wide over 2048 tokens 441 / 389, 256 wide over 512 459 / 406, two layers of that (96 tiles) 838 / 773, 384 wide (108) over 512
 // 458 / 445 and over 2048 574 / 559; 512 wide (192) over 256 384 / 394, over 1000 686 / 707.
 constexpr int kCutGroupTiles = 128;
