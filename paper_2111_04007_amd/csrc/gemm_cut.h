@@ -103,7 +103,20 @@ struct GcOperand {
     for (int q = 0; q < PIECES; ++q) x.v[q] = *reinterpret_cast<const Piece*>(p[q] + k * kpitch);
   }
   // The last steps: k past the end reads as zero, and no piece runs over its k-row.
+  // WHOLE: with a way of its own for rows that are whole pieces (one wave for a 64x64 tile has no registers for it).
+  template <bool WHOLE>
   __device__ __forceinline__ void load_last(Raw& x, int64_t k, int64_t K, int64_t row0, int64_t rows, int lane) const {
+    if constexpr (!KMAJOR && WHOLE) {
+      if (rows % EPP == 0) {   // only k may be past the end, and reads the last k-row in its place
+#pragma unroll
+        for (int q = 0; q < PIECES; ++q) {
+          const int64_t left = K - k - piece_line(q, lane);
+          const PieceA t = *reinterpret_cast<const Piece*>(p[q] + (left > 0 ? k : k + left - 1) * kpitch);
+          x.v[q] = left > 0 ? t : PieceA{};
+        }
+        return;
+      }
+    }
 #pragma unroll
     for (int q = 0; q < PIECES; ++q) {
       const int64_t left = K - k - (KMAJOR ? piece_elem(q, lane) : piece_line(q, lane));   // k from the piece's first on
@@ -267,8 +280,8 @@ struct GcTile {
         oa.load(ra[S], k);
         ob.load(rb[S], k);
       } else if (t < mine) {
-        oa.load_last(ra[S], k, K, m0, M, lane);
-        ob.load_last(rb[S], k, K, n0, N, lane);
+        oa.template load_last<(KS > 1)>(ra[S], k, K, m0, M, lane);
+        ob.template load_last<(KS > 1)>(rb[S], k, K, n0, N, lane);
       }
     };
     auto put = [&](auto set) {

@@ -858,7 +858,7 @@ inline int dg_flavour(int tile_variant, int op) {
 // The lines are those of operands in cache and keep off where the two are close there (1024^2 over 1024 on a later measurement 8.9 / 10.1,
 // 8.8 / 9.4, 11.0 / 14.9).  With operands out of cache the small tiles are ahead further up in forward and dgrad: 1024^2 over 1024
 // 15.9 / 12.1, 15.5 / 11.2 (wgrad 17.9 / 19.0), 1024^2 over 512 10.4 / 9.3, 9.7 / 8.8 (12.3 / 15.5), 512x1024 over 1024 as wgrad 17.5 / 13.4.
-// A reduction of 8 or 16 is up to 1.2 us longer on them in dgrad and wgrad (128x128 over 16 3.8 / 4.4, 3.6 / 4.9).
+// A reduction of 8 or 16 is up to 0.4 us longer on them in dgrad and wgrad (128x128 over 16 3.8 / 4.0, 3.6 / 4.1).
 inline bool dg_cut_sooner(int op, int64_t M, int64_t N, int64_t K) {
   const int64_t t7 = ((M + 127) / 128) * ((N + 127) / 128);
   if (t7 <= 18) return true;

@@ -152,3 +152,12 @@ def test_either_side_of_a_short_reduction(op, dtype, M, N, K):
     out, want = product(op, *operands(op, dtype, M, N, K), M, N, K, dtype)
     tol = 2.5e-3 if dtype == "bf16" and op < 2 else 2e-7 + 5e-8 * K ** 0.5   # as in every remainder
     assert float((out.double() - want).norm() / want.norm()) <= tol
+
+
+@pytest.mark.parametrize("op", [0, 1, 2])
+@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 40, 24, 8), ("bf16", 8, 72, 31), ("bf16", 104, 336, 200), ("bf16", 720, 904, 1001), ("f32", 44, 20, 1025), ("f32", 444, 484, 1039), ("f32", 1000, 1024, 1290)])
+def test_whole_rows_with_a_rest_of_k(op, dtype, M, N, K):
+    """Last steps of operands whose k-rows are whole pieces, in tiles that end within the operand."""
+    out, want = product(op, *operands(op, dtype, M, N, K), M, N, K, dtype)
+    tol = 2.5e-3 if dtype == "bf16" and op < 2 else 2e-7 + 5e-8 * K ** 0.5   # as in every remainder
+    assert float((out.double() - want).norm() / want.norm()) <= tol
