@@ -521,9 +521,12 @@ __global__ __launch_bounds__(KS * kWave) void gemm_cut_group_kernel(GfGroup<T> g
 //   bf16: as many waves as keep the chip's 1024 SIMDs busy.  Measured (us, 32x32 on 8 waves / 32x32 on 4 / 64x64 on 4 / 64x64 on 1):
 //   301^3 4.6 / 5.3 / 9.2 / 16, [2001,131] over 601 7.5 / 7.5 / 10 / 18, [701,701] over 6001 50 / 46 / 47 / 59, 1001^3 18 / 17 / 15 / 22,
 //   [4001,3001] over 3001 562 / 643 / 318 / 275.
-//   A reduction of one or two steps leaves waves that share it idle: beyond one round such tiles go to one wave (64x64 on 4 / on 1, forward,
-//   dgrad, wgrad: 1550x1273 over 33 6.9 / 7.2, 12 / 7.6, 16 / 11).  (In that range a weight gradient on fewer tiles, over fewer than 64 tokens, was
-//   0.2 to 1.4 us shorter in fp32 products: 301x303 over 33 5.0 / 5.3, 701x1001 over 49 7.6 / 8.8.)
+//   Four waves on a tile also end each round with their sums' way through LDS, which a reduction of up to 256 does not pay for beyond one
+//   round, of 256 tiles, or 512 in forward, whose workgroups share a CU (64x64 on 4 / on 1, forward, dgrad, wgrad): bf16 1550x1273 (500)
+//   over 33 6.9 / 7.2, 12 / 7.6, 16 / 11 and over 200 7.9 / 9.1, 13 / 10, 18 / 18, 1803x1301 (609) over 104 11 / 8.9, 17 / 9.6, 23 / 15 and over 256
+//   11 / 8.9, 21 / 13, 27 / 21; fp32 1803x1301 over 129 27 / 19, 27 / 17, 29 / 19 (fp32 products 25, 22, 26) and over 200 as dgrad 30 / 19, 1201x1101 (342) over 255 21 / 22, 21 / 20, 23 / 22.
+//   (On fewer tiles a bf16 weight gradient over fewer than 64 tokens was 0.2 to 1.4 us shorter in fp32 products: 301x303 over 33 5.0 / 5.3,
+//   701x1001 over 49 7.6 / 8.8.)
 //   fp32 rows that are not whole 16-byte pieces, by the same rule from K = 128 on (fp32 products load such operands element by element; us,
 //   those / this, forward, dgrad, wgrad): 301x303 over 301 8.4 / 5.2, 7.8 / 5.6, 8.3 / 6.3, 513x515 over 301 13.0 / 7.5, 11.2 / 7.7, 11.1 / 8.2,
 //   1001x1003 over 201 13.8 / 11.3, 12.4 / 11.4, 16.9 / 12.5 and over 1003 39 / 24, 39 / 22, 47 / 23, 3001x3003 over 129 63 / 52, 56 / 46, 63 / 56;
@@ -538,10 +541,10 @@ __global__ __launch_bounds__(KS * kWave) void gemm_cut_group_kernel(GfGroup<T> g
 //   [1000,768] over 768 26 / 20 / 43 / 20, transposed operands 29 / 24 / 54 / 20, 256x256 over 512 6.2 / 13 / 31 / 6.6, transposed
 //   7.0 / 15 / 34 / 6.8, 128x512 over 128 4.2 / 8.2 / 17 / 3.8.
 enum GcKind : int { GC_NONE = 0, GC_32_8 = 1, GC_32_4 = 2, GC_64_4 = 3, GC_64_1 = 4 };
-inline GcKind gc_kind(bool fp32, bool pieces, int64_t tiles32, int64_t tiles64, int64_t K) {
+inline GcKind gc_kind(bool fp32, bool pieces, bool forward, int64_t tiles32, int64_t tiles64, int64_t K) {
   if (fp32 && K < (pieces ? 1024 : 128)) return GC_NONE;
   if (tiles32 <= 256) return GC_32_8;
-  if (!fp32 || !pieces) return tiles32 <= 512 ? GC_32_4 : tiles64 <= (K <= 64 ? 256 : 768) ? GC_64_4 : GC_64_1;
+  if (!fp32 || !pieces) return tiles32 <= 512 ? GC_32_4 : tiles64 <= (K > 256 ? 768 : forward ? 512 : 256) ? GC_64_4 : GC_64_1;
   if (tiles64 >= 768) return GC_64_1;
   const double r32 = (double)((tiles32 + 255) / 256), r64 = (double)((tiles64 + 255) / 256);
   const double area = gf_small_tile(tiles32, tiles64) ? 1.2 * r32 : 4.0 * r64;

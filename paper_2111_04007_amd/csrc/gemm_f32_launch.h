@@ -41,7 +41,7 @@ inline hipError_t gf_launch(const T* a, int64_t lda, const T* b, int64_t ldb, in
   const int64_t t32 = gf_tiles(M, N, 32), t64 = gf_tiles(M, N, 64);
   // whole pieces of four along the contiguous direction of both operands, from an aligned base
   const bool vec = ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 15) == 0 && lda % 4 == 0 && ldb % 4 == 0;
-  switch (gc_kind(sizeof(T) == 4, vec, t32, t64, K)) {
+  switch (gc_kind(sizeof(T) == 4, vec, AK && BK, t32, t64, K)) {
     case GC_32_8: return gc_launch<T, MODE, AK, BK, 1, 1, 8>(a, lda, b, ldb, M, N, K, epi, st);
     case GC_32_4: return gc_launch<T, MODE, AK, BK, 1, 1, 4>(a, lda, b, ldb, M, N, K, epi, st);
     case GC_64_4: return gc_launch<T, MODE, AK, BK, 2, 2, 4>(a, lda, b, ldb, M, N, K, epi, st);

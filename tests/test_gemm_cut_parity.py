@@ -147,7 +147,7 @@ def test_whole_pieces_on_either_side_of_the_limits(op, M, N, K):
 
 
 @pytest.mark.parametrize("op", [0, 1, 2])
-@pytest.mark.parametrize("dtype,M,N,K", [("f32", 70, 65, 127), ("f32", 70, 65, 128), ("f32", 1101, 1103, 127), ("f32", 1101, 1103, 128), ("bf16", 1101, 1103, 64), ("bf16", 1101, 1103, 65), ("bf16", 999, 1003, 64)])
+@pytest.mark.parametrize("dtype,M,N,K", [("f32", 70, 65, 127), ("f32", 70, 65, 128), ("f32", 1101, 1103, 127), ("f32", 1101, 1103, 128), ("bf16", 1101, 1103, 64), ("bf16", 1101, 1103, 65), ("bf16", 999, 1003, 64), ("bf16", 1101, 1103, 256), ("bf16", 1101, 1103, 257), ("bf16", 1455, 1409, 200), ("f32", 1101, 1103, 255)])
 def test_either_side_of_a_short_reduction(op, dtype, M, N, K):
     out, want = product(op, *operands(op, dtype, M, N, K), M, N, K, dtype)
     tol = 2.5e-3 if dtype == "bf16" and op < 2 else 2e-7 + 5e-8 * K ** 0.5   # as in every remainder
