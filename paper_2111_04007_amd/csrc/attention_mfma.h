@@ -7,7 +7,7 @@
 // The EDGE form works out rows that are not finite again one by one (attention_rows.h), so that an infinity or NaN of a
 // masked token does not reach them.
 //
-// All three kernels keep two 64-row tiles in LDS (rows of D values, padded pitch)
+// All three kernels keep tiles of two matrices in LDS (64 rows each; dK/dV 32, twice)
 // and hold the other operands in registers.  Products use
 // v_mfma_f32_32x32x16_bf16 whose operand layout is: row operand lane L -> row
 // L%32, k = 8*(L/32)..+7; column operand likewise; result lane L -> column L%32,
@@ -25,6 +25,12 @@
 //     dQ^T += K^T dS^T ; also writes delta = rowsum(dO * O)
 //   backward dK/dV (per 128-key workgroup, 32 keys per wave; Q, dO tiles in LDS):
 //     S = Q K^T, dP = dO V^T ; dV^T += dO^T P ; dK^T += Q^T dS
+//
+// What bounds them: a wave's chain of fragment reads, products, softmax arithmetic and tile exchange.  The products alone, with the
+// same barriers, take a third to a half of a kernel's time, and two waves of a SIMD overlap only in part; so what pays is what
+// shortens a wave's chain or keeps two waves on a SIMD: no bank conflicts (a fifth of the LDS cycles before), tile loads that
+// need neither 64-bit addresses nor masks (buffer loads), nothing in the loop that waits for the next tile's loads (a
+// register spill does), the mask's arithmetic on the diagonal only.
 #pragma once
 #include "attention_rows.h"
 #include "common.h"
@@ -36,40 +42,57 @@ typedef short at_shortx4 __attribute__((ext_vector_type(4)));
 template <int D>
 struct AttnCfg {
   static_assert(D == 32 || D == 64 || D == 96 || D == 128, "head dim");
-  // Row pitch in elements: pitch bytes = 7*16 (D=32), 13*16 (D=64) or 19*16 (D=96,128).  An odd number
-  // of 16-byte units spreads 16 consecutive rows over all banks for ds_read_b128, and
-  // 4 consecutive rows' 32-byte segments do not overlap for the transposing reads.
-  static constexpr int PITCH = D == 32 ? 56 : (D == 64 ? 104 : 152);
+  // LDS row pitch in elements: an odd multiple of 64 bytes, so that four consecutive rows' 64-byte pieces, which 32 lanes of a
+  // transposing read take at once, lie in different quarters of the 256 bytes of banks.  Within such a piece the 16-byte chunks
+  // of row r are XOR-permuted by (r / 4) % 4: 16 consecutive rows of a 16-byte read fall into different banks as well.
+  static constexpr int PITCH = D == 32 ? 32 : (D == 128 ? 160 : 96);
   static constexpr int CH = D / 8;             // 16-byte chunks per row
-  static constexpr int CPT = 64 * CH / 256;    // chunks per thread for a 64-row tile, 256 threads
-  static constexpr int TILE = 64 * PITCH;      // elements per LDS tile
   static constexpr int KD = D / 16;            // k-steps over the head dim
   static constexpr int DB = D / 32;            // 32-wide blocks of the head dim
 };
 
-// 64 x D tile: global -> registers -> LDS, 256 threads.  EDGE: only `rows` rows and `cols` columns exist; the rest of the
-// tile is zero.  What lies outside is loaded from some element inside and replaced on the way into LDS, so that
-// there is no branch around the loads.
-template <int D, bool EDGE>
-struct AttnTileRegs {
-  bf16x8 v[AttnCfg<D>::CPT];
-  __device__ __forceinline__ void load(const bf16* __restrict__ base, int64_t row_stride, int tid, int rows, int cols) {
+// Rows of the same ROWS tokens (or of ROWS tokens each) of two matrices, D columns, on their way to LDS: waves 0 and 1 of the
+// workgroup's four move the first, 2 and 3 the second.  Buffer loads: what lies past the end of a sequence (EDGE) is outside
+// the buffer and reads as zero, and so are a head's missing columns, whose lanes hold an offset outside.
+template <int D, bool EDGE, int ROWS>
+struct AttnTilePair {
+  static constexpr int CH = AttnCfg<D>::CH, CPT = ROWS * CH / 128;   // chunks per row, per thread
+  static constexpr bool WHOLE = CH == 8 || CH == 16;                 // a load takes whole rows (else 64-byte quarters)
+  static constexpr int NV = WHOLE ? 1 : CH / 4;
+  static constexpr uint32_t OUTSIDE = 0xfffffff0u;   // past any row of the tile (a row has up to 48 MB)
+  floatx4 v[CPT];
+  uint32_t voff[NV];
+  int64_t ld2;         // bytes per row
+  const char* base;    // the sequence's first row
+  int at;
+  __device__ __forceinline__ void init(const bf16* first_row, int64_t row_stride, int t, int cols) {
+    base = reinterpret_cast<const char*>(first_row);
+    ld2 = row_stride * 2;
+    const int r = WHOLE ? t / CH : t / 4, c = WHOLE ? t % CH : t % 4;
 #pragma unroll
-    for (int i = 0; i < AttnCfg<D>::CPT; ++i) {
-      const int id = tid + i * 256, r = id / AttnCfg<D>::CH, c = id % AttnCfg<D>::CH;
-      if constexpr (EDGE) v[i] = *reinterpret_cast<const bf16x8*>(base + (r < rows ? r : 0) * row_stride + (c * 8 < cols ? c * 8 : 0));
-      else v[i] = *reinterpret_cast<const bf16x8*>(base + r * row_stride + c * 8);
-    }
+    for (int i = 0; i < NV; ++i) voff[i] = EDGE && (c + 4 * i) * 8 >= cols ? OUTSIDE : (uint32_t)(r * ld2 + (c + 4 * i) * 16);
+    at = (r * AttnCfg<D>::PITCH + (c & ~3) * 8 + ((c ^ (r >> 2)) & 3) * 8) * 2;
   }
-  __device__ __forceinline__ void store(bf16* __restrict__ lds, int tid, int rows, int cols) const {
+  // piece i: its row (beyond the thread's first) and its place in the row (bytes beyond the thread's first)
+  static __device__ __forceinline__ constexpr int row_of(int i) { return WHOLE ? i * (128 / CH) : i / (CH / 4) * 32; }
+  __device__ __forceinline__ void load(int row0, int rows, int cols) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the buffer builtins exist in the device pass only
+    const int left = rows - row0;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base + row0 * ld2), 0,
+                                                        EDGE ? (uint32_t)(((left < ROWS ? left : ROWS) - 1) * ld2 + cols * 2) : OUTSIDE, 0x00020000);
 #pragma unroll
-    for (int i = 0; i < AttnCfg<D>::CPT; ++i) {
-      const int id = tid + i * 256, r = id / AttnCfg<D>::CH, c = id % AttnCfg<D>::CH;
-      bf16x8 x = v[i];
-      if constexpr (EDGE) {
-        if (!(r < rows && c * 8 < cols)) x = bf16x8{};
-      }
-      *reinterpret_cast<bf16x8*>(lds + r * AttnCfg<D>::PITCH + c * 8) = x;
+    for (int i = 0; i < CPT; ++i) {
+      const uint32_t rows_on = (uint32_t)(row_of(i) * ld2);   // (EDGE: part of the offset that the range check sees)
+      const uint32_t off = EDGE ? __builtin_elementwise_add_sat(voff[WHOLE ? 0 : i % NV], rows_on) : voff[WHOLE ? 0 : i % NV];
+      v[i] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, EDGE ? 0 : (int)rows_on, 0));
+    }
+#endif
+  }
+  __device__ __forceinline__ void store(bf16* lds) const {
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+      const int flip = (row_of(i) >> 2 & 3) * 16;   // the swizzle of the piece's row against that of the thread's first
+      *reinterpret_cast<floatx4*>(reinterpret_cast<char*>(lds) + (at ^ flip) + row_of(i) * AttnCfg<D>::PITCH * 2 + (WHOLE ? 0 : i % NV * 64)) = v[i];
     }
   }
 };
@@ -85,30 +108,32 @@ __device__ __forceinline__ void at_load_row(bf16x8 (&f)[AttnCfg<D>::KD], const b
   }
 }
 
-// Row operand from an LDS tile: row (row_base + lane%32), columns col0 + 8*(lane/32) .. +7.
+// Row operand from an LDS tile: row (row_base + lane%32), columns 16t + 8*(lane/32) .. +7.  row_base: a multiple of 32.
 template <int D>
-__device__ __forceinline__ bf16x8 at_row_frag(const bf16* tile, int row_base, int col0, int lane) {
-  return *reinterpret_cast<const bf16x8*>(tile + (row_base + (lane & 31)) * AttnCfg<D>::PITCH + col0 + 8 * (lane >> 5));
+__device__ __forceinline__ bf16x8 at_row_frag(const bf16* tile, int row_base, int t, int lane) {
+  const int c = ((t & 1) * 2 + (lane >> 5)) ^ (lane >> 2 & 3);
+  return *reinterpret_cast<const bf16x8*>(tile + (row_base + (lane & 31)) * AttnCfg<D>::PITCH + (t >> 1) * 32 + c * 8);
 }
 
 // Transposed row operand: operand row = tile column (col_base + lane%32); its 8 k-slots are
 // tile rows r0 + 4*(lane/32) + {0..3} and r0 + 8 + 4*(lane/32) + {0..3} -- the order in
-// which a lane holds the rows of a 32x32 MFMA result, i.e. of P / dS.
+// which a lane holds the rows of a 32x32 MFMA result, i.e. of P / dS.  r0: a multiple of 16.
 template <int D>
 __device__ __forceinline__ bf16x8 at_tr_frag(const bf16* tile, int r0, int col_base, int lane) {
-  const int j = lane & 15;
-  const bf16* p = tile + (r0 + 4 * (lane >> 5) + (j >> 2)) * AttnCfg<D>::PITCH + col_base + ((lane >> 4) & 1) * 16 + 4 * (j & 3);
-  at_shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) at_shortx4*)p);
-  at_shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) at_shortx4*)(p + 8 * AttnCfg<D>::PITCH));
+  const int j = lane & 15, hf = lane >> 5, c = (lane >> 4 & 1) * 2 + (j >> 1 & 1);
+  const bf16* p = tile + (r0 + 4 * hf + (j >> 2)) * AttnCfg<D>::PITCH + col_base + 4 * (j & 1);
+  at_shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) at_shortx4*)(p + (c ^ hf) * 8));
+  at_shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) at_shortx4*)(p + 8 * AttnCfg<D>::PITCH + (c ^ hf ^ 2) * 8));
   union { struct { at_shortx4 a, b; } s; bf16x8 v; } u;
   u.s.a = lo; u.s.b = hi;
   return u.v;
 }
 
 // acc += A B with the accumulator pinned to the accumulation registers.  With one wave per
-// SIMD the dK/dV kernel spreads over both halves of the register file, and left to itself the
-// compiler keeps these long-lived accumulators in the ordinary half and copies all 16
-// registers across around every product.  The product is opaque to the compiler here, so the
+// SIMD a kernel spreads over both halves of the register file, and left to itself the
+// compiler may keep long-lived accumulators in the ordinary half and copy all 16
+// registers across around every product.  (The dK/dV kernel did until it fitted two waves per SIMD, where the compiler's own products
+// are as fast.)  The product is opaque to the compiler here, so the
 // wait states around it are inserted by hand: two between an operand's last VALU write and the product (a conversion or
 // register move may stand directly before it; the product then multiplied what the register held before, now and then:
 // dK of d = 32 with dropout up to infinity), and those a later read of the result needs (at_mfma_settle).
@@ -200,8 +225,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
                                                             float* __restrict__ lse, int s, int heads,
                                                             float scale_log2e, DropArgs drop, int d) {
   using C = AttnCfg<D>;
-  __shared__ __attribute__((aligned(16))) bf16 sk[C::TILE];
-  __shared__ __attribute__((aligned(16))) bf16 sv[C::TILE];
+  __shared__ __attribute__((aligned(16))) bf16 sk[64 * C::PITCH];
+  __shared__ __attribute__((aligned(16))) bf16 sv[64 * C::PITCH];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hf = lane >> 5;
   // Grid: x = (batch, head), y = query block.  Workgroups are dispatched in x-fastest order,
   // so under the causal mask every head's longest (latest) query blocks start first and only
@@ -227,48 +252,55 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
   float m = -INFINITY, l = 0.f;
 
   const int nkt = (s + 63) / 64, nkb = CAUSAL && (!EDGE || (q0 + 128) / 64 < nkt) ? (q0 + 128) / 64 : nkt;
-  AttnTileRegs<D, EDGE> rk, rv;
-  rk.load(base + h, ld, tid, s, cols);
-  rv.load(base + 2 * h, ld, tid, s, cols);
+  AttnTilePair<D, EDGE, 64> rt;   // waves 0 and 1 move the K tile, 2 and 3 the V tile
+  const int second = __builtin_amdgcn_readfirstlane(wave >> 1);
+  rt.init(base + h + (second ? h : 0), ld, tid & 127, cols);
+  rt.load(0, s, cols);
   for (int kb = 0; kb < nkb; ++kb) {
     if (kb) __syncthreads();
-    rk.store(sk, tid, s - kb * 64, cols);
-    rv.store(sv, tid, s - kb * 64, cols);
+    rt.store(second ? sv : sk);
     __syncthreads();
-    if (kb + 1 < nkb) {
-      rk.load(base + (int64_t)(kb + 1) * 64 * ld + h, ld, tid, s - (kb + 1) * 64, cols);
-      rv.load(base + (int64_t)(kb + 1) * 64 * ld + 2 * h, ld, tid, s - (kb + 1) * 64, cols);
-    }
+    if (kb + 1 < nkb) rt.load((kb + 1) * 64, s, cols);
     const int k0 = kb * 64;
-    if (CAUSAL && k0 > qw + 31) continue;  // whole key block is in this wave's future
+    if (CAUSAL && k0 > qw_s + 31) continue;  // whole key block is in this wave's future
+    // Fragments are fetched a batch of products ahead (left alone, the compiler pairs every read with its product and waits), the
+    // first V^T fragments before the last scores are multiplied; the fences keep it that way.
     floatx16 sc[2];
 #pragma unroll
-    for (int sb = 0; sb < 2; ++sb) {
+    for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) sc[sb][r] = 0.f;
-      // fragments fetched as one batch ahead of their products (see the dK/dV kernel)
-      bf16x8 kfr[C::KD];
+    constexpr int KB = D == 96 ? 3 : (D == 32 ? 2 : 4), NB = 2 * C::KD / KB;
+    bf16x8 kfr[2][KB], vtr[2][C::DB];
+    auto k_frags = [&](int b) {
 #pragma unroll
-      for (int t = 0; t < C::KD; ++t) kfr[t] = at_row_frag<D>(sk, sb * 32, 16 * t, lane);
+      for (int t = 0; t < KB; ++t) kfr[b & 1][t] = at_row_frag<D>(sk, (b * KB + t) / C::KD * 32, (b * KB + t) % C::KD, lane);
+    };
+    auto v_frags = [&](int t) {
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db) vtr[t & 1][db] = at_tr_frag<D>(sv, 16 * t, db * 32, lane);
+    };
+    k_frags(0);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if (b + 1 < NB) k_frags(b + 1);
+      else v_frags(0);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int t = 0; t < C::KD; ++t)
-        sc[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[t], qf[t], sc[sb], 0, 0, 0);
+      for (int t = 0; t < KB; ++t) {
+        const int sb = (b * KB + t) / C::KD;
+        sc[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[b & 1][t], qf[(b * KB + t) % C::KD], sc[sb], 0, 0, 0);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
-    // V^T fragments of the first 32 keys: in flight during the softmax arithmetic
-    bf16x8 vtr[2][C::DB];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int db = 0; db < C::DB; ++db) vtr[t][db] = at_tr_frag<D>(sv, 16 * t, db * 32, lane);
+    v_frags(1);
     __builtin_amdgcn_sched_barrier(0);
     // Raw scores stay in the accumulators until the exponential: the row maximum is taken on
     // them (the scale is positive), and scale and shift fold into one fused multiply-add.
     // Only key blocks that straddle the diagonal pay for the mask.
     float p[2][16];
     float mx = -INFINITY;
-    if ((CAUSAL && k0 + 63 > qw) || (EDGE && k0 + 64 > s)) {
+    if ((CAUSAL && k0 + 63 > qw_s) || (EDGE && k0 + 64 > s)) {
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
@@ -281,15 +313,15 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
     for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[sb][r]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     // The running reference m only moves when a row's maximum grows by more than 2^8: until
     // then the exponentials are taken against the old reference (they stay below 256, l and
     // the output carry the same factor and the final division removes it), and the block
     // skips rescaling the output accumulators.  Key 0 is visible to every query, so the
     // first block always sets a finite reference.
-    const float m_cand = fmaxf(m, mx * scale_log2e);
-    const bool grow = m_cand > m + 8.0f;
-    if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+    // (Each half wave has seen half of a row's scores: only where one of them grows do they compare.)
+    if (__builtin_amdgcn_ballot_w64(fmaxf(m, mx * scale_log2e) > m + 8.0f) != 0) {
+      const float m_cand = fmaxf(m, fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2e);
+      const bool grow = m_cand > m + 8.0f;
       const float m_new = grow ? m_cand : m;
       const float alpha = __builtin_amdgcn_exp2f(m - m_new);
       m = m_new;
@@ -326,28 +358,20 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int sb = 0; sb < 2; ++sb) {
+    for (int t = 0; t < 4; ++t) {
+      const bf16x8 pf = at_pack8(&p[t >> 1][8 * (t & 1)]);
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const bf16x8 pf = at_pack8(&p[sb][8 * t]);
+      for (int db = 0; db < C::DB; ++db)
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vtr[t & 1][db], pf, o[db], 0, 0, 0);
+      if constexpr (EDGE) {
+        const bf16x8 pl = at_pack8_rest(&p[t >> 1][8 * (t & 1)], pf);
 #pragma unroll
         for (int db = 0; db < C::DB; ++db)
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vtr[t][db], pf, o[db], 0, 0, 0);
-        if constexpr (EDGE) {
-          const bf16x8 pl = at_pack8_rest(&p[sb][8 * t], pf);
-#pragma unroll
-          for (int db = 0; db < C::DB; ++db)
-            o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vtr[t][db], pl, o[db], 0, 0, 0);
-        }
+          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vtr[t & 1][db], pl, o[db], 0, 0, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
-      if (sb == 0) {  // the second 32 keys' fragments, into the same registers
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int db = 0; db < C::DB; ++db) vtr[t][db] = at_tr_frag<D>(sv, 32 + 16 * t, db * 32, lane);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      if (t < 2) v_frags(t + 2);   // into the registers just multiplied
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
   l += __shfl_xor(l, 32, 64);
@@ -387,8 +411,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
                                                                float* __restrict__ delta, int s, int heads,
                                                                float scale, float scale_log2e, DropArgs drop, int d) {
   using C = AttnCfg<D>;
-  __shared__ __attribute__((aligned(16))) bf16 sk[C::TILE];
-  __shared__ __attribute__((aligned(16))) bf16 sv[C::TILE];
+  __shared__ __attribute__((aligned(16))) bf16 sk[64 * C::PITCH];
+  __shared__ __attribute__((aligned(16))) bf16 sv[64 * C::PITCH];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hf = lane >> 5;
   const int qb = gridDim.y - 1 - blockIdx.y;   // grid as in the forward kernel: long query blocks of every head first
   const int head = blockIdx.x % heads, bi = blockIdx.x / heads;
@@ -424,52 +448,52 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
     for (int r = 0; r < 16; ++r) dq[i][r] = 0.f;
 
   const int nkt = (s + 63) / 64, nkb = CAUSAL && (!EDGE || (q0 + 128) / 64 < nkt) ? (q0 + 128) / 64 : nkt;
-  AttnTileRegs<D, EDGE> rk, rv;
-  rk.load(base + h, ld, tid, s, cols);
-  rv.load(base + 2 * h, ld, tid, s, cols);
+  AttnTilePair<D, EDGE, 64> rt;   // waves 0 and 1 move the K tile, 2 and 3 the V tile
+  const int second = __builtin_amdgcn_readfirstlane(wave >> 1);
+  rt.init(base + h + (second ? h : 0), ld, tid & 127, cols);
+  rt.load(0, s, cols);
   for (int kb = 0; kb < nkb; ++kb) {
     if (kb) __syncthreads();
-    rk.store(sk, tid, s - kb * 64, cols);
-    rv.store(sv, tid, s - kb * 64, cols);
+    rt.store(second ? sv : sk);
     __syncthreads();
-    if (kb + 1 < nkb) {
-      rk.load(base + (int64_t)(kb + 1) * 64 * ld + h, ld, tid, s - (kb + 1) * 64, cols);
-      rv.load(base + (int64_t)(kb + 1) * 64 * ld + 2 * h, ld, tid, s - (kb + 1) * 64, cols);
-    }
+    if (kb + 1 < nkb) rt.load((kb + 1) * 64, s, cols);
     const int k0 = kb * 64;
     // (no per-wave skip of key blocks in this wave's future: the mask zeroes them, and a
     // branch around the products costs registers)
-    const bool need_mask = (CAUSAL && k0 + 63 > qw) || (EDGE && k0 + 64 > s);
+    const bool need_mask = (CAUSAL && k0 + 63 > qw_s) || (EDGE && k0 + 64 > s);
+    // Fragments are fetched a batch ahead of their products, across the two halves of the tile (see the forward kernel).
+    constexpr int KB = D == 96 ? 3 : (D == 128 && DROP && !EDGE ? 1 : 2), NB = C::KD / KB;
+    bf16x8 kfr[2][KB], vfr[2][KB], ktr[2][C::DB];
+    auto rows = [&](int sb, int b) {
+#pragma unroll
+      for (int t = 0; t < KB; ++t) {
+        kfr[b & 1][t] = at_row_frag<D>(sk, sb * 32, b * KB + t, lane);
+        vfr[b & 1][t] = at_row_frag<D>(sv, sb * 32, b * KB + t, lane);
+      }
+    };
+    auto k_cols = [&](int sb, int t) {
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db) ktr[t][db] = at_tr_frag<D>(sk, sb * 32 + 16 * t, db * 32, lane);
+    };
+    if (D < 128) rows(0, 0);
 #pragma unroll
     for (int sb = 0; sb < 2; ++sb) {
       floatx16 sc, dp;
 #pragma unroll
       for (int r = 0; r < 16; ++r) { sc[r] = 0.f; dp[r] = 0.f; }
-      // fragments fetched in batches ahead of their products (see the dK/dV kernel)
-      constexpr int KH = (C::KD + 1) / 2;
+      if (D == 128) rows(sb, 0);
 #pragma unroll
-      for (int t0 = 0; t0 < C::KD; t0 += KH) {
-        bf16x8 kfr[KH], vfr[KH];
-#pragma unroll
-        for (int t = 0; t < KH; ++t)
-          if (t0 + t < C::KD) {
-            kfr[t] = at_row_frag<D>(sk, sb * 32, 16 * (t0 + t), lane);
-            vfr[t] = at_row_frag<D>(sv, sb * 32, 16 * (t0 + t), lane);
-          }
+      for (int b = 0; b < NB; ++b) {
+        if (b + 1 < NB) rows(sb, b + 1);
+        else k_cols(sb, 0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int t = 0; t < KH; ++t)
-          if (t0 + t < C::KD) {
-            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[t], qf[t0 + t], sc, 0, 0, 0);
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[t], gf[t0 + t], dp, 0, 0, 0);
-          }
+        for (int t = 0; t < KB; ++t) {
+          sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[b & 1][t], qf[b * KB + t], sc, 0, 0, 0);
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[b & 1][t], gf[b * KB + t], dp, 0, 0, 0);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
-      // K^T fragments of the last product: in flight during the arithmetic below
-      bf16x8 ktr[2][C::DB];
-#pragma unroll
-      for (int db = 0; db < C::DB; ++db) ktr[0][db] = at_tr_frag<D>(sk, sb * 32, db * 32, lane);
-      __builtin_amdgcn_sched_barrier(0);
       if (DROP) {  // dP = dropout'(dO V^T): same mask words as the forward kernel
         uint32_t w[4];
         // (a query past the end must not take its quad to another row of patches: it stores nothing, so any word serves)
@@ -481,11 +505,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
 #pragma unroll
           for (int e = 0; e < 4; ++e) dp[4 * g + e] = drop_keep(drop, w[g], e) ? dp[4 * g + e] * drop.scale : 0.f;
       }
-      // Below d = 128 only key blocks that straddle or follow the diagonal pay for the mask
-      // (a branch on the wave's position); at d = 128 the kernel sits at the register limit,
-      // the branch costs a spill, and masking every block was measured faster.
-      constexpr bool MASK_BRANCH = D < 128;
-      if (MASK_BRANCH && need_mask) {
+      if (need_mask) {   // blocks that straddle or follow the diagonal, or the end of the sequence
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int key = k0 + sb * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
@@ -495,16 +515,12 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
       float ds[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, -l2));
-        if (!MASK_BRANCH && need_mask) {
-          const int key = k0 + sb * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
-          if ((CAUSAL && key > query) || (EDGE && key >= s)) pr = 0.f;
-        }
+        const float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, -l2));
         ds[r] = pr * (dp[r] - dl);
       }
       __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int db = 0; db < C::DB; ++db) ktr[1][db] = at_tr_frag<D>(sk, sb * 32 + 16, db * 32, lane);
+      k_cols(sb, 1);
+      if (D < 128 && sb == 0) rows(1, 0);   // (at d = 128 there is no register left for it)
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
@@ -545,16 +561,29 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(const bf16* __
 // ---------------------------------------------------------------------------
 // backward, key side: dK and dV
 // ---------------------------------------------------------------------------
+// Waves per SIMD.  Two waves have 256 registers each: dK, dV, K and V of 32 keys are 96 (d = 64) to 192 (d = 128) of them.  The
+// forms whose masks or second parts of P and dS do not fit run on one wave with twice the registers; a spill is worse (its reload waits
+// for the next tile's loads: 64 heads of 128 over 2048 tokens, causal, 8 registers spilled 180 us, none 130).
+constexpr int attn_dkv_waves(int d, bool drop, bool edge) { return (edge && d == 128) || (drop && (d == 128 || (edge && d == 96))) ? 1 : 2; }
+// 32 queries per step, two stages, one barrier per step.  From the last queries to the first: under the causal mask the key blocks
+// of a head, which start together, then read the same tiles at the same time.
+//
+// us for dQ, dK and dV against the form on one wave per SIMD that fetched 64-query tiles through 64-bit addresses: 64 heads of 128
+// over 2048 tokens 350 / 254, 80 of 96 over 1024 123 / 90 (all causal), 128 of 64 over 512 47 / 45, 50 of 64 over 1000 (EDGE) 87 / 65.
 template <int D, bool CAUSAL, bool DROP, bool EDGE>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __restrict__ qkv, const float* __restrict__ lse,
+__global__ __launch_bounds__(256, attn_dkv_waves(D, DROP, EDGE)) void attn_bwd_dkv_mfma_kernel(const bf16* __restrict__ qkv, const float* __restrict__ lse,
                                                                 const bf16* __restrict__ dctx,
                                                                 const float* __restrict__ delta, bf16* __restrict__ dqkv,
                                                                 int s, int heads, float scale, float scale_log2e,
                                                                 DropArgs drop, int d) {
   using C = AttnCfg<D>;
-  __shared__ __attribute__((aligned(16))) bf16 sq[C::TILE];
-  __shared__ __attribute__((aligned(16))) bf16 sg[C::TILE];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hf = lane >> 5;
+  constexpr int TILE = 32 * C::PITCH;
+  // At d = 128 two waves have no registers for V: its fragments, and the first of K, are kept in LDS (each wave's own).
+  constexpr bool VLDS = D == 128 && attn_dkv_waves(D, DROP, EDGE) == 2;
+  __shared__ __attribute__((aligned(16))) bf16 sqg[2][2][TILE];   // [stage][Q, dO]
+  __shared__ __attribute__((aligned(16))) bf16x8 svf[VLDS ? 4 * (C::KD + 1) * 64 : 1];
+  __shared__ __attribute__((aligned(16))) float sstat[2][2][32];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hf = lane >> 5;
   // grid: x = (batch, head), y = key block; early key blocks (most queries under the causal
   // mask) of every head are dispatched first
   const int kblk = blockIdx.y;
@@ -563,7 +592,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
   const int64_t ld = 3 * (int64_t)h;
   const bf16* base = qkv + (int64_t)bi * s * ld + head * cols;
   const bf16* gbase = dctx + (int64_t)bi * s * h + head * cols;
-  const int kb0 = kblk * 128, kw = kb0 + wave * 32, kw_s = __builtin_amdgcn_readfirstlane(kw);  // this wave's first key
+  const int kb0 = kblk * 128, kw = kb0 + wave * 32;  // this wave's first key
   const int key = kw + (lane & 31);
   const int64_t sbase = ((int64_t)bi * heads + head) * s;
 
@@ -571,101 +600,98 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
   bf16x8 kf[C::KD], vf[C::KD];
   at_load_row<D, EDGE>(kf, base + (int64_t)key_row * ld + h, hf, cols);
   at_load_row<D, EDGE>(vf, base + (int64_t)key_row * ld + 2 * h, hf, cols);
+  bf16x8* svw = svf + (VLDS ? wave * (C::KD + 1) * 64 + lane : 0);
+  if constexpr (VLDS) {
+#pragma unroll
+    for (int t = 0; t < C::KD; ++t) svw[t * 64] = vf[t];
+    svw[C::KD * 64] = kf[0];
+  }
   floatx16 dk[C::DB], dv[C::DB];
 #pragma unroll
   for (int i = 0; i < C::DB; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) { dk[i][r] = 0.f; dv[i][r] = 0.f; }
 
-  // Per 64-query tile the statistics lse (scaled to base 2) and delta ride along with the
-  // Q / dO tiles: threads 0..63 prefetch lse, 64..127 delta, into registers and then LDS,
-  // so the inner loop never waits on a global load.
-  __shared__ __attribute__((aligned(16))) float sstat[2][64];
-  const int qs = CAUSAL ? kb0 / 64 : 0, nqb = (s + 63) / 64;
-  AttnTileRegs<D, EDGE> rq, rg;
+  const int qs = CAUSAL ? kb0 / 32 : 0, nqb = (s + 31) / 32;
+  AttnTilePair<D, EDGE, 32> rt;   // waves 0 and 1 move the Q tile, 2 and 3 the dO tile
+  const int second = wave >> 1;
+  rt.init(second ? gbase : base, second ? (int64_t)h : ld, tid & 127, cols);
+  // Waves 0 and 1 also carry the tile's lse and delta (zero for queries past the end, whose rows of Q and dO are zero).
   float rstat = 0.f;
-  auto load_stat = [&](int qb) {
-    const bool in = !EDGE || qb * 64 + (tid & 63) < s;   // queries past the end: probability 2^-inf = 0, dO = 0
-    if (tid < 64) rstat = in ? lse[sbase + qb * 64 + tid] * 1.4426950408889634f : INFINITY;
-    else if (tid < 128) rstat = in ? delta[sbase + qb * 64 + tid - 64] : 0.f;
+  [[maybe_unused]] const float* stats = (wave == 0 ? lse : delta) + sbase;
+  auto load = [&](int qb) {
+    rt.load(qb * 32, s, cols);
+#if defined(__HIP_DEVICE_COMPILE__)
+    if (wave < 2) rstat = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(stats), 0, s * 4, 0x00020000), (lane & 31) * 4, qb * 128, 0));
+#endif
   };
-  rq.load(base + (int64_t)qs * 64 * ld, ld, tid, s - qs * 64, cols);
-  rg.load(gbase + (int64_t)qs * 64 * h, h, tid, s - qs * 64, cols);
-  load_stat(qs);
-  for (int qb = qs; qb < nqb; ++qb) {
-    if (qb > qs) __syncthreads();
-    rq.store(sq, tid, s - qb * 64, cols);
-    rg.store(sg, tid, s - qb * 64, cols);
-    if (tid < 128) sstat[tid >> 6][tid & 63] = rstat;
-    __syncthreads();
-    if (qb + 1 < nqb) {
-      rq.load(base + (int64_t)(qb + 1) * 64 * ld, ld, tid, s - (qb + 1) * 64, cols);
-      rg.load(gbase + (int64_t)(qb + 1) * 64 * h, h, tid, s - (qb + 1) * 64, cols);
-      load_stat(qb + 1);
-    }
-    const int q0 = qb * 64;
-    // (A wave whose keys all follow the tile's queries is not skipped: that happens in a
-    // workgroup's first tile only, the mask zeroes its contribution, and a branch around the
-    // products makes the compiler copy all accumulators.)
-    const bool need_mask = CAUSAL && (q0 < kw + 31);
-    // Order of one 64-query tile (one wave per SIMD: nothing but this order overlaps the LDS
-    // with the matrix pipe).  Per 32-query half `sb`: the row fragments of Q and dO for S and
-    // dP (all k-steps) and the first half of the transposed fragments for dV/dK go out as one
-    // batch; S and dP are multiplied while the tail of that batch is still landing; the second
-    // half of the transposed fragments is fetched under the softmax arithmetic; and the row
-    // fragments of the NEXT half are fetched before this half's dV/dK products are issued, so
-    // they land under those products.  The scheduling fences keep it that way (left alone,
-    // the compiler pairs every read with its product and waits for each one).
-    bf16x8 qfr[C::KD], gfr[C::KD];
-    auto fetch_rows = [&](int sb) {
+  auto store = [&](int st) {
+    rt.store(sqg[st][second]);
+    if (wave < 2 && lane < 32) sstat[st][wave][lane] = wave == 0 ? rstat * 1.4426950408889634f : -rstat;
+  };
+  load(nqb - 1);
+  store((nqb - 1) & 1);
+  __syncthreads();
+  for (int qb = nqb - 1; qb >= qs; --qb) {
+    const int st = qb & 1;
+    if (qb > qs) load(qb - 1);
+    const int q0 = qb * 32;
+    if (!CAUSAL || q0 + 31 >= kw) {   // else every key of this wave follows the tile's queries
+      const bool need_mask = CAUSAL && (q0 < kw + 31);
+      const bf16* tq = sqg[st][0];
+      const bf16* tg = sqg[st][1];
+      // Fragments are fetched a batch of products ahead; the fences keep the order (see the forward kernel).
+      constexpr int KB = D == 128 || (EDGE && D == 96) ? 1 : 2;
+      bf16x8 qfr[2][KB], gfr[2][KB], vfr[2][KB];
+      auto fetch = [&](int b) {
 #pragma unroll
-      for (int t = 0; t < C::KD; ++t) {
-        qfr[t] = at_row_frag<D>(sq, sb * 32, 16 * t, lane);
-        gfr[t] = at_row_frag<D>(sg, sb * 32, 16 * t, lane);
-      }
-    };
-    // (At d = 64 the kernel fits two waves per SIMD, which overlap by themselves; fetching a
-    // half ahead would cost the registers that allow it.)
-    // (The EDGE form at d = 128 has no registers left for it either.)
-    constexpr bool AHEAD = D > 64 && !(EDGE && D == 128);
-    if (AHEAD) fetch_rows(0);
-#pragma unroll
-    for (int sb = 0; sb < 2; ++sb) {
-      if (!AHEAD) fetch_rows(sb);
-      bf16x8 gtr[2][C::DB], qtr[2][C::DB];
-#pragma unroll
-      for (int db = 0; db < C::DB; ++db) {
-        gtr[0][db] = at_tr_frag<D>(sg, sb * 32, db * 32, lane);
-        qtr[0][db] = at_tr_frag<D>(sq, sb * 32, db * 32, lane);
-      }
-      __builtin_amdgcn_sched_barrier(0);
+        for (int t = 0; t < KB; ++t) {
+          qfr[b & 1][t] = at_row_frag<D>(tq, 0, b * KB + t, lane);
+          gfr[b & 1][t] = at_row_frag<D>(tg, 0, b * KB + t, lane);
+          if constexpr (VLDS) vfr[b & 1][t] = svw[(b * KB + t) * 64];
+        }
+      };
       floatx16 sc, dp;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { sc[r] = 0.f; dp[r] = 0.f; }
+      for (int r = 0; r < 16; ++r) { sc[r] = 0.f; dp[r] = DROP ? 0.f : sstat[st][1][8 * (r >> 2) + 4 * hf + (r & 3)]; }   // dP - delta in one sum
+      constexpr int NB = C::KD / KB;
+      fetch(0);
 #pragma unroll
-      for (int t = 0; t < C::KD; ++t) {
-        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qfr[t], kf[t], sc, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gfr[t], vf[t], dp, 0, 0, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
+      for (int b = 0; b < NB; ++b) {
+        if (b + 1 < NB) fetch(b + 1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int db = 0; db < C::DB; ++db) {
-        gtr[1][db] = at_tr_frag<D>(sg, sb * 32 + 16, db * 32, lane);
-        qtr[1][db] = at_tr_frag<D>(sq, sb * 32 + 16, db * 32, lane);
+        for (int t = 0; t < KB; ++t) {
+          sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qfr[b & 1][t], VLDS && b * KB + t == 0 ? svw[C::KD * 64] : kf[b * KB + t], sc, 0, 0, 0);
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gfr[b & 1][t], VLDS ? vfr[b & 1][t] : vf[b * KB + t], dp, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
+      // The last products' column operands, pair number k = (16 queries t, block db): PF pairs in flight.
+      constexpr int NP = 2 * C::DB, PF = EDGE ? (D == 96 ? 1 : 2) : (D == 96 && !DROP ? 3 : (D >= 96 ? 2 : NP));
+      bf16x8 gtr[PF], qtr[PF];
+      auto cols_of = [&](int k) {
+        gtr[k % PF] = at_tr_frag<D>(tg, 16 * (k / C::DB), k % C::DB * 32, lane);
+        qtr[k % PF] = at_tr_frag<D>(tq, 16 * (k / C::DB), k % C::DB * 32, lane);
+      };
+#pragma unroll
+      for (int k = 0; k < PF; ++k) cols_of(k);
       __builtin_amdgcn_sched_barrier(0);
+      if (need_mask) {   // tiles that straddle the diagonal: exp2(-inf) = 0
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (q0 + 8 * (r >> 2) + 4 * hf + (r & 3) < key) sc[r] = -INFINITY;
+      }
       float pr[16], ds[16];
-      // Each group g of 4 consecutive queries is the 4 rows of one mask patch and this lane's
-      // key one of its columns; the four lanes of a quad share the patch column, so each
-      // generates the patch of group g = lane%4 only and the quad exchanges the words.
       uint32_t own[4];
       const bool patches = DROP && !(EDGE && (s & 3));   // groups of 4 queries are rows of patches
-      if (patches) drop_patch(drop, ((uint32_t)(sbase + q0 + sb * 32 + 4 * hf) >> 2) + 2u * (uint32_t)(lane & 3), (uint32_t)key >> 2, own);
+      if (patches) drop_patch(drop, ((uint32_t)(sbase + q0 + 4 * hf) >> 2) + 2u * (uint32_t)(lane & 3), (uint32_t)key >> 2, own);
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int ql = sb * 32 + 8 * g + 4 * hf;  // 4 consecutive queries of the tile
-        const floatx4 l4 = *reinterpret_cast<const floatx4*>(&sstat[0][ql]);
-        const floatx4 d4 = *reinterpret_cast<const floatx4*>(&sstat[1][ql]);
+        const int ql = 8 * g + 4 * hf;  // 4 consecutive queries of the tile
+        const floatx4 l4 = *reinterpret_cast<const floatx4*>(&sstat[st][0][ql]);
+        floatx4 d4 = {0.f, 0.f, 0.f, 0.f};
+        if (DROP) d4 = *reinterpret_cast<const floatx4*>(&sstat[st][1][ql]);
         uint32_t mw[4];
         if (patches) {
 #pragma unroll
@@ -677,49 +703,35 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int r = 4 * g + e;
-          float p = __builtin_amdgcn_exp2f(sc[r] * scale_log2e - l4[e]);
-          if (need_mask && (q0 + ql + e < key)) p = 0.f;
+          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, -l4[e]));
           float f = 1.0f;
           if (DROP) f = drop_keep(drop, mw[e], key & 3) ? drop.scale : 0.f;
           pr[r] = p * f;
-          ds[r] = p * (dp[r] * f - d4[e]);
+          ds[r] = DROP ? p * (dp[r] * f + d4[e]) : p * dp[r];
         }
       }
-      __builtin_amdgcn_sched_barrier(0);
-      if (AHEAD && sb == 0) {  // the second half's row fragments: in flight during this half's dV/dK products
-        fetch_rows(1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      bf16x8 pf, df, pl, dl;
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const bf16x8 pf = at_pack8(&pr[8 * t]);
-        const bf16x8 df = at_pack8(&ds[8 * t]);
-#pragma unroll
-        for (int db = 0; db < C::DB; ++db) {
-          at_mfma_acc(dv[db], gtr[t][db], pf);
-          at_mfma_acc(dk[db], qtr[t][db], df);
+      for (int k = 0; k < NP; ++k) {
+        const int t = k / C::DB, db = k % C::DB;
+        if (db == 0) {
+          pf = at_pack8(&pr[8 * t]);
+          df = at_pack8(&ds[8 * t]);
+          if constexpr (EDGE) { pl = at_pack8_rest(&pr[8 * t], pf); dl = at_pack8_rest(&ds[8 * t], df); }
         }
+        dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gtr[k % PF], pf, dv[db], 0, 0, 0);
+        dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qtr[k % PF], df, dk[db], 0, 0, 0);
         if constexpr (EDGE) {
-          const bf16x8 pl = at_pack8_rest(&pr[8 * t], pf);
-          const bf16x8 dl8 = at_pack8_rest(&ds[8 * t], df);
-#pragma unroll
-          for (int db = 0; db < C::DB; ++db) {
-            at_mfma_acc(dv[db], gtr[t][db], pl);
-            at_mfma_acc(dk[db], qtr[t][db], dl8);
-          }
+          dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gtr[k % PF], pl, dv[db], 0, 0, 0);
+          dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qtr[k % PF], dl, dk[db], 0, 0, 0);
         }
+        if (k + PF < NP) cols_of(k + PF);   // into the registers just multiplied
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    // The products above are opaque to the compiler, which therefore adds no wait states
-    // between them and anything it may place around the loop's back-edge that reads dk / dv
-    // (a copy, a spill).  Settle once per tile: the accumulators are architecturally current
-    // at every point outside the run of products.
-    at_mfma_settle();
-    __builtin_amdgcn_sched_barrier(0);
+    if (qb > qs) store(st ^ 1);
+    __syncthreads();
   }
-  at_mfma_settle();
-  __builtin_amdgcn_sched_barrier(0);  // the reads of dK/dV below stay below the wait
   const uint32_t bad = EDGE ? ar_bad_rows(at_probe<D>(dk, at_probe<D>(dv, 0.f))) : 0;
   if (!EDGE || (key < s && !(bad >> (ar_lane() & 31) & 1))) {
     bf16* krow = dqkv + ((int64_t)bi * s + key) * ld + h + head * cols;
@@ -736,7 +748,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma_kernel(const bf16* __re
         *reinterpret_cast<bf16x4*>(vrow + db * 32 + 8 * g + 4 * hf) = c;
       }
   }
-  if constexpr (EDGE) at_bad_rows(bad, kw_s, s, heads, [&](int i, int ln, int hd, int b) {
+  if constexpr (EDGE) at_bad_rows(bad, kw, s, heads, [&](int i, int ln, int hd, int b) {
     const int64_t at = (int64_t)b * s * heads * d + hd * d, at3 = 3 * at - 2 * hd * d;
     ar_dkv<bf16>(qkv + at3, dctx + at, lse, delta, dqkv + at3, i, s, heads * d, d, CAUSAL, scale, ((int64_t)b * heads + hd) * s, drop, ln);
   });

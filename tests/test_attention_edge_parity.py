@@ -99,3 +99,34 @@ def test_other_forms_leave_shapes_they_do_not_take_to_the_row_kernels(variant, d
 def test_attention_edge_rising_row_maxima(b, s, heads, d, causal):
     """Both branches of the thresholded rescale after the first block, as for the whole tiles."""
     run_attention_case("bf16", b, s, heads, d, causal, variant=2, seed=70 + d, key_ramp=(0.5, 4.0))
+
+
+@pytest.mark.parametrize("variant,b,s,heads,d,causal", [
+    (2, 2, 31, 1, 64, 1), (2, 1, 32, 2, 128, 0), (2, 2, 97, 1, 96, 1), (2, 1, 161, 2, 128, 1), (2, 2, 225, 1, 32, 0), (2, 1, 289, 2, 88, 0),
+    (1, 2, 128, 3, 64, 0), (1, 1, 384, 1, 96, 1), (1, 2, 256, 2, 128, 1), (1, 1, 512, 1, 128, 0),
+])
+def test_attention_steps_of_32_queries(variant, b, s, heads, d, causal):
+    """The key side walks 32 queries at a time, last to first: one step, a last step of one row, first and last waves that start or
+    end elsewhere than their workgroup.  Same bound as the other shapes."""
+    run_attention_case("bf16", b, s, heads, d, causal, variant=variant, seed=110 + d)
+
+
+@pytest.mark.parametrize("d", [64, 96, 128])
+def test_attention_on_whole_tiles_takes_any_alignment(d):
+    """Tensors that start at an odd element: bit for bit the results of aligned ones."""
+    b, s, heads = 1, 128, 2
+    T, h = b * s, heads * d
+
+    def shifted(t):
+        buf = torch.empty(t.numel() + 9, dtype=t.dtype, device="cuda")
+        buf[1:1 + t.numel()] = t.reshape(-1)
+        return buf[1:1 + t.numel()].view(t.shape)
+
+    qkv, dctx = rnd((T, 3 * h), "bf16", 3), rnd((T, h), "bf16", 4)
+    got = []
+    for q, g in ((qkv, dctx), (shifted(qkv), shifted(dctx))):
+        ctx, dqkv, lse = torch.empty_like(dctx), torch.empty_like(qkv), torch.empty(heads * s, device="cuda")
+        B.op_attention_fwd(q, ctx, lse, b, s, heads, d, 1, variant=1)
+        B.op_attention_bwd(q, ctx, lse, g, dqkv, torch.empty_like(lse), b, s, heads, d, 1, variant=1)
+        got.append((ctx, lse, dqkv))
+    assert all(torch.equal(x, y) for x, y in zip(*got))
