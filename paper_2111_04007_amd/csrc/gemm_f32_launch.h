@@ -4,6 +4,7 @@
 
 #include "gemm_cut.h"
 #include "gemm_f32.h"
+#include "gemm_f32_few.h"
 
 namespace varuna {
 
@@ -35,6 +36,15 @@ inline hipError_t gc_launch(const T* a, int64_t lda, const T* b, int64_t ldb, in
   return hipGetLastError();
 }
 
+template <bool BK, int MODE>
+inline hipError_t few_launch(const float* a, const float* b, int64_t M, int64_t N, int64_t K, const EpiArgs<float>& epi, hipStream_t st) {
+  const dim3 grid((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16)), block(kFewWaves * kWave);
+  if (K <= 128) hipLaunchKernelGGL((gemm_f32_few_kernel<BK, MODE, 1>), grid, block, 0, st, a, b, (int)M, (int)N, (int)K, epi);
+  else if (K <= 256) hipLaunchKernelGGL((gemm_f32_few_kernel<BK, MODE, 2>), grid, block, 0, st, a, b, (int)M, (int)N, (int)K, epi);
+  else hipLaunchKernelGGL((gemm_f32_few_kernel<BK, MODE, 4>), grid, block, 0, st, a, b, (int)M, (int)N, (int)K, epi);
+  return hipGetLastError();
+}
+
 template <typename T, int MODE, bool AK, bool BK>
 inline hipError_t gf_launch(const T* a, int64_t lda, const T* b, int64_t ldb, int64_t M, int64_t N, int64_t K,
                             const EpiArgs<T>& epi, hipStream_t st) {
@@ -49,6 +59,9 @@ inline hipError_t gf_launch(const T* a, int64_t lda, const T* b, int64_t ldb, in
     case GC_NONE: break;
   }
   if constexpr (sizeof(T) == 4) {
+    if constexpr (AK) {
+      if (vec && gf_few(M, N, K)) return few_launch<BK, MODE>(a, b, M, N, K, epi, st);
+    }
     if (gf_small_tile(t32, t64)) return gf_launch_tile<MODE, AK, BK, 32, 32, 32, 32, 8, 128>(vec, a, lda, b, ldb, M, N, K, epi, st);
     return gf_launch_tile<MODE, AK, BK, 64, 64, 32, 32, 1, 64>(vec, a, lda, b, ldb, M, N, K, epi, st);
   }
