@@ -197,6 +197,14 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * KS * kWave) void gemm_f32_k
   gf_tile<MODE, AK, BK, BM, BN, WM, WN, KS, BKT, VEC>(a, lda, b, ldb, M, N, K, tiles_m, tiles_n, epi, logical);
 }
 
+// A layer norm in front of a product (gemm_f32_few.h): parameters, and where the normalised rows, the statistics (mean, then reciprocal standard
+// deviation) and a copy of the rows go (each may be null).
+struct LnIn {
+  const float *gamma, *beta;
+  float *y, *stats, *copy;
+  float eps;
+};
+
 // Several weight gradients out[M,N] += a[K,M]^T b[K,N] over the same K in one launch: the products of a small stage are a few
 // microseconds each, less than what lies between two launches, and those of a larger one each end with a partly filled
 // round.  Job j owns workgroups first[j] .. first[j+1]-1, a multiple of 8 of them; those past its last tile end at once.
@@ -245,6 +253,11 @@ inline bool gf_few(int64_t M, int64_t N, int64_t K) {
 template <typename T>
 hipError_t launch_gemm_f32(int op, int mode, const T* a, const T* b, int64_t M, int64_t N, int64_t K, const EpiArgs<T>& epi,
                            hipStream_t st);
+
+// The same product in front of which a layer norm of a's rows stands (EPI_BIAS and EPI_BIAS_GELU), in one launch, where it takes the shape and the
+// tensors (ln_gemm_f32_takes).  A norm on its own is a launch of 3 us, most of it latency: steps of two layers 128 wide, four micro-batches of 128 tokens, 668 -> 598 us.
+bool ln_gemm_f32_takes(const float* b, const LnIn& ln, int64_t M, int64_t N, int64_t K);
+hipError_t launch_ln_gemm_f32(int mode, const float* a, const float* b, int64_t M, int64_t N, int64_t K, const EpiArgs<float>& epi, const LnIn& ln, hipStream_t st);
 
 // `n` weight gradients over K (all of a layer, of several layers), in one launch of gemm_f32.hip.  One by one against one launch:
 // two layers 128 wide over 128 tokens 8 x 3.9 against 6.5 us, one layer 768 wide over 1000 tokens 206 against 164 us.

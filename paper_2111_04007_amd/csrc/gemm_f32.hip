@@ -4,6 +4,18 @@ namespace varuna {
 
 template hipError_t launch_gemm_f32<float>(int, int, const float*, const float*, int64_t, int64_t, int64_t, const EpiArgs<float>&, hipStream_t);
 
+bool ln_gemm_f32_takes(const float* b, const LnIn& ln, int64_t M, int64_t N, int64_t K) {
+  const void* p[] = {b, ln.gamma, ln.beta, ln.y, ln.copy};   // (a: buffer loads, which take any float's address)
+  for (const void* q : p)
+    if ((reinterpret_cast<uintptr_t>(q) & 15) != 0) return false;
+  return K % 4 == 0 && K <= 512 && gf_few(M, N, K);
+}
+hipError_t launch_ln_gemm_f32(int mode, const float* a, const float* b, int64_t M, int64_t N, int64_t K, const EpiArgs<float>& epi, const LnIn& ln, hipStream_t st) {
+  if (mode == EPI_BIAS) return few_launch<true, EPI_BIAS, true>(a, b, M, N, K, epi, ln, st);
+  if (mode == EPI_BIAS_GELU) return few_launch<true, EPI_BIAS_GELU, true>(a, b, M, N, K, epi, ln, st);
+  return hipErrorInvalidValue;
+}
+
 // Odd rows: from 128 tokens on as launch_gemm_cut_group, below in fp32 products (gc_kind).  Micro-batches of whole steps (us, 32x32 on 4
 // waves / 64x64 on 4 / 64x64 on 1 / fp32 products): 66 wide over 2048 tokens 279 / 293 / 352 / 299, 258 wide (783 tiles) over 512 401 / 413 / 414 / 453, 390 wide
 // (2041) over 8192 2180 / 2169 / 2220 / 3401, 774 wide (7250) over 512 895 / 892 / 849 / 1131.

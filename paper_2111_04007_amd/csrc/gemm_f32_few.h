@@ -6,6 +6,9 @@
 // unit u, the products take them in the same order on both sides), what the epilogue reads is fetched with them, and the only barrier is the
 // one where the eight sums meet.  Tiles of 16x16 rather than 32x32: four times as many workgroups, each with half as much
 // to load (64 KB at K = 512, 0.4 us of a CU's path from L2).
+//
+// LN: A is the layer norm of x, whose statistics the workgroup takes from its own registers on the way (two more barriers); the workgroups of the
+// first tile column store the normalised rows, the statistics and a copy of x where they are wanted.  K up to 512: the rows stay in registers.
 #pragma once
 #include "common.h"
 #include "gemm_f32.h"
@@ -45,10 +48,11 @@ struct FewLoader {
   }
 };
 
-template <bool BK, int MODE, int U>
+template <bool BK, int MODE, int U, bool LN>
 __global__ __launch_bounds__(kFewWaves* kWave) void gemm_f32_few_kernel(const float* __restrict__ a, const float* __restrict__ b, int M, int N, int K,
-                                                                        EpiArgs<float> epi) {
+                                                                        EpiArgs<float> epi, LnIn ln) {
   __shared__ float red[kFewWaves][256];
+  __shared__ float part[LN ? 2 : 1][kFewWaves][16];
   const int tid = threadIdx.x, lane = tid % kWave, i16 = lane & 15, quad = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
@@ -59,6 +63,15 @@ __global__ __launch_bounds__(kFewWaves* kWave) void gemm_f32_few_kernel(const fl
   fa.init(a, M, K, m);
   fb.init(b, N, K, n);
   fa.load(wave, quad, K);
+  floatx4 fg[LN ? U : 1], fs[LN ? U : 1];
+  if constexpr (LN) {
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const int k = (wave + kFewWaves * j) * 16 + 4 * quad, kk = k < K ? k : 0;
+      fg[j] = *reinterpret_cast<const floatx4*>(ln.gamma + kk);
+      fs[j] = *reinterpret_cast<const floatx4*>(ln.beta + kk);
+    }
+  }
   fb.load(wave, quad, K);
   // Thread t < 256 finishes element t of the tile: row 4 * (t % 64 / 16) + t / 64, column t % 16.
   const int om = m0 + 4 * quad + wave, on = n0 + i16;
@@ -69,6 +82,47 @@ __global__ __launch_bounds__(kFewWaves* kWave) void gemm_f32_few_kernel(const fl
   }
   __builtin_amdgcn_sched_barrier(0);   // everything is on its way before the first wait
 
+  if constexpr (LN) {
+    // mean, then the centred second moment, as in norm_reduce.h
+    auto row_sum = [&](float s, int which) {
+      s += __shfl_xor(s, 16, kWave);
+      s += __shfl_xor(s, 32, kWave);
+      if (quad == 0) part[which][wave][i16] = s;
+      __syncthreads();
+      float t = 0.f;
+#pragma unroll
+      for (int w = 0; w < kFewWaves; ++w) t += part[which][w][i16];
+      return t;
+    };
+    const bool store = blockIdx.x == 0 && m0 + i16 < M;
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s += fa.v[j][e];
+    const float mean = row_sum(s, 0) / (float)K;
+    s = 0.f;
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const int k = (wave + kFewWaves * j) * 16 + 4 * quad;
+      if (k < K && store && ln.copy) *reinterpret_cast<floatx4*>(ln.copy + (int64_t)m * K + k) = fa.v[j];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        fa.v[j][e] = k < K ? fa.v[j][e] - mean : 0.f;
+        s += fa.v[j][e] * fa.v[j][e];
+      }
+    }
+    const float rstd = 1.0f / sqrtf(row_sum(s, 1) / (float)K + ln.eps);
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const int k = (wave + kFewWaves * j) * 16 + 4 * quad;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) fa.v[j][e] = k < K ? fg[j][e] * (fa.v[j][e] * rstd) + fs[j][e] : 0.f;
+      if (k < K && store && ln.y) *reinterpret_cast<floatx4*>(ln.y + (int64_t)m * K + k) = fa.v[j];
+    }
+    if (store && ln.stats && tid < 16) { ln.stats[m] = mean; ln.stats[M + m] = rstd; }
+  }
+
   floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
   auto products = [&](const floatx4 (&x)[U], const floatx4 (&y)[U]) {
 #pragma unroll
@@ -76,7 +130,7 @@ __global__ __launch_bounds__(kFewWaves* kWave) void gemm_f32_few_kernel(const fl
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j][e], y[j][e], acc[j & 1], 0, 0, 0);
   };
-  if constexpr (U == 4) {   // longer reductions: the next 512 k in flight during the products of these
+  if constexpr (!LN && U == 4) {   // longer reductions: the next 512 k in flight during the products of these
     na = fa;
     nb = fb;
     int u = wave + kFewWaves * U;

@@ -36,12 +36,12 @@ inline hipError_t gc_launch(const T* a, int64_t lda, const T* b, int64_t ldb, in
   return hipGetLastError();
 }
 
-template <bool BK, int MODE>
-inline hipError_t few_launch(const float* a, const float* b, int64_t M, int64_t N, int64_t K, const EpiArgs<float>& epi, hipStream_t st) {
+template <bool BK, int MODE, bool LN>
+inline hipError_t few_launch(const float* a, const float* b, int64_t M, int64_t N, int64_t K, const EpiArgs<float>& epi, const LnIn& ln, hipStream_t st) {
   const dim3 grid((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16)), block(kFewWaves * kWave);
-  if (K <= 128) hipLaunchKernelGGL((gemm_f32_few_kernel<BK, MODE, 1>), grid, block, 0, st, a, b, (int)M, (int)N, (int)K, epi);
-  else if (K <= 256) hipLaunchKernelGGL((gemm_f32_few_kernel<BK, MODE, 2>), grid, block, 0, st, a, b, (int)M, (int)N, (int)K, epi);
-  else hipLaunchKernelGGL((gemm_f32_few_kernel<BK, MODE, 4>), grid, block, 0, st, a, b, (int)M, (int)N, (int)K, epi);
+  if (K <= 128) hipLaunchKernelGGL((gemm_f32_few_kernel<BK, MODE, 1, LN>), grid, block, 0, st, a, b, (int)M, (int)N, (int)K, epi, ln);
+  else if (K <= 256) hipLaunchKernelGGL((gemm_f32_few_kernel<BK, MODE, 2, LN>), grid, block, 0, st, a, b, (int)M, (int)N, (int)K, epi, ln);
+  else hipLaunchKernelGGL((gemm_f32_few_kernel<BK, MODE, 4, LN>), grid, block, 0, st, a, b, (int)M, (int)N, (int)K, epi, ln);
   return hipGetLastError();
 }
 
@@ -60,7 +60,7 @@ inline hipError_t gf_launch(const T* a, int64_t lda, const T* b, int64_t ldb, in
   }
   if constexpr (sizeof(T) == 4) {
     if constexpr (AK) {
-      if (vec && gf_few(M, N, K)) return few_launch<BK, MODE>(a, b, M, N, K, epi, st);
+      if (vec && gf_few(M, N, K)) return few_launch<BK, MODE, false>(a, b, M, N, K, epi, LnIn{}, st);
     }
     if (gf_small_tile(t32, t64)) return gf_launch_tile<MODE, AK, BK, 32, 32, 32, 32, 8, 128>(vec, a, lda, b, ldb, M, N, K, epi, st);
     return gf_launch_tile<MODE, AK, BK, 64, 64, 32, 32, 1, 64>(vec, a, lda, b, ldb, M, N, K, epi, st);

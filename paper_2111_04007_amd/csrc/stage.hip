@@ -383,6 +383,24 @@ struct StageOps {
     return D.causal ? dense * 0.5 : dense;
   }
 
+  // A layer norm (parameters from `norm` on) of x and the product that follows it (weight and bias from `weight` on).  x_in: where x still
+  // has to be taken from (and stored to x), or null.  save: xn and stats are read later.
+  hipError_t norm_gemm(int l, int norm, int weight, int mode, int64_t N, T* x, const T* x_in, T* xn, float* stats, bool save, T* out, T* aux_out) {
+    hipError_t e;
+    const T* from = x_in ? x_in : x;
+    T* copy = x_in ? x : nullptr;
+    if constexpr (std::is_same<T, float>::value) {
+      const LnIn ln{param(l, norm), param(l, norm + 1), save ? xn : nullptr, stats, copy, D.eps};
+      if (!S->prof_on && ln_gemm_f32_takes(param(l, weight), ln, D.T, N, D.h))   // (timed by kind of kernel they are launches of their own)
+        return launch_ln_gemm_f32(mode, from, param(l, weight), D.T, N, D.h, EpiArgs<float>{param(l, weight + 1), nullptr, out, aux_out, nullptr, N, DropArgs{}}, ln, st);
+    }
+    {
+      Bracket br(S, st, VARUNA_K_LN_FWD, 0, 2.0 * D.E * sizeof(T));
+      if ((e = launch_layernorm_fwd<T>(from, param(l, norm), param(l, norm + 1), xn, stats, D.T, D.h, D.eps, st, copy))) return e;
+    }
+    return gemm(VARUNA_K_GEMM_FWD, GEMM_FWD, mode, D.T, N, D.h, xn, param(l, weight), param(l, weight + 1), nullptr, out, aux_out, nullptr);
+  }
+
   // One layer forward.  rs: ring slot of the wgrad operands (xn1, ctx, xn2, g).
   // save: also store stats, lse, u.  skip_mlp2: stop after GeLU.  x_in: where x still has to be taken from (its first reader,
   // the LayerNorm, stores it to x), or null.
@@ -395,21 +413,13 @@ struct StageOps {
     float* stats1 = save ? wsp<float>(A.stats1) : nullptr;
     float* stats2 = save ? wsp<float>(A.stats2) : nullptr;
     float* lse = save ? wsp<float>(A.lse) : nullptr;
-    {
-      Bracket br(S, st, VARUNA_K_LN_FWD, 0, 2.0 * D.E * sizeof(T));
-      if ((e = launch_layernorm_fwd<T>(x_in ? x_in : x, param(l, VARUNA_P_LN1_G), param(l, VARUNA_P_LN1_B), xn1, stats1, T_, D.h, D.eps, st, x_in ? x : nullptr))) return e;
-    }
-    if ((e = gemm(VARUNA_K_GEMM_FWD, GEMM_FWD, EPI_BIAS, T_, 3 * D.h, D.h, xn1, param(l, VARUNA_P_WQKV), param(l, VARUNA_P_BQKV), nullptr, qkv, nullptr, nullptr))) return e;
+    if ((e = norm_gemm(l, VARUNA_P_LN1_G, VARUNA_P_WQKV, EPI_BIAS, 3 * D.h, x, x_in, xn1, stats1, save, qkv, nullptr))) return e;
     {
       Bracket br(S, st, VARUNA_K_ATTN_FWD, attn_flops_fwd(), 4.0 * D.E * sizeof(T));
       if ((e = AttnDispatch<T>::fwd(0, qkv, ctx, lse, D.b, D.s, D.a, D.d, D.causal, drop_args(DROP_SITE_ATTN, l, mb), st))) return e;
     }
     if ((e = gemm(VARUNA_K_GEMM_FWD, GEMM_FWD, EPI_BIAS_RES, T_, D.h, D.h, ctx, param(l, VARUNA_P_WO), param(l, VARUNA_P_BO), x, x1, nullptr, nullptr, drop_args(DROP_SITE_PROJ, l, mb)))) return e;
-    {
-      Bracket br(S, st, VARUNA_K_LN_FWD, 0, 2.0 * D.E * sizeof(T));
-      if ((e = launch_layernorm_fwd<T>(x1, param(l, VARUNA_P_LN2_G), param(l, VARUNA_P_LN2_B), xn2, stats2, T_, D.h, D.eps, st))) return e;
-    }
-    if ((e = gemm(VARUNA_K_GEMM_FWD, GEMM_FWD, EPI_BIAS_GELU, T_, D.f, D.h, xn2, param(l, VARUNA_P_W1), param(l, VARUNA_P_B1), nullptr, g, save ? u : nullptr, nullptr))) return e;
+    if ((e = norm_gemm(l, VARUNA_P_LN2_G, VARUNA_P_W1, EPI_BIAS_GELU, D.f, x1, nullptr, xn2, stats2, save, g, save ? u : nullptr))) return e;
     if (skip_mlp2) return hipSuccess;
     return gemm(VARUNA_K_GEMM_FWD, GEMM_FWD, EPI_BIAS_RES, T_, D.h, D.f, g, param(l, VARUNA_P_W2), param(l, VARUNA_P_B2), x1, y, nullptr, nullptr, drop_args(DROP_SITE_MLP, l, mb));
   }

@@ -3,7 +3,8 @@ limits that send a product there."""
 import pytest
 import torch
 
-from paper_2111_04007_amd import binding as B
+from paper_2111_04007_amd import binding as B, synth
+from tests import parity_util as U
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +55,21 @@ def test_values_behind_the_operands_stay_out(op):
     B.op_gemm(op, 0, a, b, out, bias=bias if op == 0 else None, M=M, N=N, K=K)
     want = a.double() @ (b.double().t() if op == 0 else b.double())
     assert float((out.double() - want).norm() / want.norm()) <= 1e-6
+
+
+@pytest.mark.parametrize("h,heads,s,b,f", [(100, 5, 33, 1, 0), (128, 2, 17, 2, 40), (256, 4, 50, 1, 0), (260, 2, 16, 1, 516), (512, 8, 31, 1, 0), (516, 6, 20, 1, 0), (42, 3, 20, 1, 0)])
+def test_layer_norm_in_front_of_a_product(h, heads, s, b, f):
+    """Forward, recompute and backward of stages whose norms join the product that follows (widths up to 512 in whole 16-byte pieces) and of two whose
+    do not, at the fp32 path's tolerance; inputs that start at an odd element give the same bits."""
+    cfg = synth.StageConfig("norm-product", 2, h, heads, s, b, 2, f or 4 * h, True, "f32", 0.05, seed=h)
+    params = synth.make_params(cfg, perturb=0.05)
+    xs, dys = synth.make_activations(cfg, 2)
+    st, ys, dxs = U.gpu_stage_step(cfg, params, xs, dys)
+    U.compare_step(cfg, st, ys, dxs, U.oracle_stage_step(cfg, params, xs, dys), label=f"h={h}")
+    x = torch.as_tensor(xs[0]).reshape(b * s, h).float().cuda()
+    odd = torch.empty(x.numel() + 1, device="cuda")[1:].view_as(x).copy_(x)
+    y, z = torch.empty_like(x), torch.empty_like(x)
+    st.forward(0, x, y)
+    st.forward(1, odd, z)
+    assert torch.equal(y, z)
+    st.close()
