@@ -61,6 +61,25 @@ template <typename T>
 hipError_t launch_attention_bwd_f32(const T* qkv, const T* ctx, const float* lse, const T* dctx, T* dqkv, float* delta, int b,
                                     int s, int heads, int d, int causal, const DropArgs& drop, hipStream_t st);
 
+// fp32 in tiles of 16 (attention_f32_16.h) against tiles of 32: half the rows per workgroup, so twice as many workgroups with half a chain each, for twice
+// the operand traffic per product.  Under the causal mask it is the faster form at every size measured; without it where it takes fewer
+// rounds of 256 workgroups in rows, or rows are short (up to 256), and where those two are equal forward above d = 96 and backward up to it.  us,
+// forward and backward, 32 (or one wave per row) / 16: 4 heads of 64 over 64 tokens 6.9 / 4.0, 13.8 / 6.3; 24 of 64 over 500 causal 25 / 19,
+// 77 / 56 and full (768 workgroups) 34 / 27, 121 / 90; 128 of 64 over 1000 causal 237 / 221, 1033 / 905; 64 of 128 over 64 15 / 6.5, 51 / 19;
+// 2 of 128 over 2000 160 / 64, 575 / 184.  Full, equal rounds: 12 of 64 over 512 19.7 / 20.3, 67 / 55, 256 of 64 over 512 239 / 292, 991 / 942, 8 of
+// 128 over 1000 86 / 64, 295 / 306.
+// Where one wave per row was the choice for up to 255 rows, or up to 512 above d = 64, it still is: such calls hold those kernels' bits.
+inline bool attn_f32_16(bool backward, int b, int s, int heads, int d, bool causal) {
+  const int64_t rows = (int64_t)b * heads * s, pairs = (int64_t)b * heads;
+  if (d % 4 != 0 || d > 128 || !attn_grid_ok(b, heads)) return false;
+  if (rows <= (d <= 64 ? 255 : 512) && attn_rows_sooner(true, true, backward, b, s, heads, d)) return false;
+  const int64_t rounds16 = (pairs * ((s + 15) / 16) + 255) / 256, rounds32 = (pairs * ((s + 31) / 32) + 255) / 256;
+  return causal || s <= 256 || rounds16 < 2 * rounds32 || (backward ? d <= 96 : d > 96);
+}
+hipError_t launch_attention_fwd_f32_16(const float* qkv, float* ctx, float* lse, int b, int s, int heads, int d, int causal, const DropArgs& drop, hipStream_t st);
+hipError_t launch_attention_bwd_f32_16(const float* qkv, const float* ctx, const float* lse, const float* dctx, float* dqkv, float* delta, int b, int s,
+                                        int heads, int d, int causal, const DropArgs& drop, hipStream_t st);
+
 template <typename T>
 hipError_t launch_attention_fwd_simple(const T* qkv, T* ctx, float* lse, int b, int s, int heads, int d, int causal,
                                        const DropArgs& drop, hipStream_t st);

@@ -136,11 +136,12 @@ __device__ __forceinline__ void ar_dq(const T* __restrict__ base, const T* __res
   ar_store(dqkv + i * ld, a0 * scale, a1 * scale, d, lane);
 }
 
-// dK and dV of key `key`; dqkv: the head's Q columns of the first token, as in base.
+// dK and dV of key `key`; dqkv: the head's Q columns of the first token, as in base.  ctx: null, or where delta is not in place yet, the head's
+// context columns it is summed from.
 template <typename T>
 __device__ __forceinline__ void ar_dkv(const T* __restrict__ base, const T* __restrict__ dctx, const float* __restrict__ lse,
                                        const float* __restrict__ delta, T* __restrict__ dqkv, int key, int s, int h, int d, bool causal,
-                                       float scale, int64_t stat, const DropArgs& drop, int lane) {
+                                       float scale, int64_t stat, const DropArgs& drop, int lane, const T* __restrict__ ctx = nullptr) {
   const int64_t ld = 3 * (int64_t)h;
   const T *k = base + h + key * ld, *v = k + h;
   float k0_ = 0.f, k1_ = 0.f, v0_ = 0.f, v1_ = 0.f;
@@ -152,7 +153,8 @@ __device__ __forceinline__ void ar_dkv(const T* __restrict__ base, const T* __re
       float f = 1.0f;
       if (drop.thr != 0) f = drop_keep(drop, drop_row_word(drop, (uint32_t)(stat + i), (uint32_t)key >> 2), key & 3) ? drop.scale : 0.f;
       pp = pr * f;
-      ds = pr * (ar_dot(dctx + (int64_t)i * h, v, d) * f - delta[stat + i]);
+      const float dl = ctx ? ar_dot(dctx + (int64_t)i * h, ctx + (int64_t)i * h, d) : delta[stat + i];
+      ds = pr * (ar_dot(dctx + (int64_t)i * h, v, d) * f - dl);
     }
     const int n = s - i0 < kWave ? s - i0 : kWave;
     ar_weighted(k0_, k1_, base + i0 * ld, ld, n, ds, d, lane);
