@@ -660,8 +660,12 @@ __device__ __forceinline__ void dg_tile(
     // in flight per CU (the accumulators own the register file), so the old tile is
     // streamed into the now idle LDS with the same direct loads as the operands: each wave
     // pulls its own sub-tile in passes of 32 rows x WN floats, double-buffered, adds its
-    // accumulators and stores.  Chunks of 16 B are XOR-swizzled by the row so that 16 lanes
-    // reading one column of 16 rows hit distinct banks.
+    // accumulators in place and stores the sums out of LDS, consecutive lanes along a row.  Chunks of 16 B are
+    // XOR-swizzled by the row so that 16 lanes reading one column of 16 rows hit distinct banks.
+    // Bound by memory (old values in, sums out).  Stored straight from the accumulators' layout an instruction wrote 32 bytes of
+    // each of 32 rows; as whole rows, before / after (us, += over 2048 tokens, operands out of cache): 12288x3072 210 / 196 on 256x256
+    // tiles, 194 / 188 on 128x128; 4096^2 84 / 79, 91 / 88; 8192^2 340 / 322, 333 / 323.  Without any epilogue 12288x3072 takes
+    // 143 and 140, and 302 MB in and out take 66 by themselves.  Slower still: stores past the caches, fp32 atomics, more passes in registers.
     constexpr int CPR = WN / 4;                 // 16-byte chunks per row of the pass block
     constexpr int PASS_BYTES = 32 * WN * 4;
     constexpr int NINS = PASS_BYTES / 1024;     // direct loads per pass
@@ -696,20 +700,31 @@ __device__ __forceinline__ void dg_tile(
       if constexpr (MODE == EPI_ACCUM_F32) {
         if (i + 1 < TM) __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(NINS)); else __builtin_amdgcn_s_waitcnt(DG_WAIT_VM(0));
       }
-      const unsigned char* buf = mybuf + (i & 1) * PASS_BYTES;
+      unsigned char* buf = mybuf + (i & 1) * PASS_BYTES;
       float* crow = cbase + (int64_t)(i * 32 + frow) * epi.ldc;
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int c = j * 8 + g * 2 + fchunk;
+          floatx4* slot = reinterpret_cast<floatx4*>(buf + frow * (WN * 4) + ((c ^ (frow & 15)) << 4));
           floatx4 v = {0.f, 0.f, 0.f, 0.f};   // EPI_STORE_F32: a partial sum of its own, nothing to add to
-          if constexpr (MODE == EPI_ACCUM_F32)
-            v = *reinterpret_cast<const floatx4*>(buf + frow * (WN * 4) + ((c ^ (frow & 15)) << 4));
+          if constexpr (MODE == EPI_ACCUM_F32) v = *slot;
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] += acc[i][j][g * 4 + e];
-          if (!EDGE || (i * 32 + frow < rows_left && c * 4 < cols_left)) *reinterpret_cast<floatx4*>(crow + c * 4) = v;
+          if constexpr (MODE == EPI_ACCUM_F32) *slot = v;
+          else if (!EDGE || (i * 32 + frow < rows_left && c * 4 < cols_left)) *reinterpret_cast<floatx4*>(crow + c * 4) = v;
         }
+      if constexpr (MODE == EPI_ACCUM_F32) {
+        __builtin_amdgcn_s_waitcnt(DG_WAIT_LGKM0);
+#pragma unroll
+        for (int q = 0; q < NINS; ++q) {
+          const int slot = q * 64 + lane, row = slot / CPR, c = slot % CPR;
+          const floatx4 v = *reinterpret_cast<const floatx4*>(buf + row * (WN * 4) + ((c ^ (row & 15)) << 4));
+          if (!EDGE || (i * 32 + row < rows_left && c * 4 < cols_left))
+            *reinterpret_cast<floatx4*>(cbase + (int64_t)(i * 32 + row) * epi.ldc + c * 4) = v;
+        }
+      }
       if (MODE == EPI_ACCUM_F32 && i + 2 < TM) {
         __builtin_amdgcn_s_waitcnt(DG_WAIT_LGKM0);  // this buffer's LDS reads are done before it is refilled
         issue_pass(i + 2);
