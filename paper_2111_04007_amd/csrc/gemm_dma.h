@@ -796,6 +796,8 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_group_kernel(DgGroup g, 
 //   20: 128x256, 21: 256x128, 4 waves, three stages of both operands (LS 5)
 //   24: 128x192 in that form, forward only; the library takes it in place of 20 where dg_narrow says so
 //   22, 23: as 19, 18 for sizes that are no multiples of the tile (EDGE)
+// What a debug query reports is dg_pick's and dg_group_choice's word; 20 -> 24 (dg_narrow) and 128x128 -> 256x256 for weight gradients
+// (dg_wgrad_wide, dg_group_wide) are decided when the product is launched.
 // ---------------------------------------------------------------------------
 inline bool dg_variant_tile(int variant, GemmTile* t) {
   switch (variant) {
@@ -916,6 +918,17 @@ inline bool dg_narrow(int64_t M, int64_t N) {
   return 0.75 * 1.04 * (double)((narrow + 255) / 256) < (double)((wide + 255) / 256);
 }
 
+// Whether one weight gradient that dg_pick gives to 128x128 tiles because its sides are multiples of 128 but not of 256 takes the EDGE form of
+// the 256x256 ones (23): by the same rounds as dg_choose_variant, 1.05 for EDGE.  From 600 tiles on (just above one round of 128x128
+// the two are even) and from 512 on in K (shorter ones spend their time in the epilogue: 9984x1152 over 64 23.4 / 26.7).
+// Measured, 128x128 / 256x256 (us): 1920x7680 over 512, 2048, 8192 45 / 40, 99 / 74, 357 / 213; 5760x1920 over 2048 74 / 65; 9984x1152 75 / 67;
+// where 128x128 stay: 2944^2 over 1024 40 / 41, 4480^2 over 2048 118 / 129, 6016x2944 104 / 116, 1920^2 26 / 47.
+inline bool dg_wgrad_wide(int64_t M, int64_t N, int64_t K) {
+  if (dg_shape_ok(5, M, N, K, M, N) || !dg_shape_ok(23, M, N, K, M, N)) return false;
+  const int64_t t5 = ((M + 255) / 256) * ((N + 255) / 256), t7 = (M / 128) * (N / 128);
+  return K >= 512 && t7 >= 600 && (double)((t5 + 255) / 256) * 4.0 / 1.15 * 1.05 <= (double)((t7 + 511) / 512) * 2.0;
+}
+
 // Split-K for weight-gradient GEMMs whose output has too few tiles to fill the chip: the
 // reduction is cut into `splits` equal parts, each workgroup row of the grid writes its
 // partial tile (EPI_STORE_F32) and splitk_reduce adds the partials to the accumulator in a
@@ -945,6 +958,7 @@ inline int dg_wgrad_splits(int64_t M, int64_t N, int64_t K) {
 // 2048 tokens 594 / 512 and 2358 / 1853; of 530 groups 576 to 7168 wide, 1 to 4 layers, 512 to 32768 tokens, none is more than 2 %
 // slower than one by one.  Whole steps with 8 stacked micro-batches (TFLOP/s): 1024 wide 624 / 642 and 3072 wide 833 / 887, both
 // on 256x256 tiles; 1920 wide over 32768 tokens on 128x128 tiles 806 / 758.
+// (Measured while the += still stored 32-byte pieces; the larger tiles have gained more since: dg_group_wide.)
 inline int dg_group_choice(const DgJob* jobs, int n, int64_t K) {
   if (!dg_flavours().group) return 0;   // a named weight-gradient configuration runs one by one
   int64_t t5 = 0, t7 = 0;
@@ -966,6 +980,29 @@ inline int dg_group_choice(const DgJob* jobs, int n, int64_t K) {
   if (cost5 <= cost7 && (plain5 || edge)) return plain5 ? 18 : 23;
   if (K > 8192) return 0;
   return plain7 ? 19 : 22;
+}
+// Whether a group that dg_group_choice gives to 128x128 tiles takes 256x256 ones after all (18; 23 where some matrix is no multiple of them).  In us
+// per 1024 tokens and round: 256x256 tiles take 24 in whole rounds and 25 of epilogue per round's worth of tiles, 128x128 tiles 15 and
+// 10 and refill as they drain, 0.3 of a round lost at the end (fitted over 512 and more tiles; off by up to 7 %, below 2048 tokens by more).
+// Measured, 128x128 / 256x256 (us, all weight gradients): one layer 1920 wide over 4096 tokens 393 / 362, two 793 / 700, 1024 wide over 4096
+// 137 / 121, 1536 wide 261 / 231, 1280 wide, two layers over 8192 711 / 629; where 128x128 stay: 1600 wide, two layers over 2000 313 / 317,
+// 4096 wide over 1024 581 / 625.
+inline int dg_group_wide(int variant, const DgJob* jobs, int n, int64_t K) {
+  if ((variant != 19 && variant != 22) || K < 2048) return variant;
+  int64_t t5 = 0, t7 = 0;
+  bool plain = true, edge = true;
+  for (int i = 0; i < n; ++i) {
+    const int64_t M = jobs[i].M, N = jobs[i].N;
+    plain = plain && dg_shape_ok(18, M, N, K, M, N);
+    edge = edge && dg_shape_ok(23, M, N, K, M, N);
+    t5 += ((M + 255) / 256) * ((N + 255) / 256);
+    t7 += ((M + 127) / 128) * ((N + 127) / 128);
+  }
+  const double k = (double)K / 1024.0;
+  const double us256 = 25.0 * (double)t5 / 256.0 + 24.0 * k * (double)((t5 + 255) / 256);
+  const double us128 = ((double)t7 / 512.0 + 0.3) * (10.0 + 15.0 * k);
+  if (!(plain || edge) || us256 > 0.97 * us128) return variant;
+  return plain ? 18 : 23;
 }
 hipError_t launch_gemm_group(int variant, const DgJob* jobs, int n, int64_t K, hipStream_t st);   // gemm_wgrad.hip
 

@@ -280,6 +280,7 @@ template <> struct GemmDispatch<bf16> {
       v = ptr_ok ? dg_pick(op, M, N, K, lda, ldb) : -1;
       if (v == 0) v = -1;
       if (v == 20 && op == GEMM_FWD && dg_narrow(M, N)) v = 24;
+      if (v == 19 && op == GEMM_WGRAD && mode == EPI_ACCUM_F32 && splits == 1 && dg_flavours().group && dg_wgrad_wide(M, N, K)) v = 23;
     }
     if (v >= 5) {
       if (!ptr_ok || !dg_shape_ok(v, M, N, K, lda, ldb) || (v == 24 && op != GEMM_FWD)) return hipErrorInvalidConfiguration;
@@ -577,7 +578,7 @@ struct StageOps {
         const int v = wgrad_group_choice(jobs, n, K, aligned);
         if (v != 0) {
           Bracket br(S, st, VARUNA_K_GEMM_WGRAD, flops, bytes);
-          if ((e = v > 0 ? launch_gemm_group(v, jobs, n, K, st) : launch_gemm_cut_group(jobs, n, K, st))) return e;
+          if ((e = v > 0 ? launch_gemm_group(dg_group_wide(v, jobs, n, K), jobs, n, K, st) : launch_gemm_cut_group(jobs, n, K, st))) return e;
           continue;
         }
       } else {
