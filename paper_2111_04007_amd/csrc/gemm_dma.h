@@ -254,6 +254,10 @@ struct DgInterleaveMask {
 // bf16 epilogue of one wave's (TM*32) x WN sub-tile whose first output is (row0, col0), through a
 // private LDS buffer of 32 rows x WN floats.  acc[i][j][r] is row m = lane%32 of the 32x32 block,
 // column n = 8*(r/4) + 4*(lane/32) + r%4.  Columns WN of the sub-tile from block J0 on (32 or a multiple of 64 at a time).
+// Bound by memory: what it reads of the output's shape (aux_in) goes out a pass ahead, and the bias once.  Read where they are used, each of the
+// 16 or 32 row groups waited for a round trip, behind its predecessor's store.  Before / after (us, operands out of cache): residual
+// 4096x7680x1920 153 / 116, 4096x4096x1024 63 / 44, 4096x1024x1024 17.3 / 14.0, 2000x1600x1600 22.1 / 18.8 (without the residual 102, 36, 13.1, 17.9);
+// GeLU' 4096x7680x1920 135 / 121, 4096x1920x1920 46.6 / 38.3; bias alone 4096x12288x3072 247 / 236, 4096x3072x1024 32.8 / 28.6.
 template <int MODE, int TM, int TN, int WN, bool EDGE, int J0 = 0>
 __device__ __forceinline__ void dg_epilogue_bf16(floatx16 (&acc)[TM][TN], unsigned char* buf, const EpiArgs<bf16>& epi,
                                                  int64_t row0, int64_t col0, int lane, int64_t rows, int64_t cols) {
@@ -262,10 +266,22 @@ __device__ __forceinline__ void dg_epilogue_bf16(floatx16 (&acc)[TM][TN], unsign
   constexpr int SW = WN == 32 ? 7 : 15;     // chunks are XOR-permuted within groups of SW + 1
   constexpr int LPR = WN / 8;               // lanes per output row (8 columns each)
   constexpr int RPI = 64 / LPR;             // rows per store instruction
+  constexpr int NSUB = 32 / RPI;            // store instructions per pass
   const int frow = lane & 31, fchunk = lane >> 5;
   const int rrow = lane / LPR, rcol = (lane % LPR) * 8;
+  const int64_t col = col0 + J0 * 32 + rcol;
+  auto inside = [&](int i, int sub) { return !EDGE || (row0 + i * 32 + sub * RPI + rrow < rows && col < cols); };   // (cols is a multiple of 8)
+  bf16x8 bias = {}, aux[2][NSUB] = {};
+  if (epi_reads_bias(MODE) && (!EDGE || col < cols)) bias = *reinterpret_cast<const bf16x8*>(epi.bias + col);
+  auto fetch = [&](int i) {
+#pragma unroll
+    for (int sub = 0; sub < NSUB; ++sub)
+      if (inside(i, sub)) aux[i & 1][sub] = *reinterpret_cast<const bf16x8*>(epi.aux_in + (row0 + i * 32 + sub * RPI + rrow) * epi.ldc + col);
+  };
+  if constexpr (epi_reads_aux(MODE)) fetch(0);
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
+    if (epi_reads_aux(MODE) && i + 1 < TM) fetch(i + 1);
 #pragma unroll
     for (int j = 0; j < WN / 32; ++j)
 #pragma unroll
@@ -276,13 +292,12 @@ __device__ __forceinline__ void dg_epilogue_bf16(floatx16 (&acc)[TM][TN], unsign
       }
     __builtin_amdgcn_s_waitcnt(DG_WAIT_LGKM0);  // own writes landed (the buffer is private to the wave)
 #pragma unroll
-    for (int sub = 0; sub < 32 / RPI; ++sub) {
+    for (int sub = 0; sub < NSUB; ++sub) {
       const int r = sub * RPI + rrow, c0 = rcol / 4;
       const floatx4 lo = *reinterpret_cast<const floatx4*>(buf + r * ROWB + (((c0 & ~SW) | ((c0 ^ r) & SW)) << 4));
       const floatx4 hi = *reinterpret_cast<const floatx4*>(buf + r * ROWB + ((((c0 + 1) & ~SW) | (((c0 + 1) ^ r) & SW)) << 4));
       float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      if (!EDGE || (row0 + i * 32 + r < rows && col0 + J0 * 32 + rcol < cols))   // (cols is a multiple of 8)
-        gemm_epilogue8<MODE>(epi, row0 + i * 32 + r, col0 + J0 * 32 + rcol, v);
+      if (inside(i, sub)) gemm_epilogue8<MODE>(epi, row0 + i * 32 + r, col, v, bias, aux[i & 1][sub]);
     }
     __builtin_amdgcn_s_waitcnt(DG_WAIT_LGKM0);  // reads done before the next pass overwrites
   }

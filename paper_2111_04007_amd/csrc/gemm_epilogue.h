@@ -17,15 +17,18 @@ struct GemmTile { int bm, bn; };
 template <typename T> struct WgradJob { const T* a; const T* b; float* out; int M, N; };
 constexpr int kMaxGroupJobs = 16;
 
-// Eight consecutive columns of one output row.
+constexpr bool epi_reads_bias(int mode) { return mode == EPI_BIAS || mode == EPI_BIAS_GELU || mode == EPI_BIAS_RES; }
+constexpr bool epi_reads_aux(int mode) { return mode == EPI_BIAS_RES || mode == EPI_DGELU; }
+
+// Eight consecutive columns of one output row; bv: their bias, av: their aux_in, read by the caller ahead of earlier rows' stores (a store
+// may alias a later read for all the compiler knows, and a read behind it waits for the store as well).
 template <int MODE>
-__device__ __forceinline__ void gemm_epilogue8(const EpiArgs<bf16>& e, int64_t m, int64_t n, const float* acc) {
+__device__ __forceinline__ void gemm_epilogue8(const EpiArgs<bf16>& e, int64_t m, int64_t n, const float* acc, const bf16x8& bv, const bf16x8& av) {
   const int64_t idx = m * e.ldc + n;
   float o[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) o[i] = acc[i];
-  if (MODE == EPI_BIAS || MODE == EPI_BIAS_GELU || MODE == EPI_BIAS_RES) {
-    const bf16x8 bv = *reinterpret_cast<const bf16x8*>(e.bias + n);
+  if (epi_reads_bias(MODE)) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] += (float)bv[i];
   }
@@ -49,14 +52,12 @@ __device__ __forceinline__ void gemm_epilogue8(const EpiArgs<bf16>& e, int64_t m
         o[4 + i] = drop_keep(e.drop, w1, i) ? o[4 + i] * e.drop.scale : 0.f;
       }
     }
-    const bf16x8 rv = *reinterpret_cast<const bf16x8*>(e.aux_in + idx);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] += (float)rv[i];
+    for (int i = 0; i < 8; ++i) o[i] += (float)av[i];
   }
   if (MODE == EPI_DGELU) {
-    const bf16x8 uv = *reinterpret_cast<const bf16x8*>(e.aux_in + idx);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] *= gelu_logistic_grad_f((float)uv[i]);
+    for (int i = 0; i < 8; ++i) o[i] *= gelu_logistic_grad_f((float)av[i]);
   }
   bf16x8 ov;
 #pragma unroll
