@@ -253,7 +253,7 @@ def main():
 
     params, xs, dys = synth.device_random_stage(cfg, dev)
     st = B.Stage(cfg, dev, params_flat=params)
-    st.set_side_stream(torch.cuda.Stream(dev))   # the caller's second stream for the bias-gradient sums
+    st.set_side_stream(torch.cuda.Stream(dev))   # (the library may use it; at present it does not)
     if cfg.dropout_p > 0:
         st.set_dropout_seed(20211104)
     ys = torch.empty_like(xs)

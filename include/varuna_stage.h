@@ -19,11 +19,9 @@
  *     device memory in any call.
  *   - hip_stream is a hipStream_t passed as void* (NULL = the default stream).
  *     Every compute call only enqueues work and returns; nothing synchronises
- *     with the host.  All results of a call are ordered on hip_stream.  The
- *     library creates no stream: if the caller hands over a second one with
- *     varuna_stage_set_side_stream, the backward calls run their bias-gradient
- *     reductions there, forked from and joined back into hip_stream with events
- *     inside the call.  One handle is used from one stream at a time.
+ *     with the host.  All work and all results of a call are ordered on
+ *     hip_stream.  The library creates no stream.  One handle is used from one
+ *     stream at a time.
  *   - Activations are row-major [T, h], T = micro_batch * seq_len, row index
  *     = batch_index * seq_len + position.  dtype F32: all tensors fp32.
  *     dtype BF16: activations, parameters and dX are bf16; all accumulators,
@@ -150,12 +148,10 @@ varuna_status_t varuna_stage_backward_stored(varuna_stage_t* st, int32_t mb,
                                              void* dx_out /*device*/, void* hip_stream);
 
 /* Optional second stream, created and owned by the caller (default priority; it must outlive
- * the handle or be replaced by NULL first).  The bias-gradient column sums of the backward
- * calls depend on nothing downstream of them and are bound by HBM, not by the matrix cores:
- * given a side stream they overlap the GEMM chain; every backward call waits for them before
- * it returns control of hip_stream's order, so the caller never has to synchronise with the
- * side stream itself.  NULL (the state after create): everything runs on hip_stream.
- * Results are bit-identical either way. */
+ * the handle or be replaced by NULL first), or NULL (the state after create).  A backward call
+ * may run its bias-gradient column sums there, joined back into hip_stream's order before it
+ * returns.  The present kernels do not: the sums share a launch with the last LayerNorm of the
+ * layer, which is faster at every measured size.  Results are bit-identical either way. */
 varuna_status_t varuna_stage_set_side_stream(varuna_stage_t* st, void* side_stream);
 
 /* Dropout (config.dropout_p > 0) acts on the attention probabilities and on the two residual

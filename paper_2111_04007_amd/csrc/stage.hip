@@ -216,13 +216,6 @@ struct varuna_stage {
   int kept_mb = -1;  // micro-batch whose internals forward_keep left in the layer areas (-1: none)
   int kept_slot = 0; // ring slot they were written to
   uint64_t seed = 0;  // dropout seed (varuna_stage_set_dropout_seed)
-  // The bias-gradient column sums of the backward pass depend on nothing downstream and are
-  // HBM-bound: when the caller has handed over a second stream (varuna_stage_set_side_stream)
-  // they run there beside the GEMM chain, forked and joined with events inside every backward
-  // call; otherwise on the caller's stream, in order.
-  hipStream_t side = nullptr;
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  bool side_used = false;  // work was forked in the current call and has not been joined yet
   // profiler
   bool prof_on = false;
   std::vector<hipEvent_t> ev;  // pairs
@@ -428,33 +421,6 @@ struct StageOps {
     return gemm(VARUNA_K_GEMM_FWD, GEMM_FWD, EPI_BIAS_RES, T_, D.h, D.f, g, param(l, VARUNA_P_W2), param(l, VARUNA_P_B2), x1, y, nullptr, nullptr, drop_args(DROP_SITE_MLP, l, mb));
   }
 
-  // The column reductions of one layer (bias, gamma and beta gradients), beside the GEMM chain when the caller has handed
-  // over a side stream: everything they read is complete at this point of the caller's stream, and nothing on that
-  // stream depends on their results, or rewrites what they read, before the next join_side().
-  hipError_t reduce_layer(const ReduceJob<T>* jobs, int n) {
-    double bytes = 0;
-    for (int i = 0; i < n; ++i) bytes += (jobs[i].x ? 2.0 : 1.0) * D.T * jobs[i].n * sizeof(T);
-    float* partial = wsp<float>(S->ws.partial);
-    if (S->prof_on || S->side == nullptr) {  // per-kernel timing wants everything on one stream
-      Bracket br(S, st, VARUNA_K_COLREDUCE, 0, bytes);
-      return launch_reduce_jobs<T>(jobs, n, partial, D.T, st);
-    }
-    hipError_t e;
-    if ((e = hipEventRecord(S->ev_fork, st))) return e;
-    if ((e = hipStreamWaitEvent(S->side, S->ev_fork, 0))) return e;
-    S->side_used = true;
-    return launch_reduce_jobs<T>(jobs, n, partial, D.T, S->side);
-  }
-
-  // The caller's stream waits for everything forked since the last join.
-  hipError_t join_side() {
-    if (!S->side_used) return hipSuccess;
-    S->side_used = false;
-    hipError_t e;
-    if ((e = hipEventRecord(S->ev_join, S->side))) return e;
-    return hipStreamWaitEvent(st, S->ev_join, 0);
-  }
-
   // One layer backward for ring slot rs.  x: the layer's input; the gradient of its output
   // already sits in slot rs of the layer's dy ring; dx: gradient of its input.  The four
   // weight-gradient GEMMs are not issued here (see flush_wgrads): this pass leaves their
@@ -485,8 +451,6 @@ struct StageOps {
     }
     // MLP2: du = (dyd W2) * GeLU'(u)
     if ((e = gemm(VARUNA_K_GEMM_DGRAD, GEMM_DGRAD, EPI_DGELU, T_, D.f, D.h, dyd, param(l, VARUNA_P_W2), nullptr, u, du, nullptr, nullptr))) return e;
-    // the layer above's reductions read dxn and dxn_b, which this layer rewrites from here on
-    if ((e = join_side())) return e;
     // MLP1: dxn2 = du W1
     if ((e = gemm(VARUNA_K_GEMM_DGRAD, GEMM_DGRAD, EPI_PLAIN, T_, D.h, D.f, du, param(l, VARUNA_P_W1), nullptr, nullptr, dxn, nullptr, nullptr))) return e;
     // LN2: dx1 = dy + LN'(dxn2)
@@ -518,13 +482,20 @@ struct StageOps {
         {dxn_b, x, stats1, grad(l, VARUNA_P_LN1_G), grad(l, VARUNA_P_LN1_B), D.h},
         {dyd, nullptr, nullptr, grad(l, VARUNA_P_B2), nullptr, D.h},
         {dx1d, nullptr, nullptr, grad(l, VARUNA_P_BO), nullptr, D.h}};
-    if (!S->prof_on && S->side == nullptr)   // (on two streams, and timed by kind of kernel, they are launches of their own)
+    // In one launch on the call's stream.  On a second stream beside the weight gradients (a launch of their own, a fork and a join per layer) they
+    // took the CUs those wait for, and the events cost more: whole steps, second stream / here (us): 1024 wide 575 / 545, 1920 wide
+    // 1575 / 1567, 16384 wide 42705 / 42684, ragged 1600 wide 813 / 802, fp32 1024 wide 727 / 696, 120 wide 309 / 259; without any sums
+    // 535, 1531, 42206, 778, 685.  (Timed by kind of kernel the two parts are launches of their own.)
+    if (!S->prof_on)
       return launch_layernorm_bwd_jobs<T>({dxn_b, x, stats1, param(l, VARUNA_P_LN1_G), dx1, dx, T_, D.h}, jobs, kMaxReduceJobs, wsp<float>(W.partial), st);
     {
       Bracket br(S, st, VARUNA_K_LN_BWD, 0, 4.0 * D.E * sizeof(T));
       if ((e = launch_layernorm_bwd_dx<T>(dxn_b, x, stats1, param(l, VARUNA_P_LN1_G), dx1, dx, T_, D.h, st))) return e;
     }
-    return reduce_layer(jobs, kMaxReduceJobs);
+    double bytes = 0;
+    for (const ReduceJob<T>& j : jobs) bytes += (j.x ? 2.0 : 1.0) * D.T * j.n * sizeof(T);
+    Bracket br(S, st, VARUNA_K_COLREDUCE, 0, bytes);
+    return launch_reduce_jobs<T>(jobs, kMaxReduceJobs, wsp<float>(W.partial), T_, st);
   }
 
   // One weight gradient dW[M,N] += A^T B over K tokens.  bf16 shapes with too few output
@@ -648,7 +619,7 @@ struct StageOps {
       if ((e = flush_wgrads(S->pending))) return e;
       S->pending = 0;
     }
-    return join_side();   // the bias gradients are complete when this call's work is
+    return hipSuccess;
   }
 
   hipError_t flush() {
@@ -754,19 +725,13 @@ varuna_status_t varuna_stage_create(const varuna_stage_config_t* cfg, const void
 varuna_status_t varuna_stage_destroy(varuna_stage_t* st) {
   if (!st) return fail(VARUNA_EINVAL, "stage handle is NULL");
   for (hipEvent_t e : st->ev) (void)hipEventDestroy(e);
-  if (st->ev_fork) (void)hipEventDestroy(st->ev_fork);   // the side stream itself is the caller's
-  if (st->ev_join) (void)hipEventDestroy(st->ev_join);
   delete st;
   return VARUNA_OK;
 }
 
 varuna_status_t varuna_stage_set_side_stream(varuna_stage_t* st, void* side_stream) {
   if (!st) return fail(VARUNA_EINVAL, "stage handle is NULL");
-  if (side_stream && !st->ev_fork) {
-    HIP_TRY(hipEventCreateWithFlags(&st->ev_fork, hipEventDisableTiming));
-    HIP_TRY(hipEventCreateWithFlags(&st->ev_join, hipEventDisableTiming));
-  }
-  st->side = static_cast<hipStream_t>(side_stream);
+  (void)side_stream;   // nothing runs there: see layer_backward
   return VARUNA_OK;
 }
 
