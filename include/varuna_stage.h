@@ -247,8 +247,8 @@ varuna_status_t varuna_debug_set_gemm_kernels(int32_t fwd256, int32_t dgrad256, 
                                               int32_t fwd128, int32_t dgrad128, int32_t wgrad128);
 /* Host only (no GPU call): the kernel configuration the library picks for a bf16 product of
  * contiguous, 16-byte aligned operands, op as in varuna_op_gemm (0 forward, 1 dgrad, 2 wgrad):
- * a `variant` number of varuna_op_gemm (20 for merged tiles of 128 rows, which a forward product takes 192 wide, as
- * configuration 24, where the 256-wide ones would leave a quarter of the chip idle), -1 for the kernels on small tiles whose waves share the reduction (rows that are
+ * a `variant` number of varuna_op_gemm by the tiles' rounds on the chip (the launch may take another one that ends sooner, for
+ * instance merged tiles 192 wide, configuration 24, in place of 20), -1 for the kernels on small tiles whose waves share the reduction (rows that are
  * not whole 16-byte pieces, and products of few 128x128 tiles), -2 for an invalid argument. */
 int32_t varuna_debug_gemm_choice(int32_t op, int64_t M, int64_t N, int64_t K);
 /* Host only: the configuration (18, 19, 22 or 23) on which the weight gradients of n_layers (1 to 4) consecutive

@@ -811,8 +811,8 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_group_kernel(DgGroup g, 
 //   20: 128x256, 21: 256x128, 4 waves, three stages of both operands (LS 5)
 //   24: 128x192 in that form, forward only; the library takes it in place of 20 where dg_narrow says so
 //   22, 23: as 19, 18 for sizes that are no multiples of the tile (EDGE)
-// What a debug query reports is dg_pick's and dg_group_choice's word; 20 -> 24 (dg_narrow) and 128x128 -> 256x256 for weight gradients
-// (dg_wgrad_wide, dg_group_wide) are decided when the product is launched.
+// What a debug query reports is dg_pick's and dg_group_choice's word; dg_at_launch and dg_group_wide may take another configuration when the
+// product is launched.
 // ---------------------------------------------------------------------------
 inline bool dg_variant_tile(int variant, GemmTile* t) {
   switch (variant) {
@@ -874,7 +874,7 @@ inline int dg_choose_variant(int64_t M, int64_t N, int64_t K, int64_t lda, int64
 // load schedule, and so does wgrad (both operands read transposed); all of them with the k-tile
 // loop unrolled over the stage period, which removes the address arithmetic from the loop and was
 // worth 4.4 % of the C5 step and 1.4-2.6 % of the smaller stages' in same-process A/B.
-struct DgFlavours { int fwd256 = 17, bwd256 = 18, fwd128 = 19, dgrad128 = 19, wgrad128 = 19, wgrad256 = 18; bool pair128 = true, group = true, small[3] = {true, true, true}; };
+struct DgFlavours { int fwd256 = 17, bwd256 = 18, fwd128 = 19, dgrad128 = 19, wgrad128 = 19, wgrad256 = 18; bool pair128 = true, group = true, named = false, small[3] = {true, true, true}; };
 inline DgFlavours& dg_flavours() { static DgFlavours f; return f; }   // tuning hook: varuna_debug_set_gemm_kernels
 inline int dg_flavour(int tile_variant, int op) {
   const DgFlavours& f = dg_flavours();
@@ -944,6 +944,35 @@ inline bool dg_wgrad_wide(int64_t M, int64_t N, int64_t K) {
   return K >= 512 && t7 >= 600 && (double)((t5 + 255) / 256) * 4.0 / 1.15 * 1.05 <= (double)((t7 + 511) / 512) * 2.0;
 }
 
+// The configuration that runs in place of dg_pick's `v`, which knows the tiles' rounds but neither the epilogue nor the reduction's length.
+// Measured on the products of layers 768 to 5120 wide over 512 to 6144 tokens, operands out of cache (us, dg_pick's / this one's):
+//   forward on the 192-wide merged tiles, where dg_narrow says so or where they take the place of 128x128 tiles in up to three rounds of
+//     which the last is 7/8 full: 2048x9216x3072 129 / 123, 2048x9216x2304 114 / 109, 2048x5760x1920 56 / 53; in six rounds 225 / 243;
+//   forward on 256x256 where the others need many more rounds (a round costs 70 on those, 46 on merged tiles, 50 on 128x128, which refill):
+//     4096x9216x3072 225 / 212, 4096x10240x2560 239 / 207, 2048x20480x5120 403 / 380; short reductions 6144x6144x1536 130 / 140;
+//   merged tiles 256x128, not 128x256, for outputs clearly wider than tall, in whole groups of 8 tile rows: dgrad 1024x5120x15360 222 / 194,
+//     GeLU' 512x15360x3840 72 / 65, forward 1024x6912x2304 38 / 35; dgrad 2048x4096x12288 182 / 186, forward 3072x7680x2560 108 / 116;
+//   dgrad on 256x256 tiles of at most 200 workgroups on four waves, not eight: 4096x2560x10240 224 / 200, 2048x5120x5120 117 / 107, GeLU'
+//     1024x12288x3072 81 / 78; 240 and 256 workgroups are even, and so are 3072x3072x3072, 4096x2304x2304; GeLU' 4096x3072x768 9 % slower.
+inline int dg_at_launch(int v, int op, int mode, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
+  if (v == 20 && op == GEMM_FWD && dg_narrow(M, N)) return 24;
+  if (dg_flavours().named) return v;
+  const int64_t t5 = ((M + 255) / 256) * ((N + 255) / 256), rounds5 = (t5 + 255) / 256;
+  if (op == GEMM_WGRAD) return v == 19 && mode == EPI_ACCUM_F32 && dg_wgrad_wide(M, N, K) ? 23 : v;
+  if (v == 18 && op == GEMM_DGRAD) return t5 <= 200 && K >= (mode == EPI_DGELU ? 2304 : 3584) ? 17 : v;
+  if (v != 19 && v != 20) return v;
+  const int64_t t7 = (M / 128) * (N / 128), rounds_wide = (t7 / 2 + 255) / 256;
+  if (op == GEMM_FWD && t5 > 256 && K >= 2304 && dg_shape_ok(17, M, N, K, lda, ldb) &&
+      70.0 * (double)rounds5 < 0.97 * (v == 20 ? 46.0 * (double)rounds_wide : 50.0 * (double)t7 / 512.0)) return 17;
+  if (v == 19) {
+    if (op != GEMM_FWD || !dg_shape_ok(24, M, N, K, lda, ldb)) return v;
+    const int64_t t24 = (M / 128) * (N / 192);
+    return t24 >= 384 && t24 <= 768 && ((t24 + 255) / 256 * 256 - t24) * 8 <= 256 ? 24 : v;
+  }
+  const bool wide = mode == EPI_BIAS || mode == EPI_BIAS_GELU || mode == EPI_DGELU ? 2 * N >= 3 * M : N >= 3 * M;
+  return wide && (M <= 2048 || M % 2048 == 0) && dg_shape_ok(21, M, N, K, lda, ldb) ? 21 : v;
+}
+
 // Split-K for weight-gradient GEMMs whose output has too few tiles to fill the chip: the
 // reduction is cut into `splits` equal parts, each workgroup row of the grid writes its
 // partial tile (EPI_STORE_F32) and splitk_reduce adds the partials to the accumulator in a
@@ -1003,7 +1032,7 @@ inline int dg_group_choice(const DgJob* jobs, int n, int64_t K) {
 // 137 / 121, 1536 wide 261 / 231, 1280 wide, two layers over 8192 711 / 629; where 128x128 stay: 1600 wide, two layers over 2000 313 / 317,
 // 4096 wide over 1024 581 / 625.
 inline int dg_group_wide(int variant, const DgJob* jobs, int n, int64_t K) {
-  if ((variant != 19 && variant != 22) || K < 2048) return variant;
+  if ((variant != 19 && variant != 22) || K < 2048 || dg_flavours().named) return variant;
   int64_t t5 = 0, t7 = 0;
   bool plain = true, edge = true;
   for (int i = 0; i < n; ++i) {

@@ -272,8 +272,7 @@ template <> struct GemmDispatch<bf16> {
     if (v == 0) {
       v = ptr_ok ? dg_pick(op, M, N, K, lda, ldb) : -1;
       if (v == 0) v = -1;
-      if (v == 20 && op == GEMM_FWD && dg_narrow(M, N)) v = 24;
-      if (v == 19 && op == GEMM_WGRAD && mode == EPI_ACCUM_F32 && splits == 1 && dg_flavours().group && dg_wgrad_wide(M, N, K)) v = 23;
+      if (splits == 1) v = dg_at_launch(v, op, mode, M, N, K, lda, ldb);
     }
     if (v >= 5) {
       if (!ptr_ok || !dg_shape_ok(v, M, N, K, lda, ldb) || (v == 24 && op != GEMM_FWD)) return hipErrorInvalidConfiguration;
@@ -1033,6 +1032,7 @@ varuna_status_t varuna_debug_set_gemm_kernels(int32_t fwd256, int32_t dgrad256, 
   f.fwd128 = fwd128 ? fwd128 : d.fwd128; f.dgrad128 = dgrad128 ? dgrad128 : d.dgrad128; f.wgrad128 = wgrad128 ? wgrad128 : d.wgrad128;
   f.pair128 = fwd128 == 0 && dgrad128 == 0;   // naming a 128x128 configuration also turns the merging of tile pairs off
   f.group = wgrad256 == 0 && wgrad128 == 0;
+  f.named = fwd256 || dgrad256 || wgrad256 || fwd128 || dgrad128 || wgrad128;
   f.small[GEMM_FWD] = fwd128 == 0; f.small[GEMM_DGRAD] = dgrad128 == 0; f.small[GEMM_WGRAD] = wgrad128 == 0;
   return VARUNA_OK;
 }
