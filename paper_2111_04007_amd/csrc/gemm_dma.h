@@ -953,11 +953,20 @@ inline bool dg_wgrad_wide(int64_t M, int64_t N, int64_t K) {
 //   merged tiles 256x128, not 128x256, for outputs clearly wider than tall, in whole groups of 8 tile rows: dgrad 1024x5120x15360 222 / 194,
 //     GeLU' 512x15360x3840 72 / 65, forward 1024x6912x2304 38 / 35; dgrad 2048x4096x12288 182 / 186, forward 3072x7680x2560 108 / 116;
 //   dgrad on 256x256 tiles of at most 200 workgroups on four waves, not eight: 4096x2560x10240 224 / 200, 2048x5120x5120 117 / 107, GeLU'
-//     1024x12288x3072 81 / 78; 240 and 256 workgroups are even, and so are 3072x3072x3072, 4096x2304x2304; GeLU' 4096x3072x768 9 % slower.
+//     1024x12288x3072 81 / 78; 240 and 256 workgroups are even, and so are 3072x3072x3072, 4096x2304x2304; GeLU' 4096x3072x768 9 % slower;
+//   the ragged form of the 256x256 tiles for sides that are odd multiples of 128, where its rounds cost less (70 each, against 48 of 128x128 tiles
+//     however those are merged, 42 under GeLU', whose epilogue is the longer one there; a single round against more than 1.2): forward 1920x7680x1920
+//     80 / 53, 4224x3712x3712 129 / 100, 2048x5760x1920 54 / 50, 4480x6912x2304 179 / 130, 6016x4224x1408 94 / 71; dgrad 1408x10752x3584 137 / 96,
+//     GeLU' 143 / 109; not 4096x5760x1920 91 / 97 (2.81 rounds of 128x128), 3200x4992x1664 63 / 76 (1.90), GeLU' 2944x9216x2304 138 / 143 (3.23).
 inline int dg_at_launch(int v, int op, int mode, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
+  const int64_t t5 = ((M + 255) / 256) * ((N + 255) / 256), rounds5 = (t5 + 255) / 256;
+  if ((v == 19 || v == 20 || v == 21) && op != GEMM_WGRAD && !dg_flavours().named && K >= 1024 && !dg_shape_ok(5, M, N, K, lda, ldb) &&
+      dg_shape_ok(23, M, N, K, lda, ldb)) {
+    const double f7 = (double)((M / 128) * (N / 128)) / 512.0;
+    if (70.0 * (double)rounds5 <= (mode == EPI_DGELU ? 42.0 : 48.0) * f7 || (rounds5 == 1 && mode != EPI_DGELU && f7 > 1.2)) return 23;
+  }
   if (v == 20 && op == GEMM_FWD && dg_narrow(M, N)) return 24;
   if (dg_flavours().named) return v;
-  const int64_t t5 = ((M + 255) / 256) * ((N + 255) / 256), rounds5 = (t5 + 255) / 256;
   if (op == GEMM_WGRAD) return v == 19 && mode == EPI_ACCUM_F32 && dg_wgrad_wide(M, N, K) ? 23 : v;
   if (v == 18 && op == GEMM_DGRAD) return t5 <= 200 && K >= (mode == EPI_DGELU ? 2304 : 3584) ? 17 : v;
   if (v != 19 && v != 20) return v;

@@ -307,7 +307,7 @@ template <> struct AttnDispatch<bf16> {
   // variant 0: library's choice; 1: MFMA kernels on whole tiles (refused where they do not fit); 2: their EDGE form; 3: fp32
   // products (what the two cannot address, up to head dim 128); everything else, and 2 and 3 where they do not take the
   // shape: one wave per row.  The EDGE form takes what the whole tiles do not (any length, head dims that are multiples of 8 up to
-  // 128): against the row kernels, which read their operands element by element, 594 -> 29 us forward and 2409 -> 98 us
+  // 128): against the row kernels, which read their operands element by element, 594 -> 23 us forward and 2409 -> 65 us
   // backward at 2 x 1000 tokens, 25 heads of 64, and no slower at one row.
   static int choose(int variant, int b, int s, int a, int d, bool aligned, bool vec, bool backward) {
     if (variant == 0) {

@@ -17,6 +17,11 @@ pytestmark = pytest.mark.gpu
     (1, 0, 1536, 5120, 448, 20, 21),
     (1, 0, 2048, 5120, 3584, 18, 17),     # four waves
     (1, 3, 1024, 10240, 2304, 18, 17),
+    (0, 0, 1920, 7680, 1024, 19, 23),     # sides of odd multiples of 128: the ragged form of the large tiles
+    (0, 1, 4480, 6912, 1088, 20, 23),
+    (0, 2, 6016, 4224, 1024, 19, 23),
+    (1, 0, 1408, 10752, 1152, 19, 23),
+    (1, 3, 1408, 10752, 1024, 19, 23),
 ])
 def test_other_configurations_at_launch(op, epi, M, N, K, choice, runs):
     """The same bits as the named configuration, and a bf16 output's rounding (2^-9 in the norm, 2^-8 of the largest value) against fp64."""
