@@ -616,13 +616,14 @@ __global__ __launch_bounds__(256, attn_dkv_waves(D, DROP, EDGE)) void attn_bwd_d
   AttnTilePair<D, EDGE, 32> rt;   // waves 0 and 1 move the Q tile, 2 and 3 the dO tile
   const int second = wave >> 1;
   rt.init(second ? gbase : base, second ? (int64_t)h : ld, tid & 127, cols);
-  // Waves 0 and 1 also carry the tile's lse and delta (zero for queries past the end, whose rows of Q and dO are zero).
+  // Waves 0 and 1 also carry the tile's lse and delta (zero for queries past the end, whose rows of Q and dO are zero: EDGE, where the whole
+  // offset is the part that the range check sees, as in AttnTilePair).
   float rstat = 0.f;
   [[maybe_unused]] const float* stats = (wave == 0 ? lse : delta) + sbase;
   auto load = [&](int qb) {
     rt.load(qb * 32, s, cols);
 #if defined(__HIP_DEVICE_COMPILE__)
-    if (wave < 2) rstat = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(stats), 0, s * 4, 0x00020000), (lane & 31) * 4, qb * 128, 0));
+    if (wave < 2) rstat = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(stats), 0, s * 4, 0x00020000), (lane & 31) * 4 + (EDGE ? qb * 128 : 0), EDGE ? 0 : qb * 128, 0));
 #endif
   };
   auto store = [&](int st) {

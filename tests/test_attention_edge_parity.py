@@ -130,3 +130,21 @@ def test_attention_on_whole_tiles_takes_any_alignment(d):
         B.op_attention_bwd(q, ctx, lse, g, dqkv, torch.empty_like(lse), b, s, heads, d, 1, variant=1)
         got.append((ctx, lse, dqkv))
     assert all(torch.equal(x, y) for x, y in zip(*got))
+
+
+@pytest.mark.parametrize("b,s,heads,d,causal", [(1, 33, 1, 64, 1), (1, 70, 2, 96, 0), (2, 129, 2, 128, 1), (1, 1000, 1, 40, 1)])
+def test_statistics_past_the_last_query_are_not_read(b, s, heads, d, causal):
+    """The last tile of 32 queries is partly filled.  What lies behind the log-sum-exps and the deltas (here NaN) has no part in it, and neither
+    have those of the next head, which hold a NaN: the same bits as without either."""
+    h, n = heads * d, b * heads * s
+    qkv, dctx = rnd((b * s, 3 * h), "bf16", 3), rnd((b * s, h), "bf16", 4)
+    got = []
+    for behind in (0.0, float("nan")):
+        ctx, dqkv = torch.empty_like(dctx), torch.empty_like(qkv)
+        lse, delta = (torch.full((n + 64,), behind, device="cuda") for _ in range(2))
+        B.op_attention_fwd(qkv, ctx, lse, b, s, heads, d, causal, variant=2)
+        if heads > 1:
+            lse.view(-1)[s:s + 31] += behind   # the second head of the first sequence, its first 31 queries
+        B.op_attention_bwd(qkv, ctx, lse, dctx, dqkv, delta, b, s, heads, d, causal, variant=2)
+        got.append((lse[:s], delta[:s], dqkv[:s].view(s, 3, heads, d)[:, :, 0].clone()))
+    assert all(torch.equal(x, y) for x, y in zip(*got))
