@@ -678,10 +678,16 @@ __global__ __launch_bounds__(256, attn_dkv_waves(D, DROP, EDGE)) void attn_bwd_d
 #pragma unroll
       for (int k = 0; k < PF; ++k) cols_of(k);
       __builtin_amdgcn_sched_barrier(0);
-      if (need_mask) {   // tiles that straddle the diagonal: exp2(-inf) = 0
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const floatx4 l4 = *reinterpret_cast<const floatx4*>(&sstat[st][0][8 * g + 4 * hf]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sc[4 * g + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[4 * g + e], scale_log2e, -l4[e]));
+      }
+      if (need_mask) {   // tiles that straddle the diagonal; after the exponential: a masked query's log-sum-exp may be a NaN
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if (q0 + 8 * (r >> 2) + 4 * hf + (r & 3) < key) sc[r] = -INFINITY;
+          if (q0 + 8 * (r >> 2) + 4 * hf + (r & 3) < key) sc[r] = 0.f;
       }
       float pr[16], ds[16];
       uint32_t own[4];
@@ -690,7 +696,6 @@ __global__ __launch_bounds__(256, attn_dkv_waves(D, DROP, EDGE)) void attn_bwd_d
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int ql = 8 * g + 4 * hf;  // 4 consecutive queries of the tile
-        const floatx4 l4 = *reinterpret_cast<const floatx4*>(&sstat[st][0][ql]);
         floatx4 d4 = {0.f, 0.f, 0.f, 0.f};
         if (DROP) d4 = *reinterpret_cast<const floatx4*>(&sstat[st][1][ql]);
         uint32_t mw[4];
@@ -704,11 +709,10 @@ __global__ __launch_bounds__(256, attn_dkv_waves(D, DROP, EDGE)) void attn_bwd_d
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int r = 4 * g + e;
-          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, -l4[e]));
           float f = 1.0f;
           if (DROP) f = drop_keep(drop, mw[e], key & 3) ? drop.scale : 0.f;
-          pr[r] = p * f;
-          ds[r] = DROP ? p * (dp[r] * f + d4[e]) : p * dp[r];
+          pr[r] = sc[r] * f;
+          ds[r] = DROP ? sc[r] * (dp[r] * f + d4[e]) : sc[r] * dp[r];
         }
       }
       bf16x8 pf, df, pl, dl;

@@ -92,3 +92,20 @@ def test_stage_forward_is_causal(dtype, heads, d, s, drop):
     assert bool(torch.isnan(y[token]).any())
     same(y[:token], clean[:token], U.TOL[dtype], "outputs before the token")
     st.close()
+
+
+@pytest.mark.parametrize("d", [64, 96, 128])
+@pytest.mark.parametrize("value", [INF, NAN])
+def test_masked_query_on_whole_tiles(d, value):
+    """Whole tiles: a query that is not finite, and with it its log-sum-exp, has no part in dV of the keys after it nor in dQ of other queries, in the
+    diagonal tile it lies in either: the bits of a clean call."""
+    s, heads = 256, 2
+    h, dims = heads * d, (1, s, heads, d, 1)
+    qkv, dctx = rnd((s, 3 * h), "bf16", 11 + d), rnd((s, h), "bf16", 12 + d)
+    clean = backward(qkv, *forward(qkv, dims, 1), dctx, dims, 1)
+    for token in (40, 200):
+        bad = qkv.clone()
+        bad[token, 3] = value
+        got = backward(bad, *forward(bad, dims, 1), dctx, dims, 1)
+        assert torch.equal(got[token + 1:, 2 * h:], clean[token + 1:, 2 * h:])
+        assert torch.equal(got[:token, :h], clean[:token, :h]) and torch.equal(got[token + 1:, :h], clean[token + 1:, :h])
