@@ -272,7 +272,10 @@ enum {
   VARUNA_K_COUNT
 };
 /* While enabled, each kernel launch is bracketed by HIP events on the stream it
- * runs on.  Events come from a fixed pool created here (no device memory). */
+ * runs on.  Events come from a fixed pool created here (no device memory).  Results are
+ * bit-identical either way.  A launch that joins work of two classes counts for the one that
+ * has its FLOPs (a small fp32 layer's norms are part of the products that follow them); the
+ * last LayerNorm of a layer's backward and the column sums, otherwise one launch, are two. */
 varuna_status_t varuna_stage_profile_enable(varuna_stage_t* st, int32_t on);
 /* Synchronises the recorded events, adds their durations per class into
  * ms[VARUNA_K_COUNT], launches[...] and flops[...] (algorithmic FLOPs of the

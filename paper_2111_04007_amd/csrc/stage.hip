@@ -387,8 +387,10 @@ struct StageOps {
     T* copy = x_in ? x : nullptr;
     if constexpr (std::is_same<T, float>::value) {
       const LnIn ln{param(l, norm), param(l, norm + 1), save ? xn : nullptr, stats, copy, D.eps};
-      if (!S->prof_on && ln_gemm_f32_takes(param(l, weight), ln, D.T, N, D.h))   // (timed by kind of kernel they are launches of their own)
+      if (ln_gemm_f32_takes(param(l, weight), ln, D.T, N, D.h)) {   // also where kernels are timed: its statistics are other sums than the norm's own
+        Bracket br(S, st, VARUNA_K_GEMM_FWD, 2.0 * D.T * N * D.h, ((double)D.E * (1 + (ln.y != nullptr) + (copy != nullptr)) + (double)N * (D.h + D.T)) * sizeof(T));
         return launch_ln_gemm_f32(mode, from, param(l, weight), D.T, N, D.h, EpiArgs<float>{param(l, weight + 1), nullptr, out, aux_out, nullptr, N, DropArgs{}}, ln, st);
+      }
     }
     {
       Bracket br(S, st, VARUNA_K_LN_FWD, 0, 2.0 * D.E * sizeof(T));
