@@ -61,7 +61,9 @@ template <typename T>
 hipError_t launch_attention_bwd_f32(const T* qkv, const T* ctx, const float* lse, const T* dctx, T* dqkv, float* delta, int b,
                                     int s, int heads, int d, int causal, const DropArgs& drop, hipStream_t st);
 
-// fp32 in tiles of 16 (attention_f32_16.h) against tiles of 32: half the rows per workgroup, so twice as many workgroups with half a chain each, for twice
+// fp32 in tiles of 16 (attention_f32_16.h): head dims up to 128 in whole 16-byte pieces (the tensors must be 16-byte aligned).
+inline bool attn_f32_16_supported(int d) { return d % 4 == 0 && d <= 128; }
+// Whether a call they take goes there.  Against tiles of 32: half the rows per workgroup, so twice as many workgroups with half a chain each, for twice
 // the operand traffic per product.  Under the causal mask it is the faster form at every size measured; without it where it takes fewer
 // rounds of 256 workgroups in rows, or rows are short (up to 256), and where those two are equal forward above d = 96 and backward up to it.  us,
 // forward and backward, 32 (or one wave per row) / 16: 4 heads of 64 over 64 tokens 6.9 / 4.0, 13.8 / 6.3; 24 of 64 over 500 causal 25 / 19,
@@ -71,7 +73,6 @@ hipError_t launch_attention_bwd_f32(const T* qkv, const T* ctx, const float* lse
 // Where one wave per row was the choice for up to 255 rows, or up to 512 above d = 64, it still is: such calls hold those kernels' bits.
 inline bool attn_f32_16(bool backward, int b, int s, int heads, int d, bool causal) {
   const int64_t rows = (int64_t)b * heads * s, pairs = (int64_t)b * heads;
-  if (d % 4 != 0 || d > 128 || !attn_grid_ok(b, heads)) return false;
   if (rows <= (d <= 64 ? 255 : 512) && attn_rows_sooner(true, true, backward, b, s, heads, d)) return false;
   const int64_t rounds16 = (pairs * ((s + 15) / 16) + 255) / 256, rounds32 = (pairs * ((s + 31) / 32) + 255) / 256;
   return causal || s <= 256 || rounds16 < 2 * rounds32 || (backward ? d <= 96 : d > 96);
