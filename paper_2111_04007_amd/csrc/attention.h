@@ -63,17 +63,29 @@ hipError_t launch_attention_bwd_f32(const T* qkv, const T* ctx, const float* lse
 
 // fp32 in tiles of 16 (attention_f32_16.h): head dims up to 128 in whole 16-byte pieces (the tensors must be 16-byte aligned).
 inline bool attn_f32_16_supported(int d) { return d % 4 == 0 && d <= 128; }
-// Whether a call they take goes there.  Against tiles of 32: half the rows per workgroup, so twice as many workgroups with half a chain each, for twice
+// Whether a call they take ends sooner with one wave per row: rows of a few tokens leave most of a tile empty, which counts where the tiles take more
+// than one round (2 to 4 workgroups a CU forward, 4 to 1 backward), and one or two tokens also within one.  Longest row by padded head dim {32, 64, 96, 128}: with any
+// number of heads, with more than p1, with more than p2; set on 1900 shapes (d 16 .. 128, s 1 .. 192, 1 .. 16384 heads), where the choice is within 8 % of the better
+// form on 99 in 100.  us, per row / tiles of 16, forward and backward: one token, 4096 heads of 128 8.7 / 31, 24 / 166, of 64 6.6 / 12.7, 15 / 52, 16 heads of 128
+// 5.1 / 5.5, 6.8 / 7.7; four tokens, 1024 heads of 128 9.2 / 9.6, 25 / 45, 128 heads 5.8 / 5.4, 9.3 / 7.7; 64 tokens, 2 heads of 64 7.3 / 4.5, 14.3 / 6.8; 192 tokens, 1
+// head of 128 26 / 10, 71 / 22.
+inline bool attn_f32_16_rows(bool backward, int b, int s, int heads, int d) {
+  struct Limit { int any, p1, s1, p2, s2; };
+  constexpr Limit limit[2][4] = {{{0, 1024, 2, 1024, 2}, {0, 1024, 3, 1024, 3}, {0, 768, 3, 768, 3}, {2, 512, 4, 512, 4}},
+                                 {{1, 1535, 3, 1535, 3}, {2, 767, 4, 767, 4}, {2, 128, 4, 767, 8}, {2, 128, 4, 767, 8}}};
+  const Limit& l = limit[backward][(d + 31) / 32 - 1];
+  const int64_t pairs = (int64_t)b * heads;
+  return s <= (pairs > l.p2 ? l.s2 : pairs > l.p1 ? l.s1 : l.any);
+}
+// Whether the other calls they take go there.  Against tiles of 32: half the rows per workgroup, so twice as many workgroups with half a chain each, for twice
 // the operand traffic per product.  Under the causal mask it is the faster form at every size measured; without it where it takes fewer
 // rounds of 256 workgroups in rows, or rows are short (up to 256), and where those two are equal forward above d = 96 and backward up to it.  us,
-// forward and backward, 32 (or one wave per row) / 16: 4 heads of 64 over 64 tokens 6.9 / 4.0, 13.8 / 6.3; 24 of 64 over 500 causal 25 / 19,
+// forward and backward, 32 / 16: 4 heads of 64 over 64 tokens 7.4 / 4.6, 24 / 6.8; 24 of 64 over 500 causal 25 / 19,
 // 77 / 56 and full (768 workgroups) 34 / 27, 121 / 90; 128 of 64 over 1000 causal 237 / 221, 1033 / 905; 64 of 128 over 64 15 / 6.5, 51 / 19;
 // 2 of 128 over 2000 160 / 64, 575 / 184.  Full, equal rounds: 12 of 64 over 512 19.7 / 20.3, 67 / 55, 256 of 64 over 512 239 / 292, 991 / 942, 8 of
 // 128 over 1000 86 / 64, 295 / 306.
-// Where one wave per row was the choice for up to 255 rows, or up to 512 above d = 64, it still is: such calls hold those kernels' bits.
 inline bool attn_f32_16(bool backward, int b, int s, int heads, int d, bool causal) {
-  const int64_t rows = (int64_t)b * heads * s, pairs = (int64_t)b * heads;
-  if (rows <= (d <= 64 ? 255 : 512) && attn_rows_sooner(true, true, backward, b, s, heads, d)) return false;
+  const int64_t pairs = (int64_t)b * heads;
   const int64_t rounds16 = (pairs * ((s + 15) / 16) + 255) / 256, rounds32 = (pairs * ((s + 31) / 32) + 255) / 256;
   return causal || s <= 256 || rounds16 < 2 * rounds32 || (backward ? d <= 96 : d > 96);
 }

@@ -286,24 +286,31 @@ template <> struct GemmDispatch<bf16> {
 // fp32.  variant 0: library's choice; -1: one wave per row (few or short rows, head dims above 128); 4: fp32 products in tiles of 16; else, and 4
 // where it does not take the call: in tiles of 32.
 template <typename T> struct AttnDispatch {
-  static bool per_row(int variant, int b, int s, int a, int d, bool vec, bool backward) {
-    return variant == -1 || !attn_f32_supported(d) || !attn_grid_ok(b, a) || (variant == 0 && attn_rows_sooner(true, vec, backward, b, s, a, d));
-  }
-  static bool tiles16(int variant, int b, int s, int a, int d, bool causal, bool aligned, bool backward) {
-    return attn_f32_16_supported(d) && attn_grid_ok(b, a) && aligned && (variant == 4 || (variant == 0 && attn_f32_16(backward, b, s, a, d, causal)));
+  // -1, 4, or 3 for tiles of 32.  vec: attn_f32_vec of what is read; aligned: all tensors
+  static int choose(int variant, int b, int s, int a, int d, bool causal, bool aligned, bool vec, bool backward) {
+    if (variant == -1 || !attn_f32_supported(d) || !attn_grid_ok(b, a)) return -1;
+    if (attn_f32_16_supported(d) && aligned) {
+      if (variant == 0) return attn_f32_16_rows(backward, b, s, a, d) ? -1 : attn_f32_16(backward, b, s, a, d, causal) ? 4 : 3;
+      return variant == 4 ? 4 : 3;
+    }
+    return variant == 0 && attn_rows_sooner(true, vec, backward, b, s, a, d) ? -1 : 3;
   }
   static hipError_t fwd(int variant, const T* qkv, T* ctx, float* lse, int b, int s, int a, int d, int causal,
                         const DropArgs& drop, hipStream_t st) {
-    if (tiles16(variant, b, s, a, d, causal, aligned16(qkv) && aligned16(ctx), false)) return launch_attention_fwd_f32_16(qkv, ctx, lse, b, s, a, d, causal, drop, st);
-    if (per_row(variant, b, s, a, d, attn_f32_vec<T>(qkv, qkv, qkv, d), false)) return launch_attention_fwd_simple<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
-    return launch_attention_fwd_f32<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
+    switch (choose(variant, b, s, a, d, causal, aligned16(qkv) && aligned16(ctx), attn_f32_vec<T>(qkv, qkv, qkv, d), false)) {
+      case 4: return launch_attention_fwd_f32_16(qkv, ctx, lse, b, s, a, d, causal, drop, st);
+      case 3: return launch_attention_fwd_f32<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
+      default: return launch_attention_fwd_simple<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
+    }
   }
   static hipError_t bwd(int variant, const T* qkv, const T* ctx, const float* lse, const T* dctx, T* dqkv,
                         float* delta, int b, int s, int a, int d, int causal, const DropArgs& drop, hipStream_t st) {
-    if (tiles16(variant, b, s, a, d, causal, aligned16(qkv) && aligned16(ctx) && aligned16(dctx) && aligned16(dqkv), true))
-      return launch_attention_bwd_f32_16(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
-    if (per_row(variant, b, s, a, d, attn_f32_vec<T>(qkv, ctx, dctx, d), true)) return launch_attention_bwd_simple<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
-    return launch_attention_bwd_f32<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
+    switch (choose(variant, b, s, a, d, causal, aligned16(qkv) && aligned16(ctx) && aligned16(dctx) && aligned16(dqkv),
+                   attn_f32_vec<T>(qkv, ctx, dctx, d), true)) {
+      case 4: return launch_attention_bwd_f32_16(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
+      case 3: return launch_attention_bwd_f32<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
+      default: return launch_attention_bwd_simple<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
+    }
   }
 };
 

@@ -44,15 +44,18 @@ def test_dropout_fp32(heads, d, s, causal, b):
 
 
 @pytest.mark.parametrize("dtype,b,s,heads,d,fwd,bwd,causal", [
-    ("f32", 1, 64, 8, 128, -1, -1, 1), ("f32", 4, 64, 16, 128, 4, 4, 1), ("f32", 1, 193, 1, 128, 4, 4, 1), ("f32", 1, 64, 2, 64, 4, -1, 1), ("f32", 1, 65, 2, 64, 4, 4, 1),
-    ("f32", 1, 256, 2, 63, -1, -1, 1), ("f32", 2, 257, 16, 63, 3, 3, 1), ("f32", 1, 33, 1, 32, 4, -1, 1), ("f32", 1, 32, 2, 16, -1, -1, 1),
+    ("f32", 1, 64, 8, 128, 4, 4, 1), ("f32", 4, 64, 16, 128, 4, 4, 1), ("f32", 1, 193, 1, 128, 4, 4, 1), ("f32", 1, 64, 2, 64, 4, 4, 1), ("f32", 1, 65, 2, 64, 4, 4, 1),
+    ("f32", 1, 256, 2, 63, -1, -1, 1), ("f32", 2, 257, 16, 63, 3, 3, 1), ("f32", 1, 33, 1, 32, 4, 4, 1), ("f32", 1, 32, 2, 16, 4, 4, 1),
+    ("f32", 1, 2, 4, 128, -1, -1, 0), ("f32", 1, 3, 4, 128, 4, 4, 0), ("f32", 1, 1, 4, 32, 4, -1, 1), ("f32", 1, 2, 4, 32, 4, 4, 0),   # a few tokens, few heads
+    ("f32", 64, 2, 17, 32, -1, 4, 0), ("f32", 64, 3, 24, 32, 4, -1, 1), ("f32", 64, 3, 17, 64, -1, -1, 0), ("f32", 64, 4, 17, 64, 4, -1, 1), ("f32", 64, 5, 17, 64, 4, 4, 1),
+    ("f32", 64, 3, 13, 96, -1, -1, 1), ("f32", 64, 8, 13, 96, 4, -1, 0), ("f32", 64, 9, 13, 96, 4, 4, 1), ("f32", 8, 4, 16, 96, 4, 4, 1), ("f32", 3, 4, 43, 128, 4, -1, 1), ("f32", 64, 5, 13, 128, 4, -1, 1),
     ("f32", 8, 270, 2, 64, 3, 4, 0), ("f32", 8, 270, 2, 100, 4, 3, 0), ("f32", 8, 256, 2, 64, 4, 4, 0), ("f32", 8, 270, 2, 64, 4, 4, 1),
     ("bf16", 1, 48, 4, 20, 3, -1, 1), ("bf16", 1, 64, 16, 92, -1, -1, 1), ("bf16", 1, 70, 2, 92, 3, 3, 1), ("bf16", 1, 192, 1, 127, -1, -1, 1), ("bf16", 1, 200, 1, 127, 3, 3, 1),
     ("bf16", 1, 100, 2, 7, 3, 3, 1),
 ])
 def test_short_rows_go_to_the_row_kernels(dtype, b, s, heads, d, fwd, bwd, causal):
-    """Both sides of the lines between the forms: the library's choice is, bit for bit, the form named here, and where that is one of fp32's two
-    tile sizes, not the other one (several tiles, so that the two sum in other orders)."""
+    """Both sides of the lines between the forms: the library's choice is, bit for bit, the form named here, and in fp32 not the nearest other one
+    (for tiles of 16 one wave per row up to 32 tokens and tiles of 32 beyond, for these two tiles of 16): the forms sum in other orders."""
     import torch
     from paper_2111_04007_amd import binding as B
     from tests.test_ops_parity import rnd
@@ -69,11 +72,9 @@ def test_short_rows_go_to_the_row_kernels(dtype, b, s, heads, d, fwd, bwd, causa
 
     got = call(0, 0)
     assert all(torch.equal(x, y) for x, y in zip(got, call(fwd, bwd)))
-    other = call(7 - fwd if dtype == "f32" and fwd > 0 else fwd, 7 - bwd if dtype == "f32" and bwd > 0 else bwd)
-    if dtype == "f32" and fwd > 0 and d % 4 == 0:
-        assert not torch.equal(got[0], other[0])
-    if dtype == "f32" and bwd > 0 and d % 4 == 0:
-        assert not torch.equal(got[2], other[2])
+    if dtype == "f32" and d % 4 == 0:
+        other = call(*(-1 if v == 4 and s <= 32 else 3 if v == 4 else 4 for v in (fwd, bwd)))
+        assert not torch.equal(got[2], other[2]) and (s == 1 or not torch.equal(got[0], other[0]))
 
 
 @pytest.mark.parametrize("dtype,variant,b,s,heads,d,causal,peak", [
