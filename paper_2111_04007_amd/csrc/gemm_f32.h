@@ -240,12 +240,14 @@ inline bool gf_small_tile(int64_t tiles32, int64_t tiles64) {
 
 // Products of few output elements, or of short sums, go to gemm_f32_few.h (forward and dgrad, whole 16-byte pieces), in
 // 16x16 tiles.  Measured (us, tiles of 32 or 64 / that, forward and dgrad): 128x128 (64 tiles) over 128 3.6 / 2.4, 3.6 / 2.3 and over 512
-// 6.2 / 3.7, 6.2 / 3.2, 128x512 (256) over 900 9.9 / 4.3, 9.8 / 4.6, 256x512 (512) over 512 6.3 / 5.6, 6.4 / 4.7 and over 1000
+// 6.2 / 3.7, 6.2 / 3.2, 128x512 (256) over 900 9.9 / 4.3, 9.8 / 4.3, 256x512 (512) over 512 6.3 / 5.6, 6.4 / 4.7 and over 1000
 // 9.9 / 7.0, 9.8 / 6.9, 512x512 (1024) over 64 3.7 / 3.2, 3.8 / 3.0 and over 128 3.8 / 3.9, 3.9 / 3.4, 2000x256 (2000) over 64 4.9 / 4.5,
 // 4.8 / 4.2; beyond, 256x768 (768) over 256 4.6 / 4.7, 4.7 / 4.0, 500x384 (768) over 384 5.6 / 6.4, 5.5 / 5.4, 512x512 over 512 6.5 / 9.1, 6.5 / 6.8.
+// From 1024 k on the kernels on bf16 pieces take products this small (gc_kind); these take two batches of 512 k and address an operand (at
+// most 32768 rows of it) with 32 bits.
 inline bool gf_few(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = gf_tiles(M, N, 16);
-  return tiles <= 512 || (tiles <= 2048 && tiles * K <= 1 << 17);
+  return K < 1024 && (tiles <= 512 || (tiles <= 2048 && tiles * K <= 1 << 17));
 }
 
 // One product on contiguous operands (forward: a [M,K], b [N,K]; dgrad: [M,K], [K,N]; wgrad: [K,M], [K,N]), in

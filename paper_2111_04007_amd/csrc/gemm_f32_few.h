@@ -1,8 +1,8 @@
-// fp32 products of few output elements (gf_few: at most 512 tiles of 16x16, more of short sums): out = A B^T or A B with fp32 products (v_mfma_f32_16x16x4_f32), A [M,K]
+// fp32 products of few output elements (gf_few: at most 512 tiles of 16x16, more of short sums; less than 1024 k): out = A B^T or A B with fp32 products (v_mfma_f32_16x16x4_f32), A [M,K]
 // k-major, whole 16-byte pieces.  One workgroup of 8 waves per 16x16 tile; a wave takes every eighth 16 k.
 //
 // What bounds such a product is latency: a launch, one way to memory, the sums' way through LDS.  So there is no staging: a wave's
-// operands, up to 64 k of both, go straight into registers in one batch (a lane holds k-values 16u + 4*(lane/16) .. +3 of row lane%16 of its
+// operands, up to 64 k of both, go straight into registers in one batch, or two above 512 k (a lane holds k-values 16u + 4*(lane/16) .. +3 of row lane%16 of its
 // unit u, the products take them in the same order on both sides), what the epilogue reads is fetched with them, and the only barrier is the
 // one where the eight sums meet.  Tiles of 16x16 rather than 32x32: four times as many workgroups, each with half as much
 // to load (64 KB at K = 512, 0.4 us of a CU's path from L2).
@@ -58,8 +58,8 @@ __global__ __launch_bounds__(kFewWaves* kWave) void gemm_f32_few_kernel(const fl
   const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
   const int m = m0 + i16 < M ? m0 + i16 : M - 1, n = n0 + i16 < N ? n0 + i16 : N - 1;   // rows past the end repeat the last one
   const int units = (K + 15) / 16;
-  FewLoader<true, U> fa, na;
-  FewLoader<BK, U> fb, nb;
+  FewLoader<true, U> fa;
+  FewLoader<BK, U> fb;
   fa.init(a, M, K, m);
   fb.init(b, N, K, n);
   fa.load(wave, quad, K);
@@ -130,29 +130,20 @@ __global__ __launch_bounds__(kFewWaves* kWave) void gemm_f32_few_kernel(const fl
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j][e], y[j][e], acc[j & 1], 0, 0, 0);
   };
-  if constexpr (!LN && U == 4) {   // longer reductions: the next 512 k in flight during the products of these
-    na = fa;
-    nb = fb;
-    int u = wave + kFewWaves * U;
-    while (u < units) {
-      na.load(u, quad, K);
-      nb.load(u, quad, K);
+  bool more = false;
+  if constexpr (!LN && U == 4) {   // more than 512 k: the others in flight during the products of these
+    more = wave + kFewWaves * U < units;
+    if (more) {
+      auto na = fa;
+      auto nb = fb;
+      na.load(wave + kFewWaves * U, quad, K);
+      nb.load(wave + kFewWaves * U, quad, K);
       __builtin_amdgcn_sched_barrier(0);
       products(fa.v, fb.v);
-      u += kFewWaves * U;
-      if (u >= units) {
-        fa = na;
-        fb = nb;
-        break;
-      }
-      fa.load(u, quad, K);
-      fb.load(u, quad, K);
-      __builtin_amdgcn_sched_barrier(0);
       products(na.v, nb.v);
-      u += kFewWaves * U;
     }
   }
-  products(fa.v, fb.v);
+  if (!more) products(fa.v, fb.v);
 #pragma unroll
   for (int r = 0; r < 4; ++r) red[wave][r * 64 + lane] = acc[0][r] + acc[1][r];
   __syncthreads();
