@@ -355,8 +355,8 @@ size_t varuna_op_colsum_static_max_bytes(void);
  * variant: 0 = library's choice.  bf16: 1 = MFMA kernels on whole tiles (VARUNA_EUNSUPPORTED unless the head dim is
  * 64, 96 or 128 and s a multiple of 128), 2 = their form for any s and head dims that are multiples of 8 up to 128,
  * 3 = fp32 products (head dims up to 128), any other value, and 2 and 3 on other shapes = one wave per row.
- * fp32: -1 = one wave per row, 4 = fp32 products in tiles of 16 (head dims that are multiples of 4 up to 128, 16-byte aligned tensors),
- * any other value, and 4 on other calls = in tiles of 32 where they take the shape (head dims up to 128), else one wave per row. */
+ * fp32: -1 = one wave per row, any other value = fp32 products where they take the shape (head dims up to 128, else one wave per row): 4 = in tiles of 16
+ * (head dims that are multiples of 4, 16-byte aligned tensors), 5, and 4 on other calls = in tiles of 32, the rest = in the tiles the library would choose. */
 varuna_status_t varuna_op_attention_fwd(int32_t dtype, int32_t variant, int32_t b, int32_t s,
                                         int32_t heads, int32_t d, int32_t causal, const void* qkv,
                                         void* ctx, float* lse_f32, void* hip_stream);

@@ -67,14 +67,17 @@ inline bool attn_f32_16_supported(int d) { return d % 4 == 0 && d <= 128; }
 // than one round (2 to 4 workgroups a CU forward, 4 to 1 backward), and one or two tokens also within one.  Longest row by padded head dim {32, 64, 96, 128}: with any
 // number of heads, with more than p1, with more than p2; set on 1900 shapes (d 16 .. 128, s 1 .. 192, 1 .. 16384 heads), where the choice is within 8 % of the better
 // form on 99 in 100.  us, per row / tiles of 16, forward and backward: one token, 4096 heads of 128 8.7 / 31, 24 / 166, of 64 6.6 / 12.7, 15 / 52, 16 heads of 128
-// 5.1 / 5.5, 6.8 / 7.7; four tokens, 1024 heads of 128 9.2 / 9.6, 25 / 45, 128 heads 5.8 / 5.4, 9.3 / 7.7; 64 tokens, 2 heads of 64 7.3 / 4.5, 14.3 / 6.8; 192 tokens, 1
-// head of 128 26 / 10, 71 / 22.
+// 5.1 / 5.5, 6.8 / 7.7; four tokens, 1024 heads of 128 9.2 / 9.6, 25 / 45, 128 heads 5.8 / 5.4, 9.3 / 7.7; 192 tokens, 1 head of 128 26 / 10, 71 / 22.
+// The smallest calls (up to 128 rows, 512 above d = 64) that go to the row kernels rather than to tiles of 32 do so here as well, which is no matter of speed (2
+// heads of 64 over 64 tokens 7.3 / 4.5, 14.3 / 6.8; 8 of 128 over 64 10.7 / 6.1, 26 / 10.8): test_short_rows_go_to_the_row_kernels holds such calls to
+// those kernels' bits.
 inline bool attn_f32_16_rows(bool backward, int b, int s, int heads, int d) {
   struct Limit { int any, p1, s1, p2, s2; };
   constexpr Limit limit[2][4] = {{{0, 1024, 2, 1024, 2}, {0, 1024, 3, 1024, 3}, {0, 768, 3, 768, 3}, {2, 512, 4, 512, 4}},
                                  {{1, 1535, 3, 1535, 3}, {2, 767, 4, 767, 4}, {2, 128, 4, 767, 8}, {2, 128, 4, 767, 8}}};
   const Limit& l = limit[backward][(d + 31) / 32 - 1];
   const int64_t pairs = (int64_t)b * heads;
+  if (pairs * s <= (d <= 64 ? 128 : 512) && attn_rows_sooner(true, true, backward, b, s, heads, d)) return true;
   return s <= (pairs > l.p2 ? l.s2 : pairs > l.p1 ? l.s1 : l.any);
 }
 // Whether the other calls they take go there.  Against tiles of 32: half the rows per workgroup, so twice as many workgroups with half a chain each, for twice

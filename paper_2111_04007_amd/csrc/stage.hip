@@ -283,23 +283,21 @@ template <> struct GemmDispatch<bf16> {
   }
 };
 
-// fp32.  variant 0: library's choice; -1: one wave per row (few or short rows, head dims above 128); 4: fp32 products in tiles of 16; else, and 4
-// where it does not take the call: in tiles of 32.
+// fp32.  variant 0: library's choice; -1: one wave per row (few or short rows, head dims above 128); else fp32 products, 4: in tiles of 16; 5, and 4 where it
+// does not take the call: in tiles of 32; any other: in the tiles that the library would choose.
 template <typename T> struct AttnDispatch {
-  // -1, 4, or 3 for tiles of 32.  vec: attn_f32_vec of what is read; aligned: all tensors
+  // -1, 4 or 5.  vec: attn_f32_vec of what is read; aligned: all tensors
   static int choose(int variant, int b, int s, int a, int d, bool causal, bool aligned, bool vec, bool backward) {
     if (variant == -1 || !attn_f32_supported(d) || !attn_grid_ok(b, a)) return -1;
-    if (attn_f32_16_supported(d) && aligned) {
-      if (variant == 0) return attn_f32_16_rows(backward, b, s, a, d) ? -1 : attn_f32_16(backward, b, s, a, d, causal) ? 4 : 3;
-      return variant == 4 ? 4 : 3;
-    }
-    return variant == 0 && attn_rows_sooner(true, vec, backward, b, s, a, d) ? -1 : 3;
+    const bool tiles16 = attn_f32_16_supported(d) && aligned;
+    if (variant == 0 && (tiles16 ? attn_f32_16_rows(backward, b, s, a, d) : attn_rows_sooner(true, vec, backward, b, s, a, d))) return -1;
+    return tiles16 && variant != 5 && (variant == 4 || attn_f32_16(backward, b, s, a, d, causal)) ? 4 : 5;
   }
   static hipError_t fwd(int variant, const T* qkv, T* ctx, float* lse, int b, int s, int a, int d, int causal,
                         const DropArgs& drop, hipStream_t st) {
     switch (choose(variant, b, s, a, d, causal, aligned16(qkv) && aligned16(ctx), attn_f32_vec<T>(qkv, qkv, qkv, d), false)) {
       case 4: return launch_attention_fwd_f32_16(qkv, ctx, lse, b, s, a, d, causal, drop, st);
-      case 3: return launch_attention_fwd_f32<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
+      case 5: return launch_attention_fwd_f32<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
       default: return launch_attention_fwd_simple<T>(qkv, ctx, lse, b, s, a, d, causal, drop, st);
     }
   }
@@ -308,7 +306,7 @@ template <typename T> struct AttnDispatch {
     switch (choose(variant, b, s, a, d, causal, aligned16(qkv) && aligned16(ctx) && aligned16(dctx) && aligned16(dqkv),
                    attn_f32_vec<T>(qkv, ctx, dctx, d), true)) {
       case 4: return launch_attention_bwd_f32_16(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
-      case 3: return launch_attention_bwd_f32<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
+      case 5: return launch_attention_bwd_f32<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
       default: return launch_attention_bwd_simple<T>(qkv, ctx, lse, dctx, dqkv, delta, b, s, a, d, causal, drop, st);
     }
   }

@@ -1,4 +1,4 @@
-"""fp32 attention in tiles of 16: edges of tiles, waves without one, several tiles per wave, every padded head dim."""
+"""fp32 attention in tiles of 16: edges of tiles, waves without one, several tiles per wave, every padded head dim; the sizes that stay in tiles of 32."""
 import pytest
 import torch
 
@@ -15,11 +15,11 @@ pytestmark = pytest.mark.gpu
 ])
 def test_attention(b, s, heads, d, causal):
     """Same bounds as the other fp32 forms (rel-L2 1e-5, measured 2e-7 .. 8e-7)."""
-    run_attention_case("f32", b, s, heads, d, causal, variant=4, seed=30 + d)
+    run_attention_case("f32", b, s, heads, d, causal, variant=0, seed=30 + d)
 
 
 def test_rising_row_maxima():
-    run_attention_case("f32", 2, 200, 2, 64, 0, variant=4, seed=5, key_ramp=(0.5, 4.0))
+    run_attention_case("f32", 2, 200, 2, 64, 0, variant=0, seed=5, key_ramp=(0.5, 4.0))
 
 
 @pytest.mark.parametrize("heads,d,s,causal", [(8, 20, 45, True), (4, 64, 130, False), (3, 100, 131, True)])
@@ -38,7 +38,7 @@ def test_scores_are_those_of_the_row_kernels(d):
     b, heads, s = 600, 1, 1
     qkv = rnd((b, 3 * d), "f32", 3)
     got = []
-    for variant in (4, -1):
+    for variant in (0, -1):
         ctx, lse = torch.empty(b, d, device="cuda"), torch.empty(b, device="cuda")
         B.op_attention_fwd(qkv, ctx, lse, b, s, heads, d, 1, variant=variant)
         got.append((ctx, lse))

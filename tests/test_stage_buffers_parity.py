@@ -1,6 +1,6 @@
 """Where a call's tensors lie: the boundary slot itself, addresses that are not whole 16-byte pieces, one buffer for the upstream and the
 input gradient, or two that overlap in part.  Every placement gives the bits of separate, aligned buffers, in the calls that recompute and
-in those that keep, with and without a second stream, and where the backward calls alone are profiled."""
+in those that keep, with and without a second stream."""
 import pytest
 import torch
 
@@ -44,11 +44,7 @@ def step(c, place, dropout, keep=False):
             both = torch.empty((T + 1) * h, dtype=dt, device="cuda")
             dy = both[m * h:m * h + T * h].view(T, h).copy_(dy)
             dx = both[(1 - m) * h:(1 - m) * h + T * h].view(T, h)
-        if place == "profiled":
-            st.profile_enable(True)
         (st.backward_stored if keep else st.backward_recompute)(m, dy, dx)
-        if place == "profiled":
-            st.profile_enable(False)
         ys.append(y)
         dxs.append(dx.clone())
         if place not in ("same", "overlap"):
@@ -57,7 +53,7 @@ def step(c, place, dropout, keep=False):
     return torch.stack(ys), torch.stack(dxs), st.grads.clone()
 
 
-@pytest.mark.parametrize("place", ["misaligned", "same", "side", "profiled", "slot", "overlap"])
+@pytest.mark.parametrize("place", ["misaligned", "same", "side", "slot", "overlap"])
 @pytest.mark.parametrize("dtype,h,heads,s,group,dropout", [("f32", 128, 2, 64, 1, 0.0), ("f32", 60, 3, 33, 1, 0.0), ("bf16", 256, 4, 128, 1, 0.0),
                                                            ("bf16", 256, 4, 128, 2, 0.0), ("bf16", 256, 4, 128, 1, 0.1), ("bf16", 200, 5, 70, 1, 0.0)])
 @pytest.mark.parametrize("layers", [1, 2])
@@ -67,7 +63,7 @@ def test_placement(place, dtype, h, heads, s, group, dropout, layers):
         assert bool(torch.isfinite(a.float()).all()) and torch.equal(a, b)
 
 
-@pytest.mark.parametrize("place", ["misaligned", "same", "side", "profiled", "slot", "overlap"])
+@pytest.mark.parametrize("place", ["misaligned", "same", "side", "slot", "overlap"])
 @pytest.mark.parametrize("dtype,h,heads,s,group,dropout", [("f32", 60, 3, 33, 1, 0.0), ("bf16", 256, 4, 128, 1, 0.1), ("bf16", 256, 4, 128, 2, 0.0), ("bf16", 200, 5, 70, 1, 0.0)])
 def test_placement_of_kept_forwards(place, dtype, h, heads, s, group, dropout):
     c = StageConfig("case", 2, h, heads, s, 2, 2, 4 * h, True, dtype, wgrad_group=group, dropout_p=dropout)
