@@ -245,16 +245,20 @@ varuna_status_t varuna_stage_debug_saved_region(const varuna_stage_t* st, size_t
  * thread-safe, for same-process A/B timing only: results of every configuration agree to rounding but not bit for bit. */
 varuna_status_t varuna_debug_set_gemm_kernels(int32_t fwd256, int32_t dgrad256, int32_t wgrad256,
                                               int32_t fwd128, int32_t dgrad128, int32_t wgrad128);
-/* Host only (no GPU call): the kernel configuration the library picks for a bf16 product of
- * contiguous, 16-byte aligned operands, op as in varuna_op_gemm (0 forward, 1 dgrad, 2 wgrad):
- * a `variant` number of varuna_op_gemm by the tiles' rounds on the chip (the launch may take another one that ends sooner, for
- * instance merged tiles 192 wide, configuration 24, in place of 20), -1 for the kernels on small tiles whose waves share the reduction (rows that are
- * not whole 16-byte pieces, and products of few 128x128 tiles), -2 for an invalid argument. */
+/* Host only (no GPU call): the kernel configuration of a bf16 product of contiguous, 16-byte aligned operands by the tiles' rounds on the
+ * chip alone, op as in varuna_op_gemm (0 forward, 1 dgrad, 2 wgrad): a `variant` number of varuna_op_gemm, -1 for the kernels on small
+ * tiles whose waves share the reduction (rows that are not whole 16-byte pieces, and products of few 128x128 tiles), -2 for an
+ * invalid argument.  What runs is varuna_debug_gemm_launch's answer. */
 int32_t varuna_debug_gemm_choice(int32_t op, int64_t M, int64_t N, int64_t K);
-/* Host only: the configuration (18, 19, 22 or 23) on which the weight gradients of n_layers (1 to 4) consecutive
- * bf16 layers over `tokens` stacked tokens (16-byte aligned) run as one launch, -1 if they share one launch of the small tiles
- * (at most 128 tiles of 128x128 in all; more layers than that run one by one), 0 if they run one by one, -2 for an invalid argument. */
+/* The configuration that runs, epi as in varuna_op_gemm: the same, or another one that epilogue and length of the reduction let end sooner. */
+int32_t varuna_debug_gemm_launch(int32_t op, int32_t epi, int64_t M, int64_t N, int64_t K);
+/* Host only: the configuration (18, 19, 22 or 23) by the tiles' rounds for the weight gradients of n_layers (1 to 4) consecutive
+ * bf16 layers over `tokens` stacked tokens (16-byte aligned) in one launch, -1 if they share one launch of the small tiles
+ * (at most 128 tiles of 128x128 in all; more layers than that run one by one), 0 if they run one by one, -2 for an invalid argument.  What runs is
+ * varuna_debug_wgrad_group_launch's answer. */
 int32_t varuna_debug_wgrad_group_choice(int32_t n_layers, int64_t hidden, int64_t mlp, int64_t tokens);
+/* What runs: the same, or over long reductions larger tiles (18 or 23). */
+int32_t varuna_debug_wgrad_group_launch(int32_t n_layers, int64_t hidden, int64_t mlp, int64_t tokens);
 
 /* ---- per-kernel timing (HIP events on the caller's stream) -------------- */
 

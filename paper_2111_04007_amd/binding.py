@@ -34,7 +34,7 @@ EXPORTS = (
     "varuna_op_colreduce_scratch_bytes", "varuna_op_attention_fwd", "varuna_op_attention_bwd",
     "varuna_op_colsum_static", "varuna_op_colsum_static_max_bytes", "varuna_probe_mfma_rate",
     "varuna_debug_set_gemm_kernels",
-    "varuna_debug_gemm_choice", "varuna_debug_wgrad_group_choice",
+    "varuna_debug_gemm_choice", "varuna_debug_gemm_launch", "varuna_debug_wgrad_group_choice", "varuna_debug_wgrad_group_launch",
 )
 
 
@@ -106,7 +106,9 @@ def load():
         "varuna_op_colsum_static_max_bytes": (sz, []),
         "varuna_debug_set_gemm_kernels": (i32, [i32] * 6),
         "varuna_debug_gemm_choice": (i32, [i32, i64, i64, i64]),
+        "varuna_debug_gemm_launch": (i32, [i32, i32, i64, i64, i64]),
         "varuna_debug_wgrad_group_choice": (i32, [i32, i64, i64, i64]),
+        "varuna_debug_wgrad_group_launch": (i32, [i32, i64, i64, i64]),
         "varuna_probe_mfma_rate": (i32, [vp, i64, i32, i32, i32, vp, C.POINTER(C.c_double), vp]),
         "varuna_op_attention_fwd": (i32, [i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp]),
         "varuna_op_attention_bwd": (i32, [i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp]),
@@ -312,13 +314,23 @@ def debug_set_gemm_kernels(fwd256=0, dgrad256=0, wgrad256=0, fwd128=0, dgrad128=
 
 
 def debug_gemm_choice(op: int, M: int, N: int, K: int) -> int:
-    """Host only: the bf16 GEMM kernel configuration the library picks for this product."""
+    """Host only: the bf16 GEMM kernel configuration of this product by its tiles' rounds alone."""
     return int(load().varuna_debug_gemm_choice(op, M, N, K))
 
 
+def debug_gemm_launch(op: int, epi: int, M: int, N: int, K: int) -> int:
+    """Host only: the bf16 GEMM kernel configuration this product runs on (aligned operands)."""
+    return int(load().varuna_debug_gemm_launch(op, epi, M, N, K))
+
+
 def debug_wgrad_group_choice(n_layers: int, hidden: int, mlp: int, tokens: int) -> int:
-    """Host only: the configuration on which these layers' bf16 weight gradients share a launch (0: one by one)."""
+    """Host only: the configuration, by their tiles' rounds alone, on which these layers' bf16 weight gradients share a launch (0: one by one)."""
     return int(load().varuna_debug_wgrad_group_choice(n_layers, hidden, mlp, tokens))
+
+
+def debug_wgrad_group_launch(n_layers: int, hidden: int, mlp: int, tokens: int) -> int:
+    """Host only: the configuration on which they do share one."""
+    return int(load().varuna_debug_wgrad_group_launch(n_layers, hidden, mlp, tokens))
 
 
 def probe_mfma_rate(operands, waves_per_simd: int, iters: int, sink, pattern: int = 0, stream=None) -> float:

@@ -815,8 +815,8 @@ __global__ __launch_bounds__(WGM* WGN* kWave) void gemm_group_kernel(DgGroup g, 
 //   20: 128x256, 21: 256x128, 4 waves, three stages of both operands (LS 5)
 //   24: 128x192 in that form, forward only; the library takes it in place of 20 where dg_narrow says so
 //   22, 23: as 19, 18 for sizes that are no multiples of the tile (EDGE)
-// What a debug query reports is dg_pick's and dg_group_choice's word; dg_at_launch and dg_group_wide may take another configuration when the
-// product is launched.
+// dg_pick and dg_group_choice go by the tiles' rounds (the debug queries _choice); dg_at_launch and dg_group_wide may take another configuration when the
+// product is launched (the queries _launch).
 // ---------------------------------------------------------------------------
 inline bool dg_variant_tile(int variant, GemmTile* t) {
   switch (variant) {
@@ -1042,8 +1042,8 @@ inline int dg_group_choice(const DgJob* jobs, int n, int64_t K) {
 // per 1024 tokens and round: 256x256 tiles take 24 in whole rounds and 25 of epilogue per round's worth of tiles, 128x128 tiles 15 and
 // 10 and refill as they drain, 0.3 of a round lost at the end (fitted over 512 and more tiles; off by up to 7 %, below 2048 tokens by more).
 // Measured, 128x128 / 256x256 (us, all weight gradients): one layer 1920 wide over 4096 tokens 393 / 362, two 793 / 700, 1024 wide over 4096
-// 137 / 121, 1536 wide 261 / 231, 1280 wide, two layers over 8192 711 / 629; where 128x128 stay: 1600 wide, two layers over 2000 313 / 317,
-// 4096 wide over 1024 581 / 625.
+// 137 / 121, 1536 wide 261 / 231; where 128x128 stay: 1600 wide, two layers over 2000 313 / 317, 4096 wide over 1024 581 / 625 (and, 2 % below
+// the line by the estimate, 1280 wide, two layers over 8192 711 / 629).
 inline int dg_group_wide(int variant, const DgJob* jobs, int n, int64_t K) {
   if ((variant != 19 && variant != 22) || K < 2048 || dg_flavours().named) return variant;
   int64_t t5 = 0, t7 = 0;

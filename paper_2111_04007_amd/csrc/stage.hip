@@ -200,6 +200,11 @@ int wgrad_group_choice(const DgJob* jobs, int n, int64_t K, bool aligned) {
   for (int i = 0; i < n; ++i) tiles += gf_tiles(jobs[i].M, jobs[i].N, 128);
   return tiles <= kCutGroupTiles ? -1 : 0;
 }
+// The same, where the launch takes larger tiles than that after all.
+int wgrad_group_launch(const DgJob* jobs, int n, int64_t K, bool aligned) {
+  const int v = wgrad_group_choice(jobs, n, K, aligned);
+  return v > 0 ? dg_group_wide(v, jobs, n, K) : v;
+}
 
 }  // namespace
 
@@ -261,6 +266,12 @@ template <> struct GemmDispatch<float> {
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 template <> struct GemmDispatch<bf16> {
+  // What the library runs a product of contiguous, 16-byte aligned operands on (-1: gemm_cut.h)
+  static int choose(int op, int mode, int64_t M, int64_t N, int64_t K) {
+    const int64_t lda = (op == GEMM_WGRAD) ? M : K, ldb = (op == GEMM_FWD) ? K : N;
+    const int v = N % 8 == 0 ? dg_pick(op, M, N, K, lda, ldb) : 0;
+    return v == 0 ? -1 : dg_at_launch(v, op, mode, M, N, K, lda, ldb);
+  }
   // variant 0: library's choice; -1: force the kernels of gemm_cut.h; >0: that MFMA configuration
   static hipError_t run(int op, int mode, int variant, int64_t M, int64_t N, int64_t K, const bf16* a,
                         const bf16* b, const EpiArgs<bf16>& e, hipStream_t s, int splits = 1) {
@@ -268,12 +279,7 @@ template <> struct GemmDispatch<bf16> {
     const int64_t ldb = (op == GEMM_FWD) ? K : N;
     const bool ptr_ok = aligned16(a) && aligned16(b) && aligned16(e.bias) && aligned16(e.aux_in) &&
                         aligned16(e.out) && aligned16(e.aux_out) && aligned16(e.out_f32) && (N % 8 == 0);
-    int v = variant;
-    if (v == 0) {
-      v = ptr_ok ? dg_pick(op, M, N, K, lda, ldb) : -1;
-      if (v == 0) v = -1;
-      if (splits == 1) v = dg_at_launch(v, op, mode, M, N, K, lda, ldb);
-    }
+    const int v = variant != 0 ? variant : ptr_ok ? choose(op, mode, M, N, K) : -1;
     if (v >= 5) {
       if (!ptr_ok || !dg_shape_ok(v, M, N, K, lda, ldb) || (v == 24 && op != GEMM_FWD)) return hipErrorInvalidConfiguration;
       return launch_gemm_dma(op, mode, v, a, lda, b, ldb, M, N, K, e, s, splits);
@@ -556,10 +562,10 @@ struct StageOps {
         bytes += ((double)jobs[i].M + jobs[i].N) * K * sizeof(T) + 8.0 * mn;
       }
       if constexpr (std::is_same<T, bf16>::value) {
-        const int v = wgrad_group_choice(jobs, n, K, aligned);
+        const int v = wgrad_group_launch(jobs, n, K, aligned);
         if (v != 0) {
           Bracket br(S, st, VARUNA_K_GEMM_WGRAD, flops, bytes);
-          if ((e = v > 0 ? launch_gemm_group(dg_group_wide(v, jobs, n, K), jobs, n, K, st) : launch_gemm_cut_group(jobs, n, K, st))) return e;
+          if ((e = v > 0 ? launch_gemm_group(v, jobs, n, K, st) : launch_gemm_cut_group(jobs, n, K, st))) return e;
           continue;
         }
       } else {
@@ -910,17 +916,21 @@ varuna_status_t varuna_stage_profile_collect(varuna_stage_t* st, double* ms, int
 
 // ---- single operations -------------------------------------------------------
 
+// The epilogue of varuna_op_gemm's op and epi, or -1.
+static int gemm_mode(int32_t op, int32_t epi) {
+  if (op == GEMM_FWD && epi >= 0 && epi <= 2) return epi;
+  if (op == GEMM_DGRAD && (epi == 0 || epi == 3)) return epi == 0 ? EPI_PLAIN : EPI_DGELU;
+  return op == GEMM_WGRAD && epi == 0 ? EPI_ACCUM_F32 : -1;
+}
+
 varuna_status_t varuna_op_gemm(int32_t dtype, int32_t op, int32_t epi, int32_t variant, int64_t M, int64_t N, int64_t K,
                                const void* a, const void* b, const void* bias, const void* aux_in, void* out,
                                void* aux_out, void* hip_stream) {
   if (M < 1 || N < 1 || K < 1 || M > (1ll << 30) || N > (1ll << 30) || K > (1ll << 30)) return fail(VARUNA_EINVAL, "bad GEMM size");
   if (!a || !b || !out) return fail(VARUNA_EINVAL, "NULL operand");
-  int mode;
-  if (op == GEMM_FWD && epi >= 0 && epi <= 2) mode = epi;
-  else if (op == GEMM_DGRAD && (epi == 0 || epi == 3)) mode = epi == 0 ? EPI_PLAIN : EPI_DGELU;
-  else if (op == GEMM_WGRAD && epi == 0) mode = EPI_ACCUM_F32;
-  else if (op == GEMM_WGRAD && epi == 4 && dtype == VARUNA_BF16 && variant >= 5) mode = EPI_PLAIN;  // tuning aid: no accumulate
-  else return fail(VARUNA_EINVAL, "unknown op/epilogue combination %d/%d", op, epi);
+  int mode = gemm_mode(op, epi);
+  if (op == GEMM_WGRAD && epi == 4 && dtype == VARUNA_BF16 && variant >= 5) mode = EPI_PLAIN;  // tuning aid: no accumulate
+  if (mode < 0) return fail(VARUNA_EINVAL, "unknown op/epilogue combination %d/%d", op, epi);
   if (op == GEMM_FWD && !bias) return fail(VARUNA_EINVAL, "forward GEMM needs a bias");
   if ((mode == EPI_BIAS_RES || mode == EPI_DGELU) && !aux_in) return fail(VARUNA_EINVAL, "epilogue needs aux_in");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
@@ -1055,16 +1065,34 @@ int32_t varuna_debug_gemm_choice(int32_t op, int64_t M, int64_t N, int64_t K) {
   return v == 0 ? -1 : v;
 }
 
-int32_t varuna_debug_wgrad_group_choice(int32_t n_layers, int64_t hidden, int64_t mlp, int64_t tokens) {
+int32_t varuna_debug_gemm_launch(int32_t op, int32_t epi, int64_t M, int64_t N, int64_t K) {
+  const int mode = gemm_mode(op, epi);
+  if (mode < 0 || M < 1 || N < 1 || K < 1 || M > (1ll << 30) || N > (1ll << 30) || K > (1ll << 30)) return -2;
+  return GemmDispatch<bf16>::choose(op, mode, M, N, K);
+}
+
+// The weight gradients of n_layers layers; how many, or 0 for an invalid argument.
+static int debug_wgrad_jobs(DgJob* jobs, int32_t n_layers, int64_t hidden, int64_t mlp, int64_t tokens) {
   if (n_layers < 1 || n_layers > kMaxGroupJobs / 4 || hidden < 1 || mlp < 1 || hidden > (1 << 20) || mlp > (1 << 22) || tokens < 1 || tokens > (1ll << 30))
-    return -2;
+    return 0;
   const int h = (int)hidden, f = (int)mlp;
-  DgJob jobs[kMaxGroupJobs];
   for (int l = 0; l < n_layers; ++l) {
     const int mn[4][2] = {{h, f}, {f, h}, {h, h}, {3 * h, h}};
     for (int i = 0; i < 4; ++i) jobs[4 * l + i] = {nullptr, nullptr, nullptr, mn[i][0], mn[i][1]};
   }
-  return wgrad_group_choice(jobs, 4 * n_layers, tokens, true);
+  return 4 * n_layers;
+}
+
+int32_t varuna_debug_wgrad_group_choice(int32_t n_layers, int64_t hidden, int64_t mlp, int64_t tokens) {
+  DgJob jobs[kMaxGroupJobs];
+  const int n = debug_wgrad_jobs(jobs, n_layers, hidden, mlp, tokens);
+  return n > 0 ? wgrad_group_choice(jobs, n, tokens, true) : -2;
+}
+
+int32_t varuna_debug_wgrad_group_launch(int32_t n_layers, int64_t hidden, int64_t mlp, int64_t tokens) {
+  DgJob jobs[kMaxGroupJobs];
+  const int n = debug_wgrad_jobs(jobs, n_layers, hidden, mlp, tokens);
+  return n > 0 ? wgrad_group_launch(jobs, n, tokens, true) : -2;
 }
 
 varuna_status_t varuna_probe_mfma_rate(const void* operands, int64_t n_elems, int32_t waves_per_simd, int32_t pattern,
