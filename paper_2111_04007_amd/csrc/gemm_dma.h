@@ -950,8 +950,9 @@ inline bool dg_wgrad_wide(int64_t M, int64_t N, int64_t K) {
 
 // The configuration that runs in place of dg_pick's `v`, which knows the tiles' rounds but neither the epilogue nor the reduction's length.
 // Measured on the products of layers 768 to 5120 wide over 512 to 6144 tokens, operands out of cache (us, dg_pick's / this one's):
-//   forward on the 192-wide merged tiles, where dg_narrow says so or where they take the place of 128x128 tiles in up to three rounds of
-//     which the last is 7/8 full: 2048x9216x3072 129 / 123, 2048x9216x2304 114 / 109, 2048x5760x1920 56 / 53; in six rounds 225 / 243;
+//   forward on the 192-wide merged tiles, where dg_narrow says so or, from 1536 k on, where they take the place of 128x128 tiles in up to three rounds
+//     of which the last is 7/8 full: 2048x9216x3072 129 / 123, GeLU 2048x9216x2304 114 / 109, 6144x3072x1536 67.2 / 64.9; in six rounds 225 / 243; shorter
+//     reductions (128x128 tiles / these) 6144x3072x512 30.0 / 32.8, GeLU 6144x3072x1024 52 / 55, residual 4096x4608x64 22 / 27;
 //   forward on 256x256 where the others need many more rounds (a round costs 70 on those, 46 on merged tiles, 50 on 128x128, which refill):
 //     4096x9216x3072 225 / 212, 4096x10240x2560 239 / 207, 2048x20480x5120 403 / 380; short reductions 6144x6144x1536 130 / 140;
 //   merged tiles 256x128, not 128x256, for outputs clearly wider than tall, in whole groups of 8 tile rows: dgrad 1024x5120x15360 222 / 194,
@@ -980,7 +981,7 @@ inline int dg_at_launch(int v, int op, int mode, int64_t M, int64_t N, int64_t K
   if (v == 19) {
     if (op != GEMM_FWD || !dg_shape_ok(24, M, N, K, lda, ldb)) return v;
     const int64_t t24 = (M / 128) * (N / 192);
-    return t24 >= 384 && t24 <= 768 && ((t24 + 255) / 256 * 256 - t24) * 8 <= 256 ? 24 : v;
+    return K >= 1536 && t24 >= 384 && t24 <= 768 && ((t24 + 255) / 256 * 256 - t24) * 8 <= 256 ? 24 : v;
   }
   const bool wide = mode == EPI_BIAS || mode == EPI_BIAS_GELU || mode == EPI_DGELU ? 2 * N >= 3 * M : N >= 3 * M;
   return wide && (M <= 2048 || M % 2048 == 0) && dg_shape_ok(21, M, N, K, lda, ldb) ? 21 : v;

@@ -8,8 +8,8 @@ FWD, DGRAD, WGRAD = 0, 1, 2
 
 
 @pytest.mark.parametrize("op,epi,M,N,K,choice,runs", [
-    (FWD, 0, 6144, 3072, 64, 19, 24), (FWD, 0, 6144, 3840, 64, 20, 20), (FWD, 0, 8192, 3072, 64, 20, 20),      # 192-wide merged tiles: up to three rounds
-    (FWD, 2, 2048, 5760, 192, 19, 24), (FWD, 0, 2048, 3072, 3072, 20, 24),
+    (FWD, 0, 6144, 3072, 1536, 19, 24), (FWD, 0, 6144, 3840, 1536, 20, 20), (FWD, 0, 8192, 3072, 1536, 20, 20),      # 192-wide merged tiles: up to three rounds
+    (FWD, 1, 6144, 3072, 1472, 19, 19), (FWD, 0, 2048, 9216, 64, 19, 19), (FWD, 2, 2048, 5760, 192, 19, 19), (FWD, 0, 2048, 3072, 3072, 20, 24),   # and long reductions
     (FWD, 1, 4096, 10240, 2304, 20, 17), (FWD, 1, 4096, 10240, 2240, 20, 21),                                   # 256x256: long reductions
     (FWD, 2, 4096, 9216, 2304, 19, 17), (FWD, 2, 4096, 9216, 2240, 19, 19),
     (FWD, 0, 1024, 6912, 64, 20, 21), (FWD, 0, 3072, 7680, 2560, 20, 20),                                       # merged tiles turned: clearly wide, whole groups of rows
