@@ -962,13 +962,18 @@ inline bool dg_wgrad_wide(int64_t M, int64_t N, int64_t K) {
 //   the ragged form of the 256x256 tiles for sides that are odd multiples of 128, where its rounds cost less (70 each, against 48 of 128x128 tiles
 //     however those are merged, 42 under GeLU', whose epilogue is the longer one there; a single round against more than 1.2): forward 1920x7680x1920
 //     80 / 53, 4224x3712x3712 129 / 100, 2048x5760x1920 54 / 50, 4480x6912x2304 179 / 130, 6016x4224x1408 94 / 71; dgrad 1408x10752x3584 137 / 96,
-//     GeLU' 143 / 109; not 4096x5760x1920 91 / 97 (2.81 rounds of 128x128), 3200x4992x1664 63 / 76 (1.90), GeLU' 2944x9216x2304 138 / 143 (3.23).
+//     GeLU' 143 / 109; not 4096x5760x1920 91 / 97 (2.81 rounds of 128x128), 3200x4992x1664 63 / 76 (1.90), GeLU' 2944x9216x2304 138 / 143 (3.23).  Merged tiles that
+//     nearly fill three rounds cost less than two of these, except 128x256 ones on a wide output: not 2304x10880x1792 residual 102 / 114 (2.99 of 3 rounds),
+//     3072x8064x2688 127 / 133, GeLU 19328x1280x3008 143 / 160, 12800x1920x3200 159 / 170; but GeLU 1920x12800x3200 202 / 159 (2.93), and six against four
+//     8832x5632x1472 168 / 152, dgrad 11776x4224x1152 141 / 126 (GeLU 13312x3712x1536 164 / 172).
 inline int dg_at_launch(int v, int op, int mode, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
   const int64_t t5 = ((M + 255) / 256) * ((N + 255) / 256), rounds5 = (t5 + 255) / 256;
   if ((v == 19 || v == 20 || v == 21) && op != GEMM_WGRAD && !dg_flavours().named && K >= 1024 && !dg_shape_ok(5, M, N, K, lda, ldb) &&
       dg_shape_ok(23, M, N, K, lda, ldb)) {
-    const double f7 = (double)((M / 128) * (N / 128)) / 512.0;
-    if (70.0 * (double)rounds5 <= (mode == EPI_DGELU ? 42.0 : 48.0) * f7 || (rounds5 == 1 && mode != EPI_DGELU && f7 > 1.2)) return 23;
+    const int64_t t7 = (M / 128) * (N / 128);
+    const double f7 = (double)t7 / 512.0;
+    const bool merged = rounds5 == 2 && (t7 + 511) / 512 == 3 && (v == 21 || (v == 20 && 2 * N < 3 * M));
+    if (!merged && (70.0 * (double)rounds5 <= (mode == EPI_DGELU ? 42.0 : 48.0) * f7 || (rounds5 == 1 && mode != EPI_DGELU && f7 > 1.2))) return 23;
   }
   if (v == 20 && op == GEMM_FWD && dg_narrow(M, N)) return 24;
   if (dg_flavours().named) return v;

@@ -18,6 +18,7 @@ FWD, DGRAD, WGRAD = 0, 1, 2
     (DGRAD, 3, 1024, 10240, 2304, 18, 17), (DGRAD, 3, 1024, 10240, 2240, 18, 18),
     (FWD, 0, 1920, 7680, 1024, 19, 23), (FWD, 0, 1920, 7680, 960, 19, 19), (FWD, 1, 4480, 6912, 1088, 20, 23), (FWD, 2, 6016, 4224, 1024, 19, 23),   # odd multiples of 128
     (FWD, 1, 4096, 5760, 1920, 21, 21), (FWD, 0, 3200, 4992, 1664, 19, 19),
+    (FWD, 2, 2304, 10880, 1792, 21, 21), (FWD, 0, 8064, 3072, 2816, 20, 20), (FWD, 1, 1920, 12800, 3200, 20, 23), (FWD, 0, 8832, 5632, 1472, 20, 23),   # against merged tiles in three rounds
     (DGRAD, 0, 1408, 10752, 1152, 19, 23), (DGRAD, 3, 1408, 10752, 1024, 19, 23), (DGRAD, 0, 2944, 9216, 2304, 19, 23), (DGRAD, 3, 2944, 9216, 2304, 19, 19),
     (WGRAD, 0, 1920, 7680, 512, 19, 23), (WGRAD, 0, 1920, 7680, 448, 19, 19), (WGRAD, 0, 7680, 1920, 576, 19, 23), (WGRAD, 0, 9984, 1152, 512, 19, 23),
     (WGRAD, 0, 384, 25600, 640, 19, 23), (WGRAD, 0, 384, 25472, 640, 19, 19), (WGRAD, 0, 4480, 4480, 2048, 19, 19),
