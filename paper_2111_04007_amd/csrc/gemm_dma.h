@@ -939,13 +939,16 @@ inline bool dg_narrow(int64_t M, int64_t N) {
 
 // Whether one weight gradient that dg_pick gives to 128x128 tiles because its sides are multiples of 128 but not of 256 takes the EDGE form of
 // the 256x256 ones (23): by the same rounds as dg_choose_variant, 1.05 for EDGE.  From 600 tiles on (just above one round of 128x128
-// the two are even) and from 512 on in K (shorter ones spend their time in the epilogue: 9984x1152 over 64 23.4 / 26.7).
+// the two are even) and from 512 on in K (shorter ones spend their time in the epilogue: 9984x1152 over 64 23.4 / 26.7).  Below 768 k a part of a round of
+// 128x128 tiles, which refill, counts as that part and a half, not as a whole one: 8832x2944 (3.1 rounds) over 512 68 / 72, 5760x4480 (3.08) over 576 73 / 76.
 // Measured, 128x128 / 256x256 (us): 1920x7680 over 512, 2048, 8192 45 / 40, 99 / 74, 357 / 213; 5760x1920 over 2048 74 / 65; 9984x1152 75 / 67;
 // where 128x128 stay: 2944^2 over 1024 40 / 41, 4480^2 over 2048 118 / 129, 6016x2944 104 / 116, 1920^2 26 / 47.
 inline bool dg_wgrad_wide(int64_t M, int64_t N, int64_t K) {
   if (dg_shape_ok(5, M, N, K, M, N) || !dg_shape_ok(23, M, N, K, M, N)) return false;
   const int64_t t5 = ((M + 255) / 256) * ((N + 255) / 256), t7 = (M / 128) * (N / 128);
-  return K >= 512 && t7 >= 600 && (double)((t5 + 255) / 256) * 4.0 / 1.15 * 1.05 <= (double)((t7 + 511) / 512) * 2.0;
+  double rounds7 = (double)((t7 + 511) / 512);
+  if (K < 768 && (double)t7 / 512.0 + 0.5 < rounds7) rounds7 = (double)t7 / 512.0 + 0.5;
+  return K >= 512 && t7 >= 600 && (double)((t5 + 255) / 256) * 4.0 / 1.15 * 1.05 <= rounds7 * 2.0;
 }
 
 // The configuration that runs in place of dg_pick's `v`, which knows the tiles' rounds but neither the epilogue nor the reduction's length.

@@ -21,7 +21,7 @@ FWD, DGRAD, WGRAD = 0, 1, 2
     (FWD, 2, 2304, 10880, 1792, 21, 21), (FWD, 0, 8064, 3072, 2816, 20, 20), (FWD, 1, 1920, 12800, 3200, 20, 23), (FWD, 0, 8832, 5632, 1472, 20, 23),   # against merged tiles in three rounds
     (DGRAD, 0, 1408, 10752, 1152, 19, 23), (DGRAD, 3, 1408, 10752, 1024, 19, 23), (DGRAD, 0, 2944, 9216, 2304, 19, 23), (DGRAD, 3, 2944, 9216, 2304, 19, 19),
     (WGRAD, 0, 1920, 7680, 512, 19, 23), (WGRAD, 0, 1920, 7680, 448, 19, 19), (WGRAD, 0, 7680, 1920, 576, 19, 23), (WGRAD, 0, 9984, 1152, 512, 19, 23),
-    (WGRAD, 0, 384, 25600, 640, 19, 23), (WGRAD, 0, 384, 25472, 640, 19, 19), (WGRAD, 0, 4480, 4480, 2048, 19, 19),
+    (WGRAD, 0, 384, 25600, 768, 19, 23), (WGRAD, 0, 384, 25472, 768, 19, 19), (WGRAD, 0, 8832, 2944, 512, 19, 19), (WGRAD, 0, 8832, 2944, 768, 19, 23), (WGRAD, 0, 6016, 7040, 640, 19, 23), (WGRAD, 0, 4480, 4480, 2048, 19, 19),
     (FWD, 0, 100, 128, 64, -1, -1), (FWD, 0, 2000, 1600, 1601, -1, -1), (FWD, 0, 2000, 6400, 1600, 23, 23), (WGRAD, 0, 8192, 8192, 2048, 18, 18),
 ])
 def test_products(op, epi, M, N, K, choice, runs):
