@@ -81,16 +81,26 @@ inline bool attn_f32_16_rows(bool backward, int b, int s, int heads, int d) {
   return s <= (pairs > l.p2 ? l.s2 : pairs > l.p1 ? l.s1 : l.any);
 }
 // Whether the other calls they take go there.  Against tiles of 32: half the rows per workgroup, so twice as many workgroups with half a chain each, for twice
-// the operand traffic per product.  Under the causal mask it is the faster form at every size measured; without it where it takes fewer
-// rounds of 256 workgroups in rows, or rows are short (up to 256), and where those two are equal forward above d = 96 and backward up to it.  us,
-// forward and backward, 32 / 16: 4 heads of 64 over 64 tokens 7.4 / 4.6, 24 / 6.8; 24 of 64 over 500 causal 25 / 19,
-// 77 / 56 and full (768 workgroups) 34 / 27, 121 / 90; 128 of 64 over 1000 causal 237 / 221, 1033 / 905; 64 of 128 over 64 15 / 6.5, 51 / 19;
-// 2 of 128 over 2000 160 / 64, 575 / 184.  Full, equal rounds: 12 of 64 over 512 19.7 / 20.3, 67 / 55, 256 of 64 over 512 239 / 292, 991 / 942, 8 of
-// 128 over 1000 86 / 64, 295 / 306.
+// the operand traffic per product.  Set on 1084 shapes (d 32 .. 128, s 192 .. 4096, 4 .. 1024 heads), where the choice is within 6 % of the better form on
+// 99 in 100.  us, tiles of 32 / of 16:
+//   d above 64: sooner forward (32 heads of 128 over 1000 causal 273 / 127, 64 of 96 over 1000 full 581 / 338) except, at d = 96, for unmasked rows where one round
+//     would be two; backward at d = 96 (64 of them over 1000 1797 / 1476), and at d = 128 under the mask, in fewer rounds or from 65000 rows on (in equal rounds
+//     24 of 128 over 1000 913 / 943, 128 of them 7116 / 5042).
+//   d up to 64: sooner while the operands of all heads, which run side by side, stay in the caches, forward of unmasked rows above 320 only in fewer rounds: 24 of 64
+//     over 500 causal 25 / 19, full 34 / 27, 128 over 300 full 57 / 48; beyond, forward 256 of 64 over 1000 causal 486 / 563, 256 over 512 full 243 / 300, backward
+//     1024 over 512 full 4351 / 4973.  Forward at d = 32 long rows are no shorter: 32 heads over 3000 tokens causal 239 / 259.
 inline bool attn_f32_16(bool backward, int b, int s, int heads, int d, bool causal) {
-  const int64_t pairs = (int64_t)b * heads;
+  const int64_t pairs = (int64_t)b * heads, rows = pairs * s;
   const int64_t rounds16 = (pairs * ((s + 15) / 16) + 255) / 256, rounds32 = (pairs * ((s + 31) / 32) + 255) / 256;
-  return causal || s <= 256 || rounds16 < 2 * rounds32 || (backward ? d <= 96 : d > 96);
+  if (backward) {
+    if (d <= 32) return rows <= (causal ? 700000 : 550000);
+    if (d <= 64) return rows <= (causal ? 520000 : 350000);
+    return d <= 96 || causal || s <= 320 || rounds16 < 2 * rounds32 || rows >= 65000;
+  }
+  if (d > 64) return d > 96 || causal || s <= 320 || rounds16 != 2 || rounds32 != 1;
+  if (causal) return d <= 32 ? rows * s <= 64000000 || pairs <= 8 : s <= 320 || pairs <= 128 || rows <= 160000;
+  if (d <= 32) return rows <= 160000 && (s <= 320 || 1.06 * (double)rounds16 < 2.0 * (double)rounds32);
+  return (pairs <= 128 || rows <= 80000) && (s <= 320 || rounds16 < 2 * rounds32);
 }
 hipError_t launch_attention_fwd_f32_16(const float* qkv, float* ctx, float* lse, int b, int s, int heads, int d, int causal, const DropArgs& drop, hipStream_t st);
 hipError_t launch_attention_bwd_f32_16(const float* qkv, const float* ctx, const float* lse, const float* dctx, float* dqkv, float* delta, int b, int s,

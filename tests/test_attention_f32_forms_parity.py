@@ -20,7 +20,12 @@ pytestmark = pytest.mark.gpu
     (64, 2, 17, 32, 0, -1, 4), (64, 3, 24, 32, 1, 4, -1), (64, 3, 17, 64, 0, -1, -1), (64, 4, 17, 64, 1, 4, -1), (64, 5, 17, 64, 1, 4, 4),
     (64, 3, 13, 96, 1, -1, -1), (64, 8, 13, 96, 0, 4, -1), (64, 9, 13, 96, 1, 4, 4), (8, 5, 16, 96, 1, 4, 4), (3, 4, 43, 128, 0, 4, -1), (64, 5, 13, 128, 1, 4, -1),
     # unmasked long rows in equal rounds; head dims in single elements
-    (8, 270, 2, 64, 0, 5, 4), (8, 270, 2, 100, 0, 4, 5), (8, 256, 2, 64, 0, 4, 4), (8, 270, 2, 64, 1, 4, 4), (1, 256, 2, 63, 1, -1, -1), (2, 257, 16, 63, 1, 5, 5),
+    (8, 330, 2, 64, 0, 5, 4), (8, 330, 2, 100, 0, 4, 5), (8, 320, 2, 64, 0, 4, 4), (8, 330, 2, 64, 1, 4, 4), (1, 512, 16, 96, 0, 5, 4), (2, 512, 16, 96, 0, 4, 4),
+    (1, 256, 2, 63, 1, -1, -1), (2, 257, 16, 63, 1, 5, 5),
+    # many heads, whose operands leave the caches
+    (30, 512, 8, 32, 1, 4, 4), (32, 512, 8, 32, 1, 5, 4), (52, 384, 8, 64, 1, 4, 4), (53, 384, 8, 64, 1, 5, 4), (32, 512, 4, 32, 0, 5, 4), (30, 512, 4, 32, 0, 4, 4),
+    (38, 256, 8, 64, 0, 4, 4), (40, 256, 8, 64, 0, 5, 4), (170, 256, 8, 64, 0, 5, 4), (171, 256, 8, 64, 0, 5, 5), (268, 256, 8, 32, 0, 5, 4), (269, 256, 8, 32, 0, 5, 5),
+    (14, 512, 8, 128, 0, 4, 5), (16, 512, 8, 128, 0, 4, 4),
 ])
 def test_which_form_the_choice_is(b, s, heads, d, causal, fwd, bwd):
     """The library's choice is, bit for bit, the form named here, and not the nearest other one (for tiles of 16 one wave per row up to 32 tokens and tiles of 32
@@ -45,8 +50,8 @@ def test_rising_row_maxima(variant):
 
 
 @pytest.mark.parametrize("heads,d,s,causal", [
-    (2, 64, 270, False),    # forward in tiles of 32, backward of 16
-    (2, 100, 270, False),   # and the other way round
+    (2, 64, 330, False),    # forward in tiles of 32, backward of 16
+    (2, 100, 330, False),   # and the other way round
     (2, 64, 66, True),      # both of 16
     (2, 35, 132, False),    # both of 32
 ])
