@@ -81,26 +81,29 @@ inline bool attn_f32_16_rows(bool backward, int b, int s, int heads, int d) {
   return s <= (pairs > l.p2 ? l.s2 : pairs > l.p1 ? l.s1 : l.any);
 }
 // Whether the other calls they take go there.  Against tiles of 32: half the rows per workgroup, so twice as many workgroups with half a chain each, for twice
-// the operand traffic per product.  Set on 1084 shapes (d 32 .. 128, s 192 .. 4096, 4 .. 1024 heads), where the choice is within 6 % of the better form on
+// the operand traffic per product.  Set on 2051 shapes (d 32 .. 128, s 192 .. 4096, 4 .. 1024 heads), where the choice is within 6 % of the better form on
 // 99 in 100.  us, tiles of 32 / of 16:
-//   d above 64: sooner forward (32 heads of 128 over 1000 causal 273 / 127, 64 of 96 over 1000 full 581 / 338) except, at d = 96, for unmasked rows where one round
-//     would be two; backward at d = 96 (64 of them over 1000 1797 / 1476), and at d = 128 under the mask, in fewer rounds or from 65000 rows on (in equal rounds
-//     24 of 128 over 1000 913 / 943, 128 of them 7116 / 5042).
-//   d up to 64: sooner while the operands of all heads, which run side by side, stay in the caches, forward of unmasked rows above 320 only in fewer rounds: 24 of 64
-//     over 500 causal 25 / 19, full 34 / 27, 128 over 300 full 57 / 48; beyond, forward 256 of 64 over 1000 causal 486 / 563, 256 over 512 full 243 / 300, backward
-//     1024 over 512 full 4351 / 4973.  Forward at d = 32 long rows are no shorter: 32 heads over 3000 tokens causal 239 / 259.
+//   d above 64: sooner forward (32 heads of 128 over 1000 causal 273 / 127, 64 of 96 over 1000 full 581 / 338) and backward (64 of 96 over 1000 1797 / 1476, 128 of 128
+//     over 1000 7116 / 5042), except backward at d = 128 unmasked in equal rounds of 256 workgroups with few rows and heads (24 of 128 over 1000 913 / 943).
+//   d up to 64, forward: sooner by the shorter chains (24 of 64 over 500 causal 25 / 19, full 34 / 27) while an XCD's L2 serves the second reading.  Workgroups go to
+//     the eight XCDs in turn, heads first, so one XCD works on pairs / gcd(pairs, 8) heads side by side; the more there are, the shorter rows must be (35 heads of 64
+//     over 840 tokens causal 64 / 58, 1664 175 / 217; 78 over 600 full 109 / 128; 256 over 512 full 243 / 300).  Unmasked rows above 320 only in fewer rounds; at d = 32
+//     long rows are no shorter (32 heads over 3000 tokens causal 239 / 259).
+//   d up to 64, backward: sooner up to several 100000 rows (128 of 64 over 1000 causal 1040 / 920, 1024 over 512 full 4351 / 4973).
 inline bool attn_f32_16(bool backward, int b, int s, int heads, int d, bool causal) {
   const int64_t pairs = (int64_t)b * heads, rows = pairs * s;
   const int64_t rounds16 = (pairs * ((s + 15) / 16) + 255) / 256, rounds32 = (pairs * ((s + 31) / 32) + 255) / 256;
+  const int64_t heads_per_xcd = pairs / (pairs % 8 == 0 ? 8 : pairs % 4 == 0 ? 4 : pairs % 2 == 0 ? 2 : 1);
   if (backward) {
     if (d <= 32) return rows <= (causal ? 700000 : 550000);
     if (d <= 64) return rows <= (causal ? 520000 : 350000);
-    return d <= 96 || causal || s <= 320 || rounds16 < 2 * rounds32 || rows >= 65000;
+    return d <= 96 || causal || s <= 320 || rounds16 < 2 * rounds32 || rows >= 65000 || heads_per_xcd > 25;
   }
-  if (d > 64) return d > 96 || causal || s <= 320 || rounds16 != 2 || rounds32 != 1;
-  if (causal) return d <= 32 ? rows * s <= 64000000 || pairs <= 8 : s <= 320 || pairs <= 128 || rows <= 160000;
-  if (d <= 32) return rows <= 160000 && (s <= 320 || 1.06 * (double)rounds16 < 2.0 * (double)rounds32);
-  return (pairs <= 128 || rows <= 80000) && (s <= 320 || rounds16 < 2 * rounds32);
+  if (d > 64) return true;
+  if (causal && d <= 32) return pairs <= 8 || (rows * s <= 64000000 && (heads_per_xcd <= 45 || s <= 400));
+  if (causal) return heads_per_xcd <= 16 || s <= (heads_per_xcd <= 25 ? 1600 : heads_per_xcd <= 45 ? 700 : 350);
+  if (s <= 224 || (s <= 320 && heads_per_xcd <= (d <= 32 ? 75 : 45))) return true;
+  return heads_per_xcd <= (s <= 900 ? 25 : 16) && (d <= 32 ? 1.06 : 1.0) * (double)rounds16 < 2.0 * (double)rounds32;
 }
 hipError_t launch_attention_fwd_f32_16(const float* qkv, float* ctx, float* lse, int b, int s, int heads, int d, int causal, const DropArgs& drop, hipStream_t st);
 hipError_t launch_attention_bwd_f32_16(const float* qkv, const float* ctx, const float* lse, const float* dctx, float* dqkv, float* delta, int b, int s,

@@ -19,13 +19,15 @@ pytestmark = pytest.mark.gpu
     (33, 1, 4, 32, 1, 4, -1), (33, 2, 4, 32, 0, 4, 4), (33, 2, 4, 64, 0, 4, -1), (33, 3, 4, 64, 1, 4, 4), (75, 2, 4, 128, 1, -1, -1), (75, 3, 4, 128, 0, 4, -1),
     (64, 2, 17, 32, 0, -1, 4), (64, 3, 24, 32, 1, 4, -1), (64, 3, 17, 64, 0, -1, -1), (64, 4, 17, 64, 1, 4, -1), (64, 5, 17, 64, 1, 4, 4),
     (64, 3, 13, 96, 1, -1, -1), (64, 8, 13, 96, 0, 4, -1), (64, 9, 13, 96, 1, 4, 4), (8, 5, 16, 96, 1, 4, 4), (3, 4, 43, 128, 0, 4, -1), (64, 5, 13, 128, 1, 4, -1),
-    # unmasked long rows in equal rounds; head dims in single elements
-    (8, 330, 2, 64, 0, 5, 4), (8, 330, 2, 100, 0, 4, 5), (8, 320, 2, 64, 0, 4, 4), (8, 330, 2, 64, 1, 4, 4), (1, 512, 16, 96, 0, 5, 4), (2, 512, 16, 96, 0, 4, 4),
-    (1, 256, 2, 63, 1, -1, -1), (2, 257, 16, 63, 1, 5, 5),
-    # many heads, whose operands leave the caches
-    (30, 512, 8, 32, 1, 4, 4), (32, 512, 8, 32, 1, 5, 4), (52, 384, 8, 64, 1, 4, 4), (53, 384, 8, 64, 1, 5, 4), (32, 512, 4, 32, 0, 5, 4), (30, 512, 4, 32, 0, 4, 4),
-    (38, 256, 8, 64, 0, 4, 4), (40, 256, 8, 64, 0, 5, 4), (170, 256, 8, 64, 0, 5, 4), (171, 256, 8, 64, 0, 5, 5), (268, 256, 8, 32, 0, 5, 4), (269, 256, 8, 32, 0, 5, 5),
-    (14, 512, 8, 128, 0, 4, 5), (16, 512, 8, 128, 0, 4, 4),
+    # unmasked rows in equal and in fewer rounds; head dims in single elements
+    (8, 330, 2, 64, 0, 5, 4), (5, 330, 5, 64, 0, 4, 4), (3, 330, 9, 64, 0, 5, 4), (3, 900, 7, 64, 0, 4, 4), (3, 912, 7, 64, 0, 5, 4), (8, 320, 2, 64, 0, 4, 4), (8, 330, 2, 64, 1, 4, 4),
+    (32, 512, 4, 32, 0, 5, 4), (30, 512, 4, 32, 0, 4, 4), (1, 512, 16, 96, 0, 4, 4), (8, 330, 2, 100, 0, 4, 5), (4, 384, 5, 128, 0, 4, 5), (7, 384, 5, 128, 0, 4, 4),
+    (14, 512, 8, 128, 0, 4, 5), (16, 512, 8, 128, 0, 4, 4), (1, 256, 2, 63, 1, -1, -1), (2, 257, 16, 63, 1, 5, 5),
+    # many heads on an XCD
+    (30, 512, 8, 32, 1, 4, 4), (32, 512, 8, 32, 1, 5, 4), (45, 416, 1, 32, 1, 4, 4), (47, 416, 1, 32, 1, 5, 4), (47, 400, 1, 32, 1, 4, 4),
+    (5, 1600, 5, 64, 1, 4, 4), (5, 1616, 5, 64, 1, 5, 4), (5, 700, 7, 64, 1, 4, 4), (5, 704, 7, 64, 1, 5, 4), (47, 350, 1, 64, 1, 4, 4), (47, 352, 1, 64, 1, 5, 4), (45, 384, 8, 64, 1, 4, 4), (46, 384, 8, 64, 1, 5, 4),
+    (9, 224, 7, 64, 0, 4, 4), (9, 232, 7, 64, 0, 5, 4), (9, 232, 5, 64, 0, 4, 4), (15, 232, 5, 32, 0, 4, 4), (11, 232, 7, 32, 0, 5, 4),
+    (170, 256, 8, 64, 0, 5, 4), (171, 256, 8, 64, 0, 5, 5), (268, 256, 8, 32, 0, 5, 4), (269, 256, 8, 32, 0, 5, 5),
 ])
 def test_which_form_the_choice_is(b, s, heads, d, causal, fwd, bwd):
     """The library's choice is, bit for bit, the form named here, and not the nearest other one (for tiles of 16 one wave per row up to 32 tokens and tiles of 32
