@@ -123,7 +123,7 @@ varuna_status_t varuna_stage_forward(varuna_stage_t* st, int32_t mb, const void*
  * per layer possibly deferred, see varuna_stage_grad_flush).  Requires a forward of
  * slot mb since that slot was last consumed (else VARUNA_ESTATE).  Calls for
  * different slots may be interleaved with forwards in any order.  dy_in is read where it lies by kernels up to the last of the
- * call, also by those on the side stream (which hip_stream waits for), so it may be overwritten by work that follows on
+ * call, so it may be overwritten by work that follows on
  * hip_stream but not by another stream before that; dx_out may be dy_in or overlap it. */
 varuna_status_t varuna_stage_backward_recompute(varuna_stage_t* st, int32_t mb,
                                                 const void* dy_in /*device*/,

@@ -132,8 +132,8 @@ __device__ __forceinline__ bf16x8 at_tr_frag(const bf16* tile, int r0, int col_b
 // acc += A B with the accumulator pinned to the accumulation registers.  With one wave per
 // SIMD a kernel spreads over both halves of the register file, and left to itself the
 // compiler may keep long-lived accumulators in the ordinary half and copy all 16
-// registers across around every product.  (The dK/dV kernel did until it fitted two waves per SIMD, where the compiler's own products
-// are as fast.)  The product is opaque to the compiler here, so the
+// registers across around every product.  (No kernel calls it now: the dK/dV kernel did until it fitted two waves per SIMD, where the compiler's own products
+// are as fast.  A test holds the wait states.)  The product is opaque to the compiler here, so the
 // wait states around it are inserted by hand: two between an operand's last VALU write and the product (a conversion or
 // register move may stand directly before it; the product then multiplied what the register held before, now and then:
 // dK of d = 32 with dropout up to infinity), and those a later read of the result needs (at_mfma_settle).

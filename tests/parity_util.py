@@ -22,7 +22,7 @@ def gpu_stage_step(cfg, params, xs, dys, device="cuda:0", interleave=False, last
     tensors; the accumulated gradients stay in stage.grads."""
     st = B.Stage(cfg, device)
     st.set_params(params)
-    if side_stream:   # the launch configuration bench.py times: bias-gradient sums beside the GEMM chain
+    if side_stream:   # as bench.py hands one over (the library runs nothing there at present)
         st.set_side_stream(torch.cuda.Stream(device))
     if cfg.dropout_p > 0:
         st.set_dropout_seed(seed)

@@ -1,4 +1,4 @@
-"""The dK/dV products are inline assembly, for which the compiler inserts no wait states: two must stand between the last
+"""A product written as inline assembly (at_mfma_acc) gets no wait states from the compiler: two must stand between the last
 write of an operand and the product (what it puts before products it knows itself)."""
 import os
 import re

@@ -246,8 +246,8 @@ def test_accumulation_reset_and_determinism():
 
 @pytest.mark.parametrize("name", ["C2", "C3", "C4"])
 def test_bf16_run_to_run_determinism_at_full_shape(name):
-    """The bf16 path (MFMA GEMMs with split-K weight gradients, MFMA attention, bias-gradient
-    sums on the side stream, grouped weight-gradient GEMMs) gives bit-identical outputs, input
+    """The bf16 path (MFMA GEMMs with split-K weight gradients, MFMA attention, a second
+    stream handed over, grouped weight-gradient GEMMs) gives bit-identical outputs, input
     gradients and accumulated gradients on two independent runs: nothing in it adds floats
     in an order that depends on timing."""
     cfg = CONFIGS[name].replace(n_micro_batches=2, wgrad_group=2)
@@ -275,7 +275,7 @@ def test_bf16_run_to_run_determinism_at_full_shape(name):
     assert torch.isfinite(ga).all()
     assert torch.equal(ga, gb)
     assert all(torch.equal(a, b) for a, b in zip(ya + dxa, yb + dxb))
-    yc, dxc, gc = run(side=False)     # everything on the caller's stream: the same bits
+    yc, dxc, gc = run(side=False)     # without the second stream: the same bits
     assert torch.equal(ga, gc)
     assert all(torch.equal(a, b) for a, b in zip(ya + dxa, yc + dxc))
 
